@@ -144,8 +144,7 @@ def log_profile(args, prof):
                       f"algo={r['algo_bytes'] / 1e9:8.3f}GB ({gbs:7.1f} GB/s) events={r['events']} aux={r['aux']}")
 
 
-PHASES = ("prefix", "nbr-hash", "compact", "disjoint", "group", "open", "pairs", "hand-over", "pairs-short",
-          "pairs-vpairs", "pairs-long")
+PHASES = ("prefix", "nbr-hash", "compact", "disjoint", "shared", "open", "pairs", "hand-over", "runs")
 
 
 def log_phases(args, ctr):
@@ -157,8 +156,6 @@ def log_phases(args, ctr):
             log(args, f"  stage {s} phases: " + " ".join(f"{n}={100.0 * v / tot:.1f}%" for n, v in zip(PHASES, ph)))
             # the wall clock the kernels read runs at 100 MHz
             log(args, f"  stage {s}: longest single centre {int(ctr[16 + 12 * s + 11]) / 1e5:.2f} ms")
-    log(args, f"  aggregated pairs: long runs {int(ctr[12])}, pairs sharing several vertices {int(ctr[13])}, "
-              f"centres enumerated {int(ctr[14])}")
 
 
 def add_profiles(acc, prof):

@@ -201,11 +201,9 @@ int hgt_apply_batches(hgt_batch* batches, uint32_t n, void* stream);
                                   * caller's.  Where the capture fails the round
                                   * is launched kernel by kernel. */
 #define HGT_BATCHES_AUTOTUNE 2u  /* launch choices (workgroups per CU of the
-                                  * global histogram stage, whether centres skip
-                                  * the 148 KB stage, slots of the per-wave
-                                  * 2-hop hashes, the vertex-pair count from
-                                  * which a dense centre goes to the 2-hop
-                                  * kernel) picked per key of the round:
+                                  * global histogram stage, slots of the
+                                  * per-wave 2-hop hashes, pairs per slice of a
+                                  * dense centre) picked per key of the round:
                                   * tracked families, number of graphs, changes
                                   * and the 2-hop load of the heaviest centre,
                                   * in log2/log4 buckets.  Each choice is timed
@@ -457,12 +455,10 @@ int hgt_profile_read(hgt_graph* g, hgt_kernel_time* out_host, uint32_t n_max, ui
 /* Waits for the graph's work and copies the raw device counters of the
  * profile (algorithmic bytes, hand-overs between kernel stages, wall-clock
  * ticks per phase of the hyperedge-delta stages: counters 16 + 12 s + p for
- * stage s and phase p = 0 member prefix, 1 neighbour hash, 2 compaction,
- * 3 disjoint-pair classes, 4 vertex grouping, 5 open paths, 6 intersecting
- * pairs (all of them when enumerated; the correction of pairs sharing several
- * vertices when aggregated), 7 hand-over, 8 aggregated: short runs, 9 vertex
- * pairs, 10 long runs; 12-14 the aggregated phase's long runs, corrected
- * pairs and enumerating centres; 56.. temporal counters) to
+ * stage s (0: LDS, 2: global) and phase p = 0 member prefix, 1 neighbour hash,
+ * 2 compaction, 3 disjoint-pair classes, 4 vertices shared by two neighbours,
+ * 5 open paths, 6 intersecting pairs, 7 hand-over, 8 runs of the shared
+ * vertices, 11 the longest centre; 56.. temporal counters) to
  * out_host[0..n_max); *n_out receives the count (64). */
 int hgt_profile_counters(hgt_graph* g, uint64_t* out_host, uint32_t n_max, uint32_t* n_out);
 

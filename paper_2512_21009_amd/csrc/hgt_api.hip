@@ -137,12 +137,12 @@ thread_local NoAllocArena* t_na = nullptr;
 thread_local int t_capture = 0;
 
 // Launch choices the autotuner picks between (workgroups per CU of the global
-// histogram stage, whether centres skip the 148 KB stage, slots of the 2-hop
-// kernels' per-wave hashes); t_tune overrides the graph's own for one round.
+// histogram stage, slots of the 2-hop kernels' per-wave hashes, size of a slice of
+// a dense centre); t_tune overrides the graph's own for one round.
 struct TuneChoice {
-    int wg_per_cu, skip_lds148;
+    int wg_per_cu;
     uint32_t wave_slots;
-    uint64_t e2_2hop;  // vertex pairs from which a hyperedge centre goes to the 2-hop kernel (0: default)
+    uint64_t slice_pairs;  // pairs per slice of a global-stage centre (0: default)
 };
 thread_local const TuneChoice* t_tune = nullptr;
 thread_local hipEvent_t t_tune_ev[2] = {nullptr, nullptr};  // recorded around an autotuned round's launches
@@ -243,7 +243,7 @@ struct PhaseCtx {
     int refs = 0;                 // graphs that use it
     hipEvent_t done = nullptr;    // recorded after the last user's phases
     DevBuf iv_list, iv_list2, iv_garena, iv_garena2;  // incident-vertex stage scratch
-    DevBuf t_ctr, t_big_list, t_big_rank, t_big_scratch, t_list1, t_rank1, t_list2, t_rank2, t_garena, t_whash;
+    DevBuf t_ctr, t_big_list, t_big_rank, t_big_scratch, t_list1, t_rank1, t_garena, t_whash;
     DevBuf t_slices, t_slice_scan;       // slices of the 2-hop kernel's centres
     DevBuf ent_x, ent_d, ent_pay, bl_cnt, bl_off, bl_cur, bl_d, bl_pay, nb_scratch, bl_scan;
     // per-graph phase descriptors: device copies and their pinned staging, one
@@ -295,17 +295,13 @@ struct hgt_graph {
     uint64_t compactions = 0;       // pool compactions since build
     uint64_t graph_launches = 0;    // rounds launched as captured HIP graphs (with this graph first)
     int force_stage = 0;            // HGT_FORCE_STAGE (tests): see He2Params
-    int pair_agg = 1;               // HGT_PAIR_AGG=0: pairs enumerated per run (see He2Params)
-    int global_wg_per_cu = 4;       // HGT_GLOBAL_WG_PER_CU: workgroups per CU of the global stage
+    int global_wg_per_cu = 2;       // HGT_GLOBAL_WG_PER_CU: workgroups per CU of the global stage
     int iv_direct = 0;              // HGT_IV_DIRECT=1 (tests): incident-vertex owners without maps
     int iv_wg_per_cu = 8;           // HGT_IV_WG_PER_CU: workgroups per CU of the incident-vertex global stage
     uint32_t slice_lh = 0;          // HGT_SLICE_LH (tests): list entries per slice of a 2-hop kernel centre
-    uint64_t e2_2hop = 0;           // HGT_E2_2HOP: vertex pairs from which a centre goes to the 2-hop kernel
-    uint32_t w_2hop = 0;            // HGT_W_2HOP: neighbour-row entries from which it does
+    uint64_t slice_pairs = 0;       // HGT_SLICE_PAIRS: pairs per slice of a global-stage centre (0: default)
     int iv_force_stage = 0;         // HGT_IV_FORCE_STAGE (tests): incident-vertex stages below it pass owners on
     uint32_t wave_slots = 8192;     // HGT_WAVE_SLOTS (tests): slots of the 2-hop kernels' per-wave global hashes
-    int skip_lds148 = 1;            // HGT_SKIP_LDS148=0: centres go through the 148 KB stage (one workgroup
-                                    // per CU) instead of straight to the global one (four per CU)
     BatchSummary* h_sum = nullptr;  // pinned
     DevScalars* h_sc = nullptr;     // pinned
     // profiling: HIP events around each kernel group, algorithmic-byte counters
@@ -321,10 +317,10 @@ struct hgt_graph {
 
 namespace {
 
-enum ProfKind { PK_PLAN = 0, PK_DELTA_SMALL, PK_DELTA_BIG, PK_IV_PREP, PK_IV_PAIRS, PK_COMMIT, PK_DELTA_MED,
+enum ProfKind { PK_PLAN = 0, PK_DELTA_SMALL, PK_DELTA_BIG, PK_IV_PREP, PK_IV_PAIRS, PK_COMMIT,
                 PK_DELTA_GLOBAL, PK_NBR, PK_TMP, PK_N };
 const char* kProfNames[PK_N] = {"store_plan", "he_hist_lds32", "he_2hop", "iv_prepare", "iv_pairs", "store_commit",
-                                "he_hist_lds148", "he_hist_global", "he_nbr_pass", "temporal"};
+                                "he_hist_global", "he_nbr_pass", "temporal"};
 
 hipEvent_t prof_event(hgt_graph* g) {
     if (g->ev_used == g->ev_pool.size()) {
@@ -511,9 +507,9 @@ int ensure_plan_scratch(hgt_graph* g, const Sizes& z, PlanScratch& w) {
 
 // ---- triad phases ---------------------------------------------------------
 void phase_ctx_free(PhaseCtx& c) {
-    DevBuf* all[] = {&c.t_ctr, &c.t_whash, &c.t_big_list, &c.t_big_rank, &c.t_big_scratch, &c.t_list1, &c.t_rank1, &c.t_list2,
+    DevBuf* all[] = {&c.t_ctr, &c.t_whash, &c.t_big_list, &c.t_big_rank, &c.t_big_scratch, &c.t_list1, &c.t_rank1,
                      &c.t_slices, &c.t_slice_scan,
-                     &c.t_rank2, &c.t_garena, &c.ent_x, &c.ent_d, &c.ent_pay, &c.bl_cnt, &c.bl_off, &c.bl_cur,
+                     &c.t_garena, &c.ent_x, &c.ent_d, &c.ent_pay, &c.bl_cnt, &c.bl_off, &c.bl_cur,
                      &c.bl_d, &c.bl_pay, &c.nb_scratch, &c.bl_scan, &c.desc, &c.iv_list, &c.iv_list2, &c.iv_garena,
                      &c.iv_garena2};
     for (DevBuf* b : all) dev_free(*b);
@@ -695,11 +691,11 @@ void collect(const PhaseJob* jobs, uint32_t nj, int family, bool minus, std::vec
 struct PhaseShape {
     uint64_t n, lhm, max_card, ecap, total_ids;
     BigLayout L;
-    uint64_t grid_big, grid_small, grid_tmp, grid_2hop, grid_s0, grid_s1, grid_g, nb_grid, nb_words;
+    uint64_t grid_big, grid_small, grid_tmp, grid_2hop, grid_s0, grid_g, garena_words, nb_grid, nb_words;
     uint32_t wave_slots;
 };
 
-constexpr uint64_t kGarenaWords = 1ull << 18;  // 1 MB global arena per workgroup of the global stage
+constexpr uint64_t kGarenaWords = 1ull << 19;  // 2 MB global arena per workgroup of the global stage
 
 PhaseShape phase_shape(const hgt_graph* owner, uint64_t n, uint64_t max_lh, uint64_t sum_lh, uint64_t total_ids,
                        bool lean) {
@@ -711,7 +707,7 @@ PhaseShape phase_shape(const hgt_graph* owner, uint64_t n, uint64_t max_lh, uint
     z.L = triad_big_layout(z.lhm, z.max_card);
     // at most ~1 GiB of global tables for the large-centre kernels
     z.grid_big = std::max<uint64_t>(1, std::min<uint64_t>(lean ? 8 : n_cu * 2, (1ull << 28) / z.L.words_per_wg));
-    z.grid_small = std::min<uint64_t>(n_cu * 2, n);
+    z.grid_small = std::min<uint64_t>(n_cu * 5, n);  // the neighbour pass: 28 KB of LDS
     z.grid_tmp = std::min<uint64_t>(lean ? 32 : n_cu * 3, n);
     // 2-hop hashes in global memory, one per wave of the 2-hop kernels (64 KB each)
     z.wave_slots = t_tune ? t_tune->wave_slots : owner->wave_slots;
@@ -720,11 +716,13 @@ PhaseShape phase_shape(const hgt_graph* owner, uint64_t n, uint64_t max_lh, uint
     z.nb_words = 2 * pow2ceil64(2 * std::max<uint64_t>(z.lhm, 32)) + 3 * z.max_card + 8;
     z.nb_grid = std::max<uint64_t>(1, std::min<uint64_t>(lean ? 8 : 256, (1ull << 27) / z.nb_words));
     z.grid_s0 = std::min<uint64_t>(n_cu * 4, n);
-    z.grid_s1 = std::min<uint64_t>(n_cu, n);
-    // the global stage holds little LDS, so several workgroups share a CU and hide
-    // each other's memory latency
+    // the global stage: workgroups of 512 threads, two per CU (their counters take
+    // 65 KB of LDS); a dense centre is shared by up to 64 of them
     const int wg_per_cu = t_tune ? t_tune->wg_per_cu : owner->global_wg_per_cu;
-    z.grid_g = std::min<uint64_t>(lean ? 16 : n_cu * (uint64_t)wg_per_cu, n);
+    // (the no-allocation entry point: 16 MB of arenas at most, 1 MB per centre)
+    z.grid_g = lean ? std::min<uint64_t>(8, std::max<uint64_t>(1, n / 2))
+                    : std::min<uint64_t>(n_cu * (uint64_t)wg_per_cu, 64 * n);
+    z.garena_words = lean && n < 2 ? kGarenaWords / 2 : kGarenaWords;
     z.total_ids = total_ids;
     return z;
 }
@@ -738,8 +736,6 @@ int phase_reserve(PhaseCtx& c, int family, const PhaseShape& z) {
     rc |= ensure(c.t_big_rank, n * 4);
     rc |= ensure(c.t_list1, n * 8);
     rc |= ensure(c.t_rank1, n * 4);
-    rc |= ensure(c.t_list2, n * 8);
-    rc |= ensure(c.t_rank2, n * 4);
     rc |= ensure(c.t_big_scratch, z.grid_big * z.L.words_per_wg * 4);
     rc |= ensure(c.t_whash, z.grid_2hop * 4 * 2ull * z.wave_slots * 4);
     rc |= ensure(c.t_slices, (n + 2) * 8);
@@ -756,7 +752,7 @@ int phase_reserve(PhaseCtx& c, int family, const PhaseShape& z) {
         rc |= ensure(c.bl_cur, ids * 8);
         rc |= ensure(c.bl_scan, hgt_scan_tmp_bytes(ids));
         rc |= ensure(c.nb_scratch, z.nb_grid * z.nb_words * 4);
-        rc |= ensure(c.t_garena, z.grid_g * kGarenaWords * 4);
+        rc |= ensure(c.t_garena, z.grid_g * z.garena_words * 4);
     }
     return rc ? HGT_ENOMEM : HGT_OK;
 }
@@ -839,37 +835,32 @@ int run_phase(hgt_graph* owner, const PhaseJob* jobs, uint32_t nj, bool minus, b
             E.count = ctr + 19;
             E.list[0] = c.t_list1.as<uint64_t>();
             E.rank[0] = c.t_rank1.as<uint32_t>();
-            E.list[1] = c.t_list2.as<uint64_t>();
-            E.rank[1] = c.t_rank2.as<uint32_t>();
             E.list[2] = P.big_list;
             E.rank[2] = P.big_rank;
             const unsigned grid_g = (unsigned)z.grid_g;
             E.garena = c.t_garena.as<uint32_t>();
-            E.garena_words = kGarenaWords;
+            E.garena_words = z.garena_words;
             E.stats = stats;
             E.phase_ticks = (stats && owner->prof_phases) ? 1 : 0;
             // read again at every phase, so that a test can force the stages of a batch
             // without forcing those of the build's full count
             const char* fs = std::getenv("HGT_FORCE_STAGE");
             E.force_stage = fs ? std::atoi(fs) : owner->force_stage;
-            E.pair_agg = owner->pair_agg;
-            E.skip_lds148 = t_tune ? t_tune->skip_lds148 : owner->skip_lds148;
-            E.e2_2hop = t_tune && t_tune->e2_2hop ? t_tune->e2_2hop : owner->e2_2hop;
-            E.w_2hop = owner->w_2hop;
+            E.slice_pre = P.slice_pre;
+            E.slice_cap = n;
+            E.slice_lh = owner->slice_lh;
+            E.slice_pairs = t_tune && t_tune->slice_pairs ? t_tune->slice_pairs : owner->slice_pairs;
+            E.slice_scan_tmp = c.t_slice_scan.p;
             E.static_mode = full ? 1 : 0;
             hgt_fill_u32(ctr + 16, 0, 6, s);
             hgt_fill_u32(ctr + 5, 0, 1, s);
             {
                 ProfScope ps(owner, PK_DELTA_SMALL, s);
-                he2_launch_stage(E, 0, (unsigned)z.grid_s0, s);
-            }
-            {
-                ProfScope ps(owner, PK_DELTA_MED, s);
-                he2_launch_stage(E, 1, (unsigned)z.grid_s1, s);
+                he2_launch_lds(E, (unsigned)z.grid_s0, s);
             }
             {
                 ProfScope ps(owner, PK_DELTA_GLOBAL, s);
-                he2_launch_stage(E, 2, grid_g, s);
+                he2_launch_global(E, grid_g, s);
             }
             // centres too large for every arena: the 2-hop kernel
             TriadParams B = P;
@@ -1658,13 +1649,10 @@ int hgt_build(const hgt_build_desc* d, hgt_graph** out) {
     g->window = d->temporal_window;
     g->last_stream = s;
     if (const char* fs = std::getenv("HGT_FORCE_STAGE")) g->force_stage = std::atoi(fs);
-    if (const char* pa = std::getenv("HGT_PAIR_AGG")) g->pair_agg = std::atoi(pa) != 0;
     if (const char* gw = std::getenv("HGT_GLOBAL_WG_PER_CU")) g->global_wg_per_cu = std::max(1, std::min(16, std::atoi(gw)));
-    if (const char* sk = std::getenv("HGT_SKIP_LDS148")) g->skip_lds148 = std::atoi(sk) != 0;
     if (const char* iw = std::getenv("HGT_IV_WG_PER_CU")) g->iv_wg_per_cu = std::max(1, std::min(16, std::atoi(iw)));
     if (const char* sl = std::getenv("HGT_SLICE_LH")) g->slice_lh = (uint32_t)std::max(1, std::atoi(sl));
-    if (const char* e2 = std::getenv("HGT_E2_2HOP")) g->e2_2hop = std::strtoull(e2, nullptr, 10);
-    if (const char* w2 = std::getenv("HGT_W_2HOP")) g->w_2hop = (uint32_t)std::min<uint64_t>(std::strtoull(w2, nullptr, 10), 1u << 21);
+    if (const char* sp = std::getenv("HGT_SLICE_PAIRS")) g->slice_pairs = std::strtoull(sp, nullptr, 10);
     if (const char* iv = std::getenv("HGT_IV_DIRECT")) g->iv_direct = std::atoi(iv) != 0;
     if (const char* fs = std::getenv("HGT_IV_FORCE_STAGE")) g->iv_force_stage = std::atoi(fs);
     if (const char* ws = std::getenv("HGT_WAVE_SLOTS")) {  // a power of two, 64 .. 2^20
@@ -1855,9 +1843,8 @@ namespace {
 // best choice's is dropped, and once every remaining choice has kTuneTrials
 // trials the fastest (by its quickest trial) is kept for the key and appended
 // to the cache file, which later processes read first.
-constexpr TuneChoice kTune[] = {{4, 1, 8192, 0},       {2, 1, 8192, 0},       {8, 1, 8192, 0},
-                                {4, 0, 8192, 0},       {4, 1, 32768, 0},      {4, 1, 8192, 1u << 18},
-                                {4, 1, 8192, 1u << 21}};
+constexpr TuneChoice kTune[] = {{2, 8192, 0},        {1, 8192, 0},        {2, 8192, 1u << 17}, {2, 8192, 1u << 18},
+                                {2, 32768, 0},       {2, 8192, 1u << 20}, {2, 8192, 1u << 21}};
 constexpr int kTuneN = (int)(sizeof(kTune) / sizeof(kTune[0]));
 constexpr int kTuneTrials = 2;
 constexpr float kTuneDrop = 1.25f;
@@ -1904,9 +1891,9 @@ uint64_t tune_key(const std::vector<Pending*>& ps, int n_cu) {
            ((uint64_t)(ilog2_bucket(lh) / 2) << 8);
 }
 
-// Cache file: one line per settled key, "key choice wg_per_cu skip_lds148
-// wave_slots e2_2hop best_ms"; lines whose choice does not match this library's
-// table are ignored.
+// Cache file: one line per settled key, "key choice wg_per_cu 0 wave_slots
+// slice_pairs best_ms"; lines whose choice does not match this library's table are
+// ignored.
 void tune_load(Tuner& T) {
     if (T.loaded) return;
     T.loaded = true;
@@ -1927,8 +1914,8 @@ void tune_load(Tuner& T) {
     unsigned slots;
     float ms;
     while (std::fscanf(f, "%llx %d %d %d %u %llu %f", &key, &choice, &wg, &skip, &slots, &e2, &ms) == 7) {
-        if (choice < 0 || choice >= kTuneN || kTune[choice].wg_per_cu != wg || kTune[choice].skip_lds148 != skip ||
-            kTune[choice].wave_slots != slots || kTune[choice].e2_2hop != e2)
+        if (choice < 0 || choice >= kTuneN || kTune[choice].wg_per_cu != wg || skip != 0 ||
+            kTune[choice].wave_slots != slots || kTune[choice].slice_pairs != e2)
             continue;
         TuneEntry& t = T.tab[(uint64_t)key];
         t.pick = choice;
@@ -1953,8 +1940,8 @@ void tune_settle(Tuner& T, uint64_t key, TuneEntry& t) {
     if (T.path.empty()) return;
     if (FILE* f = std::fopen(T.path.c_str(), "a")) {
         const TuneChoice& c = kTune[best];
-        std::fprintf(f, "%llx %d %d %d %u %llu %.4f\n", (unsigned long long)key, best, c.wg_per_cu, c.skip_lds148,
-                     c.wave_slots, (unsigned long long)c.e2_2hop, t.best_ms[best]);
+        std::fprintf(f, "%llx %d %d 0 %u %llu %.4f\n", (unsigned long long)key, best, c.wg_per_cu, c.wave_slots,
+                     (unsigned long long)c.slice_pairs, t.best_ms[best]);
         std::fclose(f);
     }
 }
@@ -2212,7 +2199,6 @@ int hgt_profile_read(hgt_graph* g, hgt_kernel_time* out, uint32_t n_max, uint32_
     rows[PK_COMMIT].algo_bytes = g->store_bytes;
     rows[PK_DELTA_BIG].events = st[ST_DEFER0 + 2];
     rows[PK_DELTA_SMALL].algo_bytes = st[ST_HEB0];
-    rows[PK_DELTA_MED].algo_bytes = st[ST_HEB0 + 1];
     rows[PK_DELTA_GLOBAL].algo_bytes = st[ST_HEB0 + 2];
     rows[PK_DELTA_SMALL].events = st[ST_DEFER0];
     rows[PK_DELTA_SMALL].aux = st[ST_DEFER0 + 1];

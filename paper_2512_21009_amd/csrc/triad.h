@@ -85,9 +85,6 @@ enum TriadStat {
     ST_IV_BYTES = 5,     // algorithmic bytes gathered by the incident-vertex kernel
     ST_DEFER0 = 6,       // centres moved on by histogram-kernel stage 0, 1, 2
     ST_HEB0 = 9,         // algorithmic bytes gathered by histogram-kernel stage 0, 1, 2
-    ST_AGG_LONG = 12,    // aggregated pair phase: long runs counted by histogram
-    ST_AGG_MULTI = 13,   // ... pairs sharing two or more vertices, corrected
-    ST_AGG_ENUM = 14,    // centres whose pairs were enumerated per run instead
     ST_PH0 = 16,         // wall-clock ticks per phase of histogram-kernel stage s: ST_PH0 + HE2_PHASES s + phase
                          // (the last slot of a stage: the longest single centre, a maximum)
     ST_TMP0 = 56,        // the temporal launches' counters: ST_TMP0 + (ST_BYTES_SMALL .. ST_EXPANDED)
@@ -127,21 +124,21 @@ struct He2Params {
     const uint64_t* bl_cnt;
     const uint32_t* bl_d;
     const uint64_t* bl_pay;
-    uint32_t* queue;             // per stage (3 consecutive counters)
+    uint32_t* queue;             // per stage (3 consecutive counters; 1 is not used)
     uint32_t* count;             // items moved on by each stage (3 consecutive)
-    uint64_t* list[3];           // list[s]: items stage s could not fit; list[2] feeds
-    uint32_t* rank[3];           // the 2-hop kernel (k_delta_big), as do the densest centres
-    uint32_t* garena;            // stage-2 tables: garena_words per workgroup
+    uint64_t* list[3];           // list[s]: items stage s (0, 2) could not fit; list[0] feeds
+    uint32_t* rank[3];           // the global stage, list[2] the 2-hop kernel (k_delta_big)
+    uint32_t* garena;            // global-stage tables: garena_words per workgroup
     uint64_t garena_words;
+    uint64_t* slice_pre;         // slices of the global stage's centres (see TriadParams)
+    uint64_t slice_cap;
+    uint32_t slice_lh;           // test knob: member-list entries per slice (0: by pairs)
+    uint64_t slice_pairs;        // pairs along a centre's member lists per slice (0: the default)
+    void* slice_scan_tmp;
     uint64_t* stats;             // byte and hand-over counters (profiling), NULL = off
     int phase_ticks;             // 1 (with stats): wall-clock ticks per phase, at the cost of a
-                                 // clock read and a barrier per phase
+                                 // clock read per phase
     int force_stage;             // test knob: stages below it move every centre on
-    int skip_lds148;             // 1: the 148 KB stage moves every centre on to the global stage
-    int pair_agg;                // 1: pairs counted per shared vertex by class histograms, pairs
-                                 // sharing several vertices found through their vertex pairs
-    uint64_t e2_2hop;            // vertex pairs from which a centre goes to the 2-hop kernel (0: default)
-    uint32_t w_2hop;             // neighbour-row entries from which it does (0: default)
     int static_mode;             // full count (build): no batch ranks, no open paths through
                                  // neighbours; open triples at their centre, closed ones at the
                                  // smallest-ID centre
@@ -153,7 +150,8 @@ void he2_lists_build(NbrParams& P, uint64_t* bl_cnt, uint64_t* bl_off, uint64_t*
                      uint64_t* bl_pay, void* scan_tmp, hipStream_t s);
 // after the deletion phase: take the deleted hyperedges out of their neighbours' histograms
 void he2_remove_deleted(NbrParams& P, hipStream_t s);
-void he2_launch_stage(He2Params& P, int stage, unsigned grid, hipStream_t s);
+void he2_launch_lds(He2Params& P, unsigned grid, hipStream_t s);
+void he2_launch_global(He2Params& P, unsigned grid, hipStream_t s);  // counts the slices first
 
 // incident-vertex family
 struct IvParams {

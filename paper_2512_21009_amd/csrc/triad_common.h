@@ -134,6 +134,12 @@ __device__ __forceinline__ uint32_t wg_scan_u32(uint32_t v, uint32_t* ws, uint32
 }
 
 
+// The slice of a sliced centre that owns neighbour x (a property of x alone, so
+// every slice, whatever order its lists come in, agrees on it).
+__device__ __forceinline__ uint32_t slice_of(uint32_t x, uint32_t nslice) {
+    return (uint32_t)(((uint64_t)(x * 2654435761u) * nslice) >> 32);
+}
+
 struct Tables {
     uint8_t he[128];
     uint8_t tmp[128];

@@ -69,12 +69,6 @@ struct Shared {
     uint64_t g[8];
 };
 
-// The slice of a sliced centre that owns neighbour x (a property of x alone, so
-// every slice, whatever order its lists come in, agrees on it).
-__device__ __forceinline__ uint32_t slice_of(uint32_t x, uint32_t nslice) {
-    return (uint32_t)(((uint64_t)(x * 2654435761u) * nslice) >> 32);
-}
-
 // classify the intersecting pair (x, y) found in x's 2-hop lists
 __device__ __forceinline__ void classify(const TriadParams& P, const HeGraph& G, const Tables& T, const WgStore& S,
                                          const Shared& sh,

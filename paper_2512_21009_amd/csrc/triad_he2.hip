@@ -14,33 +14,25 @@
 // h itself, minus the batch members that rank below h (read from x's
 // batch-neighbour list) and, in the pair phase, minus the other neighbours of h
 // that meet x.
-// Neighbour pairs {x, y} of h that intersect are found by grouping the member
-// vertices of all neighbours of h by vertex in LDS (work sum_{x in N(h)} |x|),
-// each pair counted at its smallest common vertex; they get their true class in
-// place of the disjoint-pair class that the histogram pass gave them.
+// Neighbour pairs {x, y} of h that intersect get their true class in place of
+// the disjoint-pair class that the histogram pass gave them.  They are found
+// along the runs of the vertices that two or more neighbours share: a wave
+// takes a neighbour x, walks the runs of x's shared vertices and counts
+// |x & y| and |h & x & y| for every later neighbour y in a table of LDS counters
+// indexed by the neighbour's number (no hashing, no sort), then walks the runs
+// again, taking each y's counter as it empties it.
 #include "triad_common.h"
 
 namespace {
 
 using namespace tri;
 
-constexpr uint32_t ARENA_S = 8192;    // 32 KB of LDS: four workgroups per CU
-constexpr uint32_t ARENA_M = 37888;   // 148 KB of LDS: one workgroup per CU
-constexpr uint32_t K_MAX = 0xfffffu;  // neighbours with 20 bits
-constexpr int KEY_IN = 20;             // entry key: vertex << KEY_V | [vertex in h] << KEY_IN | neighbour
-constexpr int KEY_V = 21;
-constexpr uint32_t W_MAX = 1u << 21;   // entries of a centre: run starts take 21 bits
-constexpr int EMIT_HI = 20;            // vertex-pair key: lo run << EMIT_LO | hi run << EMIT_HI | neighbour
-constexpr int EMIT_LO = 41;
-// A centre with this many neighbour-row entries or neighbours goes to the 2-hop
-// kernel, which shares it among several workgroups: in dense neighbourhoods its
-// runs are long (enumerating their pairs is quadratic in one workgroup) and its
-// neighbours share many vertices (the vertex pairs of the aggregated phase blow up).
-constexpr uint32_t W_2HOP = 65536;
-constexpr uint32_t K_2HOP = 0x4000u;
-constexpr uint64_t E2_2HOP = 65536;  // ... and so does one whose neighbours hold this many vertex pairs
-                                     // (He2Params::e2_2hop overrides it)
-// entry key: vertex << 21 | [vertex in h] << 20 | neighbour index (20 bits)
+constexpr uint32_t ARENA_S = 7168;     // stage 0: 28 KB of LDS, 256 threads, four workgroups per CU
+constexpr int WG_L = 512;              // global stage: threads per workgroup
+constexpr uint32_t CNT_L = 2048;       // ... counters per wave: neighbours are taken in windows of this many
+constexpr uint32_t LDS_L = 16640;      // ... LDS words: counters of 8 waves, or two bitmaps, or a (c, f) histogram
+static_assert(LDS_L >= (WG_L / 64) * CNT_L && LDS_L >= 2 * (HGT_MAX_CARD + 1), "global stage LDS");
+constexpr uint32_t K_MAX_N = 1u << 24; // neighbours of a centre (a run cursor and its flag share a word)
 
 // open-addressing tables of any capacity: slot = multiply-shift hash scaled to cap
 __device__ __forceinline__ uint32_t fr_slot(uint32_t key, uint32_t cap) {
@@ -49,170 +41,39 @@ __device__ __forceinline__ uint32_t fr_slot(uint32_t key, uint32_t cap) {
 __device__ __forceinline__ uint32_t fr_next(uint32_t s, uint32_t cap) { return s + 1 == cap ? 0 : s + 1; }
 __device__ __forceinline__ uint32_t hash_cap(uint32_t n) { return n + n / 2 + 32; }  // load <= 2/3
 
-__device__ __forceinline__ void fr_add(uint32_t* keys, uint32_t* vals, uint32_t cap, uint32_t key, uint32_t inc) {
+// Adds inc to key's value and returns key's slot.
+__device__ __forceinline__ uint32_t fr_add(uint32_t* keys, uint32_t* vals, uint32_t cap, uint32_t key, uint32_t inc) {
     uint32_t s = fr_slot(key, cap);
     for (uint32_t probe = 0; probe < cap; probe++) {
         uint32_t k = __atomic_load_n(&keys[s], __ATOMIC_RELAXED);
         if (k == HGT_EMPTY) {
             uint32_t prev = atomicCAS(&keys[s], HGT_EMPTY, key);
-            if (prev == HGT_EMPTY || prev == key) { atomicAdd(&vals[s], inc); return; }
+            if (prev == HGT_EMPTY || prev == key) { atomicAdd(&vals[s], inc); return s; }
         } else if (k == key) {
             atomicAdd(&vals[s], inc);
-            return;
+            return s;
         }
         s = fr_next(s, cap);
     }
+    return 0;  // unreachable: tables hold more slots than keys
 }
 
-// One compare-exchange of the bitonic network between lanes: the lane whose
-// index has a zero at hb (the highest bit of the mask m) keeps the smaller key.
-__device__ __forceinline__ uint64_t cx_lanes(uint64_t x, uint32_t i, uint32_t m, uint32_t hb) {
-    const uint64_t y = __shfl_xor(x, (int)m, 64);
-    return (i & hb) ? (x > y ? x : y) : (x < y ? x : y);
-}
-
-// The steps of the network whose masks are below 64, in registers: all levels
-// up to 64 (first) or the strides 32 .. 1 of a larger level.  Keys past n enter
-// as +infinity and are not stored.
-__device__ __forceinline__ void sort_lane_steps(uint64_t* k, uint32_t n, bool first) {
-    for (uint32_t b = 0; b < n; b += HGT_WG) {
-        const uint32_t i = b + threadIdx.x;
-        uint64_t x = i < n ? k[i] : ~0ull;
-        if (first) {
-            for (uint32_t size = 2; size <= 64; size <<= 1) {
-                x = cx_lanes(x, i, size - 1, size >> 1);
-                for (uint32_t st = size >> 2; st > 0; st >>= 1) x = cx_lanes(x, i, st, st);
-            }
-        } else {
-            for (uint32_t st = 32; st > 0; st >>= 1) x = cx_lanes(x, i, st, st);
-        }
-        if (i < n) k[i] = x;
-    }
-    __syncthreads();
-}
-
-// Ascending bitonic sort of n keys in place by the whole workgroup.  Each level
-// of the network compares i with its mirror in the block (mask size - 1), then
-// with i ^ stride for stride = size/4 .. 1, the smaller key going first; absent
-// keys past n behave as +infinity, so no padding to a power of two is stored.
-// Masks of 64 and more go through memory, one pass each; the smaller ones stay
-// inside a wavefront's 64 consecutive keys and run in registers.
-__device__ __forceinline__ void sort_keys(uint64_t* k, uint32_t n) {
-    if (n < 2) return;
-    const uint32_t N = (uint32_t)pow2ceil64(n);
-    sort_lane_steps(k, n, true);
-    for (uint32_t size = 128; size <= N; size <<= 1) {
-        for (uint32_t i = threadIdx.x; i < n; i += HGT_WG) {
-            uint32_t p = i ^ (size - 1);
-            if (p > i && p < n) {
-                uint64_t a = k[i], b = k[p];
-                if (b < a) { k[i] = b; k[p] = a; }
-            }
-        }
-        __syncthreads();
-        for (uint32_t stride = size >> 2; stride >= 64; stride >>= 1) {
-            for (uint32_t i = threadIdx.x; i < n; i += HGT_WG) {
-                uint32_t p = i ^ stride;
-                if (p > i && p < n) {
-                    uint64_t a = k[i], b = k[p];
-                    if (b < a) { k[i] = b; k[p] = a; }
-                }
-            }
-            __syncthreads();
-        }
-        sort_lane_steps(k, n, false);
-    }
-}
-
-// The same sort for keys in global memory, staged through an LDS tile of TILE_K
-// keys: every tile is first sorted in LDS (all levels up to TILE_K), and in each
-// larger level only the strides of TILE_K and more go through global memory; the
-// strides below run in the tile.  Absent keys past n are +infinity as above.
-constexpr uint32_t TILE_K = 4096;  // 32 KB of LDS
-
-// one compare-exchange step in the tile: i against i ^ mask, the smaller key first
-__device__ __forceinline__ void tile_cx(uint64_t* t, uint32_t mask) {
-    for (uint32_t i = threadIdx.x; i < TILE_K; i += HGT_WG) {
-        const uint32_t p = i ^ mask;
-        if (p > i) {
-            const uint64_t a = t[i], b = t[p];
-            if (b < a) { t[i] = b; t[p] = a; }
-        }
-    }
-    __syncthreads();
-}
-
-// strides stride .. 1 of a level inside the tile (strides below 64 in registers)
-__device__ __forceinline__ void tile_strides(uint64_t* t, uint32_t stride) {
-    for (; stride >= 64; stride >>= 1) tile_cx(t, stride);
-    sort_lane_steps(t, TILE_K, false);
-}
-
-__device__ void sort_keys_tiled(uint64_t* k, uint32_t n, uint64_t* tile) {
-    if (n < 2) return;
-    const uint32_t N = (uint32_t)pow2ceil64(n);
-    // every tile sorted on its own: all levels up to TILE_K
-    for (uint32_t t0 = 0; t0 < n; t0 += TILE_K) {
-        const uint32_t m = n - t0 < TILE_K ? n - t0 : TILE_K;
-        for (uint32_t i = threadIdx.x; i < TILE_K; i += HGT_WG) tile[i] = i < m ? k[t0 + i] : ~0ull;
-        __syncthreads();
-        sort_lane_steps(tile, TILE_K, true);
-        for (uint32_t size = 128; size <= TILE_K; size <<= 1) {
-            tile_cx(tile, size - 1);
-            tile_strides(tile, size >> 2);
-        }
-        for (uint32_t i = threadIdx.x; i < m; i += HGT_WG) k[t0 + i] = tile[i];
-        __syncthreads();
-    }
-    for (uint32_t size = 2 * TILE_K; size <= N; size <<= 1) {
-        for (uint32_t i = threadIdx.x; i < n; i += HGT_WG) {  // the mirror step, in global memory
-            uint32_t p = i ^ (size - 1);
-            if (p > i && p < n) {
-                uint64_t a = k[i], b = k[p];
-                if (b < a) { k[i] = b; k[p] = a; }
-            }
-        }
-        __syncthreads();
-        for (uint32_t stride = size >> 2; stride >= TILE_K; stride >>= 1) {
-            for (uint32_t i = threadIdx.x; i < n; i += HGT_WG) {
-                uint32_t p = i ^ stride;
-                if (p > i && p < n) {
-                    uint64_t a = k[i], b = k[p];
-                    if (b < a) { k[i] = b; k[p] = a; }
-                }
-            }
-            __syncthreads();
-        }
-        for (uint32_t t0 = 0; t0 < n; t0 += TILE_K) {  // strides below TILE_K, per tile
-            const uint32_t m = n - t0 < TILE_K ? n - t0 : TILE_K;
-            for (uint32_t i = threadIdx.x; i < TILE_K; i += HGT_WG) tile[i] = i < m ? k[t0 + i] : ~0ull;
-            __syncthreads();
-            tile_strides(tile, TILE_K >> 1);
-            for (uint32_t i = threadIdx.x; i < m; i += HGT_WG) k[t0 + i] = tile[i];
-            __syncthreads();
-        }
-    }
+// A word that atomics write: in global memory they act in the L2, so it is read there.
+template <bool GLOBAL>
+__device__ __forceinline__ uint32_t ld_at(const uint32_t* p) {
+    if (GLOBAL) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return *p;
 }
 
 struct Sh2 {
-    uint32_t h, rank, hlen, lh, K, W, defer, stop;
+    uint32_t h, rank, hlen, lh, K, W, S, defer, stop, over;
     uint32_t gi, cur_g, skip;
+    uint32_t slice, nslice;
     uint64_t hoff;
+    uint32_t ws[WG_L / 64];
     uint32_t ncap;
-    uint32_t o_nh, o_ent;  // arena word offsets
-    uint32_t agg, nbig, nb1;   // aggregated pair phase: taken, long runs, long-run members of length > 1
-    uint32_t fits_g;           // ... its tables fit the global stage's arena
-    uint32_t to2;              // too many vertex pairs: the centre goes to the 2-hop kernel
-    uint64_t acc2[NWAVE * HGT_N_HE_CLASSES];  // the centre's changes, doubled (ordered pairs once)
-    uint32_t ws[NWAVE];
     uint64_t g[8];
 };
-
-__device__ __forceinline__ void acc_sub(uint64_t* acc, int cls) { acc_add(acc, cls, ~0ull); }
-__device__ __forceinline__ void acc32_add(uint32_t* acc, int cls, uint32_t v) {
-    if (cls < 255) atomicAdd(&acc[cls], v);
-}
-
 
 // ---- per-centre neighbourhood (shared by the neighbour pass and the delta kernel)
 // Builds N(h) -> c_x in the hash at keys/vals (already cleared), reading the
@@ -222,7 +83,7 @@ __device__ __forceinline__ void build_nh(const GraphView& G, uint32_t h, uint32_
     for (uint32_t p = threadIdx.x; p < lh; p += HGT_WG) {
         uint32_t k = seg_of<uint32_t>(pre, hlen, p);
         uint32_t x = G.v2h[voff[k] + (p - pre[k])];
-        if (x != h) fr_add(keys, vals, cap, x, 1u);
+        if (x != h) (void)fr_add(keys, vals, cap, x, 1u);
     }
 }
 
@@ -324,13 +185,36 @@ __device__ void nbr_pass_body(const NbrParams& P, uint32_t* arena, uint64_t aren
         build_nh(G.g, h, hlen, lh, pre, voff, keys, vals, cap);
         __syncthreads();
         uint32_t* hd = G.hpool + 2 * sh.hoff;
-        for (uint32_t s = tid; s < cap; s += HGT_WG) {
-            uint32_t x = keys[s];
-            if (x == HGT_EMPTY) continue;
-            uint32_t c = vals[s];
-            uint32_t fd = hlen > c ? 1u : 0u;
+        // the centre's entries take one range of the entry array, reserved at once (one
+        // atomic per centre on the shared cursor instead of one per entry)
+        if (P.emit_entries) {
+            if (tid == 0) sh.K = 0;
+            __syncthreads();
+            uint32_t mine = 0;
+            for (uint32_t s = tid; s < cap; s += HGT_WG) mine += ld_at<BIG>(&keys[s]) != HGT_EMPTY ? 1u : 0u;
+            if (mine) atomicAdd(&sh.K, mine);
+            __syncthreads();
+            if (tid == 0) {
+                sh.g[0] = atomicAdd((unsigned long long*)P.n_entries, (unsigned long long)sh.K);
+                sh.K = 0;
+            }
+            __syncthreads();
+        }
+        const uint64_t ebase = P.emit_entries ? sh.g[0] : 0;
+        for (uint32_t s0 = 0; s0 < cap; s0 += HGT_WG) {
+            const uint32_t s = s0 + tid;
+            const uint32_t x = s < cap ? ld_at<BIG>(&keys[s]) : HGT_EMPTY;
+            uint32_t at = 0;
             if (P.emit_entries) {
-                uint64_t q = atomicAdd((unsigned long long*)P.n_entries, 1ull);
+                const uint64_t m = __ballot(x != HGT_EMPTY);
+                if ((tid & 63) == 0 && m) at = atomicAdd(&sh.K, (uint32_t)__popcll(m));
+                at = __shfl(at, 0, 64) + __popcll(m & ((1ull << (tid & 63)) - 1));
+            }
+            if (x == HGT_EMPTY) continue;
+            const uint32_t c = ld_at<BIG>(&vals[s]);
+            const uint32_t fd = hlen > c ? 1u : 0u;
+            if (P.emit_entries) {
+                const uint64_t q = ebase + at;
                 if (q < P.entries_cap) {
                     P.ent_x[q] = (uint32_t)(G.id_base + x);
                     P.ent_d[q] = h;
@@ -420,198 +304,303 @@ __global__ void k_entries_check(Multi M, const uint64_t* n_entries_p, uint64_t c
 // ===========================================================================
 // the delta kernel
 // ===========================================================================
-// Stage s takes its centres from the batch (s = 0) or from list s-1 and moves
-// the centres whose tables do not fit its arena to list s; list 2 feeds the
-// 2-hop kernel.  Stages 0 and 1 keep the arena in LDS (32 KB, 148 KB), stage 2
-// in a 1 MB slice of global memory per workgroup.
-// |x & y|, |x & y & h| and the smallest common vertex of two sorted rows
-__device__ __forceinline__ void row_meet(const uint32_t* X, uint32_t xl, const uint32_t* Y, uint32_t yl,
-                                         const uint32_t* hm, uint32_t hlen, uint32_t& s, uint32_t& shh,
-                                         uint32_t& first) {
-    uint32_t a = 0, b = 0;
-    s = 0;
-    shh = 0;
-    first = HGT_EMPTY;
-    while (a < xl && b < yl) {
-        uint32_t va = X[a], vb = Y[b];
-        if (va < vb) a++;
-        else if (va > vb) b++;
-        else {
-            if (s == 0) first = va;
-            s++;
-            shh += contains_u32(hm, hlen, va) ? 1u : 0u;
-            a++;
-            b++;
+// Stage 0 takes its centres from the batch, keeps every table in 28 KB of LDS and
+// moves the centres that do not fit to list 0.  The global stage (stage 2) takes
+// list 0 and keeps its tables in a slice of global memory per workgroup, the
+// counters in LDS; a centre with many pairs is shared by several workgroups
+// (slices), each of which builds the tables and takes every nslice-th neighbour.
+// What does not fit there either goes to list 2, which feeds the 2-hop kernel.
+
+// Counters of the class changes of the workgroup's graph so far.  Every lane of
+// a wave adds to one of few classes, so the 32-bit pair counters are kept 32-fold
+// (a copy per lane pair: adds of one instruction meet at most two to a word) and
+// the 64-bit open-path counters too.
+constexpr int COPIES = 32;
+struct He2Acc {
+    uint32_t pair[HGT_N_HE_CLASSES * COPIES];  // signed changes
+    uint64_t open[8 * COPIES];                 // [hlen > c] << 2 | [x only] << 1 | [y only]
+    uint64_t tot[HGT_N_HE_CLASSES];
+    uint8_t cls8[8];                           // class of an open path by the same three bits
+    uint8_t pad[8];
+};
+
+__device__ __forceinline__ void pair_add(He2Acc& A, uint32_t cls, uint32_t v) {
+    if (cls < 255) atomicAdd(&A.pair[cls * COPIES + (threadIdx.x & (COPIES - 1))], v);
+}
+
+// Moves the 32-bit counters into the 64-bit totals (any wave, any time).
+__device__ __forceinline__ void pair_fold(He2Acc& A) {
+    for (uint32_t i = threadIdx.x & 63; i < HGT_N_HE_CLASSES * COPIES; i += 64) {
+        const int32_t v = (int32_t)atomicExch(&A.pair[i], 0u);
+        if (v) atomicAdd((unsigned long long*)&A.tot[i / COPIES], (unsigned long long)(int64_t)v);
+    }
+}
+constexpr uint32_t FOLD_AT = 1u << 25;  // pairs of one wave after which it folds: no counter passes 2^31
+
+// Adds the workgroup's counts to graph g's phase accumulators and clears them.
+template <int WG>
+__device__ void he2_flush_graph(const He2Params& P, uint32_t g, He2Acc& A) {
+    __syncthreads();
+    if (threadIdx.x < 64) pair_fold(A);
+    for (uint32_t i = threadIdx.x; i < 8 * COPIES; i += WG) {
+        const uint32_t c = A.cls8[i / COPIES];
+        if (A.open[i] && c < 255) atomicAdd((unsigned long long*)&A.tot[c], (unsigned long long)A.open[i]);
+        A.open[i] = 0;
+    }
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < HGT_N_HE_CLASSES; i += WG) {
+        if (g != 0xffffffffu && A.tot[i])
+            atomicAdd((unsigned long long*)&P.M.graphs[g].out_he[i], (unsigned long long)A.tot[i]);
+        A.tot[i] = 0;
+    }
+    __syncthreads();
+}
+
+// Exclusive prefix over i of f(i), i < n, by the whole workgroup: every wave takes
+// a contiguous part (one reduce pass, one scan pass, one barrier between them).
+// put(i, before) stores the prefix.  Ends without a barrier.
+template <int WG, class F, class S>
+__device__ __forceinline__ void wg_prefix(uint32_t n, uint32_t* ws, F f, S put) {
+    constexpr uint32_t NW = WG / 64;
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t per = ((n + NW * 64 - 1) / (NW * 64)) * 64;
+    const uint32_t b = wave * per < n ? wave * per : n, e = b + per < n ? b + per : n;
+    uint32_t sum = 0;
+    for (uint32_t i = b + lane; i < e; i += 64) sum += f(i);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    if (lane == 0) ws[wave] = sum;
+    __syncthreads();
+    uint32_t base = 0;
+    for (uint32_t w = 0; w < wave; w++) base += ws[w];
+    for (uint32_t i0 = b; i0 < e; i0 += 64) {
+        const uint32_t i = i0 + lane;
+        const uint32_t v = i < e ? f(i) : 0;
+        uint32_t inc = v;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t t = __shfl_up(inc, o, 64);
+            if (lane >= (uint32_t)o) inc += t;
         }
+        if (i < e) put(i, base + inc - v);
+        base += __shfl(inc, 63, 64);
     }
 }
 
-// The class adjustments of one intersecting neighbour pair {x, y} of centre h
-// (|x & y| = s, |h & x & y| = shh): in a full count the closed triad at the
-// smallest-ID centre, in a delta the open-path and disjoint-pair corrections.
-__device__ __forceinline__ void pair_class(const He2Params& P, const Tables& T, uint32_t h, uint32_t hlen,
-                                           const uint32_t* nl_x, const uint32_t* nl_meta, uint32_t xi, uint32_t yi,
-                                           uint32_t s, uint32_t shh, uint32_t* myacc32) {
-    const uint32_t mx = nl_meta[xi], my = nl_meta[yi];
+// N(h) -> c_x in the hash keys/vals, from the lists of h's members.
+template <int WG>
+__device__ __forceinline__ void he2_nh(const GraphView& G, uint32_t h, uint32_t hlen, uint32_t lh, const uint32_t* pre,
+                                       const uint64_t* voff, uint32_t* keys, uint32_t* vals, uint32_t cap) {
+    for (uint32_t s = threadIdx.x; s < cap; s += WG) { keys[s] = HGT_EMPTY; vals[s] = 0; }
+    __syncthreads();
+    for (uint32_t p = threadIdx.x; p < lh; p += WG) {
+        const uint32_t k = seg_of<uint32_t>(pre, hlen, p);
+        const uint32_t x = G.v2h[voff[k] + (p - pre[k])];
+        if (x != h) (void)fr_add(keys, vals, cap, x, 1u);
+    }
+    __syncthreads();
+}
+
+// The hash's neighbours as numbers 0 .. K-1: ID and meta (c | len << 14 | eligible
+// << 28 | h < x << 29).
+template <int WG, bool GLOBAL>
+__device__ __forceinline__ void he2_compact(const He2Params& P, const HeGraph& G, Sh2& sh, const uint32_t* keys,
+                                            const uint32_t* vals, uint32_t cap, uint32_t* nl_x, uint32_t* nl_meta) {
+    const uint32_t lane = threadIdx.x & 63;
+    for (uint32_t s0 = 0; s0 < cap; s0 += WG) {
+        const uint32_t s = s0 + threadIdx.x;
+        const uint32_t x = s < cap ? ld_at<GLOBAL>(&keys[s]) : HGT_EMPTY;
+        const uint64_t m = __ballot(x != HGT_EMPTY);
+        if (!m) continue;
+        uint32_t q = 0;
+        if (lane == 0) q = atomicAdd(&sh.K, (uint32_t)__popcll(m));
+        q = __shfl(q, 0, 64) + __popcll(m & ((1ull << lane) - 1));
+        if (x == HGT_EMPTY) continue;
+        const uint32_t c = ld_at<GLOBAL>(&vals[s]), len = G.g.h_len[x];
+        const bool elig = P.static_mode || !lower_ranked_member(G.mark[x], G.epoch, sh.rank);
+        nl_x[q] = x;
+        nl_meta[q] = c | (len << 14) | ((uint32_t)elig << 28) | ((sh.h < x ? 1u : 0u) << 29);
+    }
+    __syncthreads();
+}
+
+// Disjoint-pair classes of all eligible neighbour pairs, from a histogram over
+// (f = [|x| > c], c): every pair of neighbours as if x and y were disjoint.
+// cnt: 2 (hlen + 1) LDS words.
+template <int WG>
+__device__ void he2_disjoint(Sh2& sh, const Tables& T, He2Acc& A, const uint32_t* nl_meta, uint32_t K, uint32_t hlen,
+                             uint32_t* cnt) {
+    const uint32_t tid = threadIdx.x, lane = tid & 63, Wc = hlen + 1;
+    for (uint32_t i = tid; i < 2 * Wc; i += WG) cnt[i] = 0;
+    if (tid < 8) sh.g[tid] = 0;
+    __syncthreads();
+    for (uint32_t i = tid; i < K; i += WG) {
+        const uint32_t m = nl_meta[i];
+        if (meta_elig(m)) atomicAdd(&cnt[(meta_len(m) > meta_c(m) ? Wc : 0) + meta_c(m)], 1u);
+    }
+    __syncthreads();
+    // inclusive prefix over c of each half, one wave a half
+    if (tid < 128) {
+        uint32_t* row = cnt + (tid >> 6) * Wc;
+        uint32_t base = 0;
+        for (uint32_t i0 = 0; i0 < Wc; i0 += 64) {
+            const uint32_t i = i0 + lane;
+            uint32_t inc = i < Wc ? row[i] : 0;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t t = __shfl_up(inc, o, 64);
+                if (lane >= (uint32_t)o) inc += t;
+            }
+            if (i < Wc) row[i] = base + inc;
+            base += __shfl(inc, 63, 64);
+        }
+    }
+    __syncthreads();
+    // n_f(c) neighbours with c_x = c; S_f(k) of them with c_x >= k.  Pairs with
+    // c_x + c_y >= |h| leave nothing of h alone.
+    const uint64_t N0 = cnt[hlen], N1 = cnt[Wc + hlen];
+    uint64_t g00 = 0, g01 = 0, g11 = 0, d0 = 0, d1 = 0;
+    for (uint32_t c = 1 + tid; c <= hlen; c += WG) {
+        const uint64_t n0 = cnt[c] - cnt[c - 1], n1 = cnt[Wc + c] - cnt[Wc + c - 1];
+        const uint32_t k = hlen - c;
+        const uint64_t s0 = N0 - (k ? cnt[k - 1] : 0), s1 = N1 - (k ? cnt[Wc + k - 1] : 0);
+        g00 += n0 * s0;
+        g01 += n0 * s1;
+        g11 += n1 * s1;
+        if (2 * c >= hlen) { d0 += n0; d1 += n1; }
+    }
+    if (g00 | g01 | g11 | d0 | d1) {
+        atomicAdd((unsigned long long*)&sh.g[0], (unsigned long long)g00);
+        atomicAdd((unsigned long long*)&sh.g[1], (unsigned long long)g01);
+        atomicAdd((unsigned long long*)&sh.g[2], (unsigned long long)g11);
+        atomicAdd((unsigned long long*)&sh.g[3], (unsigned long long)d0);
+        atomicAdd((unsigned long long*)&sh.g[4], (unsigned long long)d1);
+    }
+    __syncthreads();
+    if (tid == 0) {
+        const uint64_t G00 = (sh.g[0] - sh.g[3]) / 2, G11 = (sh.g[2] - sh.g[4]) / 2, G01 = sh.g[1];
+        const uint64_t T00 = N0 * (N0 - (N0 ? 1 : 0)) / 2, T11 = N1 * (N1 - (N1 ? 1 : 0)) / 2, T01 = N0 * N1;
+        acc_add(A.tot, T.he[40 | 1], T00 - G00);
+        acc_add(A.tot, T.he[40], G00);
+        acc_add(A.tot, T.he[40 | 4 | 1], T01 - G01);
+        acc_add(A.tot, T.he[40 | 4], G01);
+        acc_add(A.tot, T.he[40 | 6 | 1], T11 - G11);
+        acc_add(A.tot, T.he[40 | 6], G11);
+    }
+}
+
+// Open paths h - x - y of one neighbour x through its histogram.
+__device__ __forceinline__ void he2_open(const He2Params& P, const HeGraph& G, const Sh2& sh, He2Acc& A, uint32_t x,
+                                         uint32_t m, uint64_t* st) {
+    const uint32_t hlen = sh.hlen, c = meta_c(m), lx = meta_len(m);
+    const uint32_t thr = lx - c;  // k < thr  <=>  x has a vertex outside h and y
+    const uint64_t* H = (const uint64_t*)(G.hpool + 2 * G.g.h_off[x]);  
+    const uint64_t xs = G.id_base + x;
+    const uint64_t bo = P.bl_off[xs], bn = P.bl_cnt[xs];
+    if (P.stats)  // x's histogram, list bounds and batch-neighbour entries
+        atomicAdd((unsigned long long*)&st[1], (unsigned long long)(8ull * lx + 16 + 8ull * bn));
+    // a_f: neighbours y with |x & y| < thr (x keeps a private vertex), b_f: the rest
+    uint64_t a0 = 0, a1 = 0, b0 = 0, b1 = 0;
+    for (uint32_t k = 1; k <= lx; k++) {
+        const uint64_t hh = H[k - 1];
+        const uint64_t h0 = (uint32_t)hh, h1 = hh >> 32;
+        if (k < thr) { a0 += h0; a1 += h1; }
+        else { b0 += h0; b1 += h1; }
+    }
+    // the histogram holds h itself: k = c, y only = |h| > c
+    if (c < thr) { if (hlen > c) a1--; else a0--; }
+    else { if (hlen > c) b1--; else b0--; }
+    // every lower-ranked batch member adjacent to x (the pair phase leaves out
+    // the ones that meet h)
+    for (uint64_t e = 0; e < bn; e++) {
+        const uint64_t pay = P.bl_pay[bo + e];
+        if ((uint32_t)(pay >> 32) >= sh.rank) continue;
+        const uint32_t k = (uint32_t)(pay >> 1) & 0x7fffffffu, f = (uint32_t)pay & 1u;
+        if (k < thr) { if (f) a1--; else a0--; }
+        else { if (f) b1--; else b0--; }
+    }
+    uint64_t* o = A.open + (hlen > c ? 4 * COPIES : 0) + (threadIdx.x & (COPIES - 1));
+    if (b0) atomicAdd((unsigned long long*)&o[0], (unsigned long long)b0);
+    if (b1) atomicAdd((unsigned long long*)&o[COPIES], (unsigned long long)b1);
+    if (a0) atomicAdd((unsigned long long*)&o[2 * COPIES], (unsigned long long)a0);
+    if (a1) atomicAdd((unsigned long long*)&o[3 * COPIES], (unsigned long long)a1);
+}
+
+// The class changes of one intersecting neighbour pair (|x & y| = s, |h & x & y| =
+// shh), both eligible: in a full count the closed triad at its smallest-ID centre, in
+// a delta the open paths h-x-y and h-y-x taken back and the true class in place of the
+// disjoint one.
+__device__ __forceinline__ void he2_pair(const He2Params& P, const Tables& T, He2Acc& A, uint32_t hlen, uint32_t mx,
+                                         uint32_t my, uint32_t s, uint32_t shh) {
     const uint32_t xl = meta_len(mx), yl = meta_len(my), cx = meta_c(mx), cy = meta_c(my);
+    const uint32_t cf = (hlen > cx + cy ? 1u : 0u) | (xl > cx ? 2u : 0u) | (yl > cy ? 4u : 0u) | 40u;
+    const uint32_t ct = (hlen + shh > cx + cy ? 1u : 0u) | (xl + shh > cx + s ? 2u : 0u) | (yl + shh > cy + s ? 4u : 0u) |
+                        (cx > shh ? 8u : 0u) | (s > shh ? 16u : 0u) | (cy > shh ? 32u : 0u) | (shh ? 64u : 0u);
+    pair_add(A, T.he[cf], ~0u);
     if (P.static_mode) {
-        // closed triple: counted at its smallest-ID centre only
-        acc32_add(myacc32, T.he[venn_code((int)hlen, (int)xl, (int)yl, (int)cx, 0, (int)cy, 0)], ~0u);
-        if (h < nl_x[xi] && h < nl_x[yi])
-            acc32_add(myacc32, T.he[venn_code((int)hlen, (int)xl, (int)yl, (int)cx, (int)s, (int)cy, (int)shh)], 1u);
+        if ((mx & my) >> 29 & 1u) pair_add(A, T.he[ct], 1u);
         return;
     }
-    // a lower-ranked batch member was already taken off its partner's open paths
-    if (meta_elig(mx) && meta_elig(my)) {
-        uint32_t base = (hlen > cx ? 1u : 0u) | 24u;
-        acc32_add(myacc32, T.he[base | (xl - cx > s ? 2u : 0u) | (yl > s ? 4u : 0u)], ~0u);
-        base = (hlen > cy ? 1u : 0u) | 24u;
-        acc32_add(myacc32, T.he[base | (yl - cy > s ? 2u : 0u) | (xl > s ? 4u : 0u)], ~0u);
-        int ct = T.he[venn_code((int)hlen, (int)xl, (int)yl, (int)cx, (int)s, (int)cy, (int)shh)];
-        int cf = T.he[venn_code((int)hlen, (int)xl, (int)yl, (int)cx, 0, (int)cy, 0)];
-        if (ct != cf) {
-            acc32_add(myacc32, ct, 1u);
-            acc32_add(myacc32, cf, ~0u);
+    pair_add(A, T.he[ct], 1u);
+    pair_add(A, A.cls8[(hlen > cx ? 4u : 0u) | (xl > cx + s ? 2u : 0u) | (yl > s ? 1u : 0u)], ~0u);
+    pair_add(A, A.cls8[(hlen > cy ? 4u : 0u) | (yl > cy + s ? 2u : 0u) | (xl > s ? 1u : 0u)], ~0u);
+}
+
+// Rows of all neighbours, a wave per 64 of them: per(xi, v, j) for every member v,
+// j counting the members of all rows (row_at[xi] + k for neighbour xi's k-th).  first:
+// the rows are laid out one after the other (row_at is written, sh.W their total);
+// else their members are read back from `stash`, where per() put them.
+template <int WG, class F>
+__device__ __forceinline__ void he2_rows(const GraphView& G, Sh2& sh, const uint32_t* nl_x, const uint32_t* nl_meta,
+                                         uint32_t* row_at, uint32_t K, const uint32_t* stash, uint32_t (*wpre)[65],
+                                         uint64_t (*woff)[64], bool first, F per) {
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (uint32_t c0 = wave * 64; c0 < K; c0 += WG) {
+        const uint32_t cnt = K - c0 < 64 ? K - c0 : 64;
+        uint32_t d = 0;
+        if (lane < cnt) {
+            d = meta_len(nl_meta[c0 + lane]);
+            if (first) woff[wave][lane] = G.h_off[nl_x[c0 + lane]];
         }
-    }
-}
-
-// ---- single-vertex pairs, aggregated.  Take neighbours x, y of h that meet
-// in exactly one vertex v (vin: v in h).  The class changes of the pair depend
-// on y only through two bits gy and through how c_y = |y & h| compares with
-// |h| - c_x (rng 0: less, 1: equal, 2: greater), so along a long run of
-// neighbours at v they are counted from a histogram over (gy, c_y).
-constexpr uint32_t RUN_DIRECT = 64;  // runs up to this length enumerate their pairs
-static_assert(RUN_DIRECT <= 64, "short-run partners are counted in 6-bit fields");
-
-__device__ __forceinline__ uint32_t single_gy(uint32_t vin, uint32_t yl, uint32_t cy) {
-    return vin ? ((yl > cy ? 1u : 0u) | (cy > 1 ? 2u : 0u)) : ((yl > cy ? 1u : 0u) | (yl - cy > 1 ? 2u : 0u));
-}
-
-// Venn codes of the closed triad {h, x, y} (ct) and of the same x, y taken as
-// disjoint (cf), for a pair meeting in one vertex (the regions of venn_code
-// with |x & y| = 1 and |h & x & y| = vin).
-__device__ __forceinline__ void single_codes(uint32_t vin, uint32_t xl, uint32_t cx, uint32_t gy, uint32_t rng, int& ct,
-                                             int& cf) {
-    cf = (rng == 0 ? 1 : 0) | (xl > cx ? 2 : 0) | ((gy & 1u) ? 4 : 0) | 8 | 32;
-    if (vin)
-        ct = (rng <= 1 ? 1 : 0) | (xl > cx ? 2 : 0) | ((gy & 1u) ? 4 : 0) | (cx > 1 ? 8 : 0) | ((gy & 2u) ? 32 : 0) | 64;
-    else
-        ct = (rng == 0 ? 1 : 0) | (xl - cx > 1 ? 2 : 0) | ((gy & 2u) ? 4 : 0) | 8 | 16 | 32;
-}
-
-// pair_class of a delta (not a full count) with every change weighted by w
-__device__ __forceinline__ void pair_class_w(const Tables& T, uint32_t hlen, uint32_t mx, uint32_t my, uint32_t s,
-                                             uint32_t shh, uint32_t w, uint32_t* myacc32) {
-    const uint32_t xl = meta_len(mx), yl = meta_len(my), cx = meta_c(mx), cy = meta_c(my);
-    const uint32_t nw = 0u - w;
-    if (meta_elig(mx) && meta_elig(my)) {
-        uint32_t base = (hlen > cx ? 1u : 0u) | 24u;
-        acc32_add(myacc32, T.he[base | (xl - cx > s ? 2u : 0u) | (yl > s ? 4u : 0u)], nw);
-        base = (hlen > cy ? 1u : 0u) | 24u;
-        acc32_add(myacc32, T.he[base | (yl - cy > s ? 2u : 0u) | (xl > s ? 4u : 0u)], nw);
-        int ct = T.he[venn_code((int)hlen, (int)xl, (int)yl, (int)cx, (int)s, (int)cy, (int)shh)];
-        int cf = T.he[venn_code((int)hlen, (int)xl, (int)yl, (int)cx, 0, (int)cy, 0)];
-        if (ct != cf) {
-            acc32_add(myacc32, ct, w);
-            acc32_add(myacc32, cf, nw);
+        uint32_t inc = d;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t t = __shfl_up(inc, o, 64);
+            if (lane >= (uint32_t)o) inc += t;
         }
-    }
-}
-
-// |x & y|, |x & y & h| and the two smallest common vertices of two sorted rows
-__device__ __forceinline__ void row_meet2(const uint32_t* X, uint32_t xl, const uint32_t* Y, uint32_t yl,
-                                          const uint32_t* hm, uint32_t hlen, uint32_t& s, uint32_t& shh,
-                                          uint32_t& f1, uint32_t& f2) {
-    uint32_t a = 0, b = 0;
-    s = 0;
-    shh = 0;
-    f1 = f2 = HGT_EMPTY;
-    while (a < xl && b < yl) {
-        uint32_t va = X[a], vb = Y[b];
-        if (va < vb) a++;
-        else if (va > vb) b++;
-        else {
-            if (s == 0) f1 = va;
-            else if (s == 1) f2 = va;
-            s++;
-            shh += contains_u32(hm, hlen, va) ? 1u : 0u;
-            a++;
-            b++;
+        const uint32_t tot = __shfl(inc, 63, 64);
+        uint32_t base = 0;
+        if (first) {
+            if (lane == 0) base = atomicAdd(&sh.W, tot);
+            base = __shfl(base, 0, 64);
+            if (lane < cnt) row_at[c0 + lane] = base + inc - d;
+        } else {
+            base = row_at[c0];
         }
-    }
-}
-
-__device__ __forceinline__ uint32_t lower_bound_u64(const uint64_t* a, uint32_t n, uint64_t key) {
-    uint32_t lo = 0, hi = n;
-    while (lo < hi) {
-        uint32_t mid = (lo + hi) >> 1;
-        if (a[mid] < key) lo = mid + 1; else hi = mid;
-    }
-    return lo;
-}
-
-// Pair number q of a run of R (pairs (a, b), a < b, ordered by a then b): the
-// largest a with a R - a (a + 1) / 2 <= q, from the quadratic's root, then
-// corrected by one step either way against rounding.
-__device__ __forceinline__ void tri_decode(uint32_t R, uint32_t q, uint32_t& a, uint32_t& b) {
-    const double r2 = 2.0 * (double)R - 1.0;
-    const double d = r2 * r2 - 8.0 * (double)q;
-    int64_t aa = (int64_t)((r2 - sqrt(d > 0.0 ? d : 0.0)) * 0.5);
-    if (aa < 0) aa = 0;
-    if (aa > (int64_t)R - 2) aa = (int64_t)R - 2;
-    auto before = [R](uint64_t x) { return x * (2ull * R - x - 1) / 2; };
-    while (aa > 0 && before((uint64_t)aa) > q) aa--;
-    while (aa + 1 <= (int64_t)R - 2 && before((uint64_t)aa + 1) <= q) aa++;
-    a = (uint32_t)aa;
-    b = a + 1 + (uint32_t)(q - before((uint64_t)aa));
-}
-
-// Neighbours x, y (vertex-pair entries ex, ey of one (u, w) run) that share u
-// and w: when u and w are their two smallest common vertices, their s single
-// changes give way to the pair's own.
-__device__ __forceinline__ void multi_pair(const GraphView& g, const Tables& T, uint32_t hlen, const uint32_t* hm,
-                                           const uint64_t* keys, const uint32_t* nl_x, const uint32_t* nl_meta,
-                                           uint64_t ex, uint64_t ey, uint64_t* stats, uint32_t* myacc32) {
-    const uint32_t xi = (uint32_t)ex & K_MAX, yi = (uint32_t)ey & K_MAX;
-    const uint32_t vu = (uint32_t)(keys[(uint32_t)(ex >> EMIT_LO)] >> KEY_V);
-    const uint32_t vw = (uint32_t)(keys[(uint32_t)(ex >> EMIT_HI) & (W_MAX - 1)] >> KEY_V);
-    const uint32_t mx = nl_meta[xi], my = nl_meta[yi];
-    uint32_t s, shh, f1, f2;
-    row_meet2(g.h2v + g.h_off[nl_x[xi]], meta_len(mx), g.h2v + g.h_off[nl_x[yi]], meta_len(my), hm, hlen, s, shh, f1, f2);
-    // the run order of u and w need not be the vertex order
-    if (!((f1 == vu && f2 == vw) || (f1 == vw && f2 == vu))) return;
-    if (stats) atomicAdd((unsigned long long*)&stats[ST_AGG_MULTI], 1ull);
-    pair_class_w(T, hlen, mx, my, s, shh, 1u, myacc32);
-    if (shh) pair_class_w(T, hlen, mx, my, 1, 1, 0u - shh, myacc32);
-    if (s > shh) pair_class_w(T, hlen, mx, my, 1, 0, 0u - (s - shh), myacc32);
-}
-
-// Adds the per-wave counts to graph g's phase accumulators and clears them.
-__device__ void he2_flush_graph(const He2Params& P, uint32_t g, uint64_t* acc_all) {
-    __syncthreads();
-    if (g != 0xffffffffu) {
-        const HeGraph& G = P.M.graphs[g];
-        for (int i = threadIdx.x; i < HGT_N_HE_CLASSES; i += HGT_WG) {
-            uint64_t s = 0;
-            for (int w = 0; w < NWAVE; w++) s += acc_all[w * HGT_N_HE_CLASSES + i];
-            if (s) atomicAdd((unsigned long long*)&G.out_he[i], (unsigned long long)s);
+        wpre[wave][lane + 1] = inc;
+        if (lane == 0) wpre[wave][0] = 0;
+        wave_sync();
+        for (uint32_t p = lane; p < tot; p += 64) {
+            const uint32_t k = seg_of<uint32_t>(wpre[wave], cnt, p);
+            const uint32_t v = first ? G.h2v[woff[wave][k] + (p - wpre[wave][k])] : stash[base + p];
+            per(c0 + k, v, base + p);
         }
+        wave_sync();
     }
-    __syncthreads();
-    for (int i = threadIdx.x; i < NWAVE * HGT_N_HE_CLASSES; i += HGT_WG) acc_all[i] = 0;
-    __syncthreads();
 }
 
-template <int STAGE>
-__device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t ARENA_WORDS, Sh2& sh, const Tables& T,
-                         uint64_t* acc_all, uint32_t* acc32_all, uint64_t* st, uint64_t* ph, uint64_t* tile) {
-    // keys in a global arena are sorted through the LDS tile; in an LDS arena in place
-    auto sort_any = [tile](uint64_t* k, uint32_t n) {
-        if (tile && n > TILE_K / 2) sort_keys_tiled(k, n, tile);
-        else sort_keys(k, n);
-    };
-    const int tid = threadIdx.x;
+template <bool BIG, int WG>
+__device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW, uint32_t* lds, Sh2& sh, const Tables& T,
+                         He2Acc& A, uint64_t* st, uint64_t* ph) {
+    constexpr uint32_t NW = WG / 64;
+    constexpr int STAGE = BIG ? 2 : 0;
+    constexpr uint32_t BM_LOG = BIG ? 18 : 14;          // bits of each vertex bitmap
+    constexpr uint32_t BM_WORDS = 1u << (BM_LOG - 5);
+    constexpr uint32_t POS = 0x7fffffffu;               // a run cursor; the top bit: the vertex lies in h
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ uint32_t wpre[NW][65];
+    __shared__ uint64_t woff[NW][64];
+    uint32_t folded = 0;    // pairs this wave counted since its last fold
     uint64_t t_mark = 0;    // thread 0: wall clock at the last phase mark (profiling)
     uint64_t t_centre = 0;  // ... at the start of the current centre
 #define HE2_MARK(i)                                     \
@@ -622,25 +611,29 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t ARE
             t_mark = t_;                                \
         }                                               \
     } while (0)
-    // this centre's changes, doubled (halved when the centre ends): a centre handed on
-    // to the next stage midway leaves nothing behind
-    uint64_t* cacc = sh.acc2 + (tid >> 6) * HGT_N_HE_CLASSES;
-    uint32_t* myacc32 = acc32_all + (tid >> 6) * HGT_N_HE_CLASSES;
     for (;;) {
         if (tid == 0) {
             uint32_t c = atomicAdd(&P.queue[STAGE], 1u);
-            sh.stop = c >= (STAGE == 0 ? P.M.total : (uint64_t)P.count[STAGE - 1]);
+            const uint64_t n = !BIG ? P.M.total : P.slice_pre[P.slice_cap + 1];
+            sh.stop = c >= n;
+            sh.slice = 0;
+            sh.nslice = 1;
             if (!sh.stop) {
                 uint32_t gi, h, rank;
-                if (STAGE == 0) {
+                if (!BIG) {
                     gi = multi_graph_of(P.M, c);
                     rank = (uint32_t)(c - P.M.base[gi]);
                     h = P.M.graphs[gi].centres[rank];
-                } else {
-                    uint64_t it = P.list[STAGE - 1][c];
+                } else {  // slice c of the centres' slices
+                    const uint32_t nc = (uint32_t)P.slice_pre[P.slice_cap];
+                    const uint32_t ci = seg_of<uint64_t>(P.slice_pre, nc, c);
+                    const uint64_t at = P.slice_pre[ci], next = ci + 1 < nc ? P.slice_pre[ci + 1] : n;
+                    sh.slice = (uint32_t)(c - at);
+                    sh.nslice = (uint32_t)(next - at);
+                    const uint64_t it = P.list[0][ci];
                     gi = (uint32_t)(it >> 32);
                     h = (uint32_t)it;
-                    rank = P.rank[STAGE - 1][c];
+                    rank = P.rank[0][ci];
                 }
                 const HeGraph& Gq = P.M.graphs[gi];
                 sh.gi = gi;
@@ -649,15 +642,15 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t ARE
                 sh.skip = *((volatile const int32_t*)Gq.status) != 0;
                 sh.hlen = Gq.g.h_len[h];
                 sh.hoff = Gq.g.h_off[h];
-                sh.defer = (3ull * sh.hlen + 4 > ARENA_WORDS / 2 || STAGE < P.force_stage || (STAGE == 1 && P.skip_lds148))
-                               ? 1u : 0u;
+                sh.defer = (3ull * sh.hlen + 4 > (BIG ? LDS_L : AW / 2) || STAGE < P.force_stage) ? 1u : 0u;
+                sh.K = sh.W = sh.S = sh.over = 0;
             }
         }
         __syncthreads();
         if (sh.stop) break;
         if (P.phase_ticks && tid == 0) t_mark = t_centre = wall_clock64();
         if (sh.gi != sh.cur_g) {  // the counts so far belong to the previous graph
-            he2_flush_graph(P, sh.cur_g, acc_all);
+            he2_flush_graph<WG>(P, sh.cur_g, A);
             if (tid == 0) sh.cur_g = sh.gi;
             __syncthreads();
         }
@@ -666,558 +659,255 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t ARE
             continue;
         }
         const HeGraph& G = P.M.graphs[sh.gi];
-        const uint32_t h = sh.h, hlen = sh.hlen;
-        // --- members of h: degree prefix and list offsets at the arena end
-        uint32_t* pre = arena + ARENA_WORDS - (3 * hlen + 4);
-        uint64_t* voff = (uint64_t*)(pre + ((hlen + 2) & ~1u));
-        if (((uintptr_t)voff & 7) != 0) voff = (uint64_t*)((uint32_t*)voff + 1);
-        if (!sh.defer) {
-            uint32_t lh = member_prefix(G.g, sh.hoff, hlen, pre, voff, sh.ws);
-            uint32_t cap = hash_cap(lh);
-            if (tid == 0) {
-                sh.lh = lh;
-                sh.ncap = cap;
-                sh.o_nh = 0;
-                uint64_t a = 2ull * cap + 3ull * hlen + 4, b = 2ull * cap + 4ull * lh + 1 + hlen + 2;
-                sh.defer = ((a > b ? a : b) > ARENA_WORDS) ? 1u : 0u;
-            }
-            __syncthreads();
-        }
-        if (sh.defer) {
-            if (tid == 0) {
-                uint32_t q = atomicAdd(&P.count[STAGE], 1u);
+        const uint32_t h = sh.h, hlen = sh.hlen, slice = sh.slice, nslice = sh.nslice;
+        // a centre that does not fit moves on whole: its first slice puts it on the list
+        auto move_on = [&]() {
+            if (tid == 0 && slice == 0) {
+                const uint32_t q = atomicAdd(&P.count[STAGE], 1u);
                 P.list[STAGE][q] = item_of(sh.gi, h);
                 P.rank[STAGE][q] = sh.rank;
                 atomicAdd((unsigned long long*)&st[0], 1ull);
             }
             HE2_MARK(7);
             __syncthreads();
+        };
+        if (sh.defer) {
+            move_on();
+            continue;
+        }
+        // --- members of h: degree prefix and list offsets, in LDS (at the arena's end in stage 0)
+        uint32_t* pre = BIG ? lds : arena + AW - (3 * hlen + 4);
+        uint64_t* voff = (uint64_t*)(pre + ((hlen + 2) & ~1u));
+        if (((uintptr_t)voff & 7) != 0) voff = (uint64_t*)((uint32_t*)voff + 1);
+        wg_prefix<WG>(hlen, sh.ws,
+                      [&](uint32_t i) {
+                          const uint32_t m = G.g.h2v[sh.hoff + i];
+                          voff[i] = G.g.v_off[m];
+                          return G.g.v_len[m];
+                      },
+                      [&](uint32_t i, uint32_t b) { pre[i] = b; });
+        __syncthreads();
+        if (tid == 0) {
+            uint32_t lh = 0;
+            for (uint32_t w = 0; w < NW; w++) lh += sh.ws[w];
+            pre[hlen] = lh;
+            sh.lh = lh;
+            const uint64_t cap = (uint64_t)lh + lh / 2 + 32;
+            sh.defer = (lh >= K_MAX_N || 2 * cap + 3ull * lh + 4 * hlen + 8 > AW) ? 1u : 0u;
+        }
+        __syncthreads();
+        if (sh.defer) {
+            move_on();
             continue;
         }
         HE2_MARK(0);
-        const uint32_t lh = sh.lh, ncap = sh.ncap;
-        uint32_t* nkeys = arena;
-        uint32_t* nvals = arena + ncap;
-        for (uint32_t s = tid; s < ncap; s += HGT_WG) { nkeys[s] = HGT_EMPTY; nvals[s] = 0; }
-        if (tid == 0) sh.K = 0;
-        __syncthreads();
-        build_nh(G.g, h, hlen, lh, pre, voff, nkeys, nvals, ncap);
-        __syncthreads();
-        HE2_MARK(1);
-        // --- compact N(h): x, meta (c | len | eligible), member offsets later
-        uint32_t* nl_x = arena + 2 * ncap;
+        // --- N(h).  Arena: hash (2 cap) | IDs, metas, row starts of the neighbours (lh each) | h's members
+        const uint32_t lh = sh.lh, cap = hash_cap(lh);
+        uint32_t* nl_x = arena + 2 * cap;
         uint32_t* nl_meta = nl_x + lh;
-        uint32_t* nl_mo = nl_meta + lh;  // lh + 1 words
-        uint32_t* nl_msh = nl_mo + lh + 1;  // members shared with another neighbour
-        for (uint32_t s = tid; s < ncap; s += HGT_WG) {
-            uint32_t x = nkeys[s];
-            if (x == HGT_EMPTY) continue;
-            uint32_t c = nvals[s];
-            uint32_t len = G.g.h_len[x];
-            bool elig = P.static_mode || !lower_ranked_member(G.mark[x], G.epoch, sh.rank);
-            uint32_t meta = c | (len << 14) | ((uint32_t)elig << 28);
-            nvals[s] = meta;
-            uint32_t q = atomicAdd(&sh.K, 1u);
-            nl_x[q] = x;
-            nl_meta[q] = meta;
-        }
-        __syncthreads();
-        const uint32_t K = sh.K;
-        // member offsets of the neighbours in the entry array
-        uint32_t* hm = nl_msh + lh;  // members of h
-        {
-            uint32_t carry = 0;
-            for (uint32_t b = 0; b < K; b += HGT_WG) {
-                uint32_t i = b + tid;
-                uint32_t v = i < K ? meta_len(nl_meta[i]) : 0;
-                uint32_t tot;
-                uint32_t ex = wg_scan_u32(v, sh.ws, &tot);
-                if (i < K) nl_mo[i] = carry + ex;
-                carry += tot;
-            }
-            if (tid == 0) {
-                nl_mo[K] = carry;
-                sh.W = carry;
-                // h's row and its members' incidence lists, each neighbour's row and metadata
-                if (P.stats)
-                    atomicAdd((unsigned long long*)&st[1],
-                              (unsigned long long)(4ull * (hlen + lh) + 20ull * K + 4ull * carry));
-                uint64_t o_ent = (uint64_t)(hm + hlen - arena);
-                o_ent = (o_ent + 1) & ~1ull;
-                uint64_t need = 2ull * carry > 2ull * hlen + 2 ? 2ull * carry : 2ull * hlen + 2;
-                sh.o_ent = (uint32_t)o_ent;
-                // too large for this arena: the next stage; too dense for any: the 2-hop kernel
-                sh.defer = (o_ent + need > ARENA_WORDS) ? 1u : 0u;
-                if (K >= K_2HOP || carry >= (P.w_2hop ? P.w_2hop : W_2HOP)) sh.defer = 2u;
-            }
-            __syncthreads();
-        }
-        if (sh.defer) {
-            if (tid == 0) {
-                const int to = sh.defer == 2u ? 2 : STAGE;
-                uint32_t q = atomicAdd(&P.count[to], 1u);
-                P.list[to][q] = item_of(sh.gi, h);
-                P.rank[to][q] = sh.rank;
-                atomicAdd((unsigned long long*)&st[0], 1ull);
-            }
-            HE2_MARK(7);
-            __syncthreads();
-            continue;
+        uint32_t* row_at = nl_meta + lh;
+        uint32_t* hm = row_at + lh;
+        uint32_t base0 = (uint32_t)(hm + hlen - arena);
+        const uint32_t lds_used = BIG ? (3 * hlen + 8) & ~1u : 0;  // pre and voff
+        if (BIG && lds_used + 2 * cap <= LDS_L) {
+            he2_nh<WG>(G.g, h, hlen, lh, pre, voff, lds + lds_used, lds + lds_used + cap, cap);
+            HE2_MARK(1);
+            he2_compact<WG, false>(P, G, sh, lds + lds_used, lds + lds_used + cap, cap, nl_x, nl_meta);
+        } else {
+            he2_nh<WG>(G.g, h, hlen, lh, pre, voff, arena, arena + cap, cap);
+            HE2_MARK(1);
+            he2_compact<WG, BIG>(P, G, sh, arena, arena + cap, cap, nl_x, nl_meta);
         }
         HE2_MARK(2);
+        const uint32_t K = sh.K;
+        for (uint32_t i = tid; i < hlen; i += WG) hm[i] = G.g.h2v[sh.hoff + i];
+        // --- vertices that two neighbours may share: a second row holding a vertex
+        // finds its bit set and sets the bit in the second bitmap (the members are
+        // stashed, so a row is gathered once)
+        uint32_t* bm = BIG ? lds : arena + base0;
+        if (!BIG) base0 += 2 * BM_WORDS;
+        uint32_t* stash = arena + base0;
+        const uint32_t room = base0 < AW ? AW - base0 : 0;  // words left for the stash and the survivors
+        if (room) {
+            for (uint32_t i = tid; i < 2 * BM_WORDS; i += WG) bm[i] = 0;
+        }
+        __syncthreads();
+        if (room)
+            he2_rows<WG>(G.g, sh, nl_x, nl_meta, row_at, K, nullptr, wpre, woff, true,
+                         [&](uint32_t, uint32_t v, uint32_t j) {
+                             if (j < room) stash[j] = v;
+                             const uint32_t b = (v * 2654435761u) >> (32 - BM_LOG);
+                             const uint32_t bit = 1u << (b & 31);
+                             if (atomicOr(&bm[b >> 5], bit) & bit) atomicOr(&bm[BM_WORDS + (b >> 5)], bit);
+                         });
+        __syncthreads();
         const uint32_t W = sh.W;
-        uint64_t* keys = (uint64_t*)(arena + sh.o_ent);
-        for (uint32_t i = tid; i < hlen; i += HGT_WG) hm[i] = G.g.h2v[sh.hoff + i];
-        // --- disjoint-pair classes of all eligible neighbour pairs (histogram over c)
-        {
-            uint32_t* cnt = (uint32_t*)keys;  // 2 (hlen + 1) words, free until the entries are written
-            const uint32_t Wc = hlen + 1;
-            for (uint32_t i = tid; i < 2 * Wc; i += HGT_WG) cnt[i] = 0;
-            if (tid < 8) sh.g[tid] = 0;
-            __syncthreads();
-            for (uint32_t i = tid; i < K; i += HGT_WG) {
-                uint32_t m = nl_meta[i];
-                if (!meta_elig(m)) continue;
-                uint32_t c = meta_c(m);
-                atomicAdd(&cnt[(meta_len(m) > c ? Wc : 0) + c], 1u);
-            }
-            __syncthreads();
-            for (uint32_t f = 0; f < 2; f++) {
-                uint32_t carry2 = 0;
-                for (uint32_t b = 0; b < Wc; b += HGT_WG) {
-                    uint32_t i = b + tid;
-                    uint32_t v = i < Wc ? cnt[f * Wc + i] : 0;
-                    uint32_t tot;
-                    uint32_t ex = wg_scan_u32(v, sh.ws, &tot);
-                    if (i < Wc) cnt[f * Wc + i] = carry2 + ex;
-                    carry2 += tot;
-                }
-                if (tid == 0) sh.g[6 + f] = carry2;
-                __syncthreads();
-            }
-            const uint64_t N0 = sh.g[6], N1 = sh.g[7];
-            uint64_t g00 = 0, g01 = 0, g11 = 0, d0 = 0, d1 = 0;
-            for (uint32_t c = 1 + tid; c <= hlen; c += HGT_WG) {
-                uint64_t n0 = (uint64_t)((c + 1 < Wc ? cnt[c + 1] : (uint32_t)N0) - cnt[c]);
-                uint64_t n1 = (uint64_t)((c + 1 < Wc ? cnt[Wc + c + 1] : (uint32_t)N1) - cnt[Wc + c]);
-                uint32_t k = hlen - c;
-                uint64_t s0 = N0 - cnt[k], s1 = N1 - cnt[Wc + k];
-                g00 += n0 * s0;
-                g01 += n0 * s1;
-                g11 += n1 * s1;
-                if (2 * c >= hlen) { d0 += n0; d1 += n1; }
-            }
-            atomicAdd((unsigned long long*)&sh.g[0], (unsigned long long)g00);
-            atomicAdd((unsigned long long*)&sh.g[1], (unsigned long long)g01);
-            atomicAdd((unsigned long long*)&sh.g[2], (unsigned long long)g11);
-            atomicAdd((unsigned long long*)&sh.g[3], (unsigned long long)d0);
-            atomicAdd((unsigned long long*)&sh.g[4], (unsigned long long)d1);
-            __syncthreads();
-            if (tid == 0) {
-                uint64_t G00 = (sh.g[0] - sh.g[3]) / 2, G11 = (sh.g[2] - sh.g[4]) / 2, G01 = sh.g[1];
-                uint64_t T00 = N0 * (N0 - (N0 ? 1 : 0)) / 2, T11 = N1 * (N1 - (N1 ? 1 : 0)) / 2, T01 = N0 * N1;
-                acc_add(cacc, T.he[40 | 1], 2 * (T00 - G00));
-                acc_add(cacc, T.he[40], 2 * (G00));
-                acc_add(cacc, T.he[40 | 4 | 1], 2 * (T01 - G01));
-                acc_add(cacc, T.he[40 | 4], 2 * (G01));
-                acc_add(cacc, T.he[40 | 6 | 1], 2 * (T11 - G11));
-                acc_add(cacc, T.he[40 | 6], 2 * (G11));
-            }
-            __syncthreads();
+        if (tid == 0) {
+            // h's row and its members' incidence lists, each neighbour's row and metadata
+            if (P.stats)
+                atomicAdd((unsigned long long*)&st[1], (unsigned long long)(4ull * (hlen + lh) + 20ull * K + 4ull * W));
         }
-        HE2_MARK(3);
-        // --- entries: (vertex, v in h, neighbour) for every member of every neighbour,
-        // sorted by vertex so that the neighbours meeting at a vertex are contiguous
-        for (uint32_t i = tid; i < K; i += HGT_WG) nl_msh[i] = 0;
-        {
-            // with a global arena, the neighbours' row offsets and entry prefix and h's
-            // members are staged in the LDS tile (free until the sort) when they fit
-            const uint32_t* mo_p = nl_mo;
-            const uint32_t* hm_p = hm;
-            const uint64_t* xo_p = nullptr;
-            if (tile && 3ull * K + 3 + hlen <= 2ull * TILE_K) {
-                uint64_t* xo = tile;
-                uint32_t* t32 = (uint32_t*)(tile + K);
-                for (uint32_t i = tid; i < K; i += HGT_WG) xo[i] = G.g.h_off[nl_x[i]];
-                for (uint32_t i = tid; i <= K; i += HGT_WG) t32[i] = nl_mo[i];
-                for (uint32_t i = tid; i < hlen; i += HGT_WG) t32[K + 1 + i] = hm[i];
-                __syncthreads();
-                xo_p = xo;
-                mo_p = t32;
-                hm_p = t32 + K + 1;
-            }
-            for (uint32_t p = tid; p < W; p += HGT_WG) {
-                uint32_t xi = seg_of<uint32_t>(mo_p, K, p);
-                const uint64_t xoff = xo_p ? xo_p[xi] : G.g.h_off[nl_x[xi]];
-                uint32_t v = G.g.h2v[xoff + (p - mo_p[xi])];
-                uint64_t inh = contains_u32(hm_p, hlen, v) ? 1ull : 0ull;
-                keys[p] = ((uint64_t)v << KEY_V) | (inh << KEY_IN) | xi;
-            }
+        if (W > room || !room) {
             __syncthreads();
+            move_on();
+            continue;
         }
-        sort_any(keys, W);
-        // vertices met by two or more neighbours; per neighbour, how many it has
-        for (uint32_t i = tid; i < W; i += HGT_WG) {
-            uint64_t v = keys[i] >> KEY_V;
-            bool shared = (i > 0 && (keys[i - 1] >> KEY_V) == v) || (i + 1 < W && (keys[i + 1] >> KEY_V) == v);
-            if (shared) atomicAdd(&nl_msh[keys[i] & K_MAX], 1u);
+        // survivors (vertex, neighbour), from the arena's end downwards
+        const uint32_t s_cap = (room - W) / 2;
+        uint32_t* s_end = arena + AW;
+        he2_rows<WG>(G.g, sh, nl_x, nl_meta, row_at, K, stash, wpre, woff, false,
+                     [&](uint32_t xi, uint32_t v, uint32_t) {
+                         const uint32_t b = (v * 2654435761u) >> (32 - BM_LOG);
+                         if (!(bm[BM_WORDS + (b >> 5)] >> (b & 31) & 1u)) return;
+                         const uint32_t q = atomicAdd(&sh.S, 1u);
+                         if (q < s_cap) {
+                             s_end[-1 - 2 * (int32_t)q] = xi;
+                             s_end[-2 - 2 * (int32_t)q] = v;
+                         }
+                     });
+        __syncthreads();
+        const uint32_t S = sh.S;
+        // --- exact groups: hash of the survivors' vertices, runs, and per neighbour its
+        // shared vertices.  The regions go where they fit: over the bitmaps and the stash,
+        // or over the hash of N(h).
+        uint32_t lo_at = 0, hi_at = BIG ? base0 : base0 - 2 * BM_WORDS;
+        const uint32_t lo_end = 2 * cap, hi_end = AW - 2 * S;
+        bool fits = S <= s_cap;
+        auto place = [&](uint32_t words) -> uint32_t {
+            uint32_t r = 0;
+            if (hi_at + words <= hi_end) { r = hi_at; hi_at += words; }
+            else if (lo_at + words <= lo_end) { r = lo_at; lo_at += words; }
+            else fits = false;
+            return r;
+        };
+        const uint32_t vcap = hash_cap(S);
+        uint32_t* tkey = arena + place(vcap);
+        uint32_t* tcur = arena + place(vcap + 1);
+        uint32_t* rx = arena + place(S);
+        uint32_t* er = arena + place(S);
+        uint32_t* ecur = arena + place(K);
+        uint32_t* cnts = BIG ? lds : arena + place(NW * K > 2 * hlen + 2 ? NW * K : 2 * hlen + 2);
+        if (!fits) {
+            __syncthreads();
+            move_on();
+            continue;
+        }
+        for (uint32_t s = tid; s < vcap; s += WG) { tkey[s] = HGT_EMPTY; tcur[s] = 0; }
+        for (uint32_t i = tid; i < K; i += WG) ecur[i] = 0;
+        __syncthreads();
+        for (uint32_t e = tid; e < S; e += WG) {
+            uint32_t* pv = s_end - 2 - 2 * (int32_t)e;
+            *pv = fr_add(tkey, tcur, vcap, *pv, 1u);
         }
         __syncthreads();
         HE2_MARK(4);
+        // run starts (vertices of one neighbour only: an empty run), flagged when the vertex lies in h
+        wg_prefix<WG>(vcap, sh.ws,
+                      [&](uint32_t s) {
+                          const uint32_t r = ld_at<BIG>(&tcur[s]) & POS;
+                          return r >= 2 ? r : 0u;
+                      },
+                      [&](uint32_t s, uint32_t b) {
+                          const uint32_t v = ld_at<BIG>(&tkey[s]);
+                          const uint32_t in = v != HGT_EMPTY && contains_u32(hm, hlen, v) ? 1u : 0u;
+                          tcur[s] = b | in << 31;
+                      });
+        if (tid == 0) {  // the end of the last run
+            uint32_t t = 0;
+            for (uint32_t w = 0; w < NW; w++) t += sh.ws[w];
+            tcur[vcap] = t;
+        }
+        __syncthreads();
+        for (uint32_t e = tid; e < S; e += WG) {
+            uint32_t* pv = s_end - 2 - 2 * (int32_t)e;
+            const uint32_t s = *pv;
+            if ((ld_at<BIG>(&tcur[s + 1]) & POS) == (ld_at<BIG>(&tcur[s]) & POS)) *pv = HGT_EMPTY;
+            else atomicAdd(&ecur[pv[1]], 1u);
+        }
+        __syncthreads();
+        wg_prefix<WG>(K, sh.ws, [&](uint32_t i) { return ld_at<BIG>(&ecur[i]); },
+                      [&](uint32_t i, uint32_t b) { ecur[i] = b; });
+        __syncthreads();
+        for (uint32_t e = tid; e < S; e += WG) {
+            const uint32_t* pv = s_end - 2 - 2 * (int32_t)e;
+            const uint32_t s = *pv;
+            if (s == HGT_EMPTY) continue;
+            const uint32_t xi = pv[1];
+            rx[atomicAdd(&tcur[s], 1u) & POS] = xi;
+            er[atomicAdd(&ecur[xi], 1u)] = s;
+        }
+        __syncthreads();
+        // now run s is [end of s - 1, tcur[s]) and neighbour i's shared vertices [ecur[i-1], ecur[i])
+        HE2_MARK(8);
+        // --- disjoint-pair classes (the first slice); the histogram lies over the counters in the global stage
+        if (slice == 0) {
+            he2_disjoint<WG>(sh, T, A, nl_meta, K, hlen, cnts);
+            __syncthreads();
+        }
+        HE2_MARK(3);
         // --- open paths h - x - y through the histograms, per eligible neighbour
-        for (uint32_t i = P.static_mode ? K : tid; i < K; i += HGT_WG) {
-            uint32_t m = nl_meta[i];
-            if (!meta_elig(m)) continue;
-            uint32_t x = nl_x[i];
-            uint32_t c = meta_c(m), lx = meta_len(m);
-            uint32_t thr = lx - c;  // k < thr  <=>  x has a vertex outside h and y
-            uint32_t base = (hlen > c ? 1u : 0u) | 24u;
-            const uint32_t* H = G.hpool + 2 * G.g.h_off[x];
-            const uint64_t xs = G.id_base + x;
-            if (P.stats)  // x's histogram, list bounds and batch-neighbour entries
-                atomicAdd((unsigned long long*)&st[1], (unsigned long long)(8ull * lx + 16 + 8ull * P.bl_cnt[xs]));
-            // a_f: neighbours y with |x & y| < thr (x keeps a private vertex), b_f: the rest
-            uint64_t a0 = 0, a1 = 0, b0 = 0, b1 = 0;
-            for (uint32_t k = 1; k <= lx; k++) {
-                uint32_t h0 = H[2 * (k - 1)], h1 = H[2 * (k - 1) + 1];
-                if (k < thr) { a0 += h0; a1 += h1; }
-                else { b0 += h0; b1 += h1; }
+        if (!P.static_mode)
+            for (uint32_t i = tid; i < K; i += WG) {
+                const uint32_t m = nl_meta[i], x = nl_x[i];
+                if (meta_elig(m) && (nslice == 1 || slice_of(x, nslice) == slice)) he2_open(P, G, sh, A, x, m, st);
             }
-            // the histogram holds h itself: k = c, y only = |h| > c
-            if (c < thr) { if (hlen > c) a1--; else a0--; }
-            else { if (hlen > c) b1--; else b0--; }
-            // every lower-ranked batch member adjacent to x (the pair phase leaves out
-            // the ones that meet h)
-            uint64_t bo = P.bl_off[xs], bn = P.bl_cnt[xs];
-            for (uint64_t e = 0; e < bn; e++) {
-                uint64_t pay = P.bl_pay[bo + e];
-                if ((uint32_t)(pay >> 32) >= sh.rank) continue;
-                uint32_t k = (uint32_t)(pay >> 1) & 0x7fffffffu, f = (uint32_t)pay & 1u;
-                if (k < thr) { if (f) a1--; else a0--; }
-                else { if (f) b1--; else b0--; }
-            }
-            acc_add(cacc, T.he[base | 2], 2 * (a0));
-            acc_add(cacc, T.he[base | 2 | 4], 2 * (a1));
-            acc_add(cacc, T.he[base], 2 * (b0));
-            acc_add(cacc, T.he[base | 4], 2 * (b1));
-        }
-        if (P.phase_ticks) __syncthreads();
         HE2_MARK(5);
-        // --- intersecting neighbour pairs, aggregated.  Every pair of neighbours in the
-        // run of a shared vertex v is first taken as meeting only at v: its changes are
-        // enumerated along runs of up to RUN_DIRECT entries and counted from a (gy, c_y)
-        // histogram along longer runs, the closed-class changes once per ordered pair
-        // (twice per pair, halved at the end).  Pairs that share s >= 2 vertices were
-        // so counted once at each of them; they are found through the vertex pairs
-        // (u, w) that each neighbour holds among its shared vertices (sorted, so the
-        // neighbours holding u and w are contiguous), each at its two smallest common
-        // vertices, and get their true changes in place of the s single ones.  Layout
-        // after the entries: long runs, histogram, per-neighbour offsets of the shared
-        // vertices and of the vertex pairs, fill cursors, shared vertices, vertex pairs,
-        // the vertex pairs' pair numbering.
-        if (tid == 0) {
-            sh.agg = 0;
-            sh.fits_g = 0;
-            sh.to2 = 0;
-            sh.nbig = 0;
-            sh.g[6] = 0;  // shared entries of neighbours with two or more
-            sh.g[7] = 0;  // their vertex pairs
-        }
-        __syncthreads();
-        const uint32_t nb_cap = W / (RUN_DIRECT + 1) + 1, n_hist = 4u * (hlen + 1);
-        const uint64_t o_big = (uint64_t)sh.o_ent + 2ull * W, o_hist = o_big + 2ull * nb_cap, o_off = o_hist + n_hist;
-        const uint64_t o_eoff = o_off + K + 1, o_cur = o_eoff + K + 1, o_sl = o_cur + K;
-        if (!P.static_mode && P.pair_agg && W < W_2HOP) {
-            for (uint32_t i = tid; i < K; i += HGT_WG) {
-                const uint64_t m = nl_msh[i];
-                if (m >= 2) {
-                    atomicAdd((unsigned long long*)&sh.g[6], (unsigned long long)m);
-                    atomicAdd((unsigned long long*)&sh.g[7], (unsigned long long)(m * (m - 1) / 2));
-                }
-            }
-            __syncthreads();
-            if (tid == 0) {
-                const uint64_t o_emit = (o_sl + sh.g[6] + 1) & ~1ull;  // then pp: one word per vertex pair
-                const uint64_t need = o_emit + 3ull * sh.g[7];
-                sh.agg = (o_sl <= ARENA_WORDS && need <= ARENA_WORDS) ? 1u : 0u;
-                sh.fits_g = need <= P.garena_words ? 1u : 0u;
-                if (sh.g[7] >= (P.e2_2hop ? P.e2_2hop : E2_2HOP)) sh.agg = sh.fits_g = 0, sh.to2 = 1;
-            }
-            __syncthreads();
-        }
-        // no room to aggregate here: a centre that the global stage can aggregate moves on
-        // (dropping its changes so far); one that no stage can aggregate enumerates here
-        const bool hand_on = STAGE < 2 && !sh.agg && sh.fits_g;
-        if (hand_on || sh.to2) {
-            for (uint32_t i = tid; i < NWAVE * HGT_N_HE_CLASSES; i += HGT_WG) {
-                sh.acc2[i] = 0;
-                acc32_all[i] = 0;
-            }
-            if (tid == 0) {
-                const int to = sh.to2 ? 2 : STAGE;  // list 2 feeds the 2-hop kernel
-                uint32_t q = atomicAdd(&P.count[to], 1u);
-                P.list[to][q] = item_of(sh.gi, h);
-                P.rank[to][q] = sh.rank;
-                atomicAdd((unsigned long long*)&st[0], 1ull);
-            }
-            HE2_MARK(7);
-            __syncthreads();
-            continue;
-        }
-        if (P.stats && tid == 0 && !P.static_mode && !sh.agg) atomicAdd((unsigned long long*)&P.stats[ST_AGG_ENUM], 1ull);
-        if (sh.agg) {
-            const uint32_t S = (uint32_t)sh.g[6], E2 = (uint32_t)sh.g[7];
-            uint32_t* big = arena + o_big;
-            uint32_t* hist = arena + o_hist;
-            uint32_t* off = arena + o_off;
-            uint32_t* eoff = arena + o_eoff;
-            uint32_t* cur = arena + o_cur;
-            uint32_t* sl = arena + o_sl;
-            uint64_t* emit = (uint64_t*)(arena + ((o_sl + S + 1) & ~1ull));
-            {
-                uint32_t carry_s = 0, carry_e = 0;
-                for (uint32_t b = 0; b < K; b += HGT_WG) {
-                    const uint32_t i = b + tid;
-                    uint32_t m = i < K ? nl_msh[i] : 0;
-                    if (m < 2) m = 0;
-                    uint32_t tot_s, tot_e;
-                    const uint32_t ex_s = wg_scan_u32(m, sh.ws, &tot_s);
-                    const uint32_t ex_e = wg_scan_u32(m * (m - 1) / 2, sh.ws, &tot_e);
-                    if (i < K) {
-                        off[i] = carry_s + ex_s;
-                        eoff[i] = carry_e + ex_e;
-                        cur[i] = 0;
-                    }
-                    carry_s += tot_s;
-                    carry_e += tot_e;
-                }
-                if (tid == 0) {
-                    off[K] = carry_s;
-                    eoff[K] = carry_e;
-                }
-            }
-            __syncthreads();
-            // runs: shared vertices per neighbour, long runs listed, short runs enumerated
-            for (uint32_t i = tid; i < W; i += HGT_WG) {
-                const uint64_t ki = keys[i];
-                const uint64_t v = ki >> KEY_V;
-                const uint32_t st0 = lower_bound_u64(keys, W, v << KEY_V);
-                const uint32_t en = lower_bound_u64(keys, W, (v + 1) << KEY_V);
-                const uint32_t R = en - st0;
-                if (R < 2) continue;
-                const uint32_t xi = (uint32_t)ki & K_MAX;
-                if (nl_msh[xi] >= 2) sl[off[xi] + atomicAdd(&cur[xi], 1u)] = st0;
-                if (R > RUN_DIRECT) {
-                    if (i == st0) {
-                        const uint32_t q = atomicAdd(&sh.nbig, 1u);
-                        big[2 * q] = st0;
-                        big[2 * q + 1] = R;
-                    }
-                    continue;
-                }
-                const uint32_t mx = nl_meta[xi];
-                if (!meta_elig(mx)) continue;
-                const uint32_t vin = (uint32_t)(ki >> KEY_IN) & 1u;
-                const uint32_t xl = meta_len(mx), cx = meta_c(mx), dx = hlen - cx;
-                const uint32_t ob = (hlen > cx ? 1u : 0u) | 24u | (xl - cx > 1 ? 2u : 0u);
-                // partners counted per (gy, rng) cell in 6-bit fields (a run holds at most 63)
-                uint32_t n_el = 0, n_big = 0;
-                uint64_t c_lo = 0, c_hi = 0;  // cells 0..9, 10..11
-                for (uint32_t j = st0; j < en; j++) {
-                    if (j == i) continue;
-                    const uint32_t my = nl_meta[(uint32_t)keys[j] & K_MAX];
-                    if (!meta_elig(my)) continue;
-                    const uint32_t yl = meta_len(my), cy = meta_c(my);
-                    n_el++;
-                    n_big += yl > 1 ? 1u : 0u;
-                    const uint32_t cell = single_gy(vin, yl, cy) * 3u + (cy < dx ? 0u : (cy == dx ? 1u : 2u));
-                    if (cell < 10) c_lo += 1ull << (6 * cell);
-                    else c_hi += 1ull << (6 * (cell - 10));
-                }
-                if (n_big) acc32_add(myacc32, T.he[ob | 4u], 0u - n_big);
-                if (n_el > n_big) acc32_add(myacc32, T.he[ob], 0u - (n_el - n_big));
-                for (uint32_t cell = 0; cell < 12; cell++) {
-                    const uint32_t n = (uint32_t)((cell < 10 ? c_lo >> (6 * cell) : c_hi >> (6 * (cell - 10))) & 63u);
-                    if (!n) continue;
-                    int ct, cf;
-                    single_codes(vin, xl, cx, cell / 3u, cell % 3u, ct, cf);
-                    const int c1 = T.he[ct], c2 = T.he[cf];
-                    if (c1 != c2) {
-                        if (c1 < 255) atomicAdd((unsigned long long*)&cacc[c1], (unsigned long long)n);
-                        if (c2 < 255) atomicAdd((unsigned long long*)&cacc[c2], 0ull - (unsigned long long)n);
+        // --- intersecting neighbour pairs
+        const uint32_t cw = BIG ? CNT_L : K;  // counters per wave
+        uint32_t* cnt = cnts + wave * cw;
+        for (uint32_t i = lane; i < cw; i += 64) cnt[i] = 0;
+        wave_sync();
+        // a wave's neighbours are every NW-th, looked at 64 at a time.  The slices of a centre
+        // number its neighbours each in its own order, so a row belongs to the slice that its ID
+        // names and a pair to its row of smaller ID; unsliced, a pair belongs to its earlier row.
+        for (uint32_t c0 = 0; c0 * NW < K; c0 += 64) {
+          const uint32_t il = wave + NW * (c0 + lane);
+          uint32_t mx_l = 0, e0_l = 0, e1_l = 0, x_l = 0;
+          if (il < K) {
+              mx_l = nl_meta[il];
+              e0_l = il ? ld_at<BIG>(&ecur[il - 1]) : 0;
+              e1_l = ld_at<BIG>(&ecur[il]);
+              if (nslice > 1) x_l = nl_x[il];
+          }
+          uint64_t rows = __ballot(il < K && meta_elig(mx_l) && e0_l < e1_l &&
+                                   (nslice == 1 || slice_of(x_l, nslice) == slice));
+          for (; rows; rows &= rows - 1) {
+            const int r = __ffsll((unsigned long long)rows) - 1;
+            const uint32_t i = wave + NW * (c0 + r);
+            const uint32_t mx = __shfl(mx_l, r, 64), e0 = __shfl(e0_l, r, 64), e1 = __shfl(e1_l, r, 64);
+            const uint32_t x = __shfl(x_l, r, 64);
+            // lanes in groups, a group per shared vertex: few vertices, wide groups
+            const uint32_t ne = e1 - e0;
+            const uint32_t glog = ne == 1 ? 6 : ne == 2 ? 5 : ne <= 8 ? 4 : ne <= 16 ? 3 : 2;
+            const uint32_t ng = 64u >> glog, gid = lane >> glog, sub = lane & ((1u << glog) - 1);
+            auto walk = [&](uint32_t w0, uint32_t w1, auto fn) {
+                for (uint32_t e = e0 + gid; e < e1; e += ng) {
+                    const uint32_t s = er[e];
+                    const uint32_t r0 = s ? ld_at<BIG>(&tcur[s - 1]) & POS : 0, t1 = ld_at<BIG>(&tcur[s]);
+                    for (uint32_t j = r0 + sub; j < (t1 & POS); j += 1u << glog) {
+                        const uint32_t y = rx[j];
+                        if (y >= w0 && y < w1) fn(y, t1 >> 31);
                     }
                 }
+            };
+            for (uint32_t w0 = nslice == 1 ? i + 1 : 0; w0 < K; w0 += cw) {
+                const uint32_t w1 = K - w0 < cw ? K : w0 + cw;
+                walk(w0, w1, [&](uint32_t y, uint32_t in) { atomicAdd(&cnt[y - w0], 1u + (in << 16)); });
+                wave_sync();
+                walk(w0, w1, [&](uint32_t y, uint32_t) {
+                    const uint32_t v = atomicExch(&cnt[y - w0], 0u);
+                    if (!v || (nslice > 1 && nl_x[y] <= x)) return;  // taken at another shared vertex, or row
+                    const uint32_t my = nl_meta[y];
+                    if (meta_elig(my)) he2_pair(P, T, A, hlen, mx, my, v & 0xffffu, v >> 16);
+                });
+                wave_sync();
+                folded += w1 - w0;
             }
-            __syncthreads();
-            HE2_MARK(8);
-            // vertex pairs (u, w), u < w, of each neighbour's shared vertices, as run starts
-            for (uint32_t a = tid; a < S; a += HGT_WG) {
-                const uint32_t x = seg_of<uint32_t>(off, K, a);
-                const uint32_t o = off[x], m = off[x + 1] - o, j = a - o;
-                uint32_t pos = eoff[x] + j * (m - 1) - j * (j - 1) / 2;
-                const uint32_t u = sl[a];
-                for (uint32_t q = j + 1; q < m; q++) {
-                    const uint32_t w = sl[o + q];
-                    const uint32_t lo = u < w ? u : w, hi = u < w ? w : u;
-                    emit[pos++] = ((uint64_t)lo << EMIT_LO) | ((uint64_t)hi << EMIT_HI) | x;
-                }
+            if (folded >= FOLD_AT) {
+                pair_fold(A);
+                folded = 0;
             }
-            __syncthreads();
-            sort_any(emit, E2);
-            HE2_MARK(9);
-            // long runs, one at a time: histogram over (gy, c_y) of the eligible members
-            const uint32_t nbig = sh.nbig;
-            if (P.stats && tid == 0 && nbig) atomicAdd((unsigned long long*)&P.stats[ST_AGG_LONG], (unsigned long long)nbig);
-            for (uint32_t r = 0; r < nbig; r++) {
-                const uint32_t st0 = big[2 * r], R = big[2 * r + 1];
-                const uint32_t vin = (uint32_t)(keys[st0] >> KEY_IN) & 1u;
-                for (uint32_t c = tid; c < n_hist; c += HGT_WG) hist[c] = 0;
-                if (tid == 0) sh.nb1 = 0;
-                __syncthreads();
-                for (uint32_t i = st0 + tid; i < st0 + R; i += HGT_WG) {
-                    const uint32_t my = nl_meta[(uint32_t)keys[i] & K_MAX];
-                    if (!meta_elig(my)) continue;
-                    const uint32_t yl = meta_len(my), cy = meta_c(my);
-                    if (yl > 1) atomicAdd(&sh.nb1, 1u);
-                    atomicAdd(&hist[single_gy(vin, yl, cy) * (hlen + 1) + cy], 1u);
-                }
-                __syncthreads();
-                {  // inclusive prefix over the rows laid end to end
-                    uint32_t carry = 0;
-                    for (uint32_t b = 0; b < n_hist; b += HGT_WG) {
-                        const uint32_t i = b + tid;
-                        const uint32_t v = i < n_hist ? hist[i] : 0;
-                        uint32_t tot;
-                        const uint32_t ex = wg_scan_u32(v, sh.ws, &tot);
-                        if (i < n_hist) hist[i] = carry + ex + v;
-                        carry += tot;
-                    }
-                }
-                __syncthreads();
-                const uint32_t nb1 = sh.nb1, ne = hist[n_hist - 1];  // eligible members: of length > 1, all
-                for (uint32_t i = st0 + tid; i < st0 + R; i += HGT_WG) {
-                    const uint32_t mx = nl_meta[(uint32_t)keys[i] & K_MAX];
-                    if (!meta_elig(mx)) continue;
-                    const uint32_t xl = meta_len(mx), cx = meta_c(mx), dx = hlen - cx;
-                    const uint32_t ob = (hlen > cx ? 1u : 0u) | 24u | (xl - cx > 1 ? 2u : 0u);
-                    const uint64_t n_big = nb1 - (xl > 1 ? 1u : 0u), n_small = (uint64_t)(ne - 1) - n_big;
-                    if (n_big) acc_add(cacc, T.he[ob | 4u], 2 * (0ull - n_big));
-                    if (n_small) acc_add(cacc, T.he[ob], 2 * (0ull - n_small));
-                    const uint32_t gx = single_gy(vin, xl, cx);
-                    for (uint32_t g = 0; g < 4; g++) {
-                        const uint32_t row = g * (hlen + 1);
-                        const uint32_t before = hist[row];  // the rows before (nothing at c_y = 0)
-                        const uint32_t tot = hist[row + hlen] - before;
-                        uint32_t n3[3];
-                        n3[0] = dx >= 2 ? hist[row + dx - 1] - before : 0u;
-                        n3[1] = dx >= 1 ? hist[row + dx] - hist[row + dx - 1] : 0u;
-                        n3[2] = tot - n3[0] - n3[1];
-                        if (g == gx) n3[cx < dx ? 0 : (cx == dx ? 1 : 2)]--;  // x itself
-                        for (uint32_t rng = 0; rng < 3; rng++) {
-                            if (!n3[rng]) continue;
-                            int ct, cf;
-                            single_codes(vin, xl, cx, g, rng, ct, cf);
-                            const int c1 = T.he[ct], c2 = T.he[cf];
-                            if (c1 != c2) {
-                                if (c1 < 255) atomicAdd((unsigned long long*)&cacc[c1], (unsigned long long)n3[rng]);
-                                if (c2 < 255) atomicAdd((unsigned long long*)&cacc[c2], 0ull - (unsigned long long)n3[rng]);
-                            }
-                        }
-                    }
-                }
-                __syncthreads();
-            }
-            HE2_MARK(10);
-            // pairs sharing two or more vertices, at their two smallest common ones.  The
-            // pairs within every run of equal (u, w) are numbered in one index space
-            // (pp: exclusive prefix of the run heads' pair counts), so that a long run
-            // spreads over the whole workgroup.
-            uint32_t* pp = (uint32_t*)(emit + E2);
-            if (tid == 0) sh.g[5] = 0;
-            __syncthreads();
-            {
-                uint32_t carry = 0;
-                for (uint32_t b = 0; b < E2; b += HGT_WG) {
-                    const uint32_t i = b + tid;
-                    uint32_t c = 0;
-                    if (i < E2) {
-                        const uint64_t uw = emit[i] >> EMIT_HI;
-                        if (i == 0 || (emit[i - 1] >> EMIT_HI) != uw) {
-                            const uint64_t R = lower_bound_u64(emit, E2, (uw + 1) << EMIT_HI) - i;
-                            const uint64_t c64 = R * (R - 1) / 2;
-                            atomicAdd((unsigned long long*)&sh.g[5], (unsigned long long)c64);
-                            c = (uint32_t)c64;  // used only when the total fits 31 bits
-                        }
-                    }
-                    uint32_t tot;
-                    const uint32_t ex = wg_scan_u32(c, sh.ws, &tot);
-                    if (i < E2) pp[i] = carry + ex;
-                    carry += tot;
-                }
-            }
-            __syncthreads();
-            const uint64_t T2 = sh.g[5];
-            if (T2 < 0x80000000ull) {
-                for (uint32_t p = tid; p < (uint32_t)T2; p += HGT_WG) {
-                    const uint32_t i = seg_of<uint32_t>(pp, E2, p);  // the run's head
-                    const uint64_t uw = emit[i] >> EMIT_HI;
-                    const uint32_t R = lower_bound_u64(emit, E2, (uw + 1) << EMIT_HI) - i;
-                    uint32_t a, b;
-                    tri_decode(R, p - pp[i], a, b);
-                    multi_pair(G.g, T, hlen, hm, keys, nl_x, nl_meta, emit[i + a], emit[i + b], P.stats, myacc32);
-                }
-            } else {
-                for (uint32_t i = tid; i < E2; i += HGT_WG) {
-                    const uint64_t uw = emit[i] >> EMIT_HI;
-                    for (uint32_t j = i + 1; j < E2 && (emit[j] >> EMIT_HI) == uw; j++)
-                        multi_pair(G.g, T, hlen, hm, keys, nl_x, nl_meta, emit[i], emit[j], P.stats, myacc32);
-                }
-            }
-        } else {
-        // --- intersecting neighbour pairs, enumerated: the neighbours that meet at a vertex v
-        // form a run of the sorted keys and every pair of a run meets at v; a pair whose
-        // sides share several vertices is counted at its smallest common vertex (found by
-        // merging the two rows).
-            for (uint32_t i = tid; i + 1 < W; i += HGT_WG) {
-                const uint64_t ki = keys[i];
-                const uint64_t v = ki >> KEY_V;
-                if ((keys[i + 1] >> KEY_V) != v) continue;
-                const uint32_t xi = (uint32_t)ki & K_MAX;
-                const uint32_t vin = (uint32_t)(ki >> KEY_IN) & 1u;
-                const uint32_t xsh = nl_msh[xi];
-                for (uint32_t j = i + 1; j < W; j++) {
-                    const uint64_t kj = keys[j];
-                    if ((kj >> KEY_V) != v) break;
-                    const uint32_t yi = (uint32_t)kj & K_MAX;
-                    uint32_t sc = 1, shh = vin;
-                    if (xsh > 1 && nl_msh[yi] > 1) {
-                        uint32_t first;
-                        row_meet(G.g.h2v + G.g.h_off[nl_x[xi]], meta_len(nl_meta[xi]), G.g.h2v + G.g.h_off[nl_x[yi]],
-                                 meta_len(nl_meta[yi]), hm, hlen, sc, shh, first);
-                        if ((uint64_t)first != v) continue;
-                    }
-                    pair_class(P, T, h, hlen, nl_x, nl_meta, xi, yi, sc, shh, myacc32);
-                }
-            }
-        }  // aggregated or enumerated pairs
-        __syncthreads();
-        // fold the per-centre 32-bit pair counters (signed) into the 64-bit ones
-        for (uint32_t i = tid; i < NWAVE * HGT_N_HE_CLASSES; i += HGT_WG) {
-            int32_t v = (int32_t)acc32_all[i];
-            if (v) {
-                atomicAdd((unsigned long long*)&acc_all[i], (unsigned long long)(int64_t)v);
-                acc32_all[i] = 0;
-            }
-        }
-        {  // the doubled changes: over all waves, halved
-            for (uint32_t c = tid; c < HGT_N_HE_CLASSES; c += HGT_WG) {
-                int64_t s2 = 0;
-                for (int w = 0; w < NWAVE; w++) {
-                    s2 += (int64_t)sh.acc2[w * HGT_N_HE_CLASSES + c];
-                    sh.acc2[w * HGT_N_HE_CLASSES + c] = 0;
-                }
-                if (s2) atomicAdd((unsigned long long*)&acc_all[c], (unsigned long long)(s2 / 2));
-            }
+          }
         }
         __syncthreads();
         HE2_MARK(6);
@@ -1241,47 +931,73 @@ __device__ void he2_flush_stats(const He2Params& P, const uint64_t* st, const ui
         atomicAdd((unsigned long long*)&P.stats[ST_HEB0 + STAGE], (unsigned long long)st[1]);
 }
 
-#define HE2_PROLOGUE                                                                   \
-    __shared__ Sh2 sh;                                                                 \
-    __shared__ Tables T;                                                               \
-    __shared__ uint64_t acc[NWAVE][HGT_N_HE_CLASSES];                                  \
-    __shared__ uint32_t acc32[NWAVE][HGT_N_HE_CLASSES];                                \
-    __shared__ uint64_t st[2];                                                         \
-    __shared__ uint64_t ph[HE2_PHASES];                                                \
-    if (threadIdx.x < HE2_PHASES) ph[threadIdx.x] = 0;                                 \
-    if (threadIdx.x == 0) sh.cur_g = 0xffffffffu;                                      \
-    for (int i = threadIdx.x; i < 128; i += HGT_WG) T.he[i] = P.he_tab[i];             \
-    for (int i = threadIdx.x; i < NWAVE * HGT_N_HE_CLASSES; i += HGT_WG) {             \
-        (&acc[0][0])[i] = 0;                                                           \
-        (&acc32[0][0])[i] = 0;                                                         \
-    }                                                                                  \
-    if (threadIdx.x < 2) st[threadIdx.x] = 0;                                          \
-    for (int i = threadIdx.x; i < NWAVE * HGT_N_HE_CLASSES; i += HGT_WG) sh.acc2[i] = 0; \
+template <bool BIG, int WG>
+__device__ __forceinline__ void he2_kernel(const He2Params& P, uint32_t* arena, uint32_t words, uint32_t* lds) {
+    __shared__ Sh2 sh;
+    __shared__ Tables T;
+    __shared__ He2Acc A;
+    __shared__ uint64_t st[2];
+    __shared__ uint64_t ph[HE2_PHASES];
+    const uint32_t tid = threadIdx.x;
+    if (tid < HE2_PHASES) ph[tid] = 0;
+    if (tid == 0) sh.cur_g = 0xffffffffu;
+    for (uint32_t i = tid; i < 128; i += WG) T.he[i] = P.he_tab[i];
+    for (uint32_t i = tid; i < HGT_N_HE_CLASSES * COPIES; i += WG) A.pair[i] = 0;
+    for (uint32_t i = tid; i < 8 * COPIES; i += WG) A.open[i] = 0;
+    if (tid < HGT_N_HE_CLASSES) A.tot[tid] = 0;
+    // open path: h & x (8) and x & y (16), h only (1), x only (2), y only (4)
+    if (tid < 8) A.cls8[tid] = P.he_tab[24 | (tid & 4 ? 1 : 0) | (tid & 2 ? 2 : 0) | (tid & 1 ? 4 : 0)];
+    if (tid < 2) st[tid] = 0;
     __syncthreads();
+    he2_body<BIG, WG>(P, arena, words, lds, sh, T, A, st, ph);
+    he2_flush_graph<WG>(P, sh.cur_g, A);
+    he2_flush_stats<BIG ? 2 : 0>(P, st, ph);
+}
 
 __global__ void __launch_bounds__(HGT_WG) k_he2_s0(He2Params P) {
     __shared__ __attribute__((aligned(16))) uint32_t arena[ARENA_S];
-    HE2_PROLOGUE
-    he2_body<0>(P, arena, ARENA_S, sh, T, &acc[0][0], &acc32[0][0], st, ph, nullptr);
-    he2_flush_graph(P, sh.cur_g, &acc[0][0]);
-    he2_flush_stats<0>(P, st, ph);
+    he2_kernel<false, HGT_WG>(P, arena, ARENA_S, nullptr);
 }
 
-__global__ void __launch_bounds__(HGT_WG) k_he2_s1(He2Params P) {
-    __shared__ __attribute__((aligned(16))) uint32_t arena[ARENA_M];
-    HE2_PROLOGUE
-    he2_body<1>(P, arena, ARENA_M, sh, T, &acc[0][0], &acc32[0][0], st, ph, nullptr);
-    he2_flush_graph(P, sh.cur_g, &acc[0][0]);
-    he2_flush_stats<1>(P, st, ph);
+__global__ void __launch_bounds__(WG_L, 4) k_he2_s2(He2Params P) {
+    __shared__ __attribute__((aligned(16))) uint32_t lds[LDS_L];
+    he2_kernel<true, WG_L>(P, P.garena + (uint64_t)blockIdx.x * P.garena_words, (uint32_t)P.garena_words, lds);
 }
 
-__global__ void __launch_bounds__(HGT_WG) k_he2_s2(He2Params P) {
-    __shared__ uint64_t tile[TILE_K];
-    HE2_PROLOGUE
-    he2_body<2>(P, P.garena + (uint64_t)blockIdx.x * P.garena_words, (uint32_t)P.garena_words, sh, T, &acc[0][0],
-                &acc32[0][0], st, ph, tile);
-    he2_flush_graph(P, sh.cur_g, &acc[0][0]);
-    he2_flush_stats<2>(P, st, ph);
+// Slices of the global stage's centres, one wave per centre: the pairs along its
+// members' lists (sum of the squared list lengths) over SLICE_PAIRS.  A launch of few
+// centres cuts finer, so that one dense centre does not outlast the rest.
+constexpr uint64_t SLICE_PAIRS = 1ull << 19;
+constexpr uint32_t SLICES_MAX = 64;
+__global__ void k_he2_slices(Multi M, const uint64_t* __restrict__ list, const uint32_t* n_p, uint64_t cap,
+                             uint32_t slice_lh, uint64_t slice_pairs, uint64_t* pre) {
+    const int lane = threadIdx.x & 63;
+    const uint64_t c = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    const uint32_t n = *n_p;
+    if (c == 0 && lane == 0) pre[cap] = n;
+    if (c >= n) return;
+    const uint64_t it = list[c];
+    const GraphView& g = M.graphs[(uint32_t)(it >> 32)].g;
+    const uint32_t h = (uint32_t)it;
+    const uint32_t* row = g.h2v + g.h_off[h];
+    const uint32_t len = g.h_len[h];
+    uint64_t lh = 0, sq = 0;
+    for (uint32_t i = lane; i < len; i += 64) {
+        const uint64_t d = g.v_len[row[i]];
+        lh += d;
+        sq += d * d;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        lh += __shfl_xor(lh, o, 64);
+        sq += __shfl_xor(sq, o, 64);
+    }
+    if (lane == 0) {
+        const uint64_t full = slice_pairs ? slice_pairs : SLICE_PAIRS;
+        const uint64_t per = n >= 512 ? full : (full * n / 512 > full / 16 ? full * n / 512 : full / 16);
+        uint64_t sl = slice_lh ? (lh + slice_lh - 1) / slice_lh : (sq + per - 1) / per;
+        pre[c] = sl < 1 ? 1 : (sl > SLICES_MAX ? SLICES_MAX : sl);
+    }
 }
 
 }  // namespace
@@ -1312,9 +1028,15 @@ void he2_remove_deleted(NbrParams& P, hipStream_t s) {
     k_h_remove<<<2048, 256, 0, s>>>(P.M, P.n_entries, P.entries_cap, P.ent_x, P.ent_pay);
 }
 
-void he2_launch_stage(He2Params& P, int stage, unsigned grid, hipStream_t s) {
+void he2_launch_lds(He2Params& P, unsigned grid, hipStream_t s) {
+    if (P.M.total) k_he2_s0<<<grid, HGT_WG, 0, s>>>(P);
+}
+
+void he2_launch_global(He2Params& P, unsigned grid, hipStream_t s) {
     if (!P.M.total) return;
-    if (stage == 0) k_he2_s0<<<grid, HGT_WG, 0, s>>>(P);
-    else if (stage == 1) k_he2_s1<<<grid, HGT_WG, 0, s>>>(P);
-    else k_he2_s2<<<grid, HGT_WG, 0, s>>>(P);
+    const uint64_t cap = P.slice_cap;
+    k_he2_slices<<<(unsigned)((cap * 64 + 255) / 256), 256, 0, s>>>(P.M, P.list[0], &P.count[0], cap, P.slice_lh,
+                                                                    P.slice_pairs, P.slice_pre);
+    hgt_scan_u64(P.slice_pre, P.slice_pre, cap, P.slice_pre + cap, P.slice_pre + cap + 1, P.slice_scan_tmp, s);
+    k_he2_s2<<<grid, WG_L, 0, s>>>(P);
 }

@@ -396,3 +396,37 @@ def test_sliced_two_hop_centres(gpu_lib, monkeypatch):
         p.apply(b, f"sliced temporal batch {k}")
         compare_counts(p.g, p.o, p.track, f"sliced temporal batch {k}")
     p.close()
+
+
+@pytest.mark.parametrize("slice_lh", ["0", "64"])
+@pytest.mark.parametrize("shape", ["window", "mixed", "wide-row"])
+def test_global_stage_centres(gpu_lib, monkeypatch, shape, slice_lh):
+    """Centres of the global histogram stage: more neighbours than one window of
+    counters holds (2,048), rows of one to 150 members, and a hyperedge of 6,000
+    members (more than the stage's LDS takes: the 2-hop kernel); whole and shared
+    among workgroups.  The change of the counts equals the oracle's delta by
+    definition."""
+    from .test_gpu_fullsize import _gpu_delta, _oracle_delta
+    monkeypatch.setenv("HGT_FORCE_STAGE", "1")
+    if slice_lh != "0":
+        monkeypatch.setenv("HGT_SLICE_LH", slice_lh)
+    if shape == "window":
+        st = W.plain_stream("window", 2000, 2600, ("uniform", 1, 3), 2.5, 0.0, 1, 3, 3, W.SEED_BASE + 95)
+    elif shape == "mixed":
+        st = W.plain_stream("mixed", 400, 700, ("power", 1.6, 1, 150), 1.3, 0.0, 1, 30, 30, W.SEED_BASE + 96)
+    else:
+        st = W.plain_stream("wide", 9000, 60, ("uniform", 5990, 6000), 0.0, 0.0, 1, 2, 2, W.SEED_BASE + 97)
+    b = st.batches[0]
+    p = Pair(W.Stream(shape, st.n_vertices, st.initial), track=("hyperedge",))
+    before = np.array(p.g.triad_counts("hyperedge"), np.uint64)
+    args, fin = p.prepare(b, shape)
+    ids = p.g.apply_batch(*args).cpu().numpy().astype(np.int64)
+    after = np.array(p.g.triad_counts("hyperedge"), np.uint64)
+    if ("global", shape) not in _ORACLE_CACHE:
+        _ORACLE_CACHE["global", shape] = _oracle_delta(p.o, b.del_handles, b.ins, None, ("hyperedge",))
+    _, oids, want = _ORACLE_CACHE["global", shape]
+    assert ids.tolist() == [int(x) for x in oids]
+    got = _gpu_delta({"hyperedge": before}, {"hyperedge": after})["hyperedge"]
+    bad = np.nonzero(got != want["hyperedge"])[0]
+    assert len(bad) == 0, f"classes {bad.tolist()[:8]}: gpu {got[bad][:8]} oracle {want['hyperedge'][bad][:8]}"
+    p.close()
