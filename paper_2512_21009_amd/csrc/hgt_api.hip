@@ -242,7 +242,7 @@ struct PhaseCtx {
     int device = 0;
     int refs = 0;                 // graphs that use it
     hipEvent_t done = nullptr;    // recorded after the last user's phases
-    DevBuf iv_list, iv_list2, iv_garena, iv_garena2;  // incident-vertex stage scratch
+    DevBuf iv_list0, iv_list, iv_list2, iv_garena, iv_garena2;  // incident-vertex stage scratch
     DevBuf t_ctr, t_big_list, t_big_rank, t_big_scratch, t_list1, t_rank1, t_garena, t_whash;
     DevBuf t_slices, t_slice_scan;       // slices of the 2-hop kernel's centres
     DevBuf ent_x, ent_d, ent_pay, bl_cnt, bl_off, bl_cur, bl_d, bl_pay, nb_scratch, bl_scan;
@@ -510,7 +510,7 @@ void phase_ctx_free(PhaseCtx& c) {
     DevBuf* all[] = {&c.t_ctr, &c.t_whash, &c.t_big_list, &c.t_big_rank, &c.t_big_scratch, &c.t_list1, &c.t_rank1,
                      &c.t_slices, &c.t_slice_scan,
                      &c.t_garena, &c.ent_x, &c.ent_d, &c.ent_pay, &c.bl_cnt, &c.bl_off, &c.bl_cur,
-                     &c.bl_d, &c.bl_pay, &c.nb_scratch, &c.bl_scan, &c.desc, &c.iv_list, &c.iv_list2, &c.iv_garena,
+                     &c.bl_d, &c.bl_pay, &c.nb_scratch, &c.bl_scan, &c.desc, &c.iv_list0, &c.iv_list, &c.iv_list2, &c.iv_garena,
                      &c.iv_garena2};
     for (DevBuf* b : all) dev_free(*b);
     for (hipEvent_t& e : c.desc_ev) {
@@ -893,32 +893,43 @@ int run_phase(hgt_graph* owner, const PhaseJob* jobs, uint32_t nj, bool minus, b
     return HGT_OK;
 }
 
-// IV pair list: unique vertex pairs inside the changed hyperedges.
-__global__ void k_iv_gen(const uint32_t* __restrict__ ids, uint64_t n, const uint64_t* __restrict__ h_off,
+// IV pair list: unique vertex pairs inside the changed hyperedges, a wave per row.  The
+// sum of C(d, 3) takes one atomic per workgroup (one per row on the same address took
+// 0.6 ms for 50k rows of two members).
+constexpr unsigned kIvGenBlocks = 2048;
+__global__ void __launch_bounds__(256) k_iv_gen(const uint32_t* __restrict__ ids, uint64_t n,
+                         const uint64_t* __restrict__ h_off,
                          const uint32_t* __restrict__ h_len, const uint32_t* __restrict__ h2v,
                          const uint32_t* __restrict__ canon, const uint64_t* __restrict__ rel,
                          const uint64_t* __restrict__ p2off, uint64_t base, int vb, uint64_t* keys, uint64_t* t1,
                          const DevScalars* sc) {
-    if (sc->status) return;
+    if (sc->status) return;  // no kernel of this stream writes it meanwhile
+    __shared__ unsigned long long sum;
+    if (threadIdx.x == 0) sum = 0;
+    __syncthreads();
     const int lane = threadIdx.x & 63;
-    uint64_t i = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    if (i >= n) return;
-    const uint32_t* m;
-    uint64_t d;
-    if (ids) {
-        m = h2v + h_off[ids[i]];
-        d = h_len[ids[i]];
-    } else {
-        m = canon + rel[i];
-        d = rel[i + 1] - rel[i];
+    uint64_t c3 = 0;
+    for (uint64_t i = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; i < n; i += (uint64_t)gridDim.x * 4) {
+        const uint32_t* m;
+        uint64_t d;
+        if (ids) {
+            m = h2v + h_off[ids[i]];
+            d = h_len[ids[i]];
+        } else {
+            m = canon + rel[i];
+            d = rel[i + 1] - rel[i];
+        }
+        const uint64_t o = base + p2off[i];
+        for (uint64_t a = lane; a < d; a += 64) {
+            const uint64_t start = o + a * (2 * d - a - 1) / 2;
+            const uint64_t ua = m[a];
+            for (uint64_t b = a + 1; b < d; b++) keys[start + (b - a - 1)] = (ua << vb) | m[b];
+        }
+        c3 += choose3(d);
     }
-    uint64_t o = base + p2off[i];
-    for (uint64_t a = lane; a < d; a += 64) {
-        uint64_t start = o + a * (2 * d - a - 1) / 2;
-        uint64_t ua = m[a];
-        for (uint64_t b = a + 1; b < d; b++) keys[start + (b - a - 1)] = (ua << vb) | m[b];
-    }
-    if (lane == 0) atomicAdd((unsigned long long*)t1, (unsigned long long)choose3(d));
+    if (lane == 0 && c3) atomicAdd(&sum, (unsigned long long)c3);
+    __syncthreads();
+    if (threadIdx.x == 0 && sum) atomicAdd((unsigned long long*)t1, sum);
 }
 
 __global__ void k_c2(const uint64_t* __restrict__ card, uint64_t n, uint64_t* out) {
@@ -1000,13 +1011,13 @@ int iv_prepare(hgt_graph* g, const BatchIn& b, const PlanScratch& w, const Batch
     if (b.n_del) {
         k_c2<<<nblk(b.n_del), 256, 0, s>>>(w.del_card, b.n_del, p2);
         hgt_scan_u64(p2, p2, b.n_del, nullptr, nullptr, g->iv_scan.p, s);
-        k_iv_gen<<<nblk(b.n_del * 64), 256, 0, s>>>(b.del, b.n_del, g->st.h_off, g->st.h_len, g->st.h2v, nullptr,
+        k_iv_gen<<<std::min(nblk(b.n_del * 64), kIvGenBlocks), 256, 0, s>>>(b.del, b.n_del, g->st.h_off, g->st.h_len, g->st.h2v, nullptr,
                                                     nullptr, p2, 0, vb, keys, cnt + ACC_T1, g->st.sc);
     }
     if (b.n_ins) {
         k_c2<<<nblk(b.n_ins), 256, 0, s>>>(w.ins_card, b.n_ins, p2);
         hgt_scan_u64(p2, p2, b.n_ins, nullptr, nullptr, g->iv_scan.p, s);
-        k_iv_gen<<<nblk(b.n_ins * 64), 256, 0, s>>>(nullptr, b.n_ins, nullptr, nullptr, nullptr, w.canon, w.ins_rel,
+        k_iv_gen<<<std::min(nblk(b.n_ins * 64), kIvGenBlocks), 256, 0, s>>>(nullptr, b.n_ins, nullptr, nullptr, nullptr, w.canon, w.ins_rel,
                                                     p2, sum.del_pairs2, vb, keys, cnt + ACC_T1 + 1, g->st.sc);
     }
     ip.uniq = g->iv_uniq.as<uint64_t>() + 1;
@@ -1034,18 +1045,18 @@ int iv_prepare(hgt_graph* g, const BatchIn& b, const PlanScratch& w, const Batch
     return HGT_OK;
 }
 
-// Incident-vertex global stages: 1 MB per workgroup (maps of up to 65536 slots:
-// owners whose hyperedges hold up to about 43k members in all), four
-// workgroups per CU; then 16 MB per workgroup (owners up to about 700k
-// members), 32 workgroups.  The no-allocation entry point runs 16 and 2.
-constexpr uint64_t kIvGarenaWords = 1ull << 18;
-constexpr uint64_t kIvGarena2Words = 1ull << 22;
+// Incident-vertex global stages: 512 KB per workgroup (maps of up to 65536 slots:
+// owners whose hyperedges hold up to about 43k members in all), then 8 MB per
+// workgroup (owners up to about 700k members), 32 workgroups.  The no-allocation
+// entry point runs 16 and 2.
+constexpr uint64_t kIvGarenaWords = 1ull << 17;
+constexpr uint64_t kIvGarena2Words = 1ull << 21;
 inline unsigned iv_grid_global(const hgt_graph* g) { return t_na ? 16u : (unsigned)(g->n_cu * g->iv_wg_per_cu); }
 inline unsigned iv_grid_global2() { return t_na ? 2u : 32u; }
 
 int iv_reserve(hgt_graph* g, const IvPlan& ip) {
     PhaseCtx& c = ctx_of(g);
-    if (ensure(c.iv_list, (ip.n_keys + 1) * 4) || ensure(c.iv_list2, (ip.n_keys + 1) * 4) ||
+    if (ensure(c.iv_list0, (ip.n_keys + 1) * 4) || ensure(c.iv_list, (ip.n_keys + 1) * 4) || ensure(c.iv_list2, (ip.n_keys + 1) * 4) ||
         ensure(c.iv_garena, (uint64_t)iv_grid_global(g) * kIvGarenaWords * 4) ||
         ensure(c.iv_garena2, (uint64_t)iv_grid_global2() * kIvGarena2Words * 4))
         return HGT_ENOMEM;
@@ -1070,9 +1081,10 @@ int iv_phase(hgt_graph* g, const IvPlan& ip, bool minus, hipStream_t s) {
     P.out = g->counts.as<uint64_t>() + (minus ? ACC_IV_M : ACC_IV_P);
     P.status = &g->st.sc->status;
     P.queue = (uint32_t*)(ictr + 2);
-    P.count = P.queue + 3;
-    P.list = c.iv_list.as<uint32_t>();
-    P.list2 = c.iv_list2.as<uint32_t>();
+    P.count = P.queue + 4;
+    P.list[0] = c.iv_list0.as<uint32_t>();
+    P.list[1] = c.iv_list.as<uint32_t>();
+    P.list[2] = c.iv_list2.as<uint32_t>();
     P.garena = c.iv_garena.as<uint32_t>();
     P.garena_words = gwords;
     P.garena2 = c.iv_garena2.as<uint32_t>();
@@ -1081,7 +1093,9 @@ int iv_phase(hgt_graph* g, const IvPlan& ip, bool minus, hipStream_t s) {
     P.force_direct = g->iv_direct;
     P.force_stage = g->iv_force_stage;
     ProfScope ps(g, PK_IV_PAIRS, s);
-    triad_iv_launch(P, (unsigned)std::min<uint64_t>((uint64_t)g->n_cu * 4, ip.n_keys), grid_g, iv_grid_global2(), s);
+    // a wave per owner at five workgroups per CU (32 KB of LDS each), then workgroups at four
+    triad_iv_launch(P, (unsigned)std::min<uint64_t>((uint64_t)g->n_cu * 5, (ip.n_keys + 3) / 4),
+                    (unsigned)std::min<uint64_t>((uint64_t)g->n_cu * 4, ip.n_keys), grid_g, iv_grid_global2(), s);
     return HGT_OK;
 }
 

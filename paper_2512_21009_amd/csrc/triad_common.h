@@ -105,9 +105,85 @@ __device__ __forceinline__ uint32_t hash_find(const uint32_t* keys, uint32_t log
     return HGT_EMPTY;
 }
 
+
 __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
     __builtin_amdgcn_wave_barrier();
+}
+
+// Work queues.  Every take is an atomic on one address that all eight L2s share, and
+// such atomics pass at about 13 ns each whatever else runs (183k takes: 3.0 ms of a
+// kernel of small items), so a group takes several items at once where there are many:
+// at least `rounds` takes per group remain, for the balance.
+__device__ __forceinline__ uint32_t take_size(uint64_t n, uint32_t groups, uint32_t rounds = 8) {
+    const uint64_t c = n / ((uint64_t)rounds * groups);
+    return c < 1 ? 1u : c > 16 ? 16u : (uint32_t)c;
+}
+
+// Segments laid end to end, walked by one wave: lane l holds a segment of d entries
+// (0: none) and the lanes take the entries 64 at a time, so short segments fill the
+// wave and no lane waits for a longer one.  The segment of an entry comes from a
+// bitmap of the segments' starts (a broadcast read and a bit count instead of a binary
+// search).  v = load(l, r) fetches entry r of lane l's segment, U steps' worth before
+// any is used; use(ok, l, r, p, v) is called by all lanes together (ok: the lane has an
+// entry; p: its number over all segments).  Returns the number of entries.
+struct Flat {
+    uint32_t bits[128];  // starts within the window of 4096 entries, each one place early
+    uint32_t pre[64], own[64];
+};
+template <int U, class Load, class Use>
+__device__ __forceinline__ uint32_t wave_flat(Flat& F, uint32_t d, Load load, Use use) {
+    const uint32_t lane = threadIdx.x & 63;
+    uint32_t inc = d;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t t = __shfl_up(inc, o, 64);
+        if (lane >= (uint32_t)o) inc += t;
+    }
+    const uint32_t ex = inc - d, tot = __builtin_amdgcn_readlane(inc, 63);
+    if (!tot) return 0;
+    const uint64_t nz = __ballot(d != 0);
+    if (d) {
+        const uint32_t rank = __popcll(nz & ((1ull << lane) - 1));
+        F.pre[rank] = ex;
+        F.own[rank] = lane;
+    }
+    for (uint32_t w0 = 0; w0 < tot; w0 += 4096) {
+        F.bits[lane] = 0;
+        F.bits[lane + 64] = 0;
+        wave_sync();
+        if (d && ex > w0 && ex - w0 <= 4096) atomicOr(&F.bits[(ex - 1 - w0) >> 5], 1u << ((ex - 1 - w0) & 31));
+        wave_sync();
+        uint32_t kb = (uint32_t)__popcll(__ballot(d && ex <= w0)) - 1;  // the segment that entry w0 lies in
+        const uint32_t w1 = tot - w0 < 4096 ? tot : w0 + 4096;
+        for (uint32_t p0 = w0; p0 < w1; p0 += 64 * U) {
+            uint32_t l[U], r[U];
+            decltype(load(0u, 0u)) v[U];
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                const uint32_t p = p0 + 64 * u + lane, at = (p0 - w0) / 32 + 2 * u;
+                const uint32_t lo = __builtin_amdgcn_readfirstlane(F.bits[at & 127]);
+                const uint32_t hi = __builtin_amdgcn_readfirstlane(F.bits[(at + 1) & 127]);
+                const uint32_t k = kb + __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
+                kb += __popc(lo) + __popc(hi);
+                v[u] = {};
+                l[u] = 0;
+                r[u] = 0;
+                if (p < w1) {
+                    l[u] = F.own[k];
+                    r[u] = p - F.pre[k];
+                    v[u] = load(l[u], r[u]);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                const uint32_t p = p0 + 64 * u + lane;
+                if (p0 + 64 * u < w1) use(p < w1, l[u], r[u], p, v[u]);
+            }
+        }
+        wave_sync();
+    }
+    return tot;
 }
 
 // exclusive workgroup scan of one u32 per thread (all threads participate)

@@ -600,6 +600,7 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     __shared__ uint32_t wpre[NW][65];
     __shared__ uint64_t woff[NW][64];
+    uint32_t q = 0, q_end = 0;  // thread 0: work items taken
     uint32_t folded = 0;    // pairs this wave counted since its last fold
     uint64_t t_mark = 0;    // thread 0: wall clock at the last phase mark (profiling)
     uint64_t t_centre = 0;  // ... at the start of the current centre
@@ -613,8 +614,13 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
     } while (0)
     for (;;) {
         if (tid == 0) {
-            uint32_t c = atomicAdd(&P.queue[STAGE], 1u);
             const uint64_t n = !BIG ? P.M.total : P.slice_pre[P.slice_cap + 1];
+            if (q == q_end) {
+                const uint32_t take = BIG ? 1 : take_size(n, gridDim.x);
+                q = atomicAdd(&P.queue[STAGE], take);
+                q_end = q + take;
+            }
+            const uint32_t c = q++;
             sh.stop = c >= n;
             sh.slice = 0;
             sh.nslice = 1;

@@ -430,3 +430,20 @@ def test_global_stage_centres(gpu_lib, monkeypatch, shape, slice_lh):
     bad = np.nonzero(got != want["hyperedge"])[0]
     assert len(bad) == 0, f"classes {bad.tolist()[:8]}: gpu {got[bad][:8]} oracle {want['hyperedge'][bad][:8]}"
     p.close()
+
+
+@pytest.mark.parametrize("stage", ["0", "1", "2"])
+@pytest.mark.parametrize("card", [(2, 2), (1, 5), (60, 70)])
+def test_incident_vertex_owner_stages(gpu_lib, monkeypatch, stage, card):
+    """Incident-vertex owners by size: a hub that owns several times 64 touched
+    pairs (cut among waves), maps a wave holds and maps it does not, rows of one
+    and two members and of 64 and more; every stage from `stage` on."""
+    monkeypatch.setenv("HGT_IV_FORCE_STAGE", stage)
+    n = 40 if card[0] > 10 else 600
+    st = W.plain_stream("hub", 300, n, ("uniform",) + card, 1.5, 0.0, 2, n // 3, n // 3, W.SEED_BASE + 98)
+    p = Pair(st, track=("incident_vertex",))
+    compare_counts(p.g, p.o, p.track, "owners build")
+    for k, b in enumerate(st.batches):
+        p.apply(b, f"owners batch {k}")
+        compare_counts(p.g, p.o, p.track, f"owners batch {k}")
+    p.close()
