@@ -578,6 +578,7 @@ struct PhaseJob {
     uint32_t epoch;
     uint64_t max_lh, sum_lh;  // over the centres (see BatchSummary)
     uint64_t n_ids;           // IDs in use during the phase
+    uint64_t n_live, n_inc;   // live hyperedges and incidences, about
 };
 
 inline size_t desc_slot_bytes(uint64_t cap) { return cap * sizeof(HeGraph) + 2 * (cap + 1) * 8; }
@@ -677,6 +678,8 @@ void collect(const PhaseJob* jobs, uint32_t nj, int family, bool minus, std::vec
         h.out_tmp = cnt + (minus ? ACC_TMP_M : ACC_TMP_P);
         h.hpool = g->hpool.as<uint32_t>();
         h.id_base = id_base.back();
+        const double live = (double)std::max<uint64_t>(J.n_live, 1);
+        h.pair_scale = 8.0 * (double)J.n_inc / (live * live);
         G.push_back(h);
         base.push_back(base.back() + J.n);
         id_base.push_back(id_base.back() + std::max<uint64_t>(J.n_ids, 1));
@@ -761,7 +764,7 @@ int phase_reserve(PhaseCtx& c, int family, const PhaseShape& z) {
 // inserted ones on the new graphs) for every job, in one launch per kernel.
 // Counter slots in t_ctr: 0-2 neighbour pass, 5 2-hop queue for the centres the
 // histogram stages pass on, 6-8 temporal, 10-11 entry count, 16-18 stage queues,
-// 19-21 stage hand-over counts.
+// 19-21 stage hand-over counts, 24-25 the global stage's estimated work.
 int run_phase(hgt_graph* owner, const PhaseJob* jobs, uint32_t nj, bool minus, bool full, hipStream_t s) {
     PhaseCtx& c = ctx_of(owner);
     uint64_t* stats = owner->prof ? owner->stats.as<uint64_t>() : nullptr;
@@ -852,7 +855,8 @@ int run_phase(hgt_graph* owner, const PhaseJob* jobs, uint32_t nj, bool minus, b
             E.slice_pairs = t_tune && t_tune->slice_pairs ? t_tune->slice_pairs : owner->slice_pairs;
             E.slice_scan_tmp = c.t_slice_scan.p;
             E.static_mode = full ? 1 : 0;
-            hgt_fill_u32(ctr + 16, 0, 6, s);
+            E.work_total = (uint64_t*)(ctr + 24);  // 8-byte aligned slot
+            hgt_fill_u32(ctr + 16, 0, 10, s);
             hgt_fill_u32(ctr + 5, 0, 1, s);
             {
                 ProfScope ps(owner, PK_DELTA_SMALL, s);
@@ -1256,13 +1260,13 @@ int plan_end(Pending& p, hipStream_t s) {
 PhaseJob job_minus(const Pending& p) {
     hgt_graph* g = p.g;
     return PhaseJob{g, p.b.del, p.b.n_del, g->st.mark_del, p.b.epoch_del, p.sum.max_lh_del, p.sum.sum_lh_del,
-                    g->next_id};
+                    g->next_id, g->n_live, g->n_inc};
 }
 
 PhaseJob job_plus(const Pending& p) {
     hgt_graph* g = p.g;
     return PhaseJob{g, p.w.assigned, p.b.n_ins, g->st.mark_ins, p.b.epoch_ins, p.sum.max_lh_ins, p.sum.sum_lh_ins,
-                    p.sum.next_id_new};
+                    p.sum.next_id_new, g->n_live + p.b.n_ins, g->n_inc + p.n_mem};
 }
 
 // Every scratch buffer of both phases, reserved before the first kernel that
@@ -1857,8 +1861,8 @@ namespace {
 // best choice's is dropped, and once every remaining choice has kTuneTrials
 // trials the fastest (by its quickest trial) is kept for the key and appended
 // to the cache file, which later processes read first.
-constexpr TuneChoice kTune[] = {{2, 8192, 0},        {1, 8192, 0},        {2, 8192, 1u << 17}, {2, 8192, 1u << 18},
-                                {2, 32768, 0},       {2, 8192, 1u << 20}, {2, 8192, 1u << 21}};
+constexpr TuneChoice kTune[] = {{2, 8192, 0},        {1, 8192, 0},        {2, 8192, 1u << 15}, {2, 8192, 1u << 17},
+                                {2, 32768, 0},       {2, 8192, 1u << 19}, {2, 8192, 1u << 21}};
 constexpr int kTuneN = (int)(sizeof(kTune) / sizeof(kTune[0]));
 constexpr int kTuneTrials = 2;
 constexpr float kTuneDrop = 1.25f;

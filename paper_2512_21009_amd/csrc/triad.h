@@ -23,6 +23,7 @@ struct HeGraph {
     uint64_t* out_tmp;        // u64[96]
     uint32_t* hpool;          // neighbour histograms, 2 words per h2v word
     uint64_t id_base;         // first slot of this graph's IDs in the shared per-ID arrays
+    double pair_scale;        // 8 * incidences / hyperedges^2: density, for estimates of work
 };
 
 // The graphs of one launch: work item q belongs to the graph g with
@@ -133,7 +134,8 @@ struct He2Params {
     uint64_t* slice_pre;         // slices of the global stage's centres (see TriadParams)
     uint64_t slice_cap;
     uint32_t slice_lh;           // test knob: member-list entries per slice (0: by pairs)
-    uint64_t slice_pairs;        // pairs along a centre's member lists per slice (0: the default)
+    uint64_t slice_pairs;        // work per slice of a centre (0: by the launch's total)
+    uint64_t* work_total;        // one cleared word
     void* slice_scan_tmp;
     uint64_t* stats;             // byte and hand-over counters (profiling), NULL = off
     int phase_ticks;             // 1 (with stats): wall-clock ticks per phase, at the cost of a

@@ -14,24 +14,36 @@
 // h itself, minus the batch members that rank below h (read from x's
 // batch-neighbour list) and, in the pair phase, minus the other neighbours of h
 // that meet x.
-// Neighbour pairs {x, y} of h that intersect get their true class in place of
-// the disjoint-pair class that the histogram pass gave them.  They are found
-// along the runs of the vertices that two or more neighbours share: a wave
-// takes a neighbour x, walks the runs of x's shared vertices and counts
-// |x & y| and |h & x & y| for every later neighbour y in a table of LDS counters
-// indexed by the neighbour's number (no hashing, no sort), then walks the runs
-// again, taking each y's counter as it empties it.
+// Neighbour pairs {x, y} of h that intersect get their true class in place of the
+// disjoint-pair class that the histogram pass gave them.  Those that meet inside h are
+// counted by kind: neighbours with the same mask of shared members (and the same few other
+// bits) change the classes alike, so the pairs are taken between a few dozen kinds.  Those
+// that meet outside h are found along the runs of the vertices that two or more neighbours
+// share: a wave takes a neighbour x, walks the runs of x's shared vertices and counts them
+// for every later neighbour y in LDS counters indexed by the neighbour's number (no hash, no
+// sort), then takes each y whose counter is not zero.  A hyperedge of more members than a
+// mask holds finds all its pairs along the runs.
+//
+// What bounds it: gathers (lists, metas, rows, histograms: about six lines of 128 B per
+// neighbour) and the latency of their chains, so rows, histograms and lists are walked end
+// to end, four steps' loads in flight, with as many waves as the LDS holds.  Measured with
+// 100k changes on 2M hyperedges of up to 64 members (both phases): sorted entries and pairs
+// enumerated per shared vertex 37.5 ms; counters along all runs 34.8; kinds and flat walks
+// 13.7.  5k changes on 500k hyperedges, where two dense centres went to the 2-hop kernel:
+// 134 ms, 9.7, 3.0.
 #include "triad_common.h"
 
 namespace {
 
 using namespace tri;
 
-constexpr uint32_t ARENA_S = 7168;     // stage 0: 28 KB of LDS, 256 threads, four workgroups per CU
+constexpr uint32_t ARENA_S = 6144;     // stage 0: 24 KB of LDS, 256 threads, four workgroups per CU
 constexpr int WG_L = 512;              // global stage: threads per workgroup
-constexpr uint32_t CNT_L = 2048;       // ... counters per wave: neighbours are taken in windows of this many
-constexpr uint32_t LDS_L = 16640;      // ... LDS words: counters of 8 waves, or two bitmaps, or a (c, f) histogram
-static_assert(LDS_L >= (WG_L / 64) * CNT_L && LDS_L >= 2 * (HGT_MAX_CARD + 1), "global stage LDS");
+constexpr uint32_t CNT_L = 1536;       // ... counters per wave: neighbours are taken in windows of this many
+constexpr uint32_t LDS_L = 12800;      // ... LDS words: counters of 8 waves, or bitmaps, or a (c, f) histogram
+static_assert(LDS_L >= (WG_L / 64) * CNT_L, "global stage LDS");
+constexpr uint32_t MASK_BITS = 64;     // hyperedges of up to this many members: a neighbour's shared
+                                       // members are one 64-bit mask
 constexpr uint32_t K_MAX_N = 1u << 24; // neighbours of a centre (a run cursor and its flag share a word)
 
 // open-addressing tables of any capacity: slot = multiply-shift hash scaled to cap
@@ -71,7 +83,7 @@ struct Sh2 {
     uint32_t slice, nslice;
     uint64_t hoff;
     uint32_t ws[WG_L / 64];
-    uint32_t ncap;
+    uint32_t ncap, G;
     uint64_t g[8];
 };
 
@@ -112,103 +124,110 @@ __device__ __forceinline__ uint32_t member_prefix(const GraphView& G, uint64_t h
 // neighbour pass: batch-neighbour entries (x, d, k = |x & d|, [|d| > k]) and,
 // for inserted hyperedges, the histogram updates
 // ===========================================================================
+// Words a centre's tables take in the arena: hash, member prefix and offsets.
+__device__ __forceinline__ uint64_t nbr_words(uint32_t hlen, uint32_t lh) {
+    return 2ull * hash_cap(lh) + 3ull * hlen + 4;
+}
+
+constexpr uint32_t NBR_TAKE = 8;  // centres a workgroup takes at once
+
 template <bool BIG>
 __device__ void nbr_pass_body(const NbrParams& P, uint32_t* arena, uint64_t arena_words) {
     __shared__ Sh2 sh;
-    const int tid = threadIdx.x;
+    __shared__ uint32_t c_gi[NBR_TAKE], c_h[NBR_TAKE], c_rank[NBR_TAKE], c_lh[NBR_TAKE];
+    __shared__ uint64_t c_off[NBR_TAKE];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint64_t n = BIG ? (uint64_t)*P.big_count : P.M.total;
+    uint32_t take = BIG ? 1 : take_size(n, gridDim.x, 4);
+    if (take > NBR_TAKE) take = NBR_TAKE;
     for (;;) {
         if (tid == 0) {
-            uint64_t n = BIG ? (uint64_t)*P.big_count : P.M.total;
-            uint32_t c = atomicAdd(BIG ? P.big_queue : P.queue, 1u);
-            sh.stop = c >= n;
-            if (!sh.stop) {
-                uint32_t gi, h, rank;
-                if (BIG) {
-                    uint64_t it = P.big_list[c];
-                    gi = (uint32_t)(it >> 32);
-                    h = (uint32_t)it;
-                    rank = P.big_rank[c];
-                } else {
-                    gi = multi_graph_of(P.M, c);
-                    rank = (uint32_t)(c - P.M.base[gi]);
-                    h = P.M.graphs[gi].centres[rank];
-                }
-                const HeGraph& Gq = P.M.graphs[gi];
-                sh.gi = gi;
-                sh.h = h;
-                sh.rank = rank;
-                sh.skip = *((volatile const int32_t*)Gq.status) != 0;
-                sh.hlen = Gq.g.h_len[h];
-                sh.hoff = Gq.g.h_off[h];
-                // prefix + offsets must fit at the arena end
-                sh.defer = (!BIG && 3ull * sh.hlen + 4 > arena_words / 2) ? 1u : 0u;
-            }
+            const uint32_t q = atomicAdd(BIG ? P.big_queue : P.queue, take);
+            sh.stop = q >= n;
+            sh.h = q;                                              // the first of
+            sh.K = sh.stop ? 0 : (uint32_t)(n - q < take ? n - q : take);  // this many centres
         }
         __syncthreads();
         if (sh.stop) break;
-        if (sh.skip) {
-            __syncthreads();
-            continue;
-        }
-        const HeGraph& G = P.M.graphs[sh.gi];
-        if (!sh.defer) {
-            const uint32_t hlen = sh.hlen;
-            uint32_t* pre = arena + arena_words - (3 * hlen + 4);
-            uint64_t* voff = (uint64_t*)(pre + ((hlen + 2) & ~1u));
-            if (((uintptr_t)voff & 7) != 0) voff = (uint64_t*)((uint32_t*)voff + 1);
-            uint32_t lh = member_prefix(G.g, sh.hoff, hlen, pre, voff, sh.ws);
-            uint32_t cap = hash_cap(lh);
-            if (tid == 0) {
-                sh.lh = lh;
-                sh.ncap = cap;
-                sh.defer = (!BIG && 2ull * cap + 3ull * hlen + 4 > arena_words) ? 1u : 0u;
+        const uint32_t q0 = sh.h, nc = sh.K;
+        // their member lists' lengths: they bound the entries, so the centres' ranges of
+        // the entry array are reserved with one atomic
+        for (uint32_t ci = wave; ci < nc; ci += NWAVE) {
+            uint32_t gi, h, rank;
+            if (BIG) {
+                const uint64_t it = P.big_list[q0 + ci];
+                gi = (uint32_t)(it >> 32);
+                h = (uint32_t)it;
+                rank = P.big_rank[q0 + ci];
+            } else {
+                gi = multi_graph_of(P.M, q0 + ci);
+                rank = (uint32_t)(q0 + ci - P.M.base[gi]);
+                h = P.M.graphs[gi].centres[rank];
             }
-            __syncthreads();
-        }
-        if (sh.defer) {
-            if (tid == 0) {
-                uint32_t q = atomicAdd(P.big_count, 1u);
-                P.big_list[q] = item_of(sh.gi, sh.h);
-                P.big_rank[q] = sh.rank;
+            const HeGraph& Gq = P.M.graphs[gi];
+            const bool skip = *((volatile const int32_t*)Gq.status) != 0;
+            const uint32_t hlen = skip ? 0 : Gq.g.h_len[h];
+            uint32_t lh = 0;
+            if (hlen) {
+                const uint32_t* row = Gq.g.h2v + Gq.g.h_off[h];
+                for (uint32_t i = lane; i < hlen; i += 64) lh += Gq.g.v_len[row[i]];
             }
-            __syncthreads();
-            continue;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) lh += __shfl_xor(lh, o, 64);
+            if (lane == 0) {
+                c_gi[ci] = gi;
+                c_h[ci] = h;
+                c_rank[ci] = rank;
+                c_lh[ci] = lh;
+                const bool big = !BIG && nbr_words(hlen, lh) > arena_words;
+                if (big) {  // to the large kernel
+                    const uint32_t at = atomicAdd(P.big_count, 1u);
+                    P.big_list[at] = item_of(gi, h);
+                    P.big_rank[at] = rank;
+                    c_lh[ci] = 0;
+                }
+                // the lists hold h itself once per member
+                c_off[ci] = P.emit_entries && c_lh[ci] ? lh - hlen : 0;
+            }
         }
-        const uint32_t h = sh.h, hlen = sh.hlen, lh = sh.lh, cap = sh.ncap;
+        __syncthreads();
+        if (tid == 0 && P.emit_entries) {
+            uint64_t sum = 0;
+            for (uint32_t ci = 0; ci < nc; ci++) sum += c_off[ci];
+            uint64_t at = sum ? atomicAdd((unsigned long long*)P.n_entries, (unsigned long long)sum) : 0;
+            for (uint32_t ci = 0; ci < nc; ci++) {
+                const uint64_t w = c_off[ci];
+                c_off[ci] = at;
+                at += w;
+            }
+        }
+        __syncthreads();
+        for (uint32_t ci = 0; ci < nc; ci++) {
+        const uint32_t lh = c_lh[ci];
+        if (!lh) continue;  // nothing to do, or the large kernel's
+        const HeGraph& G = P.M.graphs[c_gi[ci]];
+        const uint32_t h = c_h[ci], rank = c_rank[ci], hlen = G.g.h_len[h], cap = hash_cap(lh);
+        const uint64_t hoff = G.g.h_off[h], ebase = c_off[ci];
         uint32_t* keys = arena;
         uint32_t* vals = arena + cap;
         uint32_t* pre = arena + arena_words - (3 * hlen + 4);
         uint64_t* voff = (uint64_t*)(pre + ((hlen + 2) & ~1u));
         if (((uintptr_t)voff & 7) != 0) voff = (uint64_t*)((uint32_t*)voff + 1);
+        if (tid == 0) sh.K = 0;
+        (void)member_prefix(G.g, hoff, hlen, pre, voff, sh.ws);
         for (uint32_t s = tid; s < cap; s += HGT_WG) { keys[s] = HGT_EMPTY; vals[s] = 0; }
         __syncthreads();
         build_nh(G.g, h, hlen, lh, pre, voff, keys, vals, cap);
         __syncthreads();
-        uint32_t* hd = G.hpool + 2 * sh.hoff;
-        // the centre's entries take one range of the entry array, reserved at once (one
-        // atomic per centre on the shared cursor instead of one per entry)
-        if (P.emit_entries) {
-            if (tid == 0) sh.K = 0;
-            __syncthreads();
-            uint32_t mine = 0;
-            for (uint32_t s = tid; s < cap; s += HGT_WG) mine += ld_at<BIG>(&keys[s]) != HGT_EMPTY ? 1u : 0u;
-            if (mine) atomicAdd(&sh.K, mine);
-            __syncthreads();
-            if (tid == 0) {
-                sh.g[0] = atomicAdd((unsigned long long*)P.n_entries, (unsigned long long)sh.K);
-                sh.K = 0;
-            }
-            __syncthreads();
-        }
-        const uint64_t ebase = P.emit_entries ? sh.g[0] : 0;
+        uint32_t* hd = G.hpool + 2 * hoff;
         for (uint32_t s0 = 0; s0 < cap; s0 += HGT_WG) {
             const uint32_t s = s0 + tid;
             const uint32_t x = s < cap ? ld_at<BIG>(&keys[s]) : HGT_EMPTY;
             uint32_t at = 0;
             if (P.emit_entries) {
                 const uint64_t m = __ballot(x != HGT_EMPTY);
-                if ((tid & 63) == 0 && m) at = atomicAdd(&sh.K, (uint32_t)__popcll(m));
-                at = __shfl(at, 0, 64) + __popcll(m & ((1ull << (tid & 63)) - 1));
+                if (lane == 0 && m) at = atomicAdd(&sh.K, (uint32_t)__popcll(m));
+                at = __shfl(at, 0, 64) + __popcll(m & ((1ull << lane) - 1));
             }
             if (x == HGT_EMPTY) continue;
             const uint32_t c = ld_at<BIG>(&vals[s]);
@@ -218,7 +237,7 @@ __device__ void nbr_pass_body(const NbrParams& P, uint32_t* arena, uint64_t aren
                 if (q < P.entries_cap) {
                     P.ent_x[q] = (uint32_t)(G.id_base + x);
                     P.ent_d[q] = h;
-                    P.ent_pay[q] = ((uint64_t)sh.rank << 32) | ((uint64_t)c << 1) | fd;
+                    P.ent_pay[q] = ((uint64_t)rank << 32) | ((uint64_t)c << 1) | fd;
                 }
             }
             if (P.inserting) {
@@ -228,6 +247,13 @@ __device__ void nbr_pass_body(const NbrParams& P, uint32_t* arena, uint64_t aren
                 if ((uint32_t)(G.mark[x] >> 32) != G.epoch)
                     atomicAdd(&G.hpool[2 * G.g.h_off[x] + 2 * (c - 1) + fd], 1u);
             }
+        }
+        __syncthreads();
+        // neighbours met at several members took one entry: the rest of the range is void
+        if (P.emit_entries)
+            for (uint64_t q = ebase + sh.K + tid; q < ebase + lh - hlen; q += HGT_WG)
+                if (q < P.entries_cap) P.ent_x[q] = HGT_EMPTY;
+        __syncthreads();
         }
         __syncthreads();
     }
@@ -263,6 +289,7 @@ __global__ void k_h_remove(Multi M, const uint64_t* n_entries_p, uint64_t cap, c
     if (n > cap) n = cap;
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
         uint32_t slot = ent_x[i];
+        if (slot == HGT_EMPTY) continue;
         const HeGraph& G = M.graphs[multi_graph_of_id(M, slot)];
         if (*G.status) continue;
         uint32_t x = (uint32_t)(slot - G.id_base);
@@ -279,7 +306,7 @@ __global__ void k_bl_count(const uint64_t* n_entries_p, uint64_t cap, const uint
     uint64_t n = *n_entries_p;
     if (n > cap) n = cap;
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-        atomicAdd((unsigned long long*)&bl_cnt[ent_x[i]], 1ull);
+        if (ent_x[i] != HGT_EMPTY) atomicAdd((unsigned long long*)&bl_cnt[ent_x[i]], 1ull);
 }
 
 __global__ void k_bl_scatter(const uint64_t* n_entries_p, uint64_t cap, const uint32_t* __restrict__ ent_x,
@@ -288,6 +315,7 @@ __global__ void k_bl_scatter(const uint64_t* n_entries_p, uint64_t cap, const ui
     uint64_t n = *n_entries_p;
     if (n > cap) n = cap;
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
+        if (ent_x[i] == HGT_EMPTY) continue;
         uint64_t pos = atomicAdd((unsigned long long*)&bl_cur[ent_x[i]], 1ull);
         out_d[pos] = ent_d[i];
         out_pay[pos] = ent_pay[i];
@@ -311,37 +339,30 @@ __global__ void k_entries_check(Multi M, const uint64_t* n_entries_p, uint64_t c
 // (slices), each of which builds the tables and takes every nslice-th neighbour.
 // What does not fit there either goes to list 2, which feeds the 2-hop kernel.
 
-// Counters of the class changes of the workgroup's graph so far.  Every lane of
-// a wave adds to one of few classes, so the 32-bit pair counters are kept 32-fold
-// (a copy per lane pair: adds of one instruction meet at most two to a word) and
-// the 64-bit open-path counters too.
-constexpr int COPIES = 32;
+// Counters of the class changes of the workgroup's graph so far (mod 2^64).  Every lane
+// of a wave adds to one of few classes, so the counters are kept 16-fold, a copy per
+// lane of a row of lanes: adds of one instruction meet at most four to a word.
+constexpr int COPIES = 16;
 struct He2Acc {
-    uint32_t pair[HGT_N_HE_CLASSES * COPIES];  // signed changes
+    uint64_t pair[HGT_N_HE_CLASSES * COPIES];
     uint64_t open[8 * COPIES];                 // [hlen > c] << 2 | [x only] << 1 | [y only]
     uint64_t tot[HGT_N_HE_CLASSES];
     uint8_t cls8[8];                           // class of an open path by the same three bits
-    uint8_t pad[8];
 };
 
-__device__ __forceinline__ void pair_add(He2Acc& A, uint32_t cls, uint32_t v) {
-    if (cls < 255) atomicAdd(&A.pair[cls * COPIES + (threadIdx.x & (COPIES - 1))], v);
+__device__ __forceinline__ void pair_add(He2Acc& A, uint32_t cls, uint64_t v) {
+    if (cls < 255)
+        atomicAdd((unsigned long long*)&A.pair[cls * COPIES + (threadIdx.x & (COPIES - 1))], (unsigned long long)v);
 }
-
-// Moves the 32-bit counters into the 64-bit totals (any wave, any time).
-__device__ __forceinline__ void pair_fold(He2Acc& A) {
-    for (uint32_t i = threadIdx.x & 63; i < HGT_N_HE_CLASSES * COPIES; i += 64) {
-        const int32_t v = (int32_t)atomicExch(&A.pair[i], 0u);
-        if (v) atomicAdd((unsigned long long*)&A.tot[i / COPIES], (unsigned long long)(int64_t)v);
-    }
-}
-constexpr uint32_t FOLD_AT = 1u << 25;  // pairs of one wave after which it folds: no counter passes 2^31
 
 // Adds the workgroup's counts to graph g's phase accumulators and clears them.
 template <int WG>
 __device__ void he2_flush_graph(const He2Params& P, uint32_t g, He2Acc& A) {
     __syncthreads();
-    if (threadIdx.x < 64) pair_fold(A);
+    for (uint32_t i = threadIdx.x; i < HGT_N_HE_CLASSES * COPIES; i += WG) {
+        if (A.pair[i]) atomicAdd((unsigned long long*)&A.tot[i / COPIES], (unsigned long long)A.pair[i]);
+        A.pair[i] = 0;
+    }
     for (uint32_t i = threadIdx.x; i < 8 * COPIES; i += WG) {
         const uint32_t c = A.cls8[i / COPIES];
         if (A.open[i] && c < 255) atomicAdd((unsigned long long*)&A.tot[c], (unsigned long long)A.open[i]);
@@ -489,103 +510,162 @@ __device__ void he2_disjoint(Sh2& sh, const Tables& T, He2Acc& A, const uint32_t
     }
 }
 
-// Open paths h - x - y of one neighbour x through its histogram.
-__device__ __forceinline__ void he2_open(const He2Params& P, const HeGraph& G, const Sh2& sh, He2Acc& A, uint32_t x,
-                                         uint32_t m, uint64_t* st) {
-    const uint32_t hlen = sh.hlen, c = meta_c(m), lx = meta_len(m);
-    const uint32_t thr = lx - c;  // k < thr  <=>  x has a vertex outside h and y
-    const uint64_t* H = (const uint64_t*)(G.hpool + 2 * G.g.h_off[x]);  
-    const uint64_t xs = G.id_base + x;
-    const uint64_t bo = P.bl_off[xs], bn = P.bl_cnt[xs];
-    if (P.stats)  // x's histogram, list bounds and batch-neighbour entries
-        atomicAdd((unsigned long long*)&st[1], (unsigned long long)(8ull * lx + 16 + 8ull * bn));
-    // a_f: neighbours y with |x & y| < thr (x keeps a private vertex), b_f: the rest
-    uint64_t a0 = 0, a1 = 0, b0 = 0, b1 = 0;
-    for (uint32_t k = 1; k <= lx; k++) {
-        const uint64_t hh = H[k - 1];
-        const uint64_t h0 = (uint32_t)hh, h1 = hh >> 32;
-        if (k < thr) { a0 += h0; a1 += h1; }
-        else { b0 += h0; b1 += h1; }
+// Open paths h - x - y through the histograms of up to 64 neighbours (lane l: ID x, meta m,
+// take: eligible and this workgroup's), by one wave: histograms and batch-neighbour lists
+// laid end to end.
+__device__ __forceinline__ void he2_open(const He2Params& P, const HeGraph& G, const Sh2& sh, He2Acc& A, Flat& F,
+                                         uint32_t* wm, uint64_t* woff, bool take, uint32_t x, uint32_t m, uint64_t* st) {
+    const uint32_t hlen = sh.hlen, lane = threadIdx.x & 63;
+    auto add = [&](uint32_t c, uint32_t k, uint32_t lx, uint32_t f, uint64_t v) {
+        // k = |x & y|: x has a vertex outside h and y when k < |x| - c
+        const uint32_t i = (hlen > c ? 4u : 0u) | (k < lx - c ? 2u : 0u) | f;
+        atomicAdd((unsigned long long*)&A.open[i * COPIES + (lane & (COPIES - 1))], (unsigned long long)v);
+    };
+    uint32_t lx = 0, bn = 0;
+    uint64_t bo = 0;
+    if (take) {
+        lx = meta_len(m);
+        bo = P.bl_off[G.id_base + x];
+        bn = (uint32_t)P.bl_cnt[G.id_base + x];
+        woff[lane] = G.g.h_off[x];
+        // the histogram holds h itself: k = c, y only = |h| > c
+        const uint32_t c = meta_c(m);
+        add(c, c, lx, hlen > c ? 1u : 0u, ~0ull);
+        if (P.stats)  // x's histogram, list bounds and batch-neighbour entries
+            atomicAdd((unsigned long long*)&st[1], (unsigned long long)(8ull * lx + 16 + 8ull * bn));
     }
-    // the histogram holds h itself: k = c, y only = |h| > c
-    if (c < thr) { if (hlen > c) a1--; else a0--; }
-    else { if (hlen > c) b1--; else b0--; }
-    // every lower-ranked batch member adjacent to x (the pair phase leaves out
-    // the ones that meet h)
-    for (uint64_t e = 0; e < bn; e++) {
-        const uint64_t pay = P.bl_pay[bo + e];
-        if ((uint32_t)(pay >> 32) >= sh.rank) continue;
-        const uint32_t k = (uint32_t)(pay >> 1) & 0x7fffffffu, f = (uint32_t)pay & 1u;
-        if (k < thr) { if (f) a1--; else a0--; }
-        else { if (f) b1--; else b0--; }
-    }
-    uint64_t* o = A.open + (hlen > c ? 4 * COPIES : 0) + (threadIdx.x & (COPIES - 1));
-    if (b0) atomicAdd((unsigned long long*)&o[0], (unsigned long long)b0);
-    if (b1) atomicAdd((unsigned long long*)&o[COPIES], (unsigned long long)b1);
-    if (a0) atomicAdd((unsigned long long*)&o[2 * COPIES], (unsigned long long)a0);
-    if (a1) atomicAdd((unsigned long long*)&o[3 * COPIES], (unsigned long long)a1);
+    wm[lane] = m;
+    const uint64_t* H = (const uint64_t*)G.hpool;
+    wave_flat<4>(F, lx, [&](uint32_t l, uint32_t r) { return H[woff[l] + r]; },
+                 [&](bool ok, uint32_t l, uint32_t r, uint32_t, uint64_t hh) {
+                     if (!ok || !hh) return;
+                     const uint32_t ml = wm[l];
+                     if ((uint32_t)hh) add(meta_c(ml), r + 1, meta_len(ml), 0, (uint32_t)hh);
+                     if (hh >> 32) add(meta_c(ml), r + 1, meta_len(ml), 1, hh >> 32);
+                 });
+    // minus every lower-ranked batch member adjacent to x (the pair phase leaves out the
+    // ones that meet h)
+    woff[lane] = bo;
+    wave_flat<4>(F, bn, [&](uint32_t l, uint32_t r) { return P.bl_pay[woff[l] + r]; },
+                 [&](bool ok, uint32_t l, uint32_t, uint32_t, uint64_t pay) {
+                     if (!ok || (uint32_t)(pay >> 32) >= sh.rank) return;
+                     const uint32_t ml = wm[l];
+                     add(meta_c(ml), (uint32_t)(pay >> 1) & 0x7fffffffu, meta_len(ml), (uint32_t)pay & 1u, ~0ull);
+                 });
 }
 
-// The class changes of one intersecting neighbour pair (|x & y| = s, |h & x & y| =
-// shh), both eligible: in a full count the closed triad at its smallest-ID centre, in
-// a delta the open paths h-x-y and h-y-x taken back and the true class in place of the
-// disjoint one.
+// The class changes of n intersecting neighbour pairs of one kind (|x & y| = s,
+// |h & x & y| = shh), both eligible: in a full count the closed triad at its smallest-ID
+// centre, in a delta the open paths h-x-y and h-y-x taken back and the true class in place
+// of the disjoint one.
 __device__ __forceinline__ void he2_pair(const He2Params& P, const Tables& T, He2Acc& A, uint32_t hlen, uint32_t mx,
-                                         uint32_t my, uint32_t s, uint32_t shh) {
+                                         uint32_t my, uint32_t s, uint32_t shh, uint64_t n) {
     const uint32_t xl = meta_len(mx), yl = meta_len(my), cx = meta_c(mx), cy = meta_c(my);
     const uint32_t cf = (hlen > cx + cy ? 1u : 0u) | (xl > cx ? 2u : 0u) | (yl > cy ? 4u : 0u) | 40u;
     const uint32_t ct = (hlen + shh > cx + cy ? 1u : 0u) | (xl + shh > cx + s ? 2u : 0u) | (yl + shh > cy + s ? 4u : 0u) |
                         (cx > shh ? 8u : 0u) | (s > shh ? 16u : 0u) | (cy > shh ? 32u : 0u) | (shh ? 64u : 0u);
-    pair_add(A, T.he[cf], ~0u);
+    pair_add(A, T.he[cf], 0 - n);
     if (P.static_mode) {
-        if ((mx & my) >> 29 & 1u) pair_add(A, T.he[ct], 1u);
+        if ((mx & my) >> 29 & 1u) pair_add(A, T.he[ct], n);
         return;
     }
-    pair_add(A, T.he[ct], 1u);
-    pair_add(A, A.cls8[(hlen > cx ? 4u : 0u) | (xl > cx + s ? 2u : 0u) | (yl > s ? 1u : 0u)], ~0u);
-    pair_add(A, A.cls8[(hlen > cy ? 4u : 0u) | (yl > cy + s ? 2u : 0u) | (xl > s ? 1u : 0u)], ~0u);
+    pair_add(A, T.he[ct], n);
+    pair_add(A, A.cls8[(hlen > cx ? 4u : 0u) | (xl > cx + s ? 2u : 0u) | (yl > s ? 1u : 0u)], 0 - n);
+    pair_add(A, A.cls8[(hlen > cy ? 4u : 0u) | (yl > cy + s ? 2u : 0u) | (xl > s ? 1u : 0u)], 0 - n);
 }
 
-// Rows of all neighbours, a wave per 64 of them: per(xi, v, j) for every member v,
-// j counting the members of all rows (row_at[xi] + k for neighbour xi's k-th).  first:
-// the rows are laid out one after the other (row_at is written, sh.W their total);
-// else their members are read back from `stash`, where per() put them.
+// Pairs of neighbours that meet inside h, as if they met nowhere else.  What a pair
+// changes depends on x only through its mask of shared members, min(|x| - c, c + 1) and
+// (in a full count) h < x, so neighbours are counted by these and the pairs taken by kind:
+// a few dozen kinds in place of hundreds of neighbours.  rep/cnt: gcap slots, list: K words.
+template <int WG, bool BIG, bool GLOBAL>
+__device__ void he2_kinds(const He2Params& P, Sh2& sh, const Tables& T, He2Acc& A, const uint32_t* nl_meta,
+                          const uint32_t* mask, uint32_t K, uint32_t hlen, uint32_t* rep, uint32_t gcap) {
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t* cnt = rep + gcap;
+    uint32_t* list = cnt + gcap;
+    auto mask_of = [&](uint32_t i) {
+        return (uint64_t)ld_at<BIG>(&mask[2 * i]) | (uint64_t)ld_at<BIG>(&mask[2 * i + 1]) << 32;
+    };
+    auto rest_of = [&](uint32_t m) {
+        const uint32_t c = meta_c(m), d = meta_len(m) - c;
+        return (d < c + 1 ? d : c + 1) | (P.static_mode ? m & (1u << 29) : 0u);
+    };
+    for (uint32_t s = tid; s < gcap; s += WG) { rep[s] = HGT_EMPTY; cnt[s] = 0; }
+    if (tid == 0) sh.G = 0;
+    __syncthreads();
+    for (uint32_t i = tid; i < K; i += WG) {
+        const uint32_t m = nl_meta[i];
+        if (!meta_elig(m)) continue;
+        const uint64_t mk = mask_of(i);
+        const uint32_t rs = rest_of(m);
+        uint32_t s = fr_slot((uint32_t)mk * 0x9e3779b1u ^ (uint32_t)(mk >> 32) * 0x85ebca6bu ^ rs * 0xc2b2ae35u, gcap);
+        for (uint32_t probe = 0; probe < gcap; probe++) {
+            const uint32_t r = atomicCAS(&rep[s], HGT_EMPTY, i);
+            if (r == HGT_EMPTY) list[atomicAdd(&sh.G, 1u)] = s;
+            if (r == HGT_EMPTY || (mask_of(r) == mk && rest_of(nl_meta[r]) == rs)) {
+                atomicAdd(&cnt[s], 1u);
+                break;
+            }
+            s = fr_next(s, gcap);
+        }
+    }
+    __syncthreads();
+    const uint32_t Gn = sh.G;
+    for (uint32_t a = wave; a < Gn; a += WG / 64) {
+        const uint32_t sa = list[a], ra = ld_at<GLOBAL>(&rep[sa]), na = ld_at<GLOBAL>(&cnt[sa]), ma = nl_meta[ra];
+        const uint64_t ka = mask_of(ra);
+        for (uint32_t b = a + lane; b < Gn; b += 64) {
+            const uint32_t sb = list[b], rb = ld_at<GLOBAL>(&rep[sb]);
+            const uint32_t shh = __popcll(ka & mask_of(rb));
+            if (!shh) continue;
+            const uint64_t n = a == b ? (uint64_t)na * (na - 1) / 2 : (uint64_t)na * ld_at<GLOBAL>(&cnt[sb]);
+            if (n) he2_pair(P, T, A, hlen, ma, nl_meta[rb], shh, shh, n);
+        }
+    }
+    __syncthreads();
+}
+
+// Rows of all neighbours, a wave per `per` of them: use(xi, v, j) for every member v, j
+// numbering the members of all rows; called by all lanes of a wave together with ok false
+// where there is none.  first: the chunks' places are taken (place, sh.W their total) and
+// the members fetched; else they are read back from `stash`, where the first pass put them.
 template <int WG, class F>
 __device__ __forceinline__ void he2_rows(const GraphView& G, Sh2& sh, const uint32_t* nl_x, const uint32_t* nl_meta,
-                                         uint32_t* row_at, uint32_t K, const uint32_t* stash, uint32_t (*wpre)[65],
-                                         uint64_t (*woff)[64], bool first, F per) {
+                                         uint32_t* place, uint32_t K, uint32_t per, const uint32_t* stash, Flat& fl,
+                                         uint64_t* woff, bool first, F use) {
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (uint32_t c0 = wave * 64; c0 < K; c0 += WG) {
-        const uint32_t cnt = K - c0 < 64 ? K - c0 : 64;
+    for (uint32_t c = wave; c * per < K; c += WG / 64) {
+        const uint32_t c0 = c * per, n = K - c0 < per ? K - c0 : per;
         uint32_t d = 0;
-        if (lane < cnt) {
+        if (lane < n) {
             d = meta_len(nl_meta[c0 + lane]);
-            if (first) woff[wave][lane] = G.h_off[nl_x[c0 + lane]];
+            if (first) woff[lane] = G.h_off[nl_x[c0 + lane]];
         }
-        uint32_t inc = d;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t t = __shfl_up(inc, o, 64);
-            if (lane >= (uint32_t)o) inc += t;
-        }
-        const uint32_t tot = __shfl(inc, 63, 64);
         uint32_t base = 0;
         if (first) {
-            if (lane == 0) base = atomicAdd(&sh.W, tot);
+            uint32_t tot = d;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) tot += __shfl_xor(tot, o, 64);
+            if (lane == 0) {
+                base = atomicAdd(&sh.W, tot);
+                place[c] = base;
+            }
             base = __shfl(base, 0, 64);
-            if (lane < cnt) row_at[c0 + lane] = base + inc - d;
+            wave_flat<4>(fl, d, [&](uint32_t l, uint32_t r) { return G.h2v[woff[l] + r]; },
+                         [&](bool ok, uint32_t l, uint32_t, uint32_t p, uint32_t v) { use(ok, c0 + l, v, base + p); });
         } else {
-            base = row_at[c0];
+            base = place[c];
+            uint32_t ex = d;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t t = __shfl_up(ex, o, 64);
+                if (lane >= (uint32_t)o) ex += t;
+            }
+            woff[lane] = base + ex - d;
+            wave_flat<4>(fl, d, [&](uint32_t l, uint32_t r) { return stash[woff[l] + r]; },
+                         [&](bool ok, uint32_t l, uint32_t, uint32_t p, uint32_t v) { use(ok, c0 + l, v, base + p); });
         }
-        wpre[wave][lane + 1] = inc;
-        if (lane == 0) wpre[wave][0] = 0;
-        wave_sync();
-        for (uint32_t p = lane; p < tot; p += 64) {
-            const uint32_t k = seg_of<uint32_t>(wpre[wave], cnt, p);
-            const uint32_t v = first ? G.h2v[woff[wave][k] + (p - wpre[wave][k])] : stash[base + p];
-            per(c0 + k, v, base + p);
-        }
-        wave_sync();
     }
 }
 
@@ -594,14 +674,18 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
                          He2Acc& A, uint64_t* st, uint64_t* ph) {
     constexpr uint32_t NW = WG / 64;
     constexpr int STAGE = BIG ? 2 : 0;
-    constexpr uint32_t BM_LOG = BIG ? 18 : 14;          // bits of each vertex bitmap
+    constexpr uint32_t BM_LOG = BIG ? 17 : 14;          // bits of each vertex bitmap
+    constexpr uint32_t BH_LOG = 12, BH_WORDS = 1u << (BH_LOG - 5);  // ... and of the one of h's members
     constexpr uint32_t BM_WORDS = 1u << (BM_LOG - 5);
     constexpr uint32_t POS = 0x7fffffffu;               // a run cursor; the top bit: the vertex lies in h
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    __shared__ uint32_t wpre[NW][65];
-    __shared__ uint64_t woff[NW][64];
+    __shared__ Flat flat[NW];
+    __shared__ uint64_t woff_all[NW][64];
+    __shared__ uint32_t wm_all[NW][64];
+    Flat& fl = flat[wave];
+    uint64_t* woff = woff_all[wave];
+    uint32_t* wm = wm_all[wave];
     uint32_t q = 0, q_end = 0;  // thread 0: work items taken
-    uint32_t folded = 0;    // pairs this wave counted since its last fold
     uint64_t t_mark = 0;    // thread 0: wall clock at the last phase mark (profiling)
     uint64_t t_centre = 0;  // ... at the start of the current centre
 #define HE2_MARK(i)                                     \
@@ -699,7 +783,7 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
             pre[hlen] = lh;
             sh.lh = lh;
             const uint64_t cap = (uint64_t)lh + lh / 2 + 32;
-            sh.defer = (lh >= K_MAX_N || 2 * cap + 3ull * lh + 4 * hlen + 8 > AW) ? 1u : 0u;
+            sh.defer = (lh >= K_MAX_N || 2 * cap + 2ull * lh + lh / 64 + NW + 1 + 4 * hlen + 8 > AW) ? 1u : 0u;
         }
         __syncthreads();
         if (sh.defer) {
@@ -707,13 +791,15 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
             continue;
         }
         HE2_MARK(0);
-        // --- N(h).  Arena: hash (2 cap) | IDs, metas, row starts of the neighbours (lh each) | h's members
+        // --- N(h).  Arena: hash (2 cap), later the masks of shared members | IDs and metas of
+        // the neighbours (lh each) | h's members | places of the row chunks
         const uint32_t lh = sh.lh, cap = hash_cap(lh);
+        uint32_t* mask = arena;
         uint32_t* nl_x = arena + 2 * cap;
         uint32_t* nl_meta = nl_x + lh;
-        uint32_t* row_at = nl_meta + lh;
-        uint32_t* hm = row_at + lh;
-        uint32_t base0 = (uint32_t)(hm + hlen - arena);
+        uint32_t* hm = nl_meta + lh;
+        uint32_t* place_c = hm + hlen;
+        uint32_t base0 = (uint32_t)(place_c + lh / 64 + NW + 1 - arena);
         const uint32_t lds_used = BIG ? (3 * hlen + 8) & ~1u : 0;  // pre and voff
         if (BIG && lds_used + 2 * cap <= LDS_L) {
             he2_nh<WG>(G.g, h, hlen, lh, pre, voff, lds + lds_used, lds + lds_used + cap, cap);
@@ -725,25 +811,45 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
             he2_compact<WG, BIG>(P, G, sh, arena, arena + cap, cap, nl_x, nl_meta);
         }
         HE2_MARK(2);
-        const uint32_t K = sh.K;
-        for (uint32_t i = tid; i < hlen; i += WG) hm[i] = G.g.h2v[sh.hoff + i];
-        // --- vertices that two neighbours may share: a second row holding a vertex
-        // finds its bit set and sets the bit in the second bitmap (the members are
-        // stashed, so a row is gathered once)
+        const uint32_t K = sh.K, per = K / NW + 1 < 64 ? K / NW + 1 : 64;
+        const bool masked = hlen <= MASK_BITS;
+        // --- vertices outside h that two neighbours may share: a second row holding a vertex
+        // finds its bit set and sets the bit in the second bitmap (the members are stashed, so a
+        // row is gathered once).  Members of h (a third bitmap tells) go into the neighbour's
+        // mask; with more members than a mask holds they are treated like the others.
         uint32_t* bm = BIG ? lds : arena + base0;
-        if (!BIG) base0 += 2 * BM_WORDS;
+        uint32_t* bh = bm + 2 * BM_WORDS;
+        if (!BIG) base0 += 2 * BM_WORDS + BH_WORDS;
         uint32_t* stash = arena + base0;
         const uint32_t room = base0 < AW ? AW - base0 : 0;  // words left for the stash and the survivors
         if (room) {
-            for (uint32_t i = tid; i < 2 * BM_WORDS; i += WG) bm[i] = 0;
+            for (uint32_t i = tid; i < 2 * BM_WORDS + BH_WORDS; i += WG) bm[i] = 0;
+            if (masked)
+                for (uint32_t i = tid; i < 2 * K; i += WG) mask[i] = 0;
+            __syncthreads();
+            for (uint32_t i = tid; i < hlen; i += WG) {
+                const uint32_t v = G.g.h2v[sh.hoff + i], b = (v * 2654435761u) >> (32 - BH_LOG);
+                hm[i] = v;
+                if (masked) atomicOr(&bh[b >> 5], 1u << (b & 31));
+            }
         }
         __syncthreads();
         if (room)
-            he2_rows<WG>(G.g, sh, nl_x, nl_meta, row_at, K, nullptr, wpre, woff, true,
-                         [&](uint32_t, uint32_t v, uint32_t j) {
-                             if (j < room) stash[j] = v;
-                             const uint32_t b = (v * 2654435761u) >> (32 - BM_LOG);
-                             const uint32_t bit = 1u << (b & 31);
+            he2_rows<WG>(G.g, sh, nl_x, nl_meta, place_c, K, per, nullptr, fl, woff, true,
+                         [&](bool ok, uint32_t xi, uint32_t v, uint32_t j) {
+                             if (!ok) return;
+                             const uint32_t hv = v * 2654435761u, bj = hv >> (32 - BH_LOG);
+                             uint32_t in = 0;
+                             if (bh[bj >> 5] >> (bj & 31) & 1u) {
+                                 const uint32_t k = lower_bound_u32(hm, hlen, v);
+                                 if (k < hlen && hm[k] == v) {
+                                     in = 1u << 31;
+                                     atomicOr(&mask[2 * xi + (k >> 5)], 1u << (k & 31));
+                                 }
+                             }
+                             if (j < room) stash[j] = v | in;
+                             if (in) return;
+                             const uint32_t b = hv >> (32 - BM_LOG), bit = 1u << (b & 31);
                              if (atomicOr(&bm[b >> 5], bit) & bit) atomicOr(&bm[BM_WORDS + (b >> 5)], bit);
                          });
         __syncthreads();
@@ -761,12 +867,16 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
         // survivors (vertex, neighbour), from the arena's end downwards
         const uint32_t s_cap = (room - W) / 2;
         uint32_t* s_end = arena + AW;
-        he2_rows<WG>(G.g, sh, nl_x, nl_meta, row_at, K, stash, wpre, woff, false,
-                     [&](uint32_t xi, uint32_t v, uint32_t) {
+        he2_rows<WG>(G.g, sh, nl_x, nl_meta, place_c, K, per, stash, fl, woff, false,
+                     [&](bool ok, uint32_t xi, uint32_t v, uint32_t) {
                          const uint32_t b = (v * 2654435761u) >> (32 - BM_LOG);
-                         if (!(bm[BM_WORDS + (b >> 5)] >> (b & 31) & 1u)) return;
-                         const uint32_t q = atomicAdd(&sh.S, 1u);
-                         if (q < s_cap) {
+                         const bool keep = ok && !(v >> 31) && (bm[BM_WORDS + (b >> 5)] >> (b & 31) & 1u);
+                         const uint64_t m = __ballot(keep);
+                         if (!m) return;
+                         uint32_t q = 0;
+                         if (lane == 0) q = atomicAdd(&sh.S, (uint32_t)__popcll(m));
+                         q = __shfl(q, 0, 64) + __popcll(m & ((1ull << lane) - 1));
+                         if (keep && q < s_cap) {
                              s_end[-1 - 2 * (int32_t)q] = xi;
                              s_end[-2 - 2 * (int32_t)q] = v;
                          }
@@ -776,7 +886,7 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
         // --- exact groups: hash of the survivors' vertices, runs, and per neighbour its
         // shared vertices.  The regions go where they fit: over the bitmaps and the stash,
         // or over the hash of N(h).
-        uint32_t lo_at = 0, hi_at = BIG ? base0 : base0 - 2 * BM_WORDS;
+        uint32_t lo_at = masked ? 2 * K : 0, hi_at = BIG ? base0 : base0 - 2 * BM_WORDS - BH_WORDS;
         const uint32_t lo_end = 2 * cap, hi_end = AW - 2 * S;
         bool fits = S <= s_cap;
         auto place = [&](uint32_t words) -> uint32_t {
@@ -791,8 +901,15 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
         uint32_t* tcur = arena + place(vcap + 1);
         uint32_t* rx = arena + place(S);
         uint32_t* er = arena + place(S);
+        uint32_t* el = arena + place(S);
         uint32_t* ecur = arena + place(K);
-        uint32_t* cnts = BIG ? lds : arena + place(NW * K > 2 * hlen + 2 ? NW * K : 2 * hlen + 2);
+        // the counters; before them the (c, f) histogram and the kinds of neighbours
+        const uint32_t gcap = hash_cap(K), k_words = masked ? 2 * gcap + K : 0;
+        uint32_t c_words = NW * K > 2 * hlen + 2 ? NW * K : 2 * hlen + 2;
+        if (k_words > c_words) c_words = k_words;
+        uint32_t* cnts = BIG ? lds : arena + place(c_words);
+        const bool k_lds = !BIG || k_words <= LDS_L;
+        uint32_t* kinds = k_lds ? cnts : arena + place(k_words);
         if (!fits) {
             __syncthreads();
             move_on();
@@ -843,22 +960,43 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
             er[atomicAdd(&ecur[xi], 1u)] = s;
         }
         __syncthreads();
-        // now run s is [end of s - 1, tcur[s]) and neighbour i's shared vertices [ecur[i-1], ecur[i])
+        // now run s is [end of s - 1, tcur[s]) and neighbour i's shared vertices [ecur[i-1], ecur[i]):
+        // their runs' starts and lengths in place of their slots
+        const uint32_t SE = K ? ld_at<BIG>(&ecur[K - 1]) : 0;
+        for (uint32_t e = tid; e < SE; e += WG) {
+            const uint32_t s = er[e], t1 = ld_at<BIG>(&tcur[s]), r0 = s ? ld_at<BIG>(&tcur[s - 1]) & POS : 0;
+            er[e] = r0 | (t1 & ~POS);
+            el[e] = (t1 & POS) - r0;
+        }
         HE2_MARK(8);
         // --- disjoint-pair classes (the first slice); the histogram lies over the counters in the global stage
         if (slice == 0) {
             he2_disjoint<WG>(sh, T, A, nl_meta, K, hlen, cnts);
             __syncthreads();
+            if (masked) {
+                if (k_lds) he2_kinds<WG, BIG, false>(P, sh, T, A, nl_meta, mask, K, hlen, cnts, gcap);
+                else he2_kinds<WG, BIG, true>(P, sh, T, A, nl_meta, mask, K, hlen, kinds, gcap);
+            }
         }
+        __syncthreads();
         HE2_MARK(3);
         // --- open paths h - x - y through the histograms, per eligible neighbour
         if (!P.static_mode)
-            for (uint32_t i = tid; i < K; i += WG) {
-                const uint32_t m = nl_meta[i], x = nl_x[i];
-                if (meta_elig(m) && (nslice == 1 || slice_of(x, nslice) == slice)) he2_open(P, G, sh, A, x, m, st);
+            for (uint32_t c0 = wave * per; c0 < K; c0 += NW * per) {
+                uint32_t x = 0, m = 0;
+                bool take = lane < per && c0 + lane < K;
+                if (take) {
+                    x = nl_x[c0 + lane];
+                    m = nl_meta[c0 + lane];
+                    take = meta_elig(m) && (nslice == 1 || slice_of(x, nslice) == slice);
+                }
+                he2_open(P, G, sh, A, fl, wm, woff, take, x, m, st);
             }
         HE2_MARK(5);
-        // --- intersecting neighbour pairs
+        // --- intersecting neighbour pairs (masked: those that meet outside h too)
+        auto mask_of = [&](uint32_t i) {
+            return (uint64_t)ld_at<BIG>(&mask[2 * i]) | (uint64_t)ld_at<BIG>(&mask[2 * i + 1]) << 32;
+        };
         const uint32_t cw = BIG ? CNT_L : K;  // counters per wave
         uint32_t* cnt = cnts + wave * cw;
         for (uint32_t i = lane; i < cw; i += 64) cnt[i] = 0;
@@ -882,36 +1020,62 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
             const uint32_t i = wave + NW * (c0 + r);
             const uint32_t mx = __shfl(mx_l, r, 64), e0 = __shfl(e0_l, r, 64), e1 = __shfl(e1_l, r, 64);
             const uint32_t x = __shfl(x_l, r, 64);
-            // lanes in groups, a group per shared vertex: few vertices, wide groups
-            const uint32_t ne = e1 - e0;
-            const uint32_t glog = ne == 1 ? 6 : ne == 2 ? 5 : ne <= 8 ? 4 : ne <= 16 ? 3 : 2;
-            const uint32_t ng = 64u >> glog, gid = lane >> glog, sub = lane & ((1u << glog) - 1);
-            auto walk = [&](uint32_t w0, uint32_t w1, auto fn) {
-                for (uint32_t e = e0 + gid; e < e1; e += ng) {
-                    const uint32_t s = er[e];
-                    const uint32_t r0 = s ? ld_at<BIG>(&tcur[s - 1]) & POS : 0, t1 = ld_at<BIG>(&tcur[s]);
-                    for (uint32_t j = r0 + sub; j < (t1 & POS); j += 1u << glog) {
-                        const uint32_t y = rx[j];
-                        if (y >= w0 && y < w1) fn(y, t1 >> 31);
-                    }
+            const uint64_t mkx = masked ? mask_of(i) : 0;
+            // every neighbour on the runs of x's shared vertices: fn(y, [the vertex lies in h])
+            auto walk = [&](auto fn) {
+                uint32_t tot = 0;
+                if (e1 - e0 == 1) {
+                    const uint32_t t = er[e0], R = el[e0];
+                    for (uint32_t j = lane; j < R; j += 64) fn(rx[(t & POS) + j], t >> 31);
+                    return R;
                 }
+                for (uint32_t e = e0; e < e1; e += 64) {
+                    uint32_t d = 0;
+                    if (e + lane < e1) {
+                        wm[lane] = er[e + lane];
+                        d = el[e + lane];
+                    }
+                    tot += wave_flat<4>(fl, d, [&](uint32_t l, uint32_t j) { return rx[(wm[l] & POS) + j]; },
+                                        [&](bool ok, uint32_t l, uint32_t, uint32_t, uint32_t y) {
+                                            if (ok) fn(y, wm[l] >> 31);
+                                        });
+                }
+                return tot;
             };
             for (uint32_t w0 = nslice == 1 ? i + 1 : 0; w0 < K; w0 += cw) {
                 const uint32_t w1 = K - w0 < cw ? K : w0 + cw;
-                walk(w0, w1, [&](uint32_t y, uint32_t in) { atomicAdd(&cnt[y - w0], 1u + (in << 16)); });
-                wave_sync();
-                walk(w0, w1, [&](uint32_t y, uint32_t) {
-                    const uint32_t v = atomicExch(&cnt[y - w0], 0u);
-                    if (!v || (nslice > 1 && nl_x[y] <= x)) return;  // taken at another shared vertex, or row
-                    const uint32_t my = nl_meta[y];
-                    if (meta_elig(my)) he2_pair(P, T, A, hlen, mx, my, v & 0xffffu, v >> 16);
+                const uint32_t tot = walk([&](uint32_t y, uint32_t in) {
+                    if (y >= w0 && y < w1) atomicAdd(&cnt[y - w0], 1u + (in << 16));
                 });
                 wave_sync();
-                folded += w1 - w0;
-            }
-            if (folded >= FOLD_AT) {
-                pair_fold(A);
-                folded = 0;
+                auto take = [&](uint32_t y, uint32_t v) {
+                    if (nslice > 1 && nl_x[y] <= x) return;  // the other row's
+                    const uint32_t my = nl_meta[y];
+                    if (!meta_elig(my)) return;
+                    if (masked) {  // v vertices outside h, on top of those inside
+                        const uint32_t shh = __popcll(mkx & mask_of(y));
+                        he2_pair(P, T, A, hlen, mx, my, shh + v, shh, 1);
+                        if (shh) he2_pair(P, T, A, hlen, mx, my, shh, shh, ~0ull);
+                    } else {
+                        he2_pair(P, T, A, hlen, mx, my, v & 0xffffu, v >> 16, 1);
+                    }
+                };
+                // the counted ones, by a look at all counters or by another walk, whichever is shorter
+                if (w1 - w0 <= 4 * tot + 64) {
+                    for (uint32_t y = w0 + lane; y < w1; y += 64) {
+                        const uint32_t v = cnt[y - w0];
+                        if (!v) continue;
+                        cnt[y - w0] = 0;
+                        take(y, v);
+                    }
+                } else {
+                    walk([&](uint32_t y, uint32_t) {
+                        if (y < w0 || y >= w1) return;
+                        const uint32_t v = atomicExch(&cnt[y - w0], 0u);
+                        if (v) take(y, v);  // else taken at another shared vertex
+                    });
+                }
+                wave_sync();
             }
           }
         }
@@ -960,7 +1124,7 @@ __device__ __forceinline__ void he2_kernel(const He2Params& P, uint32_t* arena, 
     he2_flush_stats<BIG ? 2 : 0>(P, st, ph);
 }
 
-__global__ void __launch_bounds__(HGT_WG) k_he2_s0(He2Params P) {
+__global__ void __launch_bounds__(HGT_WG, 4) k_he2_s0(He2Params P) {
     __shared__ __attribute__((aligned(16))) uint32_t arena[ARENA_S];
     he2_kernel<false, HGT_WG>(P, arena, ARENA_S, nullptr);
 }
@@ -970,38 +1134,61 @@ __global__ void __launch_bounds__(WG_L, 4) k_he2_s2(He2Params P) {
     he2_kernel<true, WG_L>(P, P.garena + (uint64_t)blockIdx.x * P.garena_words, (uint32_t)P.garena_words, lds);
 }
 
-// Slices of the global stage's centres, one wave per centre: the pairs along its
-// members' lists (sum of the squared list lengths) over SLICE_PAIRS.  A launch of few
-// centres cuts finer, so that one dense centre does not outlast the rest.
-constexpr uint64_t SLICE_PAIRS = 1ull << 19;
-constexpr uint32_t SLICES_MAX = 64;
-__global__ void k_he2_slices(Multi M, const uint64_t* __restrict__ list, const uint32_t* n_p, uint64_t cap,
-                             uint32_t slice_lh, uint64_t slice_pairs, uint64_t* pre) {
+// Slices of the global stage's centres.  A wave per centre estimates its work in walked
+// run entries: its lists (the rows are gathered by every slice), and the pairs of its
+// neighbours.  Those that meet inside h count when h is too long for masks (squares of the
+// list lengths); outside h, a vertex of degree d lies in about d K / E neighbours, so the
+// runs' squares sum to (K / E)^2 sum_v d^2, and sum_v d^2 is the incidences times the
+// degree of a random member, for which h's own members stand in.
+__global__ void k_he2_work(Multi M, const uint64_t* __restrict__ list, const uint32_t* n_p, uint64_t cap,
+                           uint32_t slice_lh, uint64_t* pre, uint64_t* total) {
     const int lane = threadIdx.x & 63;
-    const uint64_t c = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const uint32_t n = *n_p;
-    if (c == 0 && lane == 0) pre[cap] = n;
-    if (c >= n) return;
-    const uint64_t it = list[c];
-    const GraphView& g = M.graphs[(uint32_t)(it >> 32)].g;
-    const uint32_t h = (uint32_t)it;
-    const uint32_t* row = g.h2v + g.h_off[h];
-    const uint32_t len = g.h_len[h];
-    uint64_t lh = 0, sq = 0;
-    for (uint32_t i = lane; i < len; i += 64) {
-        const uint64_t d = g.v_len[row[i]];
-        lh += d;
-        sq += d * d;
-    }
+    uint64_t sum = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) pre[cap] = n;
+    for (uint64_t c = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; c < n;
+         c += ((uint64_t)gridDim.x * blockDim.x) >> 6) {
+        const uint64_t it = list[c];
+        const HeGraph& G = M.graphs[(uint32_t)(it >> 32)];
+        const GraphView& g = G.g;
+        const uint32_t h = (uint32_t)it;
+        const uint32_t* row = g.h2v + g.h_off[h];
+        const uint32_t len = g.h_len[h];
+        uint64_t lh = 0, sq = 0;
+        for (uint32_t i = lane; i < len; i += 64) {
+            const uint64_t d = g.v_len[row[i]];
+            lh += d;
+            sq += d * d;
+        }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        lh += __shfl_xor(lh, o, 64);
-        sq += __shfl_xor(sq, o, 64);
+        for (int o = 32; o > 0; o >>= 1) {
+            lh += __shfl_xor(lh, o, 64);
+            sq += __shfl_xor(sq, o, 64);
+        }
+        double w = (double)lh * (double)lh * G.pair_scale * ((double)lh / (len ? len : 1));
+        const double all = (double)lh * (double)lh;
+        if (w > all) w = all;
+        if (len > MASK_BITS) w += (double)sq;
+        w += 32.0 * (double)lh;
+        const uint64_t work = slice_lh ? (lh + slice_lh - 1) / slice_lh : (uint64_t)w;
+        if (lane == 0) pre[c] = work;
+        sum += work;
     }
-    if (lane == 0) {
-        const uint64_t full = slice_pairs ? slice_pairs : SLICE_PAIRS;
-        const uint64_t per = n >= 512 ? full : (full * n / 512 > full / 16 ? full * n / 512 : full / 16);
-        uint64_t sl = slice_lh ? (lh + slice_lh - 1) / slice_lh : (sq + per - 1) / per;
+    if (lane == 0 && sum) atomicAdd((unsigned long long*)total, (unsigned long long)sum);
+}
+
+// Work to slices: a quarter of a workgroup's share of the whole, so that the last ones
+// end together, and at least SLICE_MIN (what building the tables again costs).
+constexpr uint64_t SLICE_MIN = 1ull << 15;
+constexpr uint32_t SLICES_MAX = 64;
+__global__ void k_he2_cut(uint64_t cap, uint32_t slice_lh, uint64_t slice_pairs, uint32_t grid, const uint64_t* total,
+                          uint64_t* pre) {
+    const uint64_t n = pre[cap];
+    uint64_t per = *total / (4ull * grid);
+    if (per < SLICE_MIN) per = SLICE_MIN;
+    if (slice_pairs) per = slice_pairs;
+    for (uint64_t c = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; c < n; c += (uint64_t)gridDim.x * blockDim.x) {
+        const uint64_t sl = slice_lh ? pre[c] : (pre[c] + per - 1) / per;
         pre[c] = sl < 1 ? 1 : (sl > SLICES_MAX ? SLICES_MAX : sl);
     }
 }
@@ -1041,8 +1228,10 @@ void he2_launch_lds(He2Params& P, unsigned grid, hipStream_t s) {
 void he2_launch_global(He2Params& P, unsigned grid, hipStream_t s) {
     if (!P.M.total) return;
     const uint64_t cap = P.slice_cap;
-    k_he2_slices<<<(unsigned)((cap * 64 + 255) / 256), 256, 0, s>>>(P.M, P.list[0], &P.count[0], cap, P.slice_lh,
-                                                                    P.slice_pairs, P.slice_pre);
+    const unsigned waves = (unsigned)((cap + 3) / 4), blk = (unsigned)((cap + 255) / 256);
+    k_he2_work<<<waves < 1024 ? waves : 1024, 256, 0, s>>>(P.M, P.list[0], &P.count[0], cap, P.slice_lh, P.slice_pre,
+                                                           P.work_total);
+    k_he2_cut<<<blk < 256 ? blk : 256, 256, 0, s>>>(cap, P.slice_lh, P.slice_pairs, grid, P.work_total, P.slice_pre);
     hgt_scan_u64(P.slice_pre, P.slice_pre, cap, P.slice_pre + cap, P.slice_pre + cap + 1, P.slice_scan_tmp, s);
     k_he2_s2<<<grid, WG_L, 0, s>>>(P);
 }

@@ -447,3 +447,21 @@ def test_incident_vertex_owner_stages(gpu_lib, monkeypatch, stage, card):
         p.apply(b, f"owners batch {k}")
         compare_counts(p.g, p.o, p.track, f"owners batch {k}")
     p.close()
+
+
+@pytest.mark.parametrize("stage", ["0", "1"])
+@pytest.mark.parametrize("card", [(62, 66), (1, 2), (3, 12)])
+def test_shared_member_masks(gpu_lib, monkeypatch, stage, card):
+    """Neighbours counted by the mask of members they share with the centre: rows
+    around the 64 members a mask holds, single members and repeated rows (nothing
+    private), in the LDS and in the global stage; build and batches against the
+    oracle."""
+    monkeypatch.setenv("HGT_FORCE_STAGE", stage)
+    nv, n = (400, 50) if card[0] > 10 else (12, 150)
+    st = W.plain_stream("masks", nv, n, ("uniform",) + card, 0.7, 0.0, 2, 20, 15, W.SEED_BASE + 99)
+    p = Pair(st, track=("hyperedge",))
+    compare_counts(p.g, p.o, p.track, "masks build")
+    for k, b in enumerate(st.batches):
+        p.apply(b, f"masks batch {k}")
+        compare_counts(p.g, p.o, p.track, f"masks batch {k}")
+    p.close()
