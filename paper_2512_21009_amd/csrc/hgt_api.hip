@@ -245,6 +245,7 @@ struct PhaseCtx {
     DevBuf iv_list0, iv_list, iv_list2, iv_garena, iv_garena2;  // incident-vertex stage scratch
     DevBuf t_ctr, t_big_list, t_big_rank, t_big_scratch, t_list1, t_rank1, t_garena, t_whash;
     DevBuf t_slices, t_slice_scan;       // slices of the 2-hop kernel's centres
+    DevBuf p_list0, p_list1, p_scratch;  // temporal open paths: middle hyperedges, the largest ones' tables
     DevBuf ent_x, ent_d, ent_pay, bl_cnt, bl_off, bl_cur, bl_d, bl_pay, nb_scratch, bl_scan;
     // per-graph phase descriptors: device copies and their pinned staging, one
     // slot per (phase, family) so no upload overwrites one still in flight
@@ -508,7 +509,7 @@ int ensure_plan_scratch(hgt_graph* g, const Sizes& z, PlanScratch& w) {
 // ---- triad phases ---------------------------------------------------------
 void phase_ctx_free(PhaseCtx& c) {
     DevBuf* all[] = {&c.t_ctr, &c.t_whash, &c.t_big_list, &c.t_big_rank, &c.t_big_scratch, &c.t_list1, &c.t_rank1,
-                     &c.t_slices, &c.t_slice_scan,
+                     &c.t_slices, &c.t_slice_scan, &c.p_list0, &c.p_list1, &c.p_scratch,
                      &c.t_garena, &c.ent_x, &c.ent_d, &c.ent_pay, &c.bl_cnt, &c.bl_off, &c.bl_cur,
                      &c.bl_d, &c.bl_pay, &c.nb_scratch, &c.bl_scan, &c.desc, &c.iv_list0, &c.iv_list, &c.iv_list2, &c.iv_garena,
                      &c.iv_garena2};
@@ -696,7 +697,15 @@ struct PhaseShape {
     BigLayout L;
     uint64_t grid_big, grid_small, grid_tmp, grid_2hop, grid_s0, grid_g, garena_words, nb_grid, nb_words;
     uint32_t wave_slots;
+    bool tmp_lists;  // temporal: open paths per middle hyperedge, from batch-neighbour lists
 };
+
+// Largest batch-neighbour lists the temporal family takes (28 bytes per member-list entry
+// of the changed hyperedges); above, and in the no-allocation entry point, the 2-hop kernels
+// run, which need no lists.
+constexpr uint64_t kTmpListBytes = 32ull << 30;
+constexpr uint64_t kPathWords = 1ull << 20;  // 4 MB per workgroup of the largest middle hyperedges
+constexpr unsigned kPathGrid = 64;
 
 constexpr uint64_t kGarenaWords = 1ull << 19;  // 2 MB global arena per workgroup of the global stage
 
@@ -727,7 +736,36 @@ PhaseShape phase_shape(const hgt_graph* owner, uint64_t n, uint64_t max_lh, uint
                     : std::min<uint64_t>(n_cu * (uint64_t)wg_per_cu, 64 * n);
     z.garena_words = lean && n < 2 ? kGarenaWords / 2 : kGarenaWords;
     z.total_ids = total_ids;
+    z.tmp_lists = !lean && 28 * z.ecap <= kTmpListBytes;
     return z;
+}
+
+// The batch-neighbour lists, and the tables of the stages that use them.
+int lists_reserve(PhaseCtx& c, const PhaseShape& z) {
+    const uint64_t ids = z.total_ids;
+    int rc = 0;
+    rc |= ensure(c.ent_x, z.ecap * 4);
+    rc |= ensure(c.ent_d, z.ecap * 4);
+    rc |= ensure(c.ent_pay, z.ecap * 8);
+    rc |= ensure(c.bl_d, z.ecap * 4);
+    rc |= ensure(c.bl_pay, z.ecap * 8);
+    rc |= ensure(c.bl_cnt, ids * 8);
+    rc |= ensure(c.bl_off, ids * 8);
+    rc |= ensure(c.bl_cur, ids * 8);
+    rc |= ensure(c.bl_scan, hgt_scan_tmp_bytes(ids));
+    rc |= ensure(c.nb_scratch, z.nb_grid * z.nb_words * 4);
+    rc |= ensure(c.t_garena, z.grid_g * z.garena_words * 4);
+    return rc ? HGT_ENOMEM : HGT_OK;
+}
+
+// ... for the temporal family: HGT_ENOMEM leaves it to the 2-hop kernels.
+int paths_reserve(PhaseCtx& c, const PhaseShape& z) {
+    if (!z.tmp_lists) return HGT_ENOMEM;
+    int rc = lists_reserve(c, z);
+    rc |= ensure(c.p_list0, z.total_ids * 4);
+    rc |= ensure(c.p_list1, z.total_ids * 4);
+    rc |= ensure(c.p_scratch, kPathGrid * kPathWords * 4);
+    return rc ? HGT_ENOMEM : HGT_OK;
 }
 
 // Every scratch buffer of one family's phase at the shape's sizes.
@@ -744,18 +782,7 @@ int phase_reserve(PhaseCtx& c, int family, const PhaseShape& z) {
     rc |= ensure(c.t_slices, (n + 2) * 8);
     rc |= ensure(c.t_slice_scan, hgt_scan_tmp_bytes(n));
     if (family == HGT_TRIAD_HYPEREDGE) {
-        const uint64_t ids = z.total_ids;
-        rc |= ensure(c.ent_x, z.ecap * 4);
-        rc |= ensure(c.ent_d, z.ecap * 4);
-        rc |= ensure(c.ent_pay, z.ecap * 8);
-        rc |= ensure(c.bl_d, z.ecap * 4);
-        rc |= ensure(c.bl_pay, z.ecap * 8);
-        rc |= ensure(c.bl_cnt, ids * 8);
-        rc |= ensure(c.bl_off, ids * 8);
-        rc |= ensure(c.bl_cur, ids * 8);
-        rc |= ensure(c.bl_scan, hgt_scan_tmp_bytes(ids));
-        rc |= ensure(c.nb_scratch, z.nb_grid * z.nb_words * 4);
-        rc |= ensure(c.t_garena, z.grid_g * z.garena_words * 4);
+        rc |= lists_reserve(c, z);
     }
     return rc ? HGT_ENOMEM : HGT_OK;
 }
@@ -764,7 +791,8 @@ int phase_reserve(PhaseCtx& c, int family, const PhaseShape& z) {
 // inserted ones on the new graphs) for every job, in one launch per kernel.
 // Counter slots in t_ctr: 0-2 neighbour pass, 5 2-hop queue for the centres the
 // histogram stages pass on, 6-8 temporal, 10-11 entry count, 16-18 stage queues,
-// 19-21 stage hand-over counts, 24-25 the global stage's estimated work.
+// 19-21 stage hand-over counts, 24-25 the global stage's estimated work, 26-31 temporal
+// open paths.
 int run_phase(hgt_graph* owner, const PhaseJob* jobs, uint32_t nj, bool minus, bool full, hipStream_t s) {
     PhaseCtx& c = ctx_of(owner);
     uint64_t* stats = owner->prof ? owner->stats.as<uint64_t>() : nullptr;
@@ -801,15 +829,15 @@ int run_phase(hgt_graph* owner, const PhaseJob* jobs, uint32_t nj, bool minus, b
         P.big = L;
         P.stats = stats;
         const unsigned grid_small = (unsigned)z.grid_small;
-        if (family == HGT_TRIAD_HYPEREDGE) {
-            // neighbour pass: batch-neighbour entries; histogram updates for inserts
-            const uint64_t ecap = z.ecap, nb_words = z.nb_words, nb_grid = z.nb_grid;
+        // neighbour pass: batch-neighbour entries; histogram updates for inserts
+        auto neighbours = [&](bool in_window) {
             NbrParams N{};
             N.M = M;
-            N.inserting = minus ? 0 : 1;
-            N.emit_entries = full ? 0 : 1;
+            N.inserting = minus || in_window ? 0 : 1;
+            N.emit_entries = full && !in_window ? 0 : 1;
+            N.in_window = in_window ? 1 : 0;
             N.n_entries = (uint64_t*)(ctr + 10);  // 8-byte aligned slot
-            N.entries_cap = ecap;
+            N.entries_cap = z.ecap;
             N.ent_x = c.ent_x.as<uint32_t>();
             N.ent_d = c.ent_d.as<uint32_t>();
             N.ent_pay = c.ent_pay.as<uint64_t>();
@@ -819,17 +847,19 @@ int run_phase(hgt_graph* owner, const PhaseJob* jobs, uint32_t nj, bool minus, b
             N.big_list = P.big_list;
             N.big_rank = P.big_rank;
             N.big_scratch = c.nb_scratch.as<uint32_t>();
-            N.big_words = nb_words;
-            {
-                ProfScope ps_nbr(owner, PK_NBR, s);
-                he2_nbr_launch(N, grid_small, (unsigned)nb_grid, s);
-                if (!full)
-                    he2_lists_build(N, c.bl_cnt.as<uint64_t>(), c.bl_off.as<uint64_t>(), c.bl_cur.as<uint64_t>(),
-                                    c.bl_d.as<uint32_t>(), c.bl_pay.as<uint64_t>(), c.bl_scan.p, s);
-            }
+            N.big_words = z.nb_words;
+            he2_nbr_launch(N, grid_small, (unsigned)z.nb_grid, s);
+            if (N.emit_entries)
+                he2_lists_build(N, c.bl_cnt.as<uint64_t>(), c.bl_off.as<uint64_t>(), c.bl_cur.as<uint64_t>(),
+                                c.bl_d.as<uint32_t>(), c.bl_pay.as<uint64_t>(), c.bl_scan.p, s);
+            return N;
+        };
+        // the histogram stages' parameters, also the temporal pair stages'
+        auto stages = [&](uint64_t* st) {
             He2Params E{};
             E.M = M;
             E.he_tab = P.he_tab;
+            E.tmp_tab = P.tmp_tab;
             E.bl_off = c.bl_off.as<uint64_t>();
             E.bl_cnt = c.bl_cnt.as<uint64_t>();
             E.bl_d = c.bl_d.as<uint32_t>();
@@ -840,11 +870,9 @@ int run_phase(hgt_graph* owner, const PhaseJob* jobs, uint32_t nj, bool minus, b
             E.rank[0] = c.t_rank1.as<uint32_t>();
             E.list[2] = P.big_list;
             E.rank[2] = P.big_rank;
-            const unsigned grid_g = (unsigned)z.grid_g;
             E.garena = c.t_garena.as<uint32_t>();
             E.garena_words = z.garena_words;
-            E.stats = stats;
-            E.phase_ticks = (stats && owner->prof_phases) ? 1 : 0;
+            E.stats = st;
             // read again at every phase, so that a test can force the stages of a batch
             // without forcing those of the build's full count
             const char* fs = std::getenv("HGT_FORCE_STAGE");
@@ -854,17 +882,27 @@ int run_phase(hgt_graph* owner, const PhaseJob* jobs, uint32_t nj, bool minus, b
             E.slice_lh = owner->slice_lh;
             E.slice_pairs = t_tune && t_tune->slice_pairs ? t_tune->slice_pairs : owner->slice_pairs;
             E.slice_scan_tmp = c.t_slice_scan.p;
-            E.static_mode = full ? 1 : 0;
             E.work_total = (uint64_t*)(ctr + 24);  // 8-byte aligned slot
             hgt_fill_u32(ctr + 16, 0, 10, s);
             hgt_fill_u32(ctr + 5, 0, 1, s);
+            return E;
+        };
+        if (family == HGT_TRIAD_HYPEREDGE) {
+            NbrParams N;
+            {
+                ProfScope ps_nbr(owner, PK_NBR, s);
+                N = neighbours(false);
+            }
+            He2Params E = stages(stats);
+            E.phase_ticks = (stats && owner->prof_phases) ? 1 : 0;
+            E.static_mode = full ? 1 : 0;
             {
                 ProfScope ps(owner, PK_DELTA_SMALL, s);
                 he2_launch_lds(E, (unsigned)z.grid_s0, s);
             }
             {
                 ProfScope ps(owner, PK_DELTA_GLOBAL, s);
-                he2_launch_global(E, grid_g, s);
+                he2_launch_global(E, (unsigned)z.grid_g, s);
             }
             // centres too large for every arena: the 2-hop kernel
             TriadParams B = P;
@@ -883,13 +921,40 @@ int run_phase(hgt_graph* owner, const PhaseJob* jobs, uint32_t nj, bool minus, b
             TriadParams Q = P;
             Q.do_he = 0;
             Q.do_tmp = 1;
-            Q.queue = ctr + 6;
-            Q.big_queue = ctr + 7;
-            Q.big_count = ctr + 8;
             Q.stats = stats ? stats + ST_TMP0 : nullptr;
-            triad_he_prepare(Q, s);
             ProfScope ps(owner, PK_TMP, s);
-            triad_he_launch_small(Q, (unsigned)z.grid_tmp, s);
+            if (paths_reserve(c, z) == HGT_OK) {
+                // open paths per middle hyperedge, then the triples inside the centres'
+                // neighbourhoods; centres too large for every arena: the 2-hop kernel
+                (void)neighbours(true);
+                PathParams T{};
+                T.M = M;
+                T.tmp_tab = P.tmp_tab;
+                T.bl_off = c.bl_off.as<uint64_t>();
+                T.bl_cnt = c.bl_cnt.as<uint64_t>();
+                T.bl_d = c.bl_d.as<uint32_t>();
+                T.bl_pay = c.bl_pay.as<uint64_t>();
+                T.list[0] = c.p_list0.as<uint32_t>();
+                T.list[1] = c.p_list1.as<uint32_t>();
+                T.queue = ctr + 26;
+                T.count = ctr + 29;
+                T.scratch = c.p_scratch.as<uint32_t>();
+                T.words = kPathWords;
+                T.stats = Q.stats;
+                tmp_paths_launch(T, (unsigned)owner->n_cu, kPathGrid, s);
+                He2Params E = stages(Q.stats);
+                tmp_launch_lds(E, (unsigned)z.grid_s0, s);
+                tmp_launch_global(E, (unsigned)z.grid_g, s);
+                Q.paths_apart = 1;
+                Q.big_count = ctr + 21;
+                Q.big_queue = ctr + 5;
+            } else {
+                Q.queue = ctr + 6;
+                Q.big_queue = ctr + 7;
+                Q.big_count = ctr + 8;
+                triad_he_prepare(Q, s);
+                triad_he_launch_small(Q, (unsigned)z.grid_tmp, s);
+            }
             triad_he_slices(Q, s);
             triad_he_launch_big(Q, (unsigned)grid_big, s);
         }
@@ -1291,6 +1356,7 @@ int reserve_all_phases(hgt_graph* owner, std::vector<Pending*>& ps, bool upload 
             if (base.back() == 0) continue;
             const PhaseShape z = phase_shape(owner, base.back(), max_lh, sum_lh, id_base.back(), t_na != nullptr);
             if (int rc = phase_reserve(c, family, z)) return rc;
+            if (family == HGT_TRIAD_TEMPORAL) (void)paths_reserve(c, z);
             if (upload) {
                 const int slot = (phase == 0 ? 0 : 2) + (family == HGT_TRIAD_TEMPORAL ? 1 : 0);
                 if (int rc = upload_multi(c, slot, G, base, id_base, c.pre[slot], s)) return rc;

@@ -63,6 +63,8 @@ struct TriadParams {
     uint32_t* wave_hash;      // per (workgroup, wave) 2-hop hash in global memory for neighbours
     uint32_t wave_slots;      // whose 2-hop list is too long for LDS: 2 * wave_slots words each
     uint64_t* stats;          // optional counters (see TriadStat), NULL = off
+    int paths_apart;          // temporal: open paths are counted per middle hyperedge (triad_tmp.hip);
+                              // only the triples inside N(h) are counted, and their paths taken back
     int static_he;            // hyperedge family as a full count (see He2Params::static_mode)
     // Slices of the large kernel's centres (NULL: one per centre): a centre whose
     // members' lists hold many entries is shared by several workgroups, each
@@ -104,6 +106,7 @@ struct NbrParams {
     Multi M;
     int inserting;               // 1: rebuild the centres' histograms and add them to their neighbours'
     int emit_entries;            // 0: histograms only (build)
+    int in_window;               // 1: only neighbours within the graph's time window
     uint64_t* n_entries;         // batch-neighbour entries written (all graphs)
     uint64_t entries_cap;
     uint32_t* ent_x;             // id_base + x
@@ -121,6 +124,7 @@ struct NbrParams {
 struct He2Params {
     Multi M;
     const uint8_t* he_tab;
+    const uint8_t* tmp_tab;      // the temporal kernels'
     const uint64_t* bl_off;      // per ID slot: batch-neighbour list of x
     const uint64_t* bl_cnt;
     const uint32_t* bl_d;
@@ -146,6 +150,23 @@ struct He2Params {
                                  // smallest-ID centre
 };
 
+// temporal open paths per middle hyperedge (triad_tmp.hip)
+struct PathParams {
+    Multi M;
+    const uint8_t* tmp_tab;
+    const uint64_t* bl_off;      // per ID slot: the changed hyperedges within its window
+    const uint64_t* bl_cnt;
+    const uint32_t* bl_d;
+    const uint64_t* bl_pay;
+    uint32_t* list[2];           // slots by stage (capacity: all slots)
+    uint32_t* queue;             // three, then three counts
+    uint32_t* count;
+    uint32_t* scratch;           // global stage: words per workgroup
+    uint64_t words;
+    uint64_t* stats;
+};
+void tmp_paths_launch(PathParams& P, unsigned n_cu, unsigned grid_global, hipStream_t s);
+
 void he2_nbr_launch(NbrParams& P, unsigned grid_small, unsigned grid_big, hipStream_t s);
 // per-ID batch-neighbour lists over all graphs of P.M (M.total_ids slots)
 void he2_lists_build(NbrParams& P, uint64_t* bl_cnt, uint64_t* bl_off, uint64_t* bl_cur, uint32_t* bl_d,
@@ -154,6 +175,9 @@ void he2_lists_build(NbrParams& P, uint64_t* bl_cnt, uint64_t* bl_off, uint64_t*
 void he2_remove_deleted(NbrParams& P, hipStream_t s);
 void he2_launch_lds(He2Params& P, unsigned grid, hipStream_t s);
 void he2_launch_global(He2Params& P, unsigned grid, hipStream_t s);  // counts the slices first
+// the same stages for the temporal triples inside the centres' neighbourhoods
+void tmp_launch_lds(He2Params& P, unsigned grid, hipStream_t s);
+void tmp_launch_global(He2Params& P, unsigned grid, hipStream_t s);
 
 // incident-vertex family
 struct IvParams {

@@ -105,10 +105,15 @@ __device__ __forceinline__ void classify(const TriadParams& P, const HeGraph& G,
                     acc_add(acc_tmp, ct, 1);
                     acc_add(acc_tmp, cf, ~0ull);
                 }
+                if (P.paths_apart) {  // h - x - y and h - y - x are no open paths
+                    acc_add(acc_tmp, T.tmp[time_code(sh.th, sh.sh, tx, sx, ty, sy, nh, nx, ny, hx, (int)cxy, 0, 0)], ~0ull);
+                    acc_add(acc_tmp, T.tmp[time_code(sh.th, sh.sh, tx, sx, ty, sy, nh, nx, ny, 0, (int)cxy, hy, 0)], ~0ull);
+                }
             }
         }
         return;
     }
+    if (P.paths_apart) return;
     // (ii) path h - x - y with y outside the closed neighbourhood of h (its centre is x)
     if (P.static_he) return;
     if (lower_ranked_member(G.mark[y], G.epoch, sh.rank)) return;

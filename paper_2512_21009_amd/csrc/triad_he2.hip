@@ -31,6 +31,8 @@
 // enumerated per shared vertex 37.5 ms; counters along all runs 34.8; kinds and flat walks
 // 13.7.  5k changes on 500k hyperedges, where two dense centres went to the 2-hop kernel:
 // 134 ms, 9.7, 3.0.
+#include <type_traits>
+
 #include "triad_common.h"
 
 namespace {
@@ -91,10 +93,17 @@ struct Sh2 {
 // Builds N(h) -> c_x in the hash at keys/vals (already cleared), reading the
 // incidence lists of h's members through pre/voff.
 __device__ __forceinline__ void build_nh(const GraphView& G, uint32_t h, uint32_t hlen, uint32_t lh, const uint32_t* pre,
-                                         const uint64_t* voff, uint32_t* keys, uint32_t* vals, uint32_t cap) {
+                                         const uint64_t* voff, uint32_t* keys, uint32_t* vals, uint32_t cap,
+                                         bool in_window, int64_t window) {
+    const int64_t lo = in_window ? ts_sub(G.h_ts[h], window) : 0, hi = in_window ? ts_add(G.h_ts[h], window) : 0;
     for (uint32_t p = threadIdx.x; p < lh; p += HGT_WG) {
         uint32_t k = seg_of<uint32_t>(pre, hlen, p);
-        uint32_t x = G.v2h[voff[k] + (p - pre[k])];
+        const uint64_t at = voff[k] + (p - pre[k]);
+        uint32_t x = G.v2h[at];
+        if (in_window) {
+            const int64_t t = G.v2h_ts[at];
+            if (t < lo || t > hi) continue;
+        }
         if (x != h) (void)fr_add(keys, vals, cap, x, 1u);
     }
 }
@@ -217,7 +226,7 @@ __device__ void nbr_pass_body(const NbrParams& P, uint32_t* arena, uint64_t aren
         (void)member_prefix(G.g, hoff, hlen, pre, voff, sh.ws);
         for (uint32_t s = tid; s < cap; s += HGT_WG) { keys[s] = HGT_EMPTY; vals[s] = 0; }
         __syncthreads();
-        build_nh(G.g, h, hlen, lh, pre, voff, keys, vals, cap);
+        build_nh(G.g, h, hlen, lh, pre, voff, keys, vals, cap, P.in_window != 0, G.window);
         __syncthreads();
         uint32_t* hd = G.hpool + 2 * hoff;
         for (uint32_t s0 = 0; s0 < cap; s0 += HGT_WG) {
@@ -355,6 +364,48 @@ __device__ __forceinline__ void pair_add(He2Acc& A, uint32_t cls, uint64_t v) {
         atomicAdd((unsigned long long*)&A.pair[cls * COPIES + (threadIdx.x & (COPIES - 1))], (unsigned long long)v);
 }
 
+// The same for the temporal classes.
+constexpr int TCOPIES = 8;
+struct TmpAcc {
+    uint64_t pair[HGT_N_TEMPORAL_CLASSES * TCOPIES];
+};
+
+__device__ __forceinline__ void tmp_add(TmpAcc& A, int cls, uint64_t v) {
+    if (cls < 255)
+        atomicAdd((unsigned long long*)&A.pair[cls * TCOPIES + (threadIdx.x & (TCOPIES - 1))], (unsigned long long)v);
+}
+
+// A pair of neighbours of h in the window of all three: its class by arrival, and when
+// the two meet the open paths h-x-y and h-y-x taken back.
+__device__ __forceinline__ void tmp_pair(const GraphView& g, const Tables& T, TmpAcc& A, uint32_t h, uint32_t x, uint32_t y,
+                                         int64_t th, int64_t tx, int64_t ty, uint32_t hlen, uint32_t mx, uint32_t my,
+                                         uint32_t s, uint32_t shh) {
+    uint64_t qh = 0, qx = 0, qy = 0;
+    if (tx == ty || tx == th || ty == th) {  // only ties need the arrival sequence
+        qh = g.h_seq[h];
+        qx = g.h_seq[x];
+        qy = g.h_seq[y];
+    }
+    const int nh = (int)hlen, nx = (int)meta_len(mx), ny = (int)meta_len(my), hx = (int)meta_c(mx), hy = (int)meta_c(my);
+    tmp_add(A, T.tmp[time_code(th, qh, tx, qx, ty, qy, nh, nx, ny, hx, (int)s, hy, (int)shh)], 1);
+    if (!s) return;
+    tmp_add(A, T.tmp[time_code(th, qh, tx, qx, ty, qy, nh, nx, ny, hx, (int)s, 0, 0)], ~0ull);
+    tmp_add(A, T.tmp[time_code(th, qh, tx, qx, ty, qy, nh, nx, ny, 0, (int)s, hy, 0)], ~0ull);
+}
+template <int WG>
+__device__ void he2_flush_graph(const He2Params& P, uint32_t g, TmpAcc& A) {
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < HGT_N_TEMPORAL_CLASSES; i += WG) {
+        uint64_t s = 0;
+        for (int c = 0; c < TCOPIES; c++) {
+            s += A.pair[i * TCOPIES + c];
+            A.pair[i * TCOPIES + c] = 0;
+        }
+        if (g != 0xffffffffu && s) atomicAdd((unsigned long long*)&P.M.graphs[g].out_tmp[i], (unsigned long long)s);
+    }
+    __syncthreads();
+}
+
 // Adds the workgroup's counts to graph g's phase accumulators and clears them.
 template <int WG>
 __device__ void he2_flush_graph(const He2Params& P, uint32_t g, He2Acc& A) {
@@ -409,14 +460,20 @@ __device__ __forceinline__ void wg_prefix(uint32_t n, uint32_t* ws, F f, S put) 
 }
 
 // N(h) -> c_x in the hash keys/vals, from the lists of h's members.
-template <int WG>
+template <int WG, bool TMP>
 __device__ __forceinline__ void he2_nh(const GraphView& G, uint32_t h, uint32_t hlen, uint32_t lh, const uint32_t* pre,
-                                       const uint64_t* voff, uint32_t* keys, uint32_t* vals, uint32_t cap) {
+                                       const uint64_t* voff, uint32_t* keys, uint32_t* vals, uint32_t cap, int64_t w_lo,
+                                       int64_t w_hi) {
     for (uint32_t s = threadIdx.x; s < cap; s += WG) { keys[s] = HGT_EMPTY; vals[s] = 0; }
     __syncthreads();
     for (uint32_t p = threadIdx.x; p < lh; p += WG) {
         const uint32_t k = seg_of<uint32_t>(pre, hlen, p);
-        const uint32_t x = G.v2h[voff[k] + (p - pre[k])];
+        const uint64_t at = voff[k] + (p - pre[k]);
+        const uint32_t x = G.v2h[at];
+        if (TMP) {
+            const int64_t t = G.v2h_ts[at];
+            if (t < w_lo || t > w_hi) continue;
+        }
         if (x != h) (void)fr_add(keys, vals, cap, x, 1u);
     }
     __syncthreads();
@@ -669,9 +726,9 @@ __device__ __forceinline__ void he2_rows(const GraphView& G, Sh2& sh, const uint
     }
 }
 
-template <bool BIG, int WG>
+template <bool BIG, int WG, bool TMP>
 __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW, uint32_t* lds, Sh2& sh, const Tables& T,
-                         He2Acc& A, uint64_t* st, uint64_t* ph) {
+                         std::conditional_t<TMP, TmpAcc, He2Acc>& A, uint64_t* st, uint64_t* ph) {
     constexpr uint32_t NW = WG / 64;
     constexpr int STAGE = BIG ? 2 : 0;
     constexpr uint32_t BM_LOG = BIG ? 17 : 14;          // bits of each vertex bitmap
@@ -783,7 +840,7 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
             pre[hlen] = lh;
             sh.lh = lh;
             const uint64_t cap = (uint64_t)lh + lh / 2 + 32;
-            sh.defer = (lh >= K_MAX_N || 2 * cap + 2ull * lh + lh / 64 + NW + 1 + 4 * hlen + 8 > AW) ? 1u : 0u;
+            sh.defer = (lh >= K_MAX_N || 2 * cap + (TMP ? 4ull : 2ull) * lh + lh / 64 + NW + 1 + 4 * hlen + 8 > AW) ? 1u : 0u;
         }
         __syncthreads();
         if (sh.defer) {
@@ -797,22 +854,26 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
         uint32_t* mask = arena;
         uint32_t* nl_x = arena + 2 * cap;
         uint32_t* nl_meta = nl_x + lh;
-        uint32_t* hm = nl_meta + lh;
+        int64_t* nl_t = (int64_t*)(nl_meta + lh);  // 2 cap and 2 lh are even
+        uint32_t* hm = nl_meta + (TMP ? 3 * lh : lh);
         uint32_t* place_c = hm + hlen;
         uint32_t base0 = (uint32_t)(place_c + lh / 64 + NW + 1 - arena);
+        const int64_t th = TMP ? G.g.h_ts[h] : 0, w_lo = ts_sub(th, G.window), w_hi = ts_add(th, G.window);
         const uint32_t lds_used = BIG ? (3 * hlen + 8) & ~1u : 0;  // pre and voff
         if (BIG && lds_used + 2 * cap <= LDS_L) {
-            he2_nh<WG>(G.g, h, hlen, lh, pre, voff, lds + lds_used, lds + lds_used + cap, cap);
+            he2_nh<WG, TMP>(G.g, h, hlen, lh, pre, voff, lds + lds_used, lds + lds_used + cap, cap, w_lo, w_hi);
             HE2_MARK(1);
             he2_compact<WG, false>(P, G, sh, lds + lds_used, lds + lds_used + cap, cap, nl_x, nl_meta);
         } else {
-            he2_nh<WG>(G.g, h, hlen, lh, pre, voff, arena, arena + cap, cap);
+            he2_nh<WG, TMP>(G.g, h, hlen, lh, pre, voff, arena, arena + cap, cap, w_lo, w_hi);
             HE2_MARK(1);
             he2_compact<WG, BIG>(P, G, sh, arena, arena + cap, cap, nl_x, nl_meta);
         }
         HE2_MARK(2);
         const uint32_t K = sh.K, per = K / NW + 1 < 64 ? K / NW + 1 : 64;
         const bool masked = hlen <= MASK_BITS;
+        if (TMP)
+            for (uint32_t i = tid; i < K; i += WG) nl_t[i] = G.g.h_ts[nl_x[i]];
         // --- vertices outside h that two neighbours may share: a second row holding a vertex
         // finds its bit set and sets the bit in the second bitmap (the members are stashed, so a
         // row is gathered once).  Members of h (a third bitmap tells) go into the neighbour's
@@ -904,7 +965,7 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
         uint32_t* el = arena + place(S);
         uint32_t* ecur = arena + place(K);
         // the counters; before them the (c, f) histogram and the kinds of neighbours
-        const uint32_t gcap = hash_cap(K), k_words = masked ? 2 * gcap + K : 0;
+        const uint32_t gcap = hash_cap(K), k_words = masked && !TMP ? 2 * gcap + K : 0;
         uint32_t c_words = NW * K > 2 * hlen + 2 ? NW * K : 2 * hlen + 2;
         if (k_words > c_words) c_words = k_words;
         uint32_t* cnts = BIG ? lds : arena + place(c_words);
@@ -970,19 +1031,21 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
         }
         HE2_MARK(8);
         // --- disjoint-pair classes (the first slice); the histogram lies over the counters in the global stage
-        if (slice == 0) {
-            he2_disjoint<WG>(sh, T, A, nl_meta, K, hlen, cnts);
-            __syncthreads();
-            if (masked) {
-                if (k_lds) he2_kinds<WG, BIG, false>(P, sh, T, A, nl_meta, mask, K, hlen, cnts, gcap);
-                else he2_kinds<WG, BIG, true>(P, sh, T, A, nl_meta, mask, K, hlen, kinds, gcap);
+        if constexpr (!TMP) {
+            if (slice == 0) {
+                he2_disjoint<WG>(sh, T, A, nl_meta, K, hlen, cnts);
+                __syncthreads();
+                if (masked) {
+                    if (k_lds) he2_kinds<WG, BIG, false>(P, sh, T, A, nl_meta, mask, K, hlen, cnts, gcap);
+                    else he2_kinds<WG, BIG, true>(P, sh, T, A, nl_meta, mask, K, hlen, kinds, gcap);
+                }
             }
         }
         __syncthreads();
         HE2_MARK(3);
         // --- open paths h - x - y through the histograms, per eligible neighbour
-        if (!P.static_mode)
-            for (uint32_t c0 = wave * per; c0 < K; c0 += NW * per) {
+        if constexpr (!TMP)
+            for (uint32_t c0 = P.static_mode ? K : wave * per; c0 < K; c0 += NW * per) {
                 uint32_t x = 0, m = 0;
                 bool take = lane < per && c0 + lane < K;
                 if (take) {
@@ -1013,7 +1076,7 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
               e1_l = ld_at<BIG>(&ecur[il]);
               if (nslice > 1) x_l = nl_x[il];
           }
-          uint64_t rows = __ballot(il < K && meta_elig(mx_l) && e0_l < e1_l &&
+          uint64_t rows = __ballot(il < K && meta_elig(mx_l) && (TMP || e0_l < e1_l) &&
                                    (nslice == 1 || slice_of(x_l, nslice) == slice));
           for (; rows; rows &= rows - 1) {
             const int r = __ffsll((unsigned long long)rows) - 1;
@@ -1021,6 +1084,7 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
             const uint32_t mx = __shfl(mx_l, r, 64), e0 = __shfl(e0_l, r, 64), e1 = __shfl(e1_l, r, 64);
             const uint32_t x = __shfl(x_l, r, 64);
             const uint64_t mkx = masked ? mask_of(i) : 0;
+            const int64_t tx = TMP ? nl_t[i] : 0;
             // every neighbour on the runs of x's shared vertices: fn(y, [the vertex lies in h])
             auto walk = [&](auto fn) {
                 uint32_t tot = 0;
@@ -1044,15 +1108,22 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
             };
             for (uint32_t w0 = nslice == 1 ? i + 1 : 0; w0 < K; w0 += cw) {
                 const uint32_t w1 = K - w0 < cw ? K : w0 + cw;
-                const uint32_t tot = walk([&](uint32_t y, uint32_t in) {
-                    if (y >= w0 && y < w1) atomicAdd(&cnt[y - w0], 1u + (in << 16));
-                });
+                uint32_t tot = 0;
+                if (!TMP || e0 < e1)
+                    tot = walk([&](uint32_t y, uint32_t in) {
+                        if (y >= w0 && y < w1) atomicAdd(&cnt[y - w0], 1u + (in << 16));
+                    });
                 wave_sync();
                 auto take = [&](uint32_t y, uint32_t v) {
                     if (nslice > 1 && nl_x[y] <= x) return;  // the other row's
                     const uint32_t my = nl_meta[y];
                     if (!meta_elig(my)) return;
-                    if (masked) {  // v vertices outside h, on top of those inside
+                    if constexpr (TMP) {
+                        const int64_t ty = nl_t[y];
+                        if (!within(th, tx, ty, G.window)) return;
+                        const uint32_t shh = masked ? (uint32_t)__popcll(mkx & mask_of(y)) : v >> 16;
+                        tmp_pair(G.g, T, A, h, nl_x[i], nl_x[y], th, tx, ty, hlen, mx, my, masked ? shh + v : v & 0xffffu, shh);
+                    } else if (masked) {  // v vertices outside h, on top of those inside
                         const uint32_t shh = __popcll(mkx & mask_of(y));
                         he2_pair(P, T, A, hlen, mx, my, shh + v, shh, 1);
                         if (shh) he2_pair(P, T, A, hlen, mx, my, shh, shh, ~0ull);
@@ -1061,12 +1132,12 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
                     }
                 };
                 // the counted ones, by a look at all counters or by another walk, whichever is shorter
-                if (w1 - w0 <= 4 * tot + 64) {
+                // (temporal: every pair of neighbours has a class of its own)
+                if (TMP || w1 - w0 <= 4 * tot + 64) {
                     for (uint32_t y = w0 + lane; y < w1; y += 64) {
                         const uint32_t v = cnt[y - w0];
-                        if (!v) continue;
-                        cnt[y - w0] = 0;
-                        take(y, v);
+                        if (v) cnt[y - w0] = 0;
+                        if (v || TMP) take(y, v);
                     }
                 } else {
                     walk([&](uint32_t y, uint32_t) {
@@ -1101,37 +1172,54 @@ __device__ void he2_flush_stats(const He2Params& P, const uint64_t* st, const ui
         atomicAdd((unsigned long long*)&P.stats[ST_HEB0 + STAGE], (unsigned long long)st[1]);
 }
 
-template <bool BIG, int WG>
+template <bool BIG, int WG, bool TMP>
 __device__ __forceinline__ void he2_kernel(const He2Params& P, uint32_t* arena, uint32_t words, uint32_t* lds) {
     __shared__ Sh2 sh;
     __shared__ Tables T;
-    __shared__ He2Acc A;
+    __shared__ std::conditional_t<TMP, TmpAcc, He2Acc> A;
     __shared__ uint64_t st[2];
     __shared__ uint64_t ph[HE2_PHASES];
     const uint32_t tid = threadIdx.x;
     if (tid < HE2_PHASES) ph[tid] = 0;
     if (tid == 0) sh.cur_g = 0xffffffffu;
-    for (uint32_t i = tid; i < 128; i += WG) T.he[i] = P.he_tab[i];
-    for (uint32_t i = tid; i < HGT_N_HE_CLASSES * COPIES; i += WG) A.pair[i] = 0;
-    for (uint32_t i = tid; i < 8 * COPIES; i += WG) A.open[i] = 0;
-    if (tid < HGT_N_HE_CLASSES) A.tot[tid] = 0;
-    // open path: h & x (8) and x & y (16), h only (1), x only (2), y only (4)
-    if (tid < 8) A.cls8[tid] = P.he_tab[24 | (tid & 4 ? 1 : 0) | (tid & 2 ? 2 : 0) | (tid & 1 ? 4 : 0)];
+    if constexpr (TMP) {
+        for (uint32_t i = tid; i < 128; i += WG) T.tmp[i] = P.tmp_tab[i];
+        for (uint32_t i = tid; i < HGT_N_TEMPORAL_CLASSES * TCOPIES; i += WG) A.pair[i] = 0;
+    } else {
+        for (uint32_t i = tid; i < 128; i += WG) T.he[i] = P.he_tab[i];
+        for (uint32_t i = tid; i < HGT_N_HE_CLASSES * COPIES; i += WG) A.pair[i] = 0;
+        for (uint32_t i = tid; i < 8 * COPIES; i += WG) A.open[i] = 0;
+        if (tid < HGT_N_HE_CLASSES) A.tot[tid] = 0;
+        // open path: h & x (8) and x & y (16), h only (1), x only (2), y only (4)
+        if (tid < 8) A.cls8[tid] = P.he_tab[24 | (tid & 4 ? 1 : 0) | (tid & 2 ? 2 : 0) | (tid & 1 ? 4 : 0)];
+    }
     if (tid < 2) st[tid] = 0;
     __syncthreads();
-    he2_body<BIG, WG>(P, arena, words, lds, sh, T, A, st, ph);
+    he2_body<BIG, WG, TMP>(P, arena, words, lds, sh, T, A, st, ph);
     he2_flush_graph<WG>(P, sh.cur_g, A);
-    he2_flush_stats<BIG ? 2 : 0>(P, st, ph);
+    if constexpr (!TMP) he2_flush_stats<BIG ? 2 : 0>(P, st, ph);
+    else if (P.stats && tid == 0)
+        atomicAdd((unsigned long long*)&P.stats[ST_BYTES_BIG], (unsigned long long)st[1]);
 }
 
 __global__ void __launch_bounds__(HGT_WG, 4) k_he2_s0(He2Params P) {
     __shared__ __attribute__((aligned(16))) uint32_t arena[ARENA_S];
-    he2_kernel<false, HGT_WG>(P, arena, ARENA_S, nullptr);
+    he2_kernel<false, HGT_WG, false>(P, arena, ARENA_S, nullptr);
 }
 
 __global__ void __launch_bounds__(WG_L, 4) k_he2_s2(He2Params P) {
     __shared__ __attribute__((aligned(16))) uint32_t lds[LDS_L];
-    he2_kernel<true, WG_L>(P, P.garena + (uint64_t)blockIdx.x * P.garena_words, (uint32_t)P.garena_words, lds);
+    he2_kernel<true, WG_L, false>(P, P.garena + (uint64_t)blockIdx.x * P.garena_words, (uint32_t)P.garena_words, lds);
+}
+
+__global__ void __launch_bounds__(HGT_WG, 4) k_tmp_s0(He2Params P) {
+    __shared__ __attribute__((aligned(16))) uint32_t arena[ARENA_S];
+    he2_kernel<false, HGT_WG, true>(P, arena, ARENA_S, nullptr);
+}
+
+__global__ void __launch_bounds__(WG_L, 4) k_tmp_s2(He2Params P) {
+    __shared__ __attribute__((aligned(16))) uint32_t lds[LDS_L];
+    he2_kernel<true, WG_L, true>(P, P.garena + (uint64_t)blockIdx.x * P.garena_words, (uint32_t)P.garena_words, lds);
 }
 
 // Slices of the global stage's centres.  A wave per centre estimates its work in walked
@@ -1141,7 +1229,7 @@ __global__ void __launch_bounds__(WG_L, 4) k_he2_s2(He2Params P) {
 // runs' squares sum to (K / E)^2 sum_v d^2, and sum_v d^2 is the incidences times the
 // degree of a random member, for which h's own members stand in.
 __global__ void k_he2_work(Multi M, const uint64_t* __restrict__ list, const uint32_t* n_p, uint64_t cap,
-                           uint32_t slice_lh, uint64_t* pre, uint64_t* total) {
+                           uint32_t slice_lh, int tmp, uint64_t* pre, uint64_t* total) {
     const int lane = threadIdx.x & 63;
     const uint32_t n = *n_p;
     uint64_t sum = 0;
@@ -1169,6 +1257,7 @@ __global__ void k_he2_work(Multi M, const uint64_t* __restrict__ list, const uin
         const double all = (double)lh * (double)lh;
         if (w > all) w = all;
         if (len > MASK_BITS) w += (double)sq;
+        if (tmp) w += all / 16;  // every pair in the window has a class of its own
         w += 32.0 * (double)lh;
         const uint64_t work = slice_lh ? (lh + slice_lh - 1) / slice_lh : (uint64_t)w;
         if (lane == 0) pre[c] = work;
@@ -1221,17 +1310,28 @@ void he2_remove_deleted(NbrParams& P, hipStream_t s) {
     k_h_remove<<<2048, 256, 0, s>>>(P.M, P.n_entries, P.entries_cap, P.ent_x, P.ent_pay);
 }
 
-void he2_launch_lds(He2Params& P, unsigned grid, hipStream_t s) {
-    if (P.M.total) k_he2_s0<<<grid, HGT_WG, 0, s>>>(P);
-}
+namespace {
 
-void he2_launch_global(He2Params& P, unsigned grid, hipStream_t s) {
+void launch_global(He2Params& P, unsigned grid, bool tmp, hipStream_t s) {
     if (!P.M.total) return;
     const uint64_t cap = P.slice_cap;
     const unsigned waves = (unsigned)((cap + 3) / 4), blk = (unsigned)((cap + 255) / 256);
-    k_he2_work<<<waves < 1024 ? waves : 1024, 256, 0, s>>>(P.M, P.list[0], &P.count[0], cap, P.slice_lh, P.slice_pre,
-                                                           P.work_total);
+    k_he2_work<<<waves < 1024 ? waves : 1024, 256, 0, s>>>(P.M, P.list[0], &P.count[0], cap, P.slice_lh, tmp ? 1 : 0,
+                                                           P.slice_pre, P.work_total);
     k_he2_cut<<<blk < 256 ? blk : 256, 256, 0, s>>>(cap, P.slice_lh, P.slice_pairs, grid, P.work_total, P.slice_pre);
     hgt_scan_u64(P.slice_pre, P.slice_pre, cap, P.slice_pre + cap, P.slice_pre + cap + 1, P.slice_scan_tmp, s);
-    k_he2_s2<<<grid, WG_L, 0, s>>>(P);
+    if (tmp) k_tmp_s2<<<grid, WG_L, 0, s>>>(P);
+    else k_he2_s2<<<grid, WG_L, 0, s>>>(P);
 }
+
+}  // namespace
+
+void he2_launch_lds(He2Params& P, unsigned grid, hipStream_t s) {
+    if (P.M.total) k_he2_s0<<<grid, HGT_WG, 0, s>>>(P);
+}
+void he2_launch_global(He2Params& P, unsigned grid, hipStream_t s) { launch_global(P, grid, false, s); }
+
+void tmp_launch_lds(He2Params& P, unsigned grid, hipStream_t s) {
+    if (P.M.total) k_tmp_s0<<<grid, HGT_WG, 0, s>>>(P);
+}
+void tmp_launch_global(He2Params& P, unsigned grid, hipStream_t s) { launch_global(P, grid, true, s); }

@@ -465,3 +465,34 @@ def test_shared_member_masks(gpu_lib, monkeypatch, stage, card):
         p.apply(b, f"masks batch {k}")
         compare_counts(p.g, p.o, p.track, f"masks batch {k}")
     p.close()
+
+
+@pytest.mark.parametrize("window", [0, 40, 10**9])
+@pytest.mark.parametrize("shape", ["ties", "dense", "long-rows"])
+def test_temporal_paths(gpu_lib, shape, window):
+    """Open paths per middle hyperedge: equal timestamps (order by arrival), windows
+    that hold nothing else, part of the stream and all of it, middle hyperedges
+    with more neighbours than the LDS tables of either stage hold (512, 2,048),
+    and rows of more than 64 members."""
+    if shape == "ties":
+        st = W.temporal_stream("ties", 40, 150, 40, 2, 2.0, 1, 6, 0.3, 200, window, W.SEED_BASE + 101, pop_s=1.0)
+    elif shape == "dense":
+        st = W.temporal_stream("dense", 3000, 2600, 6, 1, 6.0, 1, 4, 3.0, 10**6, window, W.SEED_BASE + 102, pop_s=2.5)
+    else:
+        st = W.temporal_stream("long", 500, 120, 20, 2, 0.5, 60, 90, 7.0, 400, window, W.SEED_BASE + 103)
+    p = Pair(st, track=("temporal",))
+    if shape != "dense":  # the oracle's full recount of the dense one takes minutes
+        compare_counts(p.g, p.o, p.track, f"{shape} build")
+    for k, b in enumerate(st.batches):
+        if shape == "dense":
+            from .test_gpu_fullsize import _gpu_delta, _oracle_delta
+            before = np.array(p.g.triad_counts("temporal"), np.uint64)
+            args, _ = p.prepare(b, shape)
+            p.g.apply_batch(*args)
+            got = _gpu_delta({"temporal": before}, {"temporal": np.array(p.g.triad_counts("temporal"), np.uint64)})
+            want = _oracle_delta(p.o, b.del_handles, b.ins, b.ins.ts, ("temporal",))[2]
+            assert np.array_equal(got["temporal"], want["temporal"])
+        else:
+            p.apply(b, f"{shape} batch {k}")
+            compare_counts(p.g, p.o, p.track, f"{shape} batch {k}")
+    p.close()
