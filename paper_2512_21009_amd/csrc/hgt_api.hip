@@ -243,7 +243,7 @@ struct PhaseCtx {
     int refs = 0;                 // graphs that use it
     hipEvent_t done = nullptr;    // recorded after the last user's phases
     DevBuf iv_list0, iv_list, iv_list2, iv_garena, iv_garena2;  // incident-vertex stage scratch
-    DevBuf t_ctr, t_big_list, t_big_rank, t_big_scratch, t_list1, t_rank1, t_garena, t_whash;
+    DevBuf t_ctr, t_big_list, t_big_rank, t_big_scratch, t_list1, t_rank1, t_list2, t_rank2, t_garena, t_whash;
     DevBuf t_slices, t_slice_scan;       // slices of the 2-hop kernel's centres
     DevBuf p_list0, p_list1, p_scratch;  // temporal open paths: middle hyperedges, the largest ones' tables
     DevBuf ent_x, ent_d, ent_pay, bl_cnt, bl_off, bl_cur, bl_d, bl_pay, nb_scratch, bl_scan;
@@ -508,7 +508,8 @@ int ensure_plan_scratch(hgt_graph* g, const Sizes& z, PlanScratch& w) {
 
 // ---- triad phases ---------------------------------------------------------
 void phase_ctx_free(PhaseCtx& c) {
-    DevBuf* all[] = {&c.t_ctr, &c.t_whash, &c.t_big_list, &c.t_big_rank, &c.t_big_scratch, &c.t_list1, &c.t_rank1,
+    DevBuf* all[] = {&c.t_ctr, &c.t_whash, &c.t_big_list, &c.t_big_rank, &c.t_big_scratch, &c.t_list1, &c.t_rank1, &c.t_list2,
+                     &c.t_rank2,
                      &c.t_slices, &c.t_slice_scan, &c.p_list0, &c.p_list1, &c.p_scratch,
                      &c.t_garena, &c.ent_x, &c.ent_d, &c.ent_pay, &c.bl_cnt, &c.bl_off, &c.bl_cur,
                      &c.bl_d, &c.bl_pay, &c.nb_scratch, &c.bl_scan, &c.desc, &c.iv_list0, &c.iv_list, &c.iv_list2, &c.iv_garena,
@@ -673,6 +674,7 @@ void collect(const PhaseJob* jobs, uint32_t nj, int family, bool minus, std::vec
         h.mark = J.mark;
         h.epoch = J.epoch;
         h.window = g->window;
+        h.n_vertices = (uint32_t)g->st.n_vertices;
         h.status = &g->st.sc->status;
         uint64_t* cnt = g->counts.as<uint64_t>();
         h.out_he = cnt + (minus ? ACC_HE_M : ACC_HE_P);
@@ -695,7 +697,7 @@ void collect(const PhaseJob* jobs, uint32_t nj, int family, bool minus, std::vec
 struct PhaseShape {
     uint64_t n, lhm, max_card, ecap, total_ids;
     BigLayout L;
-    uint64_t grid_big, grid_small, grid_tmp, grid_2hop, grid_s0, grid_g, garena_words, nb_grid, nb_words;
+    uint64_t grid_big, grid_small, grid_tmp, grid_2hop, grid_s0, grid_s1, grid_g, garena_words, nb_grid, nb_words;
     uint32_t wave_slots;
     bool tmp_lists;  // temporal: open paths per middle hyperedge, from batch-neighbour lists
 };
@@ -707,7 +709,7 @@ constexpr uint64_t kTmpListBytes = 32ull << 30;
 constexpr uint64_t kPathWords = 1ull << 20;  // 4 MB per workgroup of the largest middle hyperedges
 constexpr unsigned kPathGrid = 64;
 
-constexpr uint64_t kGarenaWords = 1ull << 19;  // 2 MB global arena per workgroup of the global stage
+constexpr uint64_t kGarenaWords = 1ull << 20;  // 4 MB global arena per workgroup of the global stage
 
 PhaseShape phase_shape(const hgt_graph* owner, uint64_t n, uint64_t max_lh, uint64_t sum_lh, uint64_t total_ids,
                        bool lean) {
@@ -728,13 +730,14 @@ PhaseShape phase_shape(const hgt_graph* owner, uint64_t n, uint64_t max_lh, uint
     z.nb_words = 2 * pow2ceil64(2 * std::max<uint64_t>(z.lhm, 32)) + 3 * z.max_card + 8;
     z.nb_grid = std::max<uint64_t>(1, std::min<uint64_t>(lean ? 8 : 256, (1ull << 27) / z.nb_words));
     z.grid_s0 = std::min<uint64_t>(n_cu * 4, n);
+    z.grid_s1 = std::min<uint64_t>(n_cu * 2, 64 * n);
     // the global stage: workgroups of 512 threads, two per CU (their counters take
     // 65 KB of LDS); a dense centre is shared by up to 64 of them
     const int wg_per_cu = t_tune ? t_tune->wg_per_cu : owner->global_wg_per_cu;
     // (the no-allocation entry point: 16 MB of arenas at most, 1 MB per centre)
     z.grid_g = lean ? std::min<uint64_t>(8, std::max<uint64_t>(1, n / 2))
                     : std::min<uint64_t>(n_cu * (uint64_t)wg_per_cu, 64 * n);
-    z.garena_words = lean && n < 2 ? kGarenaWords / 2 : kGarenaWords;
+    z.garena_words = !lean ? kGarenaWords : n < 2 ? kGarenaWords / 4 : kGarenaWords / 2;
     z.total_ids = total_ids;
     z.tmp_lists = !lean && 28 * z.ecap <= kTmpListBytes;
     return z;
@@ -772,11 +775,13 @@ int paths_reserve(PhaseCtx& c, const PhaseShape& z) {
 int phase_reserve(PhaseCtx& c, int family, const PhaseShape& z) {
     const uint64_t n = z.n;
     int rc = 0;
-    rc |= ensure(c.t_ctr, 128);
+    rc |= ensure(c.t_ctr, 256);
     rc |= ensure(c.t_big_list, n * 8);
     rc |= ensure(c.t_big_rank, n * 4);
     rc |= ensure(c.t_list1, n * 8);
     rc |= ensure(c.t_rank1, n * 4);
+    rc |= ensure(c.t_list2, n * 8);
+    rc |= ensure(c.t_rank2, n * 4);
     rc |= ensure(c.t_big_scratch, z.grid_big * z.L.words_per_wg * 4);
     rc |= ensure(c.t_whash, z.grid_2hop * 4 * 2ull * z.wave_slots * 4);
     rc |= ensure(c.t_slices, (n + 2) * 8);
@@ -791,7 +796,7 @@ int phase_reserve(PhaseCtx& c, int family, const PhaseShape& z) {
 // inserted ones on the new graphs) for every job, in one launch per kernel.
 // Counter slots in t_ctr: 0-2 neighbour pass, 5 2-hop queue for the centres the
 // histogram stages pass on, 6-8 temporal, 10-11 entry count, 16-18 stage queues,
-// 19-21 stage hand-over counts, 24-25 the global stage's estimated work, 26-31 temporal
+// 19-21 stage hand-over counts, 24-27 the estimated work of stages 1 and 2, 32-37 temporal
 // open paths.
 int run_phase(hgt_graph* owner, const PhaseJob* jobs, uint32_t nj, bool minus, bool full, hipStream_t s) {
     PhaseCtx& c = ctx_of(owner);
@@ -868,6 +873,8 @@ int run_phase(hgt_graph* owner, const PhaseJob* jobs, uint32_t nj, bool minus, b
             E.count = ctr + 19;
             E.list[0] = c.t_list1.as<uint64_t>();
             E.rank[0] = c.t_rank1.as<uint32_t>();
+            E.list[1] = c.t_list2.as<uint64_t>();
+            E.rank[1] = c.t_rank2.as<uint32_t>();
             E.list[2] = P.big_list;
             E.rank[2] = P.big_rank;
             E.garena = c.t_garena.as<uint32_t>();
@@ -881,9 +888,8 @@ int run_phase(hgt_graph* owner, const PhaseJob* jobs, uint32_t nj, bool minus, b
             E.slice_cap = n;
             E.slice_lh = owner->slice_lh;
             E.slice_pairs = t_tune && t_tune->slice_pairs ? t_tune->slice_pairs : owner->slice_pairs;
-            E.slice_scan_tmp = c.t_slice_scan.p;
             E.work_total = (uint64_t*)(ctr + 24);  // 8-byte aligned slot
-            hgt_fill_u32(ctr + 16, 0, 10, s);
+            hgt_fill_u32(ctr + 16, 0, 12, s);
             hgt_fill_u32(ctr + 5, 0, 1, s);
             return E;
         };
@@ -898,7 +904,7 @@ int run_phase(hgt_graph* owner, const PhaseJob* jobs, uint32_t nj, bool minus, b
             E.static_mode = full ? 1 : 0;
             {
                 ProfScope ps(owner, PK_DELTA_SMALL, s);
-                he2_launch_lds(E, (unsigned)z.grid_s0, s);
+                he2_launch_lds(E, (unsigned)z.grid_s0, (unsigned)z.grid_s1, s);
             }
             {
                 ProfScope ps(owner, PK_DELTA_GLOBAL, s);
@@ -936,14 +942,14 @@ int run_phase(hgt_graph* owner, const PhaseJob* jobs, uint32_t nj, bool minus, b
                 T.bl_pay = c.bl_pay.as<uint64_t>();
                 T.list[0] = c.p_list0.as<uint32_t>();
                 T.list[1] = c.p_list1.as<uint32_t>();
-                T.queue = ctr + 26;
-                T.count = ctr + 29;
+                T.queue = ctr + 32;
+                T.count = ctr + 35;
                 T.scratch = c.p_scratch.as<uint32_t>();
                 T.words = kPathWords;
                 T.stats = Q.stats;
                 tmp_paths_launch(T, (unsigned)owner->n_cu, kPathGrid, s);
                 He2Params E = stages(Q.stats);
-                tmp_launch_lds(E, (unsigned)z.grid_s0, s);
+                tmp_launch_lds(E, (unsigned)z.grid_s0, (unsigned)z.grid_s1, s);
                 tmp_launch_global(E, (unsigned)z.grid_g, s);
                 Q.paths_apart = 1;
                 Q.big_count = ctr + 21;
@@ -2282,7 +2288,7 @@ int hgt_profile_read(hgt_graph* g, hgt_kernel_time* out, uint32_t n_max, uint32_
     rows[PK_IV_PAIRS].algo_bytes = st[ST_IV_BYTES];
     rows[PK_COMMIT].algo_bytes = g->store_bytes;
     rows[PK_DELTA_BIG].events = st[ST_DEFER0 + 2];
-    rows[PK_DELTA_SMALL].algo_bytes = st[ST_HEB0];
+    rows[PK_DELTA_SMALL].algo_bytes = st[ST_HEB0] + st[ST_HEB0 + 1];
     rows[PK_DELTA_GLOBAL].algo_bytes = st[ST_HEB0 + 2];
     rows[PK_DELTA_SMALL].events = st[ST_DEFER0];
     rows[PK_DELTA_SMALL].aux = st[ST_DEFER0 + 1];

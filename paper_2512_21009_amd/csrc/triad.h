@@ -23,6 +23,8 @@ struct HeGraph {
     uint64_t* out_tmp;        // u64[96]
     uint32_t* hpool;          // neighbour histograms, 2 words per h2v word
     uint64_t id_base;         // first slot of this graph's IDs in the shared per-ID arrays
+    uint32_t n_vertices;
+    uint32_t pad1;
     double pair_scale;        // 8 * incidences / hyperedges^2: density, for estimates of work
 };
 
@@ -129,18 +131,17 @@ struct He2Params {
     const uint64_t* bl_cnt;
     const uint32_t* bl_d;
     const uint64_t* bl_pay;
-    uint32_t* queue;             // per stage (3 consecutive counters; 1 is not used)
+    uint32_t* queue;             // per stage (3 consecutive counters)
     uint32_t* count;             // items moved on by each stage (3 consecutive)
-    uint64_t* list[3];           // list[s]: items stage s (0, 2) could not fit; list[0] feeds
-    uint32_t* rank[3];           // the global stage, list[2] the 2-hop kernel (k_delta_big)
+    uint64_t* list[3];           // list[s]: items stage s could not fit; list[2] feeds the
+    uint32_t* rank[3];           // 2-hop kernel (k_delta_big)
     uint32_t* garena;            // global-stage tables: garena_words per workgroup
     uint64_t garena_words;
-    uint64_t* slice_pre;         // slices of the global stage's centres (see TriadParams)
+    uint64_t* slice_pre;         // slices of the centres of stages 1 and 2 (see TriadParams)
     uint64_t slice_cap;
     uint32_t slice_lh;           // test knob: member-list entries per slice (0: by pairs)
     uint64_t slice_pairs;        // work per slice of a centre (0: by the launch's total)
-    uint64_t* work_total;        // one cleared word
-    void* slice_scan_tmp;
+    uint64_t* work_total;        // two cleared words (stages 1 and 2)
     uint64_t* stats;             // byte and hand-over counters (profiling), NULL = off
     int phase_ticks;             // 1 (with stats): wall-clock ticks per phase, at the cost of a
                                  // clock read per phase
@@ -173,10 +174,10 @@ void he2_lists_build(NbrParams& P, uint64_t* bl_cnt, uint64_t* bl_off, uint64_t*
                      uint64_t* bl_pay, void* scan_tmp, hipStream_t s);
 // after the deletion phase: take the deleted hyperedges out of their neighbours' histograms
 void he2_remove_deleted(NbrParams& P, hipStream_t s);
-void he2_launch_lds(He2Params& P, unsigned grid, hipStream_t s);
+void he2_launch_lds(He2Params& P, unsigned grid, unsigned grid_mid, hipStream_t s);
 void he2_launch_global(He2Params& P, unsigned grid, hipStream_t s);  // counts the slices first
 // the same stages for the temporal triples inside the centres' neighbourhoods
-void tmp_launch_lds(He2Params& P, unsigned grid, hipStream_t s);
+void tmp_launch_lds(He2Params& P, unsigned grid, unsigned grid_mid, hipStream_t s);
 void tmp_launch_global(He2Params& P, unsigned grid, hipStream_t s);
 
 // incident-vertex family

@@ -131,8 +131,11 @@ struct Flat {
     uint32_t bits[128];  // starts within the window of 4096 entries, each one place early
     uint32_t pre[64], own[64];
 };
-template <int U, class Load, class Use>
-__device__ __forceinline__ uint32_t wave_flat(Flat& F, uint32_t d, Load load, Use use) {
+// Lays the segments out; their entries are then walked any number of times.
+struct FlatSeg {
+    uint32_t d, ex, tot;
+};
+__device__ __forceinline__ FlatSeg flat_lay(Flat& F, uint32_t d) {
     const uint32_t lane = threadIdx.x & 63;
     uint32_t inc = d;
 #pragma unroll
@@ -140,50 +143,64 @@ __device__ __forceinline__ uint32_t wave_flat(Flat& F, uint32_t d, Load load, Us
         const uint32_t t = __shfl_up(inc, o, 64);
         if (lane >= (uint32_t)o) inc += t;
     }
-    const uint32_t ex = inc - d, tot = __builtin_amdgcn_readlane(inc, 63);
-    if (!tot) return 0;
+    const FlatSeg g{d, inc - d, (uint32_t)__builtin_amdgcn_readlane(inc, 63)};
     const uint64_t nz = __ballot(d != 0);
     if (d) {
         const uint32_t rank = __popcll(nz & ((1ull << lane) - 1));
-        F.pre[rank] = ex;
+        F.pre[rank] = g.ex;
         F.own[rank] = lane;
     }
-    for (uint32_t w0 = 0; w0 < tot; w0 += 4096) {
-        F.bits[lane] = 0;
-        F.bits[lane + 64] = 0;
-        wave_sync();
-        if (d && ex > w0 && ex - w0 <= 4096) atomicOr(&F.bits[(ex - 1 - w0) >> 5], 1u << ((ex - 1 - w0) & 31));
-        wave_sync();
-        uint32_t kb = (uint32_t)__popcll(__ballot(d && ex <= w0)) - 1;  // the segment that entry w0 lies in
-        const uint32_t w1 = tot - w0 < 4096 ? tot : w0 + 4096;
-        for (uint32_t p0 = w0; p0 < w1; p0 += 64 * U) {
-            uint32_t l[U], r[U];
-            decltype(load(0u, 0u)) v[U];
+    return g;
+}
+// The starts within the window of entries [w0, w0 + 4096).
+__device__ __forceinline__ void flat_window(Flat& F, const FlatSeg& g, uint32_t w0) {
+    const uint32_t lane = threadIdx.x & 63;
+    F.bits[lane] = 0;
+    F.bits[lane + 64] = 0;
+    wave_sync();
+    if (g.d && g.ex > w0 && g.ex - w0 <= 4096) atomicOr(&F.bits[(g.ex - 1 - w0) >> 5], 1u << ((g.ex - 1 - w0) & 31));
+    wave_sync();
+}
+template <int U, class Load, class Use>
+__device__ __forceinline__ void flat_walk(const Flat& F, const FlatSeg& g, uint32_t w0, Load load, Use use) {
+    const uint32_t lane = threadIdx.x & 63;
+    uint32_t kb = (uint32_t)__popcll(__ballot(g.d && g.ex <= w0)) - 1;  // the segment that entry w0 lies in
+    const uint32_t w1 = g.tot - w0 < 4096 ? g.tot : w0 + 4096;
+    for (uint32_t p0 = w0; p0 < w1; p0 += 64 * U) {
+        uint32_t l[U], r[U];
+        decltype(load(0u, 0u)) v[U];
 #pragma unroll
-            for (int u = 0; u < U; u++) {
-                const uint32_t p = p0 + 64 * u + lane, at = (p0 - w0) / 32 + 2 * u;
-                const uint32_t lo = __builtin_amdgcn_readfirstlane(F.bits[at & 127]);
-                const uint32_t hi = __builtin_amdgcn_readfirstlane(F.bits[(at + 1) & 127]);
-                const uint32_t k = kb + __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
-                kb += __popc(lo) + __popc(hi);
-                v[u] = {};
-                l[u] = 0;
-                r[u] = 0;
-                if (p < w1) {
-                    l[u] = F.own[k];
-                    r[u] = p - F.pre[k];
-                    v[u] = load(l[u], r[u]);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < U; u++) {
-                const uint32_t p = p0 + 64 * u + lane;
-                if (p0 + 64 * u < w1) use(p < w1, l[u], r[u], p, v[u]);
+        for (int u = 0; u < U; u++) {
+            const uint32_t p = p0 + 64 * u + lane, at = (p0 - w0) / 32 + 2 * u;
+            const uint32_t lo = __builtin_amdgcn_readfirstlane(F.bits[at & 127]);
+            const uint32_t hi = __builtin_amdgcn_readfirstlane(F.bits[(at + 1) & 127]);
+            const uint32_t k = kb + __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
+            kb += __popc(lo) + __popc(hi);
+            v[u] = {};
+            l[u] = 0;
+            r[u] = 0;
+            if (p < w1) {
+                l[u] = F.own[k];
+                r[u] = p - F.pre[k];
+                v[u] = load(l[u], r[u]);
             }
         }
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const uint32_t p = p0 + 64 * u + lane;
+            if (p0 + 64 * u < w1) use(p < w1, l[u], r[u], p, v[u]);
+        }
+    }
+}
+template <int U, class Load, class Use>
+__device__ __forceinline__ uint32_t wave_flat(Flat& F, uint32_t d, Load load, Use use) {
+    const FlatSeg g = flat_lay(F, d);
+    for (uint32_t w0 = 0; w0 < g.tot; w0 += 4096) {
+        flat_window(F, g, w0);
+        flat_walk<U>(F, g, w0, load, use);
         wave_sync();
     }
-    return tot;
+    return g.tot;
 }
 
 // exclusive workgroup scan of one u32 per thread (all threads participate)

@@ -39,9 +39,15 @@ namespace {
 
 using namespace tri;
 
-constexpr uint32_t ARENA_S = 6144;     // stage 0: 24 KB of LDS, 256 threads, four workgroups per CU
-constexpr int WG_L = 512;              // global stage: threads per workgroup
-constexpr uint32_t CNT_L = 1536;       // ... counters per wave: neighbours are taken in windows of this many
+// Stage 0: 24 KB of LDS tables, 256 threads, four workgroups per CU.  Stage 1: 54 KB, 512
+// threads, two workgroups per CU (one of 1024 threads and 118 KB: 6.6 ms against 3.5 for the
+// centres of 100k changes on 2M hyperedges that stage 0 moves on, 1.1 against 0.5 + 1.6 with
+// stage 2 for 100 dense ones).  Stage 2 (the global stage): tables in global memory, 512
+// threads, two workgroups per CU.
+constexpr uint32_t ARENA_S = 6144;
+constexpr uint32_t ARENA_M = 13824;
+constexpr int WG_M = 512, WG_L = 512;
+constexpr uint32_t CNT_L = 1536;       // stage 2: counter words per wave
 constexpr uint32_t LDS_L = 12800;      // ... LDS words: counters of 8 waves, or bitmaps, or a (c, f) histogram
 static_assert(LDS_L >= (WG_L / 64) * CNT_L, "global stage LDS");
 constexpr uint32_t MASK_BITS = 64;     // hyperedges of up to this many members: a neighbour's shared
@@ -84,7 +90,7 @@ struct Sh2 {
     uint32_t gi, cur_g, skip;
     uint32_t slice, nslice;
     uint64_t hoff;
-    uint32_t ws[WG_L / 64];
+    uint32_t ws[WG_M / 64];
     uint32_t ncap, G;
     uint64_t g[8];
 };
@@ -341,12 +347,12 @@ __global__ void k_entries_check(Multi M, const uint64_t* n_entries_p, uint64_t c
 // ===========================================================================
 // the delta kernel
 // ===========================================================================
-// Stage 0 takes its centres from the batch, keeps every table in 28 KB of LDS and
-// moves the centres that do not fit to list 0.  The global stage (stage 2) takes
-// list 0 and keeps its tables in a slice of global memory per workgroup, the
-// counters in LDS; a centre with many pairs is shared by several workgroups
-// (slices), each of which builds the tables and takes every nslice-th neighbour.
-// What does not fit there either goes to list 2, which feeds the 2-hop kernel.
+// Stage 0 takes its centres from the batch, keeps every table in 24 KB of LDS and moves
+// the centres that do not fit to list 0.  Stage 1 takes list 0 with 54 KB of LDS, stage 2
+// (the global stage) list 1 with its tables in a slice of global memory per workgroup and
+// the counters in LDS; there a centre with many pairs is shared by several workgroups
+// (slices), each of which builds the tables and takes its share of the neighbours.  What
+// does not fit there either goes to list 2, which feeds the 2-hop kernel.
 
 // Counters of the class changes of the workgroup's graph so far (mod 2^64).  Every lane
 // of a wave adds to one of few classes, so the counters are kept 16-fold, a copy per
@@ -683,55 +689,12 @@ __device__ void he2_kinds(const He2Params& P, Sh2& sh, const Tables& T, He2Acc& 
     __syncthreads();
 }
 
-// Rows of all neighbours, a wave per `per` of them: use(xi, v, j) for every member v, j
-// numbering the members of all rows; called by all lanes of a wave together with ok false
-// where there is none.  first: the chunks' places are taken (place, sh.W their total) and
-// the members fetched; else they are read back from `stash`, where the first pass put them.
-template <int WG, class F>
-__device__ __forceinline__ void he2_rows(const GraphView& G, Sh2& sh, const uint32_t* nl_x, const uint32_t* nl_meta,
-                                         uint32_t* place, uint32_t K, uint32_t per, const uint32_t* stash, Flat& fl,
-                                         uint64_t* woff, bool first, F use) {
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (uint32_t c = wave; c * per < K; c += WG / 64) {
-        const uint32_t c0 = c * per, n = K - c0 < per ? K - c0 : per;
-        uint32_t d = 0;
-        if (lane < n) {
-            d = meta_len(nl_meta[c0 + lane]);
-            if (first) woff[lane] = G.h_off[nl_x[c0 + lane]];
-        }
-        uint32_t base = 0;
-        if (first) {
-            uint32_t tot = d;
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) tot += __shfl_xor(tot, o, 64);
-            if (lane == 0) {
-                base = atomicAdd(&sh.W, tot);
-                place[c] = base;
-            }
-            base = __shfl(base, 0, 64);
-            wave_flat<4>(fl, d, [&](uint32_t l, uint32_t r) { return G.h2v[woff[l] + r]; },
-                         [&](bool ok, uint32_t l, uint32_t, uint32_t p, uint32_t v) { use(ok, c0 + l, v, base + p); });
-        } else {
-            base = place[c];
-            uint32_t ex = d;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const uint32_t t = __shfl_up(ex, o, 64);
-                if (lane >= (uint32_t)o) ex += t;
-            }
-            woff[lane] = base + ex - d;
-            wave_flat<4>(fl, d, [&](uint32_t l, uint32_t r) { return stash[woff[l] + r]; },
-                         [&](bool ok, uint32_t l, uint32_t, uint32_t p, uint32_t v) { use(ok, c0 + l, v, base + p); });
-        }
-    }
-}
-
-template <bool BIG, int WG, bool TMP>
+template <int STAGE, int WG, bool TMP>
 __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW, uint32_t* lds, Sh2& sh, const Tables& T,
                          std::conditional_t<TMP, TmpAcc, He2Acc>& A, uint64_t* st, uint64_t* ph) {
     constexpr uint32_t NW = WG / 64;
-    constexpr int STAGE = BIG ? 2 : 0;
-    constexpr uint32_t BM_LOG = BIG ? 17 : 14;          // bits of each vertex bitmap
+    constexpr bool BIG = STAGE == 2, SLICED = STAGE > 0;
+    constexpr uint32_t BM_LOG = BIG ? 17 : STAGE ? 15 : 14;  // bits of each vertex bitmap
     constexpr uint32_t BH_LOG = 12, BH_WORDS = 1u << (BH_LOG - 5);  // ... and of the one of h's members
     constexpr uint32_t BM_WORDS = 1u << (BM_LOG - 5);
     constexpr uint32_t POS = 0x7fffffffu;               // a run cursor; the top bit: the vertex lies in h
@@ -755,9 +718,9 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
     } while (0)
     for (;;) {
         if (tid == 0) {
-            const uint64_t n = !BIG ? P.M.total : P.slice_pre[P.slice_cap + 1];
+            const uint64_t n = !SLICED ? P.M.total : P.slice_pre[P.slice_cap + 1];
             if (q == q_end) {
-                const uint32_t take = BIG ? 1 : take_size(n, gridDim.x);
+                const uint32_t take = take_size(n, gridDim.x);
                 q = atomicAdd(&P.queue[STAGE], take);
                 q_end = q + take;
             }
@@ -767,7 +730,7 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
             sh.nslice = 1;
             if (!sh.stop) {
                 uint32_t gi, h, rank;
-                if (!BIG) {
+                if (!SLICED) {
                     gi = multi_graph_of(P.M, c);
                     rank = (uint32_t)(c - P.M.base[gi]);
                     h = P.M.graphs[gi].centres[rank];
@@ -777,10 +740,10 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
                     const uint64_t at = P.slice_pre[ci], next = ci + 1 < nc ? P.slice_pre[ci + 1] : n;
                     sh.slice = (uint32_t)(c - at);
                     sh.nslice = (uint32_t)(next - at);
-                    const uint64_t it = P.list[0][ci];
+                    const uint64_t it = P.list[STAGE - 1][ci];
                     gi = (uint32_t)(it >> 32);
                     h = (uint32_t)it;
-                    rank = P.rank[0][ci];
+                    rank = P.rank[STAGE - 1][ci];
                 }
                 const HeGraph& Gq = P.M.graphs[gi];
                 sh.gi = gi;
@@ -840,7 +803,7 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
             pre[hlen] = lh;
             sh.lh = lh;
             const uint64_t cap = (uint64_t)lh + lh / 2 + 32;
-            sh.defer = (lh >= K_MAX_N || 2 * cap + (TMP ? 4ull : 2ull) * lh + lh / 64 + NW + 1 + 4 * hlen + 8 > AW) ? 1u : 0u;
+            sh.defer = (lh >= K_MAX_N || 2 * cap + (TMP ? 4ull : 2ull) * lh + 4 * hlen + 8 > AW) ? 1u : 0u;
         }
         __syncthreads();
         if (sh.defer) {
@@ -849,15 +812,14 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
         }
         HE2_MARK(0);
         // --- N(h).  Arena: hash (2 cap), later the masks of shared members | IDs and metas of
-        // the neighbours (lh each) | h's members | places of the row chunks
+        // the neighbours (lh each) | h's members
         const uint32_t lh = sh.lh, cap = hash_cap(lh);
         uint32_t* mask = arena;
         uint32_t* nl_x = arena + 2 * cap;
         uint32_t* nl_meta = nl_x + lh;
         int64_t* nl_t = (int64_t*)(nl_meta + lh);  // 2 cap and 2 lh are even
         uint32_t* hm = nl_meta + (TMP ? 3 * lh : lh);
-        uint32_t* place_c = hm + hlen;
-        uint32_t base0 = (uint32_t)(place_c + lh / 64 + NW + 1 - arena);
+        uint32_t base0 = (uint32_t)(hm + hlen - arena);
         const int64_t th = TMP ? G.g.h_ts[h] : 0, w_lo = ts_sub(th, G.window), w_hi = ts_add(th, G.window);
         const uint32_t lds_used = BIG ? (3 * hlen + 8) & ~1u : 0;  // pre and voff
         if (BIG && lds_used + 2 * cap <= LDS_L) {
@@ -878,11 +840,14 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
         // finds its bit set and sets the bit in the second bitmap (the members are stashed, so a
         // row is gathered once).  Members of h (a third bitmap tells) go into the neighbour's
         // mask; with more members than a mask holds they are treated like the others.
+        uint32_t* row_at = arena + base0;  // K words: the rows' places in the stash
+        uint32_t* ecnt = row_at + K;       // K words: shared vertices of each neighbour
+        base0 += 2 * K;
         uint32_t* bm = BIG ? lds : arena + base0;
         uint32_t* bh = bm + 2 * BM_WORDS;
-        if (!BIG) base0 += 2 * BM_WORDS + BH_WORDS;
-        uint32_t* stash = arena + base0;
-        const uint32_t room = base0 < AW ? AW - base0 : 0;  // words left for the stash and the survivors
+        uint32_t* stash = arena + base0 + (BIG ? 0 : 2 * BM_WORDS + BH_WORDS);
+        const uint32_t stash0 = (uint32_t)(stash - arena);
+        const uint32_t room = stash0 < AW ? AW - stash0 : 0;
         if (room) {
             for (uint32_t i = tid; i < 2 * BM_WORDS + BH_WORDS; i += WG) bm[i] = 0;
             if (masked)
@@ -895,24 +860,44 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
             }
         }
         __syncthreads();
+        // a wave's chunks of neighbours: rows [c0, c0 + n)
+        auto chunks = [&](auto fn) __attribute__((always_inline)) {
+            for (uint32_t c0 = wave * per; c0 < K; c0 += NW * per) fn(c0, K - c0 < per ? K - c0 : per);
+        };
         if (room)
-            he2_rows<WG>(G.g, sh, nl_x, nl_meta, place_c, K, per, nullptr, fl, woff, true,
-                         [&](bool ok, uint32_t xi, uint32_t v, uint32_t j) {
-                             if (!ok) return;
-                             const uint32_t hv = v * 2654435761u, bj = hv >> (32 - BH_LOG);
-                             uint32_t in = 0;
-                             if (bh[bj >> 5] >> (bj & 31) & 1u) {
-                                 const uint32_t k = lower_bound_u32(hm, hlen, v);
-                                 if (k < hlen && hm[k] == v) {
-                                     in = 1u << 31;
-                                     atomicOr(&mask[2 * xi + (k >> 5)], 1u << (k & 31));
-                                 }
-                             }
-                             if (j < room) stash[j] = v | in;
-                             if (in) return;
-                             const uint32_t b = hv >> (32 - BM_LOG), bit = 1u << (b & 31);
-                             if (atomicOr(&bm[b >> 5], bit) & bit) atomicOr(&bm[BM_WORDS + (b >> 5)], bit);
-                         });
+            chunks([&](uint32_t c0, uint32_t n) {
+                uint32_t d = 0;
+                if (lane < n) {
+                    d = meta_len(nl_meta[c0 + lane]);
+                    woff[lane] = G.g.h_off[nl_x[c0 + lane]];
+                }
+                const FlatSeg g = flat_lay(fl, d);
+                uint32_t base = 0;
+                if (lane == 0) base = atomicAdd(&sh.W, g.tot);
+                base = __builtin_amdgcn_readfirstlane(base);
+                if (lane < n) row_at[c0 + lane] = base + g.ex;
+                for (uint32_t w0 = 0; w0 < g.tot; w0 += 4096) {
+                    flat_window(fl, g, w0);
+                    flat_walk<4>(fl, g, w0, [&](uint32_t l, uint32_t r) { return G.g.h2v[woff[l] + r]; },
+                        [&](bool ok, uint32_t l, uint32_t, uint32_t p, uint32_t v) {
+                            if (!ok) return;
+                            const uint32_t hv = v * 2654435761u, bj = hv >> (32 - BH_LOG);
+                            uint32_t in = 0;
+                            if (bh[bj >> 5] >> (bj & 31) & 1u) {
+                                const uint32_t k = lower_bound_u32(hm, hlen, v);
+                                if (k < hlen && hm[k] == v) {
+                                    in = 1u << 31;
+                                    atomicOr(&mask[2 * (c0 + l) + (k >> 5)], 1u << (k & 31));
+                                }
+                            }
+                            if (base + p < room) stash[base + p] = v | in;
+                            if (in) return;
+                            const uint32_t b = hv >> (32 - BM_LOG), bit = 1u << (b & 31);
+                            if (atomicOr(&bm[b >> 5], bit) & bit) atomicOr(&bm[BM_WORDS + (b >> 5)], bit);
+                        });
+                    wave_sync();
+                }
+            });
         __syncthreads();
         const uint32_t W = sh.W;
         if (tid == 0) {
@@ -925,49 +910,65 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
             move_on();
             continue;
         }
-        // survivors (vertex, neighbour), from the arena's end downwards
-        const uint32_t s_cap = (room - W) / 2;
-        uint32_t* s_end = arena + AW;
-        he2_rows<WG>(G.g, sh, nl_x, nl_meta, place_c, K, per, stash, fl, woff, false,
-                     [&](bool ok, uint32_t xi, uint32_t v, uint32_t) {
-                         const uint32_t b = (v * 2654435761u) >> (32 - BM_LOG);
-                         const bool keep = ok && !(v >> 31) && (bm[BM_WORDS + (b >> 5)] >> (b & 31) & 1u);
-                         const uint64_t m = __ballot(keep);
-                         if (!m) return;
-                         uint32_t q = 0;
-                         if (lane == 0) q = atomicAdd(&sh.S, (uint32_t)__popcll(m));
-                         q = __shfl(q, 0, 64) + __popcll(m & ((1ull << lane) - 1));
-                         if (keep && q < s_cap) {
-                             s_end[-1 - 2 * (int32_t)q] = xi;
-                             s_end[-2 - 2 * (int32_t)q] = v;
-                         }
-                     });
+        // Walks the stashed rows, d(xi) entries of each, and packs what keep() wants to the front
+        // of its row (a row belongs to one wave, which has read what it writes over): keep(ok, xi,
+        // entry) returns the entry's new value, HGT_EMPTY to drop it.  ecnt: the entries left.
+        auto pack = [&](auto dfn, auto keep) __attribute__((always_inline)) {
+            uint32_t left = 0;
+            chunks([&](uint32_t c0, uint32_t n) {
+                uint32_t d = 0;
+                if (lane < n) {
+                    d = dfn(c0 + lane);
+                    woff[lane] = row_at[c0 + lane];
+                }
+                wm[lane] = 0;
+                wave_flat<4>(fl, d, [&](uint32_t l, uint32_t r) { return stash[woff[l] + r]; },
+                             [&](bool ok, uint32_t l, uint32_t, uint32_t, uint32_t v) {
+                                 const uint32_t w = ok ? keep(c0 + l, v) : HGT_EMPTY;
+                                 if (w != HGT_EMPTY) stash[woff[l] + atomicAdd(&wm[l], 1u)] = w;
+                             });
+                wave_sync();
+                if (lane < n) {
+                    ecnt[c0 + lane] = wm[lane];
+                    left += wm[lane];
+                }
+                wave_sync();
+            });
+            return left;
+        };
+        {
+            const uint32_t left = pack([&](uint32_t i) { return meta_len(nl_meta[i]); },
+                                       [&](uint32_t, uint32_t v) {
+                                           const uint32_t b = (v * 2654435761u) >> (32 - BM_LOG);
+                                           return !(v >> 31) && (bm[BM_WORDS + (b >> 5)] >> (b & 31) & 1u) ? v : HGT_EMPTY;
+                                       });
+            if (left) atomicAdd(&sh.S, left);
+        }
         __syncthreads();
         const uint32_t S = sh.S;
-        // --- exact groups: hash of the survivors' vertices, runs, and per neighbour its
-        // shared vertices.  The regions go where they fit: over the bitmaps and the stash,
-        // or over the hash of N(h).
-        uint32_t lo_at = masked ? 2 * K : 0, hi_at = BIG ? base0 : base0 - 2 * BM_WORDS - BH_WORDS;
-        const uint32_t lo_end = 2 * cap, hi_end = AW - 2 * S;
-        bool fits = S <= s_cap;
+        // --- exact groups: a hash of the vertices that are left, their runs, and per neighbour
+        // the slots of those that another one holds too.  The regions go where they fit: over the
+        // bitmaps, after the stash, or over the hash of N(h).
+        uint32_t lo_at = masked ? 2 * K : 0, bm_at = base0, hi_at = stash0 + W;
+        const uint32_t lo_end = 2 * cap, bm_end = stash0;
+        bool fits = true;
         auto place = [&](uint32_t words) -> uint32_t {
             uint32_t r = 0;
-            if (hi_at + words <= hi_end) { r = hi_at; hi_at += words; }
-            else if (lo_at + words <= lo_end) { r = lo_at; lo_at += words; }
+            if (lo_at + words <= lo_end) { r = lo_at; lo_at += words; }
+            else if (bm_at + words <= bm_end) { r = bm_at; bm_at += words; }
+            else if (hi_at + words <= AW) { r = hi_at; hi_at += words; }
             else fits = false;
             return r;
         };
-        const uint32_t vcap = hash_cap(S);
-        uint32_t* tkey = arena + place(vcap);
-        uint32_t* tcur = arena + place(vcap + 1);
-        uint32_t* rx = arena + place(S);
-        uint32_t* er = arena + place(S);
-        uint32_t* el = arena + place(S);
-        uint32_t* ecur = arena + place(K);
+        const uint32_t vcap = hash_cap(S < G.n_vertices ? S : G.n_vertices);
         // the counters; before them the (c, f) histogram and the kinds of neighbours
         const uint32_t gcap = hash_cap(K), k_words = masked && !TMP ? 2 * gcap + K : 0;
-        uint32_t c_words = NW * K > 2 * hlen + 2 ? NW * K : 2 * hlen + 2;
+        const uint32_t cw = BIG ? CNT_L : K / 4 + 16;  // counter words per wave
+        uint32_t c_words = NW * cw > 2 * hlen + 2 ? NW * cw : 2 * hlen + 2;
         if (k_words > c_words) c_words = k_words;
+        uint32_t* rx = arena + place(S);
+        uint32_t* tst = arena + place(vcap + 1);  // the vertices, then the runs' starts
+        uint32_t* tcnt = arena + place(vcap);
         uint32_t* cnts = BIG ? lds : arena + place(c_words);
         const bool k_lds = !BIG || k_words <= LDS_L;
         uint32_t* kinds = k_lds ? cnts : arena + place(k_words);
@@ -976,59 +977,43 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
             move_on();
             continue;
         }
-        for (uint32_t s = tid; s < vcap; s += WG) { tkey[s] = HGT_EMPTY; tcur[s] = 0; }
-        for (uint32_t i = tid; i < K; i += WG) ecur[i] = 0;
-        __syncthreads();
-        for (uint32_t e = tid; e < S; e += WG) {
-            uint32_t* pv = s_end - 2 - 2 * (int32_t)e;
-            *pv = fr_add(tkey, tcur, vcap, *pv, 1u);
-        }
-        __syncthreads();
         HE2_MARK(4);
-        // run starts (vertices of one neighbour only: an empty run), flagged when the vertex lies in h
-        wg_prefix<WG>(vcap, sh.ws,
-                      [&](uint32_t s) {
-                          const uint32_t r = ld_at<BIG>(&tcur[s]) & POS;
-                          return r >= 2 ? r : 0u;
-                      },
-                      [&](uint32_t s, uint32_t b) {
-                          const uint32_t v = ld_at<BIG>(&tkey[s]);
-                          const uint32_t in = v != HGT_EMPTY && contains_u32(hm, hlen, v) ? 1u : 0u;
-                          tcur[s] = b | in << 31;
-                      });
-        if (tid == 0) {  // the end of the last run
-            uint32_t t = 0;
-            for (uint32_t w = 0; w < NW; w++) t += sh.ws[w];
-            tcur[vcap] = t;
+        if (S) {
+            for (uint32_t s = tid; s < vcap; s += WG) { tst[s] = HGT_EMPTY; tcnt[s] = 0; }
+            __syncthreads();
+            (void)pack([&](uint32_t i) { return ecnt[i]; }, [&](uint32_t, uint32_t v) { return fr_add(tst, tcnt, vcap, v, 1u); });
+            __syncthreads();
+            // run starts (vertices of one neighbour only: an empty run), flagged when the vertex lies in h
+            wg_prefix<WG>(vcap, sh.ws,
+                          [&](uint32_t s) {
+                              const uint32_t r = ld_at<BIG>(&tcnt[s]);
+                              return r >= 2 ? r : 0u;
+                          },
+                          [&](uint32_t s, uint32_t b) {
+                              uint32_t in = 0;
+                              if (!masked) {
+                                  const uint32_t v = ld_at<BIG>(&tst[s]);
+                                  in = v != HGT_EMPTY && contains_u32(hm, hlen, v) ? 1u << 31 : 0;
+                              }
+                              tst[s] = b | in;
+                          });
+            if (tid == 0) {  // the end of the last run
+                uint32_t t = 0;
+                for (uint32_t w = 0; w < NW; w++) t += sh.ws[w];
+                tst[vcap] = t;
+            }
+            __syncthreads();
+            (void)pack([&](uint32_t i) { return ecnt[i]; },
+                       [&](uint32_t xi, uint32_t s) {
+                           const uint32_t r0 = ld_at<BIG>(&tst[s]) & POS, r1 = ld_at<BIG>(&tst[s + 1]) & POS;
+                           if (r0 == r1) return HGT_EMPTY;
+                           rx[r0 + atomicSub(&tcnt[s], 1u) - 1] = xi;
+                           return s;
+                       });
         }
         __syncthreads();
-        for (uint32_t e = tid; e < S; e += WG) {
-            uint32_t* pv = s_end - 2 - 2 * (int32_t)e;
-            const uint32_t s = *pv;
-            if ((ld_at<BIG>(&tcur[s + 1]) & POS) == (ld_at<BIG>(&tcur[s]) & POS)) *pv = HGT_EMPTY;
-            else atomicAdd(&ecur[pv[1]], 1u);
-        }
-        __syncthreads();
-        wg_prefix<WG>(K, sh.ws, [&](uint32_t i) { return ld_at<BIG>(&ecur[i]); },
-                      [&](uint32_t i, uint32_t b) { ecur[i] = b; });
-        __syncthreads();
-        for (uint32_t e = tid; e < S; e += WG) {
-            const uint32_t* pv = s_end - 2 - 2 * (int32_t)e;
-            const uint32_t s = *pv;
-            if (s == HGT_EMPTY) continue;
-            const uint32_t xi = pv[1];
-            rx[atomicAdd(&tcur[s], 1u) & POS] = xi;
-            er[atomicAdd(&ecur[xi], 1u)] = s;
-        }
-        __syncthreads();
-        // now run s is [end of s - 1, tcur[s]) and neighbour i's shared vertices [ecur[i-1], ecur[i]):
-        // their runs' starts and lengths in place of their slots
-        const uint32_t SE = K ? ld_at<BIG>(&ecur[K - 1]) : 0;
-        for (uint32_t e = tid; e < SE; e += WG) {
-            const uint32_t s = er[e], t1 = ld_at<BIG>(&tcur[s]), r0 = s ? ld_at<BIG>(&tcur[s - 1]) & POS : 0;
-            er[e] = r0 | (t1 & ~POS);
-            el[e] = (t1 & POS) - r0;
-        }
+        // now neighbour i's shared vertices are the slots stash[row_at[i] .. + ecnt[i]) and the
+        // neighbours at slot s rx[tst[s] .. tst[s + 1])
         HE2_MARK(8);
         // --- disjoint-pair classes (the first slice); the histogram lies over the counters in the global stage
         if constexpr (!TMP) {
@@ -1060,7 +1045,6 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
         auto mask_of = [&](uint32_t i) {
             return (uint64_t)ld_at<BIG>(&mask[2 * i]) | (uint64_t)ld_at<BIG>(&mask[2 * i + 1]) << 32;
         };
-        const uint32_t cw = BIG ? CNT_L : K;  // counters per wave
         uint32_t* cnt = cnts + wave * cw;
         for (uint32_t i = lane; i < cw; i += 64) cnt[i] = 0;
         wave_sync();
@@ -1069,80 +1053,114 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
         // names and a pair to its row of smaller ID; unsliced, a pair belongs to its earlier row.
         for (uint32_t c0 = 0; c0 * NW < K; c0 += 64) {
           const uint32_t il = wave + NW * (c0 + lane);
-          uint32_t mx_l = 0, e0_l = 0, e1_l = 0, x_l = 0;
+          uint32_t mx_l = 0, e0_l = 0, n_l = 0, x_l = 0;
           if (il < K) {
               mx_l = nl_meta[il];
-              e0_l = il ? ld_at<BIG>(&ecur[il - 1]) : 0;
-              e1_l = ld_at<BIG>(&ecur[il]);
+              e0_l = row_at[il];
+              n_l = S ? ecnt[il] : 0;
               if (nslice > 1) x_l = nl_x[il];
           }
-          uint64_t rows = __ballot(il < K && meta_elig(mx_l) && (TMP || e0_l < e1_l) &&
+          uint64_t rows = __ballot(il < K && meta_elig(mx_l) && (TMP || n_l) &&
                                    (nslice == 1 || slice_of(x_l, nslice) == slice));
-          for (; rows; rows &= rows - 1) {
+          // the runs of a row's (first 64) shared vertices, fetched a row ahead
+          auto fetch = [&](int r, uint32_t from, uint32_t& at, uint32_t& len) __attribute__((always_inline)) {
+              const uint32_t e = from + lane;
+              len = 0;
+              if (e < (uint32_t)__builtin_amdgcn_readlane(n_l, r)) {
+                  const uint32_t s = stash[__builtin_amdgcn_readlane(e0_l, r) + e];
+                  at = ld_at<BIG>(&tst[s]);
+                  len = (ld_at<BIG>(&tst[s + 1]) & POS) - (at & POS);
+              }
+          };
+          uint32_t at_n = 0, len_n = 0;
+          if (rows) fetch(__ffsll((unsigned long long)rows) - 1, 0, at_n, len_n);
+          while (rows) {
             const int r = __ffsll((unsigned long long)rows) - 1;
+            rows &= rows - 1;
+            const uint32_t at_c = at_n, len_c = len_n;
+            if (rows) fetch(__ffsll((unsigned long long)rows) - 1, 0, at_n, len_n);
             const uint32_t i = wave + NW * (c0 + r);
-            const uint32_t mx = __shfl(mx_l, r, 64), e0 = __shfl(e0_l, r, 64), e1 = __shfl(e1_l, r, 64);
-            const uint32_t x = __shfl(x_l, r, 64);
+            const uint32_t mx = __builtin_amdgcn_readlane(mx_l, r), ne = __builtin_amdgcn_readlane(n_l, r);
+            const uint32_t x = __builtin_amdgcn_readlane(x_l, r);
             const uint64_t mkx = masked ? mask_of(i) : 0;
             const int64_t tx = TMP ? nl_t[i] : 0;
+            // counters of a word by what they can reach: bytes (or two, |x & y| and |h & x & y|
+            // without a mask) for rows of up to 255 members
+            const uint32_t lw = meta_len(mx) > 255 ? 0 : masked ? 2 : 1, bits = 32u >> lw;
+            const uint32_t cm = 0xffffffffu >> (32 - bits), half = 16u >> lw, win = cw << lw;
+            FlatSeg g{0, 0, 0};
+            const bool one = ne <= 64;
+            if (one && ne) {
+                wm[lane] = at_c;
+                g = flat_lay(fl, len_c);
+                if (g.tot <= 4096) flat_window(fl, g, 0);
+            }
             // every neighbour on the runs of x's shared vertices: fn(y, [the vertex lies in h])
-            auto walk = [&](auto fn) {
-                uint32_t tot = 0;
-                if (e1 - e0 == 1) {
-                    const uint32_t t = er[e0], R = el[e0];
-                    for (uint32_t j = lane; j < R; j += 64) fn(rx[(t & POS) + j], t >> 31);
-                    return R;
+            auto walk = [&](auto fn) __attribute__((always_inline)) {
+                auto load = [&](uint32_t l, uint32_t j) { return rx[(wm[l] & POS) + j]; };
+                auto use = [&](bool ok, uint32_t l, uint32_t, uint32_t, uint32_t y) {
+                    if (ok) fn(y, wm[l] >> 31);
+                };
+                if (one && g.tot <= 4096) {
+                    flat_walk<4>(fl, g, 0, load, use);
+                    return;
                 }
-                for (uint32_t e = e0; e < e1; e += 64) {
-                    uint32_t d = 0;
-                    if (e + lane < e1) {
-                        wm[lane] = er[e + lane];
-                        d = el[e + lane];
-                    }
-                    tot += wave_flat<4>(fl, d, [&](uint32_t l, uint32_t j) { return rx[(wm[l] & POS) + j]; },
-                                        [&](bool ok, uint32_t l, uint32_t, uint32_t, uint32_t y) {
-                                            if (ok) fn(y, wm[l] >> 31);
-                                        });
+                for (uint32_t e = 0; e < ne; e += 64) {
+                    uint32_t at = 0, len = 0;
+                    fetch(r, e, at, len);
+                    wave_sync();
+                    wm[lane] = at;
+                    (void)wave_flat<4>(fl, len, load, use);
                 }
-                return tot;
             };
-            for (uint32_t w0 = nslice == 1 ? i + 1 : 0; w0 < K; w0 += cw) {
-                const uint32_t w1 = K - w0 < cw ? K : w0 + cw;
-                uint32_t tot = 0;
-                if (!TMP || e0 < e1)
-                    tot = walk([&](uint32_t y, uint32_t in) {
-                        if (y >= w0 && y < w1) atomicAdd(&cnt[y - w0], 1u + (in << 16));
+            for (uint32_t w0 = nslice == 1 ? i + 1 : 0; w0 < K; w0 += win) {
+                const uint32_t w1 = K - w0 < win ? K : w0 + win;
+                if (ne)
+                    walk([&](uint32_t y, uint32_t in) {
+                        if (y >= w0 && y < w1)
+                            atomicAdd(&cnt[(y - w0) >> lw], (masked ? 1u : 1u + (in << half)) << (((y - w0) & ((1u << lw) - 1)) * bits));
                     });
                 wave_sync();
-                auto take = [&](uint32_t y, uint32_t v) {
+                auto take = [&](uint32_t y, uint32_t v) __attribute__((always_inline)) {
                     if (nslice > 1 && nl_x[y] <= x) return;  // the other row's
                     const uint32_t my = nl_meta[y];
                     if (!meta_elig(my)) return;
+                    // masked: v vertices outside h, on top of those inside
+                    const uint32_t shh = masked ? (uint32_t)__popcll(mkx & mask_of(y)) : v >> half;
+                    const uint32_t sxy = masked ? shh + v : v & ((1u << half) - 1);
                     if constexpr (TMP) {
                         const int64_t ty = nl_t[y];
-                        if (!within(th, tx, ty, G.window)) return;
-                        const uint32_t shh = masked ? (uint32_t)__popcll(mkx & mask_of(y)) : v >> 16;
-                        tmp_pair(G.g, T, A, h, nl_x[i], nl_x[y], th, tx, ty, hlen, mx, my, masked ? shh + v : v & 0xffffu, shh);
-                    } else if (masked) {  // v vertices outside h, on top of those inside
-                        const uint32_t shh = __popcll(mkx & mask_of(y));
-                        he2_pair(P, T, A, hlen, mx, my, shh + v, shh, 1);
-                        if (shh) he2_pair(P, T, A, hlen, mx, my, shh, shh, ~0ull);
+                        if (within(th, tx, ty, G.window))
+                            tmp_pair(G.g, T, A, h, nl_x[i], nl_x[y], th, tx, ty, hlen, mx, my, sxy, shh);
                     } else {
-                        he2_pair(P, T, A, hlen, mx, my, v & 0xffffu, v >> 16, 1);
+                        he2_pair(P, T, A, hlen, mx, my, sxy, shh, 1);
+                        if (masked && shh) he2_pair(P, T, A, hlen, mx, my, shh, shh, ~0ull);
                     }
                 };
                 // the counted ones, by a look at all counters or by another walk, whichever is shorter
                 // (temporal: every pair of neighbours has a class of its own)
-                if (TMP || w1 - w0 <= 4 * tot + 64) {
-                    for (uint32_t y = w0 + lane; y < w1; y += 64) {
-                        const uint32_t v = cnt[y - w0];
-                        if (v) cnt[y - w0] = 0;
-                        if (v || TMP) take(y, v);
+                const uint32_t words = (w1 - w0 + (1u << lw) - 1) >> lw;
+                if (TMP) {
+                    for (uint32_t y = w0 + lane; y < w1; y += 64)
+                        take(y, ne ? cnt[(y - w0) >> lw] >> (((y - w0) & ((1u << lw) - 1)) * bits) & cm : 0);
+                    wave_sync();
+                    if (ne)
+                        for (uint32_t k = lane; k < words; k += 64) cnt[k] = 0;
+                } else if (words <= 2 * g.tot + 64) {
+                    for (uint32_t k = lane; k < words; k += 64) {
+                        const uint32_t c = cnt[k];
+                        if (!c) continue;
+                        cnt[k] = 0;
+                        for (uint32_t b = 0; b < 1u << lw; b++) {
+                            const uint32_t v = c >> (b * bits) & cm;
+                            if (v) take(w0 + (k << lw) + b, v);
+                        }
                     }
                 } else {
                     walk([&](uint32_t y, uint32_t) {
                         if (y < w0 || y >= w1) return;
-                        const uint32_t v = atomicExch(&cnt[y - w0], 0u);
+                        const uint32_t sft = ((y - w0) & ((1u << lw) - 1)) * bits;
+                        const uint32_t v = atomicAnd(&cnt[(y - w0) >> lw], ~(cm << sft)) >> sft & cm;
                         if (v) take(y, v);  // else taken at another shared vertex
                     });
                 }
@@ -1172,7 +1190,7 @@ __device__ void he2_flush_stats(const He2Params& P, const uint64_t* st, const ui
         atomicAdd((unsigned long long*)&P.stats[ST_HEB0 + STAGE], (unsigned long long)st[1]);
 }
 
-template <bool BIG, int WG, bool TMP>
+template <int STAGE, int WG, bool TMP>
 __device__ __forceinline__ void he2_kernel(const He2Params& P, uint32_t* arena, uint32_t words, uint32_t* lds) {
     __shared__ Sh2 sh;
     __shared__ Tables T;
@@ -1195,34 +1213,32 @@ __device__ __forceinline__ void he2_kernel(const He2Params& P, uint32_t* arena, 
     }
     if (tid < 2) st[tid] = 0;
     __syncthreads();
-    he2_body<BIG, WG, TMP>(P, arena, words, lds, sh, T, A, st, ph);
+    he2_body<STAGE, WG, TMP>(P, arena, words, lds, sh, T, A, st, ph);
     he2_flush_graph<WG>(P, sh.cur_g, A);
-    if constexpr (!TMP) he2_flush_stats<BIG ? 2 : 0>(P, st, ph);
+    if constexpr (!TMP) he2_flush_stats<STAGE>(P, st, ph);
     else if (P.stats && tid == 0)
         atomicAdd((unsigned long long*)&P.stats[ST_BYTES_BIG], (unsigned long long)st[1]);
 }
 
-__global__ void __launch_bounds__(HGT_WG, 4) k_he2_s0(He2Params P) {
-    __shared__ __attribute__((aligned(16))) uint32_t arena[ARENA_S];
-    he2_kernel<false, HGT_WG, false>(P, arena, ARENA_S, nullptr);
-}
+#define HE2_STAGES(NAME, TMP)                                                                                   \
+    __global__ void __launch_bounds__(HGT_WG, 4) NAME##_s0(He2Params P) {                                       \
+        __shared__ __attribute__((aligned(16))) uint32_t arena[ARENA_S];                                        \
+        he2_kernel<0, HGT_WG, TMP>(P, arena, ARENA_S, nullptr);                                                 \
+    }                                                                                                           \
+    __global__ void __launch_bounds__(WG_M, 4) NAME##_s1(He2Params P) {                                         \
+        __shared__ __attribute__((aligned(16))) uint32_t arena[ARENA_M];                                        \
+        he2_kernel<1, WG_M, TMP>(P, arena, ARENA_M, nullptr);                                                   \
+    }                                                                                                           \
+    __global__ void __launch_bounds__(WG_L, 4) NAME##_s2(He2Params P) {                                         \
+        __shared__ __attribute__((aligned(16))) uint32_t lds[LDS_L];                                            \
+        he2_kernel<2, WG_L, TMP>(P, P.garena + (uint64_t)blockIdx.x * P.garena_words, (uint32_t)P.garena_words, \
+                                 lds);                                                                          \
+    }
+HE2_STAGES(k_he2, false)
+HE2_STAGES(k_tmp, true)
+#undef HE2_STAGES
 
-__global__ void __launch_bounds__(WG_L, 4) k_he2_s2(He2Params P) {
-    __shared__ __attribute__((aligned(16))) uint32_t lds[LDS_L];
-    he2_kernel<true, WG_L, false>(P, P.garena + (uint64_t)blockIdx.x * P.garena_words, (uint32_t)P.garena_words, lds);
-}
-
-__global__ void __launch_bounds__(HGT_WG, 4) k_tmp_s0(He2Params P) {
-    __shared__ __attribute__((aligned(16))) uint32_t arena[ARENA_S];
-    he2_kernel<false, HGT_WG, true>(P, arena, ARENA_S, nullptr);
-}
-
-__global__ void __launch_bounds__(WG_L, 4) k_tmp_s2(He2Params P) {
-    __shared__ __attribute__((aligned(16))) uint32_t lds[LDS_L];
-    he2_kernel<true, WG_L, true>(P, P.garena + (uint64_t)blockIdx.x * P.garena_words, (uint32_t)P.garena_words, lds);
-}
-
-// Slices of the global stage's centres.  A wave per centre estimates its work in walked
+// Slices of the centres of stages 1 and 2.  A wave per centre estimates its work in walked
 // run entries: its lists (the rows are gathered by every slice), and the pairs of its
 // neighbours.  Those that meet inside h count when h is too long for masks (squares of the
 // list lengths); outside h, a vertex of degree d lies in about d K / E neighbours, so the
@@ -1266,20 +1282,45 @@ __global__ void k_he2_work(Multi M, const uint64_t* __restrict__ list, const uin
     if (lane == 0 && sum) atomicAdd((unsigned long long*)total, (unsigned long long)sum);
 }
 
-// Work to slices: a quarter of a workgroup's share of the whole, so that the last ones
-// end together, and at least SLICE_MIN (what building the tables again costs).
+// Work to slices, and their exclusive prefix, by one workgroup: a slice holds a quarter of
+// a workgroup's share of the whole, so that the last ones end together, and at least
+// SLICE_MIN (what building the tables again costs).
 constexpr uint64_t SLICE_MIN = 1ull << 15;
 constexpr uint32_t SLICES_MAX = 64;
-__global__ void k_he2_cut(uint64_t cap, uint32_t slice_lh, uint64_t slice_pairs, uint32_t grid, const uint64_t* total,
-                          uint64_t* pre) {
+__global__ void __launch_bounds__(1024) k_he2_cut(uint64_t cap, uint32_t slice_lh, uint64_t slice_pairs, uint32_t grid,
+                                                  const uint64_t* total, uint64_t* pre) {
+    __shared__ uint32_t ws[16];
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint64_t n = pre[cap];
     uint64_t per = *total / (4ull * grid);
     if (per < SLICE_MIN) per = SLICE_MIN;
     if (slice_pairs) per = slice_pairs;
-    for (uint64_t c = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; c < n; c += (uint64_t)gridDim.x * blockDim.x) {
-        const uint64_t sl = slice_lh ? pre[c] : (pre[c] + per - 1) / per;
-        pre[c] = sl < 1 ? 1 : (sl > SLICES_MAX ? SLICES_MAX : sl);
+    uint64_t base = 0;
+    for (uint64_t b = 0; b < n; b += 1024) {
+        const uint64_t c = b + threadIdx.x;
+        uint32_t sl = 0;
+        if (c < n) {
+            const uint64_t w = slice_lh ? pre[c] : (pre[c] + per - 1) / per;
+            sl = w < 1 ? 1 : w > SLICES_MAX ? SLICES_MAX : (uint32_t)w;
+        }
+        uint32_t inc = sl;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t t = __shfl_up(inc, o, 64);
+            if (lane >= (uint32_t)o) inc += t;
+        }
+        if (lane == 63) ws[wave] = inc;
+        __syncthreads();
+        uint32_t before = 0, all = 0;
+        for (uint32_t w = 0; w < 16; w++) {
+            if (w < wave) before += ws[w];
+            all += ws[w];
+        }
+        if (c < n) pre[c] = base + before + inc - sl;
+        base += all;
+        __syncthreads();
     }
+    if (threadIdx.x == 0) pre[cap + 1] = base;
 }
 
 }  // namespace
@@ -1312,26 +1353,34 @@ void he2_remove_deleted(NbrParams& P, hipStream_t s) {
 
 namespace {
 
-void launch_global(He2Params& P, unsigned grid, bool tmp, hipStream_t s) {
+// Stages 1 and 2: each cuts the centres that the stage before moved on.
+void launch_sliced(He2Params& P, int stage, unsigned grid, bool tmp, hipStream_t s) {
     if (!P.M.total) return;
     const uint64_t cap = P.slice_cap;
-    const unsigned waves = (unsigned)((cap + 3) / 4), blk = (unsigned)((cap + 255) / 256);
-    k_he2_work<<<waves < 1024 ? waves : 1024, 256, 0, s>>>(P.M, P.list[0], &P.count[0], cap, P.slice_lh, tmp ? 1 : 0,
-                                                           P.slice_pre, P.work_total);
-    k_he2_cut<<<blk < 256 ? blk : 256, 256, 0, s>>>(cap, P.slice_lh, P.slice_pairs, grid, P.work_total, P.slice_pre);
-    hgt_scan_u64(P.slice_pre, P.slice_pre, cap, P.slice_pre + cap, P.slice_pre + cap + 1, P.slice_scan_tmp, s);
-    if (tmp) k_tmp_s2<<<grid, WG_L, 0, s>>>(P);
-    else k_he2_s2<<<grid, WG_L, 0, s>>>(P);
+    const unsigned waves = (unsigned)((cap + 3) / 4);
+    uint64_t* total = P.work_total + (stage - 1);
+    k_he2_work<<<waves < 1024 ? waves : 1024, 256, 0, s>>>(P.M, P.list[stage - 1], &P.count[stage - 1], cap, P.slice_lh,
+                                                           tmp ? 1 : 0, P.slice_pre, total);
+    k_he2_cut<<<1, 1024, 0, s>>>(cap, P.slice_lh, P.slice_pairs, grid, total, P.slice_pre);
+    if (stage == 1) {
+        if (tmp) k_tmp_s1<<<grid, WG_M, 0, s>>>(P);
+        else k_he2_s1<<<grid, WG_M, 0, s>>>(P);
+    } else {
+        if (tmp) k_tmp_s2<<<grid, WG_L, 0, s>>>(P);
+        else k_he2_s2<<<grid, WG_L, 0, s>>>(P);
+    }
 }
 
 }  // namespace
 
-void he2_launch_lds(He2Params& P, unsigned grid, hipStream_t s) {
+void he2_launch_lds(He2Params& P, unsigned grid, unsigned grid_mid, hipStream_t s) {
     if (P.M.total) k_he2_s0<<<grid, HGT_WG, 0, s>>>(P);
+    launch_sliced(P, 1, grid_mid, false, s);
 }
-void he2_launch_global(He2Params& P, unsigned grid, hipStream_t s) { launch_global(P, grid, false, s); }
+void he2_launch_global(He2Params& P, unsigned grid, hipStream_t s) { launch_sliced(P, 2, grid, false, s); }
 
-void tmp_launch_lds(He2Params& P, unsigned grid, hipStream_t s) {
+void tmp_launch_lds(He2Params& P, unsigned grid, unsigned grid_mid, hipStream_t s) {
     if (P.M.total) k_tmp_s0<<<grid, HGT_WG, 0, s>>>(P);
+    launch_sliced(P, 1, grid_mid, true, s);
 }
-void tmp_launch_global(He2Params& P, unsigned grid, hipStream_t s) { launch_global(P, grid, true, s); }
+void tmp_launch_global(He2Params& P, unsigned grid, hipStream_t s) { launch_sliced(P, 2, grid, true, s); }

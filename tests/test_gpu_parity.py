@@ -400,14 +400,15 @@ def test_sliced_two_hop_centres(gpu_lib, monkeypatch):
 
 @pytest.mark.parametrize("slice_lh", ["0", "64"])
 @pytest.mark.parametrize("shape", ["window", "mixed", "wide-row"])
-def test_global_stage_centres(gpu_lib, monkeypatch, shape, slice_lh):
-    """Centres of the global histogram stage: more neighbours than one window of
-    counters holds (2,048), rows of one to 150 members, and a hyperedge of 6,000
-    members (more than the stage's LDS takes: the 2-hop kernel); whole and shared
-    among workgroups.  The change of the counts equals the oracle's delta by
+@pytest.mark.parametrize("stage", ["1", "2"])
+def test_global_stage_centres(gpu_lib, monkeypatch, stage, shape, slice_lh):
+    """Centres of the histogram stages 1 (54 KB of LDS) and 2 (global memory):
+    more neighbours than one window of counters holds, rows of one to 150
+    members, and hyperedges of 6,000 members (more than the stages' LDS takes:
+    the 2-hop kernel); whole and shared among workgroups.  The change of the counts equals the oracle's delta by
     definition."""
     from .test_gpu_fullsize import _gpu_delta, _oracle_delta
-    monkeypatch.setenv("HGT_FORCE_STAGE", "1")
+    monkeypatch.setenv("HGT_FORCE_STAGE", stage)
     if slice_lh != "0":
         monkeypatch.setenv("HGT_SLICE_LH", slice_lh)
     if shape == "window":
@@ -449,15 +450,15 @@ def test_incident_vertex_owner_stages(gpu_lib, monkeypatch, stage, card):
     p.close()
 
 
-@pytest.mark.parametrize("stage", ["0", "1"])
-@pytest.mark.parametrize("card", [(62, 66), (1, 2), (3, 12)])
+@pytest.mark.parametrize("stage", ["0", "1", "2"])
+@pytest.mark.parametrize("card", [(62, 66), (1, 2), (3, 12), (250, 260)])
 def test_shared_member_masks(gpu_lib, monkeypatch, stage, card):
     """Neighbours counted by the mask of members they share with the centre: rows
-    around the 64 members a mask holds, single members and repeated rows (nothing
-    private), in the LDS and in the global stage; build and batches against the
-    oracle."""
+    around the 64 members a mask holds, around the 255 that byte counters take,
+    single members and repeated rows (nothing private), in every stage; build and
+    batches against the oracle."""
     monkeypatch.setenv("HGT_FORCE_STAGE", stage)
-    nv, n = (400, 50) if card[0] > 10 else (12, 150)
+    nv, n = (600, 50) if card[0] > 10 else (12, 150)
     st = W.plain_stream("masks", nv, n, ("uniform",) + card, 0.7, 0.0, 2, 20, 15, W.SEED_BASE + 99)
     p = Pair(st, track=("hyperedge",))
     compare_counts(p.g, p.o, p.track, "masks build")
