@@ -12,6 +12,7 @@
 
 #include "hops.h"
 #include "internal.h"
+#include "small.h"
 #include "store.h"
 #include "triad.h"
 
@@ -1058,16 +1059,30 @@ inline unsigned nblk(uint64_t n, unsigned per = 256) {
 
 struct IvPlan {
     uint64_t n_keys = 0;
-    uint64_t* uniq = nullptr;     // touched pairs (lo << 32 | hi), sorted
-    uint64_t* own = nullptr;      // the same as (owner << 32 | other), sorted
+    uint64_t* own = nullptr;      // touched pairs (owner << 32 | other), sorted
     uint64_t* n_uniq = nullptr;
     uint64_t tab_slots = 0;
 };
 
+// The touched vertex pairs of a planned batch.  A small batch's go into `small` instead
+// (one launch for the batches of a round, one workgroup each: small.hip).
 int iv_prepare(hgt_graph* g, const BatchIn& b, const PlanScratch& w, const BatchSummary& sum, IvPlan& ip,
-               hipStream_t s) {
+               std::vector<SmallIv>& small, hipStream_t s) {
     uint64_t nk = sum.del_pairs2 + sum.ins_pairs2;
     ip.n_keys = nk;
+    if (nk && nk <= kSmallPairs && b.n_del <= kSmallRows && b.n_ins <= kSmallRows) {
+        ip.tab_slots = pow2ceil64(2 * nk + 64);
+        if (ensure(g->iv_keys, nk * 8) || ensure(g->iv_uniq, 64) || ensure(g->iv_tab, ip.tab_slots * 8) ||
+            ensure(g->iv_owner, (nk + 2) * 8) || ensure(g->iv_ctr, 64))
+            return HGT_ENOMEM;
+        ip.own = g->iv_keys.as<uint64_t>();
+        ip.n_uniq = g->iv_uniq.as<uint64_t>();
+        small.push_back(SmallIv{b.del, b.n_del, b.n_ins, g->st.h_off, g->st.h_len, g->st.h2v, w.canon, w.ins_rel,
+                                g->st.v_len, g->st.sc, g->counts.as<uint64_t>() + ACC_T1, ip.own, ip.n_uniq,
+                                g->iv_tab.as<uint64_t>(), ip.tab_slots, g->iv_owner.as<uint64_t>(),
+                                g->iv_ctr.as<uint64_t>()});
+        return HGT_OK;
+    }
     uint64_t nmax = std::max<uint64_t>(nk, 1);
     uint64_t nh = std::max<uint64_t>(std::max(b.n_del, b.n_ins), 1);
     int rc = 0;
@@ -1095,7 +1110,7 @@ int iv_prepare(hgt_graph* g, const BatchIn& b, const PlanScratch& w, const Batch
         k_iv_gen<<<std::min(nblk(b.n_ins * 64), kIvGenBlocks), 256, 0, s>>>(nullptr, b.n_ins, nullptr, nullptr, nullptr, w.canon, w.ins_rel,
                                                     p2, sum.del_pairs2, vb, keys, cnt + ACC_T1 + 1, g->st.sc);
     }
-    ip.uniq = g->iv_uniq.as<uint64_t>() + 1;
+    uint64_t* uniq = g->iv_uniq.as<uint64_t>() + 1;  // (lo << 32 | hi), sorted
     ip.n_uniq = g->iv_uniq.as<uint64_t>();
     if (nk == 0) {
         hgt_fill_u64(ip.n_uniq, 0, 1, s);
@@ -1105,17 +1120,17 @@ int iv_prepare(hgt_graph* g, const BatchIn& b, const PlanScratch& w, const Batch
     uint64_t* head = g->iv_head.as<uint64_t>();
     k_uniq_heads<<<nblk(nk), 256, 0, s>>>(keys, nk, head);
     hgt_scan_u64(head, head, nk, nullptr, ip.n_uniq, g->iv_scan.p, s);
-    k_uniq_write<<<nblk(nk), 256, 0, s>>>(keys, nk, head, vb, ip.uniq);
+    k_uniq_write<<<nblk(nk), 256, 0, s>>>(keys, nk, head, vb, uniq);
     // pairs by owner (the buffer of the unsorted keys is free now)
     ip.own = keys;
-    k_iv_orient<<<nblk(nk > 262144 ? 262144 : nk), 256, 0, s>>>(ip.uniq, ip.n_uniq, g->st.v_len, ip.own);
+    k_iv_orient<<<nblk(nk > 262144 ? 262144 : nk), 256, 0, s>>>(uniq, ip.n_uniq, g->st.v_len, ip.own);
     hgt_radix_sort_u64(ip.own, g->iv_alt.as<uint64_t>(), nk, ip.n_uniq, 32 + vb, g->iv_sort.p, s);
     // hash of the touched pairs and the owner segments
     ip.tab_slots = pow2ceil64(2 * nk + 64);
     if (ensure(g->iv_tab, ip.tab_slots * 8) || ensure(g->iv_owner, (nk + 2) * 8) || ensure(g->iv_ctr, 64))
         return HGT_ENOMEM;
     uint64_t* ictr = g->iv_ctr.as<uint64_t>();
-    iv_touched_build(ip.uniq, ip.own, ip.n_uniq, g->iv_tab.as<uint64_t>(), ip.tab_slots, head,
+    iv_touched_build(uniq, ip.own, ip.n_uniq, g->iv_tab.as<uint64_t>(), ip.tab_slots, head,
                      g->iv_owner.as<uint64_t>(), ictr, nk, g->iv_scan.p, s);
     return HGT_OK;
 }
@@ -1193,6 +1208,7 @@ struct Pending {
     int is_build = 0;                       // the build: counts by the static mode of the kernels
     const uint32_t* forced_ids = nullptr;   // horizontal operations: the IDs the inserts take
     int keep_seq = 0;                       // horizontal operations: arrival sequences kept
+    bool small = false;                     // planned by one workgroup
     int rc = HGT_OK;  // this batch's result so far
 };
 
@@ -1261,8 +1277,21 @@ bool pools_bloated(const hgt_graph* g) {
     return g->h_bump > 2 * h_est + (1ull << 20) || g->v_bump > 2 * v_est + (1ull << 20);
 }
 
-// Host checks, scratch, and the non-mutating planning pass; the summary is
-// copied to pinned memory, read after the caller synchronises.
+// The planning pass kernel by kernel; the summary is copied to pinned memory.
+int plan_large(Pending& p, hipStream_t s) {
+    hgt_graph* g = p.g;
+    store_batch_begin(g->st.sc, p.w.sum, s);
+    hgt_fill_u64(g->counts.as<uint64_t>() + CNT_N, 0, ACC_N - CNT_N, s);
+    {
+        ProfScope ps(g, PK_PLAN, s);
+        store_plan(g->st, p.b, p.w, s);
+    }
+    HIP_OK(hipMemcpyAsync(g->h_sum, p.w.sum, sizeof(BatchSummary), hipMemcpyDeviceToHost, s));
+    return HGT_OK;
+}
+
+// Host checks, scratch, and the non-mutating planning pass, whose summary is read
+// after plan_wait.
 int plan_begin(Pending& p, const uint32_t* del, uint64_t n_del, const uint64_t* ins_off, const uint32_t* ins_mem,
                uint64_t n_mem, const int64_t* ins_ts, uint64_t n_ins, hipStream_t s) {
     hgt_graph* g = p.g;
@@ -1288,20 +1317,44 @@ int plan_begin(Pending& p, const uint32_t* del, uint64_t n_del, const uint64_t* 
                   p.forced_ids, p.keep_seq};
     p.n_mem = n_mem;
     g->epoch += 2;
-    uint64_t* cnt = g->counts.as<uint64_t>();
-    store_batch_begin(g->st.sc, p.w.sum, s);
-    hgt_fill_u64(cnt + CNT_N, 0, ACC_N - CNT_N, s);
-    {
-        ProfScope ps(g, PK_PLAN, s);
-        store_plan(g->st, p.b, p.w, s);
+    // The lists of a row's vertices are disjoint, so its list words fit 32 bits with the graph's.
+    p.small = n_del <= kSmallRows && n_ins <= kSmallRows && n_mem <= kSmallPairs && g->next_id <= kSmallIds &&
+              g->n_inc + n_mem <= 0xffffffffull;
+    if (p.small) return HGT_OK;  // planned with the round's other small batches (plan_wait)
+    return plan_large(p, s);
+}
+
+// Queues what plan_begin left and waits for the summaries of the batches with rc == 0.
+int plan_wait(const std::vector<Pending*>& ps, hipStream_t s) {
+    std::vector<SmallPlan> jobs;
+    for (Pending* p : ps)
+        if (p->small)
+            jobs.push_back(SmallPlan{p->g->st, p->b, p->w, p->g->counts.as<uint64_t>() + CNT_N, ACC_N - CNT_N, 0,
+                                     p->g->h_sum});
+    if (!jobs.empty()) {
+        hgt_graph* g = nullptr;
+        for (Pending* p : ps)
+            if (p->small && !g) g = p->g;
+        ProfScope sc(g, PK_PLAN, s);
+        for (size_t i = 0; i < jobs.size(); i += kSmallPlanJobs)
+            small_plan(&jobs[i], (uint32_t)std::min<size_t>(kSmallPlanJobs, jobs.size() - i), s);
+        HIP_OK(hipGetLastError());
     }
-    HIP_OK(hipMemcpyAsync(g->h_sum, p.w.sum, sizeof(BatchSummary), hipMemcpyDeviceToHost, s));
+    HIP_OK(hipStreamSynchronize(s));
+    bool again = false;  // its deleted hyperedges hold more pairs than a workgroup plans
+    for (Pending* p : ps)
+        if (p->small && p->g->h_sum->status == HGT_OK && p->g->h_sum->pad0) {
+            p->small = false;
+            again = true;
+            if (int rc = plan_large(*p, s)) return rc;
+        }
+    if (again) HIP_OK(hipStreamSynchronize(s));
     return HGT_OK;
 }
 
 // After the synchronisation: the batch's verdict, then capacities for the commit
 // and the incident-vertex pair list.
-int plan_end(Pending& p, hipStream_t s) {
+int plan_end(Pending& p, std::vector<SmallIv>& small, hipStream_t s) {
     hgt_graph* g = p.g;
     p.sum = *g->h_sum;
     if (p.sum.status != HGT_OK) return p.sum.status;
@@ -1322,9 +1375,18 @@ int plan_end(Pending& p, hipStream_t s) {
     p.w.staging_ts = g->s_staging_ts.as<int64_t>();
     if (g->track_mask & (1u << HGT_TRIAD_INCIDENT_VERTEX)) {
         ProfScope ps(g, PK_IV_PREP, s);
-        rc = iv_prepare(g, p.b, p.w, sum, p.ip, s);
+        rc = iv_prepare(g, p.b, p.w, sum, p.ip, small, s);
         if (rc) return rc;
     }
+    return HGT_OK;
+}
+
+int iv_prepare_small(hgt_graph* g, const std::vector<SmallIv>& small, hipStream_t s) {
+    if (small.empty()) return HGT_OK;
+    ProfScope ps(g, PK_IV_PREP, s);
+    for (size_t i = 0; i < small.size(); i += kSmallIvJobs)
+        small_iv(&small[i], (uint32_t)std::min<size_t>(kSmallIvJobs, small.size() - i), s);
+    HIP_OK(hipGetLastError());
     return HGT_OK;
 }
 
@@ -1408,14 +1470,27 @@ int apply_locked(hgt_graph* owner, std::vector<Pending*>& ps, hipStream_t s, boo
         if ((p->g->track_mask & (1u << HGT_TRIAD_INCIDENT_VERTEX)) && (rc = iv_phase(p->g, p->ip, true, s)))
             return rc;
     // step 3: delete, then insert
+    std::vector<SmallCommit> small;
+    hgt_graph* small_g = nullptr;
     for (Pending* p : ps) {
         hgt_graph* g = p->g;
+        if (p->small && p->sum.stage_words <= kSmallStage) {
+            if (!small_g) small_g = g;
+            small.push_back(SmallCommit{g->st, p->b, p->w, p->sum.n_touched, g->h_bump, g->v_bump, g->next_seq,
+                                        p->out_ids});
+            continue;
+        }
         {
             ProfScope sc(g, PK_COMMIT, s);
             store_commit(g->st, p->b, p->w, p->sum, g->h_bump, g->v_bump, g->next_seq, s);
         }
         if (p->out_ids && p->b.n_ins)
             HIP_OK(hipMemcpyAsync(p->out_ids, p->w.assigned, p->b.n_ins * 4, hipMemcpyDeviceToDevice, s));
+    }
+    if (!small.empty()) {
+        ProfScope sc(small_g, PK_COMMIT, s);
+        for (size_t i = 0; i < small.size(); i += kSmallCommitJobs)
+            small_commit(&small[i], (uint32_t)std::min<size_t>(kSmallCommitJobs, small.size() - i), s);
     }
     if (!t_capture && fault_injected()) return HGT_EDEVICE;
     // step 5: deltas on the new graph
@@ -1588,13 +1663,15 @@ int apply(hgt_graph* g, const uint32_t* del, uint64_t n_del, const uint64_t* ins
     int rc = plan_begin(p, del, n_del, ins_off, ins_mem, n_mem, ins_ts, n_ins, s);
     if (rc == HGT_ENOENT) set_sticky(g, rc);
     if (rc) return rc;
-    HIP_OK(hipStreamSynchronize(s));
-    rc = plan_end(p, s);
+    std::vector<Pending*> ps{&p};
+    if ((rc = plan_wait(ps, s))) return rc;
+    std::vector<SmallIv> small;
+    rc = plan_end(p, small, s);
     if (rc) {
         set_sticky(g, rc);
         return rc;
     }
-    std::vector<Pending*> ps{&p};
+    if ((rc = iv_prepare_small(g, small, s))) return rc;
     return apply_planned(g, ps, s);
 }
 
@@ -2097,7 +2174,7 @@ int apply_batches(hgt_batch* bs, uint32_t n, void* stream, uint32_t flags) {
         if (std::adjacent_find(gs.begin(), gs.end()) != gs.end()) return HGT_EINVAL;
     }
     std::vector<Pending> P(n);
-    bool any = false;
+    std::vector<Pending*> act;
     for (uint32_t i = 0; i < n; i++) {
         hgt_batch& b = bs[i];
         b.status = HGT_OK;
@@ -2111,14 +2188,19 @@ int apply_batches(hgt_batch* bs, uint32_t n, void* stream, uint32_t flags) {
         if (b.n_del == 0 && b.n_ins == 0) continue;
         P[i].rc = plan_begin(P[i], b.del_ids, b.n_del, b.ins_offsets, b.ins_members, b.n_ins_members, b.ins_ts,
                              b.n_ins, s);
-        if (P[i].rc == HGT_OK) any = true;
-    }
-    if (any) HIP_OK(hipStreamSynchronize(s));
-    std::vector<Pending*> act;
-    for (uint32_t i = 0; i < n; i++) {
-        if (P[i].rc != HGT_OK) continue;
-        P[i].rc = plan_end(P[i], s);
         if (P[i].rc == HGT_OK) act.push_back(&P[i]);
+    }
+    if (!act.empty()) {
+        if (int rc = plan_wait(act, s)) return rc;
+        act.clear();
+        std::vector<SmallIv> small;
+        for (Pending& p : P) {
+            if (p.rc != HGT_OK) continue;
+            p.rc = plan_end(p, small, s);
+            if (p.rc == HGT_OK) act.push_back(&p);
+        }
+        if (!act.empty())
+            if (int rc = iv_prepare_small(act[0]->g, small, s)) return rc;
     }
     if (!act.empty()) {
         hgt_graph* owner = act[0]->g;

@@ -233,6 +233,24 @@ __device__ __forceinline__ uint32_t slice_of(uint32_t x, uint32_t nslice) {
     return (uint32_t)(((uint64_t)(x * 2654435761u) * nslice) >> 32);
 }
 
+// slot of a touched vertex pair in the incident-vertex family's hash
+__device__ __forceinline__ uint64_t mix64(uint64_t k) {
+    k ^= k >> 33;
+    k *= 0xff51afd7ed558ccdull;
+    k ^= k >> 33;
+    k *= 0xc4ceb9fe1a85ec53ull;
+    k ^= k >> 33;
+    return k;
+}
+
+// owners: first pair index of every distinct first vertex, and of every IV_SPLIT-th pair,
+// so that an owner of many pairs is shared among waves (each builds its map: a few
+// hundred members against up to 64 scans)
+constexpr uint64_t IV_SPLIT = 64;
+__device__ __forceinline__ bool iv_head(const uint64_t* pairs, uint64_t i) {
+    return i % IV_SPLIT == 0 || (pairs[i] >> 32) != (pairs[i - 1] >> 32);
+}
+
 struct Tables {
     uint8_t he[128];
     uint8_t tmp[128];

@@ -43,15 +43,6 @@ using namespace tri;
 constexpr uint32_t IV_ARENA = 5888;       // stage 1: 23 KB of LDS per workgroup
 constexpr uint32_t IV_WAVE_WORDS = 1024;  // stage 0: 4 KB of LDS per wave
 
-__device__ __forceinline__ uint64_t mix64(uint64_t k) {
-    k ^= k >> 33;
-    k *= 0xff51afd7ed558ccdull;
-    k ^= k >> 33;
-    k *= 0xc4ceb9fe1a85ec53ull;
-    k ^= k >> 33;
-    return k;
-}
-
 __device__ __forceinline__ uint64_t pair_key(uint32_t x, uint32_t y) {
     return x < y ? ((uint64_t)x << 32 | y) : ((uint64_t)y << 32 | x);
 }
@@ -86,13 +77,6 @@ __global__ void k_iv_hash_build(const uint64_t* __restrict__ pairs, const uint64
     }
 }
 
-// owners: first pair index of every distinct first vertex, and of every IV_SPLIT-th pair,
-// so that an owner of many pairs is shared among waves (each builds its map: a few
-// hundred members against up to 64 scans)
-constexpr uint64_t IV_SPLIT = 64;
-__device__ __forceinline__ bool iv_head(const uint64_t* pairs, uint64_t i) {
-    return i % IV_SPLIT == 0 || (pairs[i] >> 32) != (pairs[i - 1] >> 32);
-}
 __global__ void k_iv_owner_heads(const uint64_t* __restrict__ pairs, const uint64_t* n_p, uint64_t* head) {
     uint64_t n = *n_p;
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)

@@ -497,3 +497,67 @@ def test_temporal_paths(gpu_lib, shape, window):
             p.apply(b, f"{shape} batch {k}")
             compare_counts(p.g, p.o, p.track, f"{shape} batch {k}")
     p.close()
+
+
+@pytest.mark.parametrize("shape", ["rows-in", "rows-out", "pairs-in", "pairs-out", "deleted-pairs-out", "long-rows",
+                                   "vertex-pairs", "long-lists"])
+def test_batches_of_one_workgroup(gpu_lib, shape):
+    """Batches on both sides of each limit of the one-workgroup plan, update and vertex
+    pair list: 2,048 rows, 8,192 (vertex, hyperedge) pairs (the deleted hyperedges' are
+    counted on the device only), 8,192 vertex pairs, 32,768 old list entries; rows that
+    are sorted by the workgroup; and the errors of such batches."""
+    from paper_2512_21009_amd import hgt
+    nv, ne, card, n_ins, n_del = {
+        "rows-in": (9000, 2500, (1, 2), 2048, 2048),
+        "rows-out": (9000, 2500, (1, 2), 2049, 2049),
+        "pairs-in": (3000, 1000, (8, 8), 512, 512),
+        "pairs-out": (3000, 1000, (8, 8), 512, 513),
+        "deleted-pairs-out": (3000, 500, (60, 90), 3, 140),
+        "long-rows": (3000, 200, (60, 300), 20, 20),
+        "vertex-pairs": (2000, 600, (17, 17), 31, 30),  # 61 * 136 = 8,296
+        "long-lists": (1500, 9000, (3, 6), 1000, 700),
+    }[shape]
+    track = ("hyperedge", "incident_vertex") if nv == 9000 or shape == "vertex-pairs" else ("hyperedge",)
+    st = W.plain_stream("wg", nv, ne, ("uniform", *card), 0.0, 0.0, 2, n_ins, n_del, W.SEED_BASE + 111)
+    p = Pair(st, track=track)
+    for k, b in enumerate(st.batches):
+        p.apply(b, f"{shape} batch {k}")
+        compare_store(p.g, p.o, f"{shape} batch {k}")
+        compare_counts(p.g, p.o, p.track, f"{shape} batch {k}")
+    before = ([p.g.triad_counts(t) for t in track], p.g.export_h2v()[1].tolist(), p.g.export_v2h()[1].tolist())
+    ins, live = st.batches[0].ins, np.array(sorted(p.gid.values()))
+    off, mem = ins.offsets.astype(np.int64), ins.members.astype(np.int64)
+    bad_mem = [np.where(np.arange(len(mem)) == len(mem) - 1, v, mem) for v in (nv, 0)]
+    bad_mem[1][off[-2]:] = mem[off[-2]]  # one vertex throughout the last row
+    bad_off = off.copy()
+    bad_off[-1] -= 1
+    cases = [(hgt.ENOENT, live[:n_del].tolist() + [p.o.next_id], off, mem),
+             (hgt.EDUP, live[:n_del].tolist() + [int(live[0])], off, mem),
+             (hgt.EINVAL, live[:n_del], off, bad_mem[0]),
+             (hgt.EINVAL, live[:n_del], bad_off, mem)]
+    if off[-1] - off[-2] > 1:
+        cases.append((hgt.EINVAL, live[:n_del], off, bad_mem[1]))
+    for code, dels, o, m in cases:
+        rc, _ = p.g.apply_batch(dev(dels, np.int32), dev(o, np.int64), dev(m, np.int32), raise_on_error=False)
+        assert rc == code, (rc, code)
+        assert ([p.g.triad_counts(t) for t in track], p.g.export_h2v()[1].tolist(), p.g.export_v2h()[1].tolist()) == before
+    p.close()
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_rounds_of_mixed_batch_sizes(gpu_lib, graph):
+    """A round of graphs with all families kept: batches of one workgroup (more than one
+    launch of them), one beyond its rows and one whose deletions are beyond its pairs."""
+    from .gpu_harness import apply_many
+    sts = [W.temporal_stream("mix", 300, 260, 4 + 3 * i, 2, 2.0, 1, 5, 7.0, 700, 150, W.SEED_BASE + 120 + i)
+           for i in range(13)]
+    sts.append(W.temporal_stream("mix", 20000, 2600, 2100, 2, 2.0, 1, 4, 7.0, 7000, 150, W.SEED_BASE + 140))
+    sts.append(W.temporal_stream("mix", 4000, 260, 20, 2, 1.0, 70, 80, 7.0, 700, 150, W.SEED_BASE + 141))
+    pairs = [Pair(s, track=ALL) for s in sts]
+    for k in range(2):
+        apply_many(pairs, [s.batches[k] for s in sts], f"mixed round {k}", **({"graph": True} if graph else {}))
+        for i, p in enumerate(pairs):
+            compare_store(p.g, p.o, f"mixed round {k} graph {i}")
+            compare_counts(p.g, p.o, ("hyperedge",) if i == 14 else ALL, f"mixed round {k} graph {i}")
+    for p in pairs:
+        p.close()
