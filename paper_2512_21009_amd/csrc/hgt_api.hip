@@ -1144,48 +1144,60 @@ constexpr uint64_t kIvGarena2Words = 1ull << 21;
 inline unsigned iv_grid_global(const hgt_graph* g) { return t_na ? 16u : (unsigned)(g->n_cu * g->iv_wg_per_cu); }
 inline unsigned iv_grid_global2() { return t_na ? 2u : 32u; }
 
-int iv_reserve(hgt_graph* g, const IvPlan& ip) {
-    PhaseCtx& c = ctx_of(g);
-    if (ensure(c.iv_list0, (ip.n_keys + 1) * 4) || ensure(c.iv_list, (ip.n_keys + 1) * 4) || ensure(c.iv_list2, (ip.n_keys + 1) * 4) ||
-        ensure(c.iv_garena, (uint64_t)iv_grid_global(g) * kIvGarenaWords * 4) ||
+int iv_reserve(hgt_graph* owner, uint64_t n_keys, uint32_t n_graphs) {
+    PhaseCtx& c = ctx_of(owner);
+    if (ensure(c.iv_list0, (n_keys + n_graphs) * 4) || ensure(c.iv_list, (n_keys + n_graphs) * 4) ||
+        ensure(c.iv_list2, (n_keys + n_graphs) * 4) ||
+        ensure(c.iv_garena, (uint64_t)iv_grid_global(owner) * kIvGarenaWords * 4) ||
         ensure(c.iv_garena2, (uint64_t)iv_grid_global2() * kIvGarena2Words * 4))
         return HGT_ENOMEM;
     return HGT_OK;
 }
 
-int iv_phase(hgt_graph* g, const IvPlan& ip, bool minus, hipStream_t s) {
-    if (ip.n_keys == 0) return HGT_OK;
-    const uint64_t gwords = kIvGarenaWords;
-    const unsigned grid_g = iv_grid_global(g);
-    PhaseCtx& c = ctx_of(g);
-    if (int rc = iv_reserve(g, ip)) return rc;
-    IvParams P{};
-    P.g = view_of(g);
-    P.pairs = ip.own;
-    P.n_pairs = ip.n_uniq;
-    uint64_t* ictr = g->iv_ctr.as<uint64_t>();
-    P.n_owners = ictr;
-    P.owner_start = g->iv_owner.as<uint64_t>();
-    P.tab = g->iv_tab.as<uint64_t>();
-    P.tab_mask = ip.tab_slots - 1;
-    P.out = g->counts.as<uint64_t>() + (minus ? ACC_IV_M : ACC_IV_P);
-    P.status = &g->st.sc->status;
-    P.queue = (uint32_t*)(ictr + 2);
-    P.count = P.queue + 4;
-    P.list[0] = c.iv_list0.as<uint32_t>();
-    P.list[1] = c.iv_list.as<uint32_t>();
-    P.list[2] = c.iv_list2.as<uint32_t>();
-    P.garena = c.iv_garena.as<uint32_t>();
-    P.garena_words = gwords;
-    P.garena2 = c.iv_garena2.as<uint32_t>();
-    P.garena2_words = kIvGarena2Words;
-    P.stats = g->prof ? g->stats.as<uint64_t>() : nullptr;
-    P.force_direct = g->iv_direct;
-    P.force_stage = g->iv_force_stage;
-    ProfScope ps(g, PK_IV_PAIRS, s);
-    // a wave per owner at five workgroups per CU (32 KB of LDS each), then workgroups at four
-    triad_iv_launch(P, (unsigned)std::min<uint64_t>((uint64_t)g->n_cu * 5, (ip.n_keys + 3) / 4),
-                    (unsigned)std::min<uint64_t>((uint64_t)g->n_cu * 4, ip.n_keys), grid_g, iv_grid_global2(), s);
+// The touched pairs of several graphs, kIvJobs graphs a launch.
+int iv_phase(hgt_graph* owner, const std::vector<std::pair<hgt_graph*, const IvPlan*>>& gs, bool minus, hipStream_t s) {
+    if (gs.empty()) return HGT_OK;
+    PhaseCtx& c = ctx_of(owner);
+    uint64_t n_all = 0;
+    for (auto& [g, ip] : gs) n_all += ip->n_keys;
+    if (int rc = iv_reserve(owner, n_all, (uint32_t)gs.size())) return rc;
+    ProfScope ps(gs[0].first, PK_IV_PAIRS, s);
+    for (size_t from = 0; from < gs.size(); from += kIvJobs) {
+        IvParams P{};
+        P.n_jobs = (uint32_t)std::min<size_t>(kIvJobs, gs.size() - from);
+        uint64_t n_keys = 0;
+        for (uint32_t k = 0; k < P.n_jobs; k++) {
+            hgt_graph* g = gs[from + k].first;
+            const IvPlan& ip = *gs[from + k].second;
+            uint64_t* ictr = g->iv_ctr.as<uint64_t>();
+            IvJob& J = P.job[k];
+            J.g = view_of(g);
+            J.pairs = ip.own;
+            J.owner_start = g->iv_owner.as<uint64_t>();
+            J.n_owners = ictr;
+            J.tab = g->iv_tab.as<uint64_t>();
+            J.tab_mask = ip.tab_slots - 1;
+            J.out = g->counts.as<uint64_t>() + (minus ? ACC_IV_M : ACC_IV_P);
+            J.status = &g->st.sc->status;
+            J.queue = (uint32_t*)(ictr + 2);
+            J.list_at = n_keys + k;
+            J.stats = g->prof ? g->stats.as<uint64_t>() : nullptr;
+            J.force_direct = g->iv_direct;
+            J.force_stage = g->iv_force_stage;
+            n_keys += ip.n_keys;
+        }
+        P.list[0] = c.iv_list0.as<uint32_t>();
+        P.list[1] = c.iv_list.as<uint32_t>();
+        P.list[2] = c.iv_list2.as<uint32_t>();
+        P.garena = c.iv_garena.as<uint32_t>();
+        P.garena_words = kIvGarenaWords;
+        P.garena2 = c.iv_garena2.as<uint32_t>();
+        P.garena2_words = kIvGarena2Words;
+        // four workgroups per CU (40 KB of LDS each): a wave per owner, then a workgroup per owner
+        triad_iv_launch(P, (unsigned)std::min<uint64_t>((uint64_t)owner->n_cu * 4, (n_keys + 3) / 4),
+                        (unsigned)std::min<uint64_t>((uint64_t)owner->n_cu * 4, n_keys), iv_grid_global(owner),
+                        iv_grid_global2(), s);
+    }
     return HGT_OK;
 }
 
@@ -1435,9 +1447,9 @@ int reserve_all_phases(hgt_graph* owner, std::vector<Pending*>& ps, bool upload 
     if (upload && c.desc_cap != cap0) return reserve_all_phases(owner, ps, upload, s);
     if (t_na)
         if (int rc = ensure(c.desc, 4 * desc_slot_bytes(1))) return rc;
-    for (Pending* p : ps)
-        if ((p->g->track_mask & (1u << HGT_TRIAD_INCIDENT_VERTEX)) && p->ip.n_keys)
-            if (int rc = iv_reserve(p->g, p->ip)) return rc;
+    uint64_t n_keys = 0;
+    for (Pending* p : ps) n_keys += p->ip.n_keys;
+    if (n_keys) return iv_reserve(owner, n_keys, (uint32_t)ps.size());
     return HGT_OK;
 }
 
@@ -1466,9 +1478,10 @@ int apply_locked(hgt_graph* owner, std::vector<Pending*>& ps, hipStream_t s, boo
     // step 2: deltas on the old graph
     rc = run_phase(owner, jobs.data(), (uint32_t)jobs.size(), true, false, s);
     if (rc) return rc;
+    std::vector<std::pair<hgt_graph*, const IvPlan*>> iv;  // graphs with touched vertex pairs
     for (Pending* p : ps)
-        if ((p->g->track_mask & (1u << HGT_TRIAD_INCIDENT_VERTEX)) && (rc = iv_phase(p->g, p->ip, true, s)))
-            return rc;
+        if (p->ip.n_keys) iv.push_back({p->g, &p->ip});
+    if ((rc = iv_phase(owner, iv, true, s))) return rc;
     // step 3: delete, then insert
     std::vector<SmallCommit> small;
     hgt_graph* small_g = nullptr;
@@ -1498,9 +1511,7 @@ int apply_locked(hgt_graph* owner, std::vector<Pending*>& ps, hipStream_t s, boo
     for (Pending* p : ps) jobs.push_back(job_plus(*p));
     rc = run_phase(owner, jobs.data(), (uint32_t)jobs.size(), false, full, s);
     if (rc) return rc;
-    for (Pending* p : ps)
-        if ((p->g->track_mask & (1u << HGT_TRIAD_INCIDENT_VERTEX)) && (rc = iv_phase(p->g, p->ip, false, s)))
-            return rc;
+    if ((rc = iv_phase(owner, iv, false, s))) return rc;
     // step 6
     for (Pending* p : ps) {
         hgt_graph* g = p->g;

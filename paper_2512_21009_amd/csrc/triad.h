@@ -181,32 +181,37 @@ void tmp_launch_lds(He2Params& P, unsigned grid, unsigned grid_mid, hipStream_t 
 void tmp_launch_global(He2Params& P, unsigned grid, hipStream_t s);
 
 // incident-vertex family
-struct IvParams {
+// One graph's touched pairs.
+struct IvJob {
     GraphView g;
     const uint64_t* pairs;       // unique touched vertex pairs owner << 32 | other, ascending (the
                                  // owner is the endpoint of higher degree)
-    const uint64_t* n_pairs;     // device count
     const uint64_t* owner_start; // first pair of every distinct u, plus the end
     const uint64_t* n_owners;
     const uint64_t* tab;         // open-addressing hash of the touched pairs (empty = ~0)
     uint64_t tab_mask;
     uint64_t* out;               // u64[2]: sum_p m_p * w_p, sum over triangles with a touched pair of m m m
     const int32_t* status;
-    uint32_t* queue;             // per stage (4)
-    uint32_t* count;             // owners moved on by stages 0, 1 and 2
-    uint32_t* list[3];           // ... and which (capacity: all owners)
+    uint32_t* queue;             // per stage (4), then the counts of owners moved on by stages 0, 1 and 2
+    uint64_t list_at;            // this graph's part of the lists below
+    uint64_t* stats;             // optional, ST_IV_BYTES
+    int force_direct;            // test knob: every owner evaluated pair by pair without a map
+    int force_stage;             // test knob: stages below it move every owner on (counted from stage 1)
+};
+constexpr uint32_t kIvJobs = 16;  // graphs per launch (kernel arguments hold 4 KB)
+struct IvParams {
+    IvJob job[kIvJobs];
+    uint32_t n_jobs;
+    uint32_t* list[3];           // owners moved on (capacity: all owners of the launch)
     uint32_t* garena;            // stage 2: garena_words per workgroup
     uint64_t garena_words;
     uint32_t* garena2;           // stage 3: garena2_words per workgroup (the largest owners)
     uint64_t garena2_words;
-    uint64_t* stats;             // optional, ST_IV_BYTES
-    int force_direct;            // test knob: every owner evaluated pair by pair without a map
-    int force_stage;             // test knob: stages below it move every owner on (counted from stage 1)
 };
 // hash of the touched pairs (canon: lo << 32 | hi) and the owner segments of own
 // (owner << 32 | other, sorted)
 void iv_touched_build(const uint64_t* canon, const uint64_t* own, const uint64_t* n_pairs, uint64_t* tab,
                       uint64_t tab_slots, uint64_t* head, uint64_t* owner_start, uint64_t* n_owners, uint64_t pairs_cap,
                       void* scan_tmp, hipStream_t s);
-void triad_iv_launch(IvParams& P, unsigned grid_wave, unsigned grid_lds, unsigned grid_global, unsigned grid_global2,
+void triad_iv_launch(const IvParams& P, unsigned grid_wave, unsigned grid_lds, unsigned grid_global, unsigned grid_global2,
                      hipStream_t s);

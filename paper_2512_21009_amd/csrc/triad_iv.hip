@@ -115,7 +115,7 @@ __device__ __forceinline__ uint32_t inter_count_min(const GraphView& g, const ui
 }
 
 // one wave: returns (lane 0) m_ab * w_ab in *s_out and the attributed triangle sum in *t_out
-__device__ void iv_pair_direct(const IvParams& P, uint32_t a, uint32_t b, uint32_t* pre, uint64_t* s_out,
+__device__ void iv_pair_direct(const IvJob& P, uint32_t a, uint32_t b, uint32_t* pre, uint64_t* s_out,
                                uint64_t* t_out) {
     const int lane = threadIdx.x & 63;
     uint32_t la = P.g.v_len[a], lb = P.g.v_len[b];
@@ -249,7 +249,7 @@ struct IvSh {
 // One owner by NW waves (1: each wave alone, 4: the workgroup together).  Returns false,
 // with nothing counted, when the map does not fit the arena.
 template <int NW, bool GLOBAL>
-__device__ bool iv_owner(const IvParams& P, uint32_t oi, uint32_t* arena, uint32_t arena_words, bool pass_on, uint32_t* sieve,
+__device__ bool iv_owner(const IvJob& P, uint32_t oi, uint32_t* arena, uint32_t arena_words, bool pass_on, uint32_t* sieve,
                          IvTile& tile, IvWave& W, uint32_t* ws, uint64_t& s_sum, uint64_t& t_sum, uint64_t& bytes) {
     const uint32_t lane = threadIdx.x & 63, wave = NW == 1 ? 0 : threadIdx.x >> 6;
     const uint32_t tid = NW == 1 ? lane : threadIdx.x;
@@ -416,7 +416,7 @@ __device__ bool iv_owner(const IvParams& P, uint32_t oi, uint32_t* arena, uint32
     return true;
 }
 
-__device__ __forceinline__ void iv_add(const IvParams& P, uint64_t s_sum, uint64_t t_sum, uint64_t bytes) {
+__device__ __forceinline__ void iv_add(const IvJob& P, uint64_t s_sum, uint64_t t_sum, uint64_t bytes) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         s_sum += __shfl_xor(s_sum, o, 64);
@@ -429,109 +429,138 @@ __device__ __forceinline__ void iv_add(const IvParams& P, uint64_t s_sum, uint64
     }
 }
 
+// The graphs of a launch in turn, each workgroup from a graph of its own: one graph's
+// owners end with a few long ones, which leave most of the chip idle (a served round of 16
+// graphs: 21.9 ms with one launch per graph and stage, 15.4 ms with one per stage).
+__device__ __forceinline__ uint32_t iv_turn(uint32_t k, uint32_t n) {
+    return (k + (uint32_t)((uint64_t)blockIdx.x * n / gridDim.x)) % n;
+}
+__device__ __forceinline__ uint32_t iv_taken(const uint32_t* queue) {  // a look before the atomic
+    return __hip_atomic_load(queue, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Stage 0: every wave takes owners of its own; maps of up to IV_WAVE_WORDS / 2 slots.
 // Three quarters of the owners of a power-law graph fit, and 20 of them share a CU
 // where workgroup-sized ones leave it to four.
-__global__ void __launch_bounds__(HGT_WG) k_iv_wave(IvParams P) {
+__global__ void __launch_bounds__(HGT_WG) k_iv_wave(IvParams A) {
     __shared__ __attribute__((aligned(16))) uint32_t arena[NWAVE][IV_WAVE_WORDS];
     __shared__ uint32_t sieve[NWAVE][IV_SIEVE];
     __shared__ IvTile tile[NWAVE];
     __shared__ IvWave W[NWAVE];
-    if (*((volatile const int32_t*)P.status)) return;  // no barrier below
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint64_t s_sum = 0, t_sum = 0, bytes = 0;
     __shared__ uint32_t moved[NWAVE][32];  // owners this wave moves on, appended 32 at a time
-    const uint64_t n = *P.n_owners;
-    const uint32_t take = take_size(n, gridDim.x * NWAVE, 2);
-    uint32_t q = 0, n_moved = 0;
-    auto append = [&]() {
-        uint32_t at = 0;
-        if (lane == 0) at = atomicAdd(&P.count[0], n_moved);
-        at = __shfl(at, 0, 64);
-        wave_sync();
-        if (lane < n_moved) P.list[0][at + lane] = moved[wave][lane];
-        wave_sync();
-        n_moved = 0;
-    };
-    if (lane == 0) q = atomicAdd(&P.queue[0], take);
-    for (;;) {
-        const uint32_t first = __shfl(q, 0, 64);
-        if (first >= n) break;
-        if (lane == 0) q = atomicAdd(&P.queue[0], take);  // the next ones, while these run
-        const uint32_t last = n - first < take ? (uint32_t)n : first + take;
-        for (uint32_t oi = first; oi < last; oi++) {
-            if (!iv_owner<1, false>(P, oi, arena[wave], IV_WAVE_WORDS, P.force_direct || 0 < P.force_stage, sieve[wave],
-                                    tile[wave], W[wave], nullptr, s_sum, t_sum, bytes)) {
-                if (lane == 0) moved[wave][n_moved] = oi;
-                if (++n_moved == 32) append();
-            }
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (uint32_t k = 0; k < A.n_jobs; k++) {
+        const IvJob& P = A.job[iv_turn(k, A.n_jobs)];
+        if (*((volatile const int32_t*)P.status)) continue;  // no barrier below
+        const uint64_t n = *P.n_owners;
+        if (k && iv_taken(&P.queue[0]) >= n) continue;
+        uint64_t s_sum = 0, t_sum = 0, bytes = 0;
+        const uint32_t take = take_size(n, gridDim.x * NWAVE, 2);
+        uint32_t q = 0, n_moved = 0;
+        auto append = [&]() {
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(&P.queue[4], n_moved);
+            at = __shfl(at, 0, 64);
             wave_sync();
+            if (lane < n_moved) A.list[0][P.list_at + at + lane] = moved[wave][lane];
+            wave_sync();
+            n_moved = 0;
+        };
+        if (lane == 0) q = atomicAdd(&P.queue[0], take);
+        for (;;) {
+            const uint32_t first = __shfl(q, 0, 64);
+            if (first >= n) break;
+            if (lane == 0) q = atomicAdd(&P.queue[0], take);  // the next ones, while these run
+            const uint32_t last = n - first < take ? (uint32_t)n : first + take;
+            for (uint32_t oi = first; oi < last; oi++) {
+                if (!iv_owner<1, false>(P, oi, arena[wave], IV_WAVE_WORDS, P.force_direct || 0 < P.force_stage,
+                                        sieve[wave], tile[wave], W[wave], nullptr, s_sum, t_sum, bytes)) {
+                    if (lane == 0) moved[wave][n_moved] = oi;
+                    if (++n_moved == 32) append();
+                }
+                wave_sync();
+            }
         }
+        if (n_moved) append();
+        iv_add(P, s_sum, t_sum, bytes);
     }
-    if (n_moved) append();
-    iv_add(P, s_sum, t_sum, bytes);
 }
 
 // Stages 1 (23 KB of LDS), 2 and 3 (global arenas): a workgroup per owner.
 template <int STAGE>
-__device__ void iv_body(const IvParams& P, uint32_t* arena, uint32_t arena_words) {
+__device__ void iv_body(const IvParams& A, uint32_t* arena, uint32_t arena_words) {
     __shared__ IvSh sh;
     __shared__ uint32_t sieve[IV_SIEVE];
     __shared__ IvTile tile;
     __shared__ IvWave W[NWAVE];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (tid == 0) sh.stop = *((volatile const int32_t*)P.status) != 0 ? 1u : 0u;
-    __syncthreads();
-    if (sh.stop) return;  // read once per workgroup: every thread leaves before the barriers below
-    uint64_t s_sum = 0, t_sum = 0, bytes = 0;
-    const uint32_t n = P.count[STAGE - 1], take = take_size(n, gridDim.x);
-    uint32_t q = 0, q_end = 0;
-    for (;;) {
-        if (tid == 0) {
-            if (q == q_end) {
-                q = atomicAdd(&P.queue[STAGE], take);
-                q_end = q + take;
-            }
-            sh.stop = q >= n;
-            if (!sh.stop) sh.oi = P.list[STAGE - 1][q++];
+    for (uint32_t k = 0; k < A.n_jobs; k++) {
+        const IvJob& P = A.job[iv_turn(k, A.n_jobs)];
+        uint32_t n = 0;
+        if (tid == 0) {  // read once per workgroup: every thread takes the same way past the barriers below
+            n = *((volatile const int32_t*)P.status) ? 0u : P.queue[3 + STAGE];
+            sh.stop = n == 0 || (k && iv_taken(&P.queue[STAGE]) >= n);
         }
         __syncthreads();
-        if (sh.stop) break;
-        const uint32_t oi = sh.oi;
-        // the tests' stage numbers: the first two stages are one to them
-        const bool pass_on = P.force_direct || STAGE - 1 < P.force_stage;
-        if (!iv_owner<NWAVE, STAGE != 1>(P, oi, arena, arena_words, pass_on, sieve, tile, W[wave], sh.ws,
+        const uint32_t none = sh.stop;
+        __syncthreads();
+        if (none) continue;
+        uint64_t s_sum = 0, t_sum = 0, bytes = 0;
+        const uint32_t take = take_size(n, gridDim.x);
+        uint32_t q = 0, q_end = 0;
+        for (;;) {
+            if (tid == 0) {
+                if (q == q_end) {
+                    q = atomicAdd(&P.queue[STAGE], take);
+                    q_end = q + take;
+                }
+                sh.stop = q >= n;
+                if (!sh.stop) sh.oi = A.list[STAGE - 1][P.list_at + q++];
+            }
+            __syncthreads();
+            if (sh.stop) break;
+            const uint32_t oi = sh.oi;
+            // the tests' stage numbers: the first two stages are one to them
+            const bool pass_on = P.force_direct || STAGE - 1 < P.force_stage;
+            if (!iv_owner<NWAVE, STAGE != 1>(P, oi, arena, arena_words, pass_on, sieve, tile, W[wave], sh.ws,
                                              s_sum, t_sum, bytes)) {
-            if (STAGE < 3) {
-                if (tid == 0) P.list[STAGE][atomicAdd(&P.count[STAGE], 1u)] = oi;
-            } else {  // too large for any map: pair by pair without one
-                const uint64_t p0 = P.owner_start[oi], p1 = P.owner_start[oi + 1];
-                const uint32_t a = (uint32_t)(P.pairs[p0] >> 32);
-                for (uint64_t q = p0 + wave; q < p1; q += NWAVE) {
-                    uint64_t so, to;
-                    iv_pair_direct(P, a, (uint32_t)P.pairs[q], W[wave].f.bits, &so, &to);
-                    if (lane == 0) {
-                        s_sum += so;
-                        t_sum += to;
+                if (STAGE < 3) {
+                    if (tid == 0) A.list[STAGE][P.list_at + atomicAdd(&P.queue[4 + STAGE], 1u)] = oi;
+                } else {  // too large for any map: pair by pair without one
+                    const uint64_t p0 = P.owner_start[oi], p1 = P.owner_start[oi + 1];
+                    const uint32_t a = (uint32_t)(P.pairs[p0] >> 32);
+                    for (uint64_t q = p0 + wave; q < p1; q += NWAVE) {
+                        uint64_t so, to;
+                        iv_pair_direct(P, a, (uint32_t)P.pairs[q], W[wave].f.bits, &so, &to);
+                        if (lane == 0) {
+                            s_sum += so;
+                            t_sum += to;
+                        }
                     }
                 }
             }
+            __syncthreads();
         }
-        __syncthreads();
+        __syncthreads();  // sh.stop has been read by all
+        iv_add(P, s_sum, t_sum, bytes);
     }
-    iv_add(P, s_sum, t_sum, bytes);
 }
 
-__global__ void __launch_bounds__(HGT_WG) k_iv_lds(IvParams P) {
+__global__ void __launch_bounds__(HGT_WG) k_iv_lds(IvParams A) {
     __shared__ __attribute__((aligned(16))) uint32_t arena[IV_ARENA];
-    iv_body<1>(P, arena, IV_ARENA);
+    iv_body<1>(A, arena, IV_ARENA);
 }
 
 template <int STAGE>
-__global__ void __launch_bounds__(HGT_WG) k_iv_global(IvParams P) {
-    uint32_t* arena = STAGE == 2 ? P.garena + (uint64_t)blockIdx.x * P.garena_words
-                                 : P.garena2 + (uint64_t)blockIdx.x * P.garena2_words;
-    iv_body<STAGE>(P, arena, (uint32_t)(STAGE == 2 ? P.garena_words : P.garena2_words));
+__global__ void __launch_bounds__(HGT_WG) k_iv_global(IvParams A) {
+    uint32_t* arena = STAGE == 2 ? A.garena + (uint64_t)blockIdx.x * A.garena_words
+                                 : A.garena2 + (uint64_t)blockIdx.x * A.garena2_words;
+    iv_body<STAGE>(A, arena, (uint32_t)(STAGE == 2 ? A.garena_words : A.garena2_words));
+}
+
+__global__ void k_iv_begin(IvParams A) {
+    const uint32_t j = threadIdx.x >> 3, w = threadIdx.x & 7;
+    if (j < A.n_jobs && w < 7) A.job[j].queue[w] = 0;
 }
 
 }  // namespace
@@ -546,9 +575,10 @@ void iv_touched_build(const uint64_t* canon, const uint64_t* own, const uint64_t
     k_iv_owner_list<<<2048, 256, 0, s>>>(own, n_pairs, head, owner_start, n_owners);
 }
 
-void triad_iv_launch(IvParams& P, unsigned grid_wave, unsigned grid_lds, unsigned grid_global, unsigned grid_global2,
-                     hipStream_t s) {
-    hgt_fill_u32(P.queue, 0, 7, s);  // the four stages' queues, the owners moved on by the first three
+void triad_iv_launch(const IvParams& P, unsigned grid_wave, unsigned grid_lds, unsigned grid_global,
+                     unsigned grid_global2, hipStream_t s) {
+    static_assert(sizeof(IvParams) <= 4096, "kernel arguments");
+    k_iv_begin<<<1, 8 * kIvJobs, 0, s>>>(P);
     k_iv_wave<<<grid_wave, HGT_WG, 0, s>>>(P);
     k_iv_lds<<<grid_lds, HGT_WG, 0, s>>>(P);
     k_iv_global<2><<<grid_global, HGT_WG, 0, s>>>(P);

@@ -547,10 +547,10 @@ def test_batches_of_one_workgroup(gpu_lib, shape):
 @pytest.mark.parametrize("graph", [False, True])
 def test_rounds_of_mixed_batch_sizes(gpu_lib, graph):
     """A round of graphs with all families kept: batches of one workgroup (more than one
-    launch of them), one beyond its rows and one whose deletions are beyond its pairs."""
+    launch of them, as of the incident-vertex pairs), one beyond its rows and one whose deletions are beyond its pairs."""
     from .gpu_harness import apply_many
     sts = [W.temporal_stream("mix", 300, 260, 4 + 3 * i, 2, 2.0, 1, 5, 7.0, 700, 150, W.SEED_BASE + 120 + i)
-           for i in range(13)]
+           for i in range(17)]
     sts.append(W.temporal_stream("mix", 20000, 2600, 2100, 2, 2.0, 1, 4, 7.0, 7000, 150, W.SEED_BASE + 140))
     sts.append(W.temporal_stream("mix", 4000, 260, 20, 2, 1.0, 70, 80, 7.0, 700, 150, W.SEED_BASE + 141))
     pairs = [Pair(s, track=ALL) for s in sts]
@@ -558,6 +558,6 @@ def test_rounds_of_mixed_batch_sizes(gpu_lib, graph):
         apply_many(pairs, [s.batches[k] for s in sts], f"mixed round {k}", **({"graph": True} if graph else {}))
         for i, p in enumerate(pairs):
             compare_store(p.g, p.o, f"mixed round {k} graph {i}")
-            compare_counts(p.g, p.o, ("hyperedge",) if i == 14 else ALL, f"mixed round {k} graph {i}")
+            compare_counts(p.g, p.o, ("hyperedge",) if i == 18 else ALL, f"mixed round {k} graph {i}")
     for p in pairs:
         p.close()
