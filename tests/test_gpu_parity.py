@@ -561,3 +561,20 @@ def test_rounds_of_mixed_batch_sizes(gpu_lib, graph):
             compare_counts(p.g, p.o, ("hyperedge",) if i == 18 else ALL, f"mixed round {k} graph {i}")
     for p in pairs:
         p.close()
+
+
+@pytest.mark.parametrize("n", [4096, 4097, 32768, 32769, 1_050_000])
+def test_sorts_at_tile_edges(gpu_lib, n):
+    """Builds and deletions whose (vertex, hyperedge) pairs fill the sort's tiles of 2,048
+    exactly and with two more, its two- and three-launch passes (32 tiles), and more than
+    one tile per workgroup (1,024 workgroups); the scans see the same sizes."""
+    st = W.plain_stream("sort", 3 * n, n, ("uniform", 2, 2), 0.0, 0.0, 1, 5, n // 2, W.SEED_BASE + 150)
+    p = Pair(st, track=("hyperedge", "incident_vertex"))
+    compare_counts(p.g, p.o, p.track, f"sort build {n}")
+    p.apply(st.batches[0], f"sort batch {n}")
+    voff, vmem = p.g.export_v2h()
+    from .gpu_harness import oracle_v2h
+    ooff, omem = oracle_v2h(p.o)
+    assert (voff.astype(np.int64) == ooff).all() and (vmem == omem).all()
+    compare_counts(p.g, p.o, p.track, f"sort batch {n}")
+    p.close()
