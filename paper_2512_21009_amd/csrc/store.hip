@@ -38,9 +38,8 @@ __global__ void k_batch_begin(DevScalars* sc, BatchSummary* sum) {
 // One thread per deleted ID: liveness, duplicates, deletion marks and sizes.
 __global__ void k_del_check(const uint32_t* __restrict__ del, uint64_t n_del, DevScalars* sc,
                             const uint64_t* __restrict__ free_bm, uint64_t* del_bm, uint64_t* mark_del,
-                            uint32_t epoch, const uint32_t* __restrict__ h_len, const uint64_t* __restrict__ h_off,
-                            const uint32_t* __restrict__ h2v, const uint32_t* __restrict__ v_len,
-                            uint64_t* del_card, BatchSummary* sum) {
+                            uint32_t epoch, const uint32_t* __restrict__ h_len, uint64_t* del_card,
+                            BatchSummary* sum) {
     uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n_del) return;
     uint32_t id = del[i];
@@ -61,11 +60,6 @@ __global__ void k_del_check(const uint32_t* __restrict__ del, uint64_t n_del, De
     del_card[i] = d;
     atomicAdd((unsigned long long*)&sum->del_members, (unsigned long long)d);
     atomicAdd((unsigned long long*)&sum->del_pairs2, (unsigned long long)choose2(d));
-    uint64_t lh = 0;
-    const uint32_t* m = h2v + h_off[id];
-    for (uint64_t k = 0; k < d; k++) lh += v_len[m[k]];
-    atomicMax((unsigned long long*)&sum->max_lh_del, (unsigned long long)lh);
-    atomicAdd((unsigned long long*)&sum->sum_lh_del, (unsigned long long)lh);
 }
 
 // One thread per insert: CSR sanity, cardinality bounds, temporal order.
@@ -238,7 +232,8 @@ __global__ void k_h2v_need(const uint32_t* __restrict__ assigned, const uint64_t
 // ---------------------------------------------------------------------------
 // (vertex, hyperedge, is_insert) pairs, sorted, and the per-vertex plan
 // ---------------------------------------------------------------------------
-__global__ void k_pairs_del(const uint32_t* __restrict__ del, uint64_t n_del, const uint64_t* __restrict__ del_poff,
+// and clears del_poff, which then takes the rows' sums of list lengths (k_split)
+__global__ void k_pairs_del(const uint32_t* __restrict__ del, uint64_t n_del, uint64_t* del_poff,
                             const uint64_t* __restrict__ h_off, const uint32_t* __restrict__ h_len,
                             const uint32_t* __restrict__ h2v, int hb, uint64_t* keys, const DevScalars* sc) {
     if (status_bad(&sc->status)) return;
@@ -248,6 +243,7 @@ __global__ void k_pairs_del(const uint32_t* __restrict__ del, uint64_t n_del, co
     uint32_t id = del[i];
     uint64_t d = h_len[id], o = h_off[id], p = del_poff[i];
     for (uint64_t k = lane; k < d; k += 64) keys[p + k] = ((uint64_t)h2v[o + k] << (hb + 1)) | ((uint64_t)id << 1);
+    if (lane == 0) del_poff[i] = 0;  // the wave has read it
 }
 
 __global__ void k_pairs_ins(const uint32_t* __restrict__ canon, const uint64_t* __restrict__ ins_rel, uint64_t n_ins,
@@ -267,83 +263,110 @@ __global__ void k_pair_count(const BatchSummary* sum, uint64_t n_ins_members, ui
 __global__ void k_heads(const uint64_t* __restrict__ keys, const uint64_t* n_pairs_p, int hb, uint64_t* head,
                         uint64_t* is_ins) {
     uint64_t n = *n_pairs_p;
-    uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    uint64_t k = keys[i];
-    head[i] = (i == 0 || (keys[i - 1] >> (hb + 1)) != (k >> (hb + 1))) ? 1 : 0;
-    is_ins[i] = k & 1ull;
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
+        uint64_t k = keys[i];
+        head[i] = (i == 0 || (keys[i - 1] >> (hb + 1)) != (k >> (hb + 1))) ? 1 : 0;
+        is_ins[i] = k & 1ull;
+    }
 }
 
 // head[] was scanned in place into tidx[] (exclusive), is_ins into ins_pre[].
 // After a failed validation the pair keys were not (all) written: the plan
 // kernels that index arrays with decoded keys then stop.
+// The deleted hyperedges' list lengths go to lh_del by their rank in the batch (a walk of
+// each row by one thread in k_del_check: 44 us a graph there, 11 without).
 __global__ void k_split(const uint64_t* __restrict__ keys, const uint64_t* n_pairs_p, int hb,
                         const uint64_t* __restrict__ tidx, const uint64_t* __restrict__ ins_pre, uint32_t* tv,
                         uint64_t* tseg, uint32_t* D_all, uint32_t* I_all, uint32_t* I_t, const uint64_t* n_touched_p,
+                        const uint32_t* __restrict__ v_len, const uint64_t* __restrict__ mark_del, uint64_t* lh_del,
                         const DevScalars* sc) {
     if (status_bad(&sc->status)) return;
     uint64_t n = *n_pairs_p;
-    uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i == 0) tseg[*n_touched_p] = n;
-    if (i >= n) return;
-    uint64_t k = keys[i];
-    uint32_t v = (uint32_t)(k >> (hb + 1));
-    uint32_t h = (uint32_t)((k >> 1) & ((1ull << hb) - 1));
-    bool hd = (i == 0) || ((keys[i - 1] >> (hb + 1)) != (k >> (hb + 1)));
-    uint64_t t = tidx[i] + (hd ? 1 : 0) - 1;
-    if (hd) {
-        tv[t] = v;
-        tseg[t] = i;
-    }
-    uint64_t ip = ins_pre[i];
-    if (k & 1ull) {
-        I_all[ip] = h;
-        I_t[ip] = (uint32_t)t;
-    } else {
-        D_all[i - ip] = h;
+    if (blockIdx.x == 0 && threadIdx.x == 0) tseg[*n_touched_p] = n;
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
+        uint64_t k = keys[i];
+        uint32_t v = (uint32_t)(k >> (hb + 1));
+        uint32_t h = (uint32_t)((k >> 1) & ((1ull << hb) - 1));
+        bool hd = (i == 0) || ((keys[i - 1] >> (hb + 1)) != (k >> (hb + 1)));
+        uint64_t t = tidx[i] + (hd ? 1 : 0) - 1;
+        if (hd) {
+            tv[t] = v;
+            tseg[t] = i;
+        }
+        uint64_t ip = ins_pre[i];
+        if (k & 1ull) {
+            I_all[ip] = h;
+            I_t[ip] = (uint32_t)t;
+        } else {
+            D_all[i - ip] = h;
+            atomicAdd((unsigned long long*)&lh_del[(uint32_t)mark_del[h]], (unsigned long long)v_len[v]);
+        }
     }
 }
 
 __global__ void k_vplan(const uint64_t* n_touched_p, const uint32_t* __restrict__ tv, const uint64_t* __restrict__ tseg,
                         const uint64_t* __restrict__ ins_pre, const uint64_t* n_pairs_p, const uint64_t* ins_total,
                         const uint32_t* __restrict__ v_len, const uint32_t* __restrict__ v_cap, VPlan p,
-                        DevScalars* sc) {
+                        uint64_t* lh_ins, uint64_t n_ins, DevScalars* sc) {
     if (status_bad(&sc->status)) return;
-    uint64_t nt = *n_touched_p;
-    uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= nt) return;
-    uint64_t s = tseg[t], e = tseg[t + 1], n = *n_pairs_p;
-    uint64_t ips = ins_pre[s];
-    uint64_t ipe = e < n ? ins_pre[e] : *ins_total;
-    uint64_t nI = ipe - ips, nD = (e - s) - nI;
-    uint32_t v = tv[t];
-    uint64_t old = v_len[v];
-    if (nD > old) { set_status(&sc->status, HGT_EDEVICE); nD = old; }
-    uint64_t nw = old - nD + nI;
-    p.dstart[t] = s - ips;
-    p.istart[t] = ips;
-    p.nD[t] = (uint32_t)nD;
-    p.nI[t] = (uint32_t)nI;
-    p.old_len[t] = old;
-    p.new_len[t] = (uint32_t)nw;
-    p.need[t] = nw > v_cap[v] ? pow2ceil64(nw < 4 ? 4 : nw) : 0;
+    const uint64_t nt = *n_touched_p, n = *n_pairs_p, step = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n_ins; j += step) lh_ins[j] = 0;
+    for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < nt; t += step) {
+        uint64_t s = tseg[t], e = tseg[t + 1];
+        uint64_t ips = ins_pre[s];
+        uint64_t ipe = e < n ? ins_pre[e] : *ins_total;
+        uint64_t nI = ipe - ips, nD = (e - s) - nI;
+        uint32_t v = tv[t];
+        uint64_t old = v_len[v];
+        if (nD > old) { set_status(&sc->status, HGT_EDEVICE); nD = old; }
+        uint64_t nw = old - nD + nI;
+        p.dstart[t] = s - ips;
+        p.istart[t] = ips;
+        p.nD[t] = (uint32_t)nD;
+        p.nI[t] = (uint32_t)nI;
+        p.old_len[t] = old;
+        p.new_len[t] = (uint32_t)nw;
+        p.need[t] = nw > v_cap[v] ? pow2ceil64(nw < 4 ? 4 : nw) : 0;
+    }
 }
 
-// per insert: sum over its members of their new incidence-list length
-__global__ void k_lh_ins(const uint32_t* __restrict__ canon, const uint64_t* __restrict__ ins_rel, uint64_t n_ins,
-                         const uint32_t* __restrict__ tv, const uint64_t* n_touched_p,
-                         const uint32_t* __restrict__ new_len, BatchSummary* sum, const DevScalars* sc) {
+// Per insert: the sum over its members of their new incidence-list length, taken along the
+// inserted pairs, which know their touched vertex (a search of the touched vertices per
+// member, a row per thread, was the longest kernel of the planning: 246 us a graph in a round
+// of 14 graphs with batches of up to 10,000 rows, under 5 us now).
+__global__ void k_lh_ins(const uint64_t* n_ins_pairs_p, const uint32_t* __restrict__ I_all,
+                         const uint32_t* __restrict__ I_t, const uint32_t* __restrict__ new_len,
+                         const uint64_t* __restrict__ mark_ins, uint64_t* lh_ins, const DevScalars* sc) {
     if (status_bad(&sc->status)) return;
-    uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n_ins) return;
-    uint32_t nt = (uint32_t)*n_touched_p;
-    uint64_t lh = 0;
-    for (uint64_t m = ins_rel[j]; m < ins_rel[j + 1]; m++) {
-        uint32_t t = lower_bound_u32(tv, nt, canon[m]);
-        if (t < nt) lh += new_len[t];
+    const uint64_t n = *n_ins_pairs_p;
+    for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (uint64_t)gridDim.x * blockDim.x)
+        atomicAdd((unsigned long long*)&lh_ins[(uint32_t)mark_ins[I_all[k]]], (unsigned long long)new_len[I_t[k]]);
+}
+
+// Their largest and their sum, of both sides.
+__global__ void __launch_bounds__(HGT_WG) k_lh_total(const uint64_t* __restrict__ lh_del, uint64_t n_del,
+                                                     const uint64_t* __restrict__ lh_ins, uint64_t n_ins,
+                                                     BatchSummary* sum, const DevScalars* sc) {
+    if (status_bad(&sc->status)) return;
+    for (int side = 0; side < 2; side++) {
+        const uint64_t* lh = side ? lh_ins : lh_del;
+        const uint64_t n = side ? n_ins : n_del;
+        uint64_t mx = 0, s = 0;
+        for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
+            mx = lh[i] > mx ? lh[i] : mx;
+            s += lh[i];
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const uint64_t m = __shfl_xor(mx, o, 64);
+            mx = m > mx ? m : mx;
+            s += __shfl_xor(s, o, 64);
+        }
+        if ((threadIdx.x & 63) == 0 && s) {
+            atomicMax((unsigned long long*)(side ? &sum->max_lh_ins : &sum->max_lh_del), (unsigned long long)mx);
+            atomicAdd((unsigned long long*)(side ? &sum->sum_lh_ins : &sum->sum_lh_del), (unsigned long long)s);
+        }
     }
-    atomicMax((unsigned long long*)&sum->max_lh_ins, (unsigned long long)lh);
-    atomicAdd((unsigned long long*)&sum->sum_lh_ins, (unsigned long long)lh);
 }
 
 __global__ void k_summary_finish(const DevScalars* sc, BatchSummary* sum, const uint64_t* n_free,
@@ -593,7 +616,7 @@ void store_plan(StoreDev& g, BatchIn& b, PlanScratch& w, hipStream_t s) {
     hgt_fill_u64(w.del_bm, 0, (g.id_cap + 63) / 64, s);
     if (n_del)
         k_del_check<<<blocks_for(n_del), 256, 0, s>>>(b.del, n_del, sc, g.free_bm, w.del_bm, g.mark_del, b.epoch_del,
-                                                      g.h_len, g.h_off, g.h2v, g.v_len, w.del_card, w.sum);
+                                                      g.h_len, w.del_card, w.sum);
     if (n_ins) {
         k_ins_check<<<blocks_for(n_ins), 256, 0, s>>>(b.ins_off, n_ins, n_mem, b.ins_ts, b.check_order, sc, w.ins_rel,
                                                       w.ins_card, w.sum);
@@ -636,17 +659,22 @@ void store_plan(StoreDev& g, BatchIn& b, PlanScratch& w, hipStream_t s) {
     k_pair_count<<<1, 64, 0, s>>>(w.sum, n_mem, w.n_pairs);
     uint64_t pmax = w.pairs_cap;
     hgt_radix_sort_u64(w.keys, w.keys_alt, pmax, w.n_pairs, g.hb + 1 + g.vb, w.sort_tmp, s);
-    k_heads<<<blocks_for(pmax), 256, 0, s>>>(w.keys, w.n_pairs, g.hb, w.head, w.is_ins);
+    const unsigned gp = std::min(blocks_for(pmax), 2048u);  // the pairs are known on the device only
+    k_heads<<<gp, 256, 0, s>>>(w.keys, w.n_pairs, g.hb, w.head, w.is_ins);
     hgt_scan_u64(w.head, w.head, pmax, w.n_pairs, w.n_touched, w.scan_tmp, s);
     hgt_scan_u64(w.is_ins, w.is_ins, pmax, w.n_pairs, w.n_ins_pairs, w.scan_tmp, s);
-    k_split<<<blocks_for(pmax), 256, 0, s>>>(w.keys, w.n_pairs, g.hb, w.head, w.is_ins, w.tv, w.tseg, w.D_all,
-                                             w.I_all, w.I_t, w.n_touched, sc);
-    k_vplan<<<blocks_for(pmax), 256, 0, s>>>(w.n_touched, w.tv, w.tseg, w.is_ins, w.n_pairs, w.n_ins_pairs, g.v_len,
-                                             g.v_cap, w.vp, sc);
+    uint64_t *lh_del = w.del_poff, *lh_ins = w.head;  // both free by then
+    k_split<<<gp, 256, 0, s>>>(w.keys, w.n_pairs, g.hb, w.head, w.is_ins, w.tv, w.tseg, w.D_all, w.I_all, w.I_t,
+                               w.n_touched, g.v_len, g.mark_del, lh_del, sc);
+    k_vplan<<<gp, 256, 0, s>>>(w.n_touched, w.tv, w.tseg, w.is_ins, w.n_pairs, w.n_ins_pairs, g.v_len, g.v_cap, w.vp,
+                               lh_ins, n_ins, sc);
     hgt_scan_u64(w.vp.need, w.vp.rel, pmax, w.n_touched, w.v2h_total, w.scan_tmp, s);
     hgt_scan_u64(w.vp.old_len, w.vp.stage_off, pmax, w.n_touched, w.stage_total, w.scan_tmp, s);
     if (n_ins)
-        k_lh_ins<<<blocks_for(n_ins), 256, 0, s>>>(w.canon, w.ins_rel, n_ins, w.tv, w.n_touched, w.vp.new_len, w.sum, sc);
+        k_lh_ins<<<std::min(blocks_for(n_mem), 2048u), 256, 0, s>>>(w.n_ins_pairs, w.I_all, w.I_t, w.vp.new_len,
+                                                                    g.mark_ins, lh_ins, sc);
+    k_lh_total<<<std::min(blocks_for(std::max(n_del, n_ins)), 64u), HGT_WG, 0, s>>>(lh_del, n_del, lh_ins, n_ins, w.sum,
+                                                                                  sc);
     k_summary_finish<<<1, 64, 0, s>>>(sc, w.sum, w.n_free, w.h2v_total, w.v2h_total, w.n_touched, w.stage_total);
 }
 
