@@ -304,7 +304,7 @@ struct hgt_graph {
     uint64_t slice_pairs = 0;       // HGT_SLICE_PAIRS: pairs per slice of a global-stage centre (0: default)
     int iv_force_stage = 0;         // HGT_IV_FORCE_STAGE (tests): incident-vertex stages below it pass owners on
     uint32_t wave_slots = 8192;     // HGT_WAVE_SLOTS (tests): slots of the 2-hop kernels' per-wave global hashes
-    BatchSummary* h_sum = nullptr;  // pinned
+    SmallHost* host = nullptr;  // pinned: the batch summary, and small batches' jobs
     DevScalars* h_sc = nullptr;     // pinned
     // profiling: HIP events around each kernel group, algorithmic-byte counters
     bool prof = false;              // HIP events around kernel groups + algorithmic-byte counters
@@ -1041,17 +1041,6 @@ __global__ void k_iv_orient(const uint64_t* __restrict__ canon, const uint64_t* 
     }
 }
 
-__global__ void k_iv_update(uint64_t* cnt, int iv, int m, int p, int t1) {
-    if (threadIdx.x || blockIdx.x) return;
-    uint64_t d1 = cnt[t1 + 1] - cnt[t1];           // change of type 1
-    uint64_t ds = cnt[p] - cnt[m];                 // change of sum m_p w_p
-    uint64_t dx = cnt[p + 1] - cnt[m + 1];         // change of the triangle sum
-    uint64_t d2 = ds - 3 * d1;
-    cnt[iv] += d1;
-    cnt[iv + 1] += d2;
-    cnt[iv + 2] += dx - d1 - d2;
-}
-
 inline unsigned nblk(uint64_t n, unsigned per = 256) {
     uint64_t b = (n + per - 1) / per;
     return (unsigned)(b ? b : 1);
@@ -1201,10 +1190,30 @@ int iv_phase(hgt_graph* owner, const std::vector<std::pair<hgt_graph*, const IvP
     return HGT_OK;
 }
 
-__global__ void k_he_tmp_update(uint64_t* cnt) {
+// The counts of a round's graphs brought up to date from their phases' sums.
+struct CountJob {
+    uint64_t* counts;
+    uint32_t iv;  // the incident-vertex counts too
+};
+constexpr uint32_t kCountJobs = 256;
+struct CountJobs {
+    CountJob j[kCountJobs];
+};
+static_assert(sizeof(CountJobs) <= 4096, "kernel arguments");
+__global__ void k_counts_update(CountJobs A) {  // a workgroup per graph
+    uint64_t* cnt = A.j[blockIdx.x].counts;
     int i = threadIdx.x;
     if (i < 30) cnt[CNT_HE + i] += cnt[ACC_HE_P + i] - cnt[ACC_HE_M + i];
     if (i < 96) cnt[CNT_TMP + i] += cnt[ACC_TMP_P + i] - cnt[ACC_TMP_M + i];
+    if (i == 96 && A.j[blockIdx.x].iv) {
+        uint64_t d1 = cnt[ACC_T1 + 1] - cnt[ACC_T1];              // change of type 1
+        uint64_t ds = cnt[ACC_IV_P] - cnt[ACC_IV_M];              // change of sum m_p w_p
+        uint64_t dx = cnt[ACC_IV_P + 1] - cnt[ACC_IV_M + 1];      // change of the triangle sum
+        uint64_t d2 = ds - 3 * d1;
+        cnt[CNT_IV] += d1;
+        cnt[CNT_IV + 1] += d2;
+        cnt[CNT_IV + 2] += dx - d1 - d2;
+    }
 }
 
 // A batch in flight: the steps before and after the one host synchronisation.
@@ -1298,7 +1307,7 @@ int plan_large(Pending& p, hipStream_t s) {
         ProfScope ps(g, PK_PLAN, s);
         store_plan(g->st, p.b, p.w, s);
     }
-    HIP_OK(hipMemcpyAsync(g->h_sum, p.w.sum, sizeof(BatchSummary), hipMemcpyDeviceToHost, s));
+    HIP_OK(hipMemcpyAsync(&g->host->sum, p.w.sum, sizeof(BatchSummary), hipMemcpyDeviceToHost, s));
     return HGT_OK;
 }
 
@@ -1338,24 +1347,24 @@ int plan_begin(Pending& p, const uint32_t* del, uint64_t n_del, const uint64_t* 
 
 // Queues what plan_begin left and waits for the summaries of the batches with rc == 0.
 int plan_wait(const std::vector<Pending*>& ps, hipStream_t s) {
-    std::vector<SmallPlan> jobs;
-    for (Pending* p : ps)
-        if (p->small)
-            jobs.push_back(SmallPlan{p->g->st, p->b, p->w, p->g->counts.as<uint64_t>() + CNT_N, ACC_N - CNT_N, 0,
-                                     p->g->h_sum});
+    std::vector<SmallHost*> jobs;
+    hgt_graph* first = nullptr;
+    for (Pending* p : ps) {
+        if (!p->small) continue;
+        SmallHost* h = p->g->host;
+        h->plan = SmallPlan{p->g->st, p->b, p->w, p->g->counts.as<uint64_t>() + CNT_N, ACC_N - CNT_N, 0, &h->sum};
+        jobs.push_back(h);
+        if (!first) first = p->g;
+    }
     if (!jobs.empty()) {
-        hgt_graph* g = nullptr;
-        for (Pending* p : ps)
-            if (p->small && !g) g = p->g;
-        ProfScope sc(g, PK_PLAN, s);
-        for (size_t i = 0; i < jobs.size(); i += kSmallPlanJobs)
-            small_plan(&jobs[i], (uint32_t)std::min<size_t>(kSmallPlanJobs, jobs.size() - i), s);
+        ProfScope sc(first, PK_PLAN, s);
+        small_plan(jobs.data(), (uint32_t)jobs.size(), s);
         HIP_OK(hipGetLastError());
     }
     HIP_OK(hipStreamSynchronize(s));
     bool again = false;  // its deleted hyperedges hold more pairs than a workgroup plans
     for (Pending* p : ps)
-        if (p->small && p->g->h_sum->status == HGT_OK && p->g->h_sum->pad0) {
+        if (p->small && p->g->host->sum.status == HGT_OK && p->g->host->sum.pad0) {
             p->small = false;
             again = true;
             if (int rc = plan_large(*p, s)) return rc;
@@ -1368,7 +1377,7 @@ int plan_wait(const std::vector<Pending*>& ps, hipStream_t s) {
 // and the incident-vertex pair list.
 int plan_end(Pending& p, std::vector<SmallIv>& small, hipStream_t s) {
     hgt_graph* g = p.g;
-    p.sum = *g->h_sum;
+    p.sum = g->host->sum;
     if (p.sum.status != HGT_OK) return p.sum.status;
     const BatchSummary& sum = p.sum;
     int rc = ensure_pool(g->h2v, g->h_bump, sum.h2v_need, s);
@@ -1483,14 +1492,15 @@ int apply_locked(hgt_graph* owner, std::vector<Pending*>& ps, hipStream_t s, boo
         if (p->ip.n_keys) iv.push_back({p->g, &p->ip});
     if ((rc = iv_phase(owner, iv, true, s))) return rc;
     // step 3: delete, then insert
-    std::vector<SmallCommit> small;
+    std::vector<SmallHost*> small;
     hgt_graph* small_g = nullptr;
     for (Pending* p : ps) {
         hgt_graph* g = p->g;
         if (p->small && p->sum.stage_words <= kSmallStage) {
             if (!small_g) small_g = g;
-            small.push_back(SmallCommit{g->st, p->b, p->w, p->sum.n_touched, g->h_bump, g->v_bump, g->next_seq,
-                                        p->out_ids});
+            g->host->commit = SmallCommit{g->st, p->b, p->w, p->sum.n_touched, g->h_bump, g->v_bump, g->next_seq,
+                                          p->out_ids};
+            small.push_back(g->host);
             continue;
         }
         {
@@ -1502,8 +1512,7 @@ int apply_locked(hgt_graph* owner, std::vector<Pending*>& ps, hipStream_t s, boo
     }
     if (!small.empty()) {
         ProfScope sc(small_g, PK_COMMIT, s);
-        for (size_t i = 0; i < small.size(); i += kSmallCommitJobs)
-            small_commit(&small[i], (uint32_t)std::min<size_t>(kSmallCommitJobs, small.size() - i), s);
+        small_commit(small.data(), (uint32_t)small.size(), s);
     }
     if (!t_capture && fault_injected()) return HGT_EDEVICE;
     // step 5: deltas on the new graph
@@ -1513,12 +1522,14 @@ int apply_locked(hgt_graph* owner, std::vector<Pending*>& ps, hipStream_t s, boo
     if (rc) return rc;
     if ((rc = iv_phase(owner, iv, false, s))) return rc;
     // step 6
-    for (Pending* p : ps) {
-        hgt_graph* g = p->g;
-        uint64_t* cnt = g->counts.as<uint64_t>();
-        k_he_tmp_update<<<1, 128, 0, s>>>(cnt);
-        if (g->track_mask & (1u << HGT_TRIAD_INCIDENT_VERTEX))
-            k_iv_update<<<1, 64, 0, s>>>(cnt, CNT_IV, ACC_IV_M, ACC_IV_P, ACC_T1);
+    for (size_t from = 0; from < ps.size(); from += kCountJobs) {
+        CountJobs A{};
+        const size_t m = std::min<size_t>(kCountJobs, ps.size() - from);
+        for (size_t i = 0; i < m; i++) {
+            hgt_graph* g = ps[from + i]->g;
+            A.j[i] = CountJob{g->counts.as<uint64_t>(), (g->track_mask & (1u << HGT_TRIAD_INCIDENT_VERTEX)) != 0};
+        }
+        k_counts_update<<<(unsigned)m, 128, 0, s>>>(A);
     }
     HIP_OK(hipGetLastError());
     return HGT_OK;
@@ -1702,7 +1713,7 @@ void destroy_graph(hgt_graph* g) {
     if (g->ph) phase_ctx_release(g->ph);
     dev_free(g->stats);
     for (hipEvent_t e : g->ev_pool) (void)hipEventDestroy(e);
-    if (g->h_sum) (void)hipHostFree(g->h_sum);
+    if (g->host) (void)hipHostFree(g->host);
     if (g->h_sc) (void)hipHostFree(g->h_sc);
     delete g;
 }
@@ -1844,7 +1855,7 @@ int hgt_build(const hgt_build_desc* d, hgt_graph** out) {
         int ncu = 0;
         if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, g->device) == hipSuccess && ncu > 0)
             g->n_cu = ncu;
-        if (hipHostMalloc((void**)&g->h_sum, sizeof(BatchSummary), hipHostMallocDefault) != hipSuccess ||
+        if (hipHostMalloc((void**)&g->host, sizeof(SmallHost), hipHostMallocDefault) != hipSuccess ||
             hipHostMalloc((void**)&g->h_sc, sizeof(DevScalars), hipHostMallocDefault) != hipSuccess) {
             rc = HGT_ENOMEM;
             break;
@@ -1968,7 +1979,7 @@ int hgt_apply_vertex_ops(hgt_graph* g, const uint32_t* edge_ids, const uint32_t*
     w.new_off = g->vo_off.as<uint64_t>();
     vops_plan(in, w, s);
     static_assert(sizeof(VopSummary) <= sizeof(BatchSummary), "summary staging");
-    VopSummary* hs = (VopSummary*)g->h_sum;  // pinned; the batch below rewrites it after its own plan
+    VopSummary* hs = (VopSummary*)&g->host->sum;  // pinned; the batch below rewrites it after its own plan
     HIP_OK(hipMemcpyAsync(hs, w.sum, sizeof(VopSummary), hipMemcpyDeviceToHost, s));
     HIP_OK(hipStreamSynchronize(s));
     const VopSummary sum = *hs;

@@ -8,8 +8,7 @@
 // (150 KB: one workgroup per CU, and a round has fewer graphs than the chip has CUs).  The
 // steps, their results and their errors are those of store.hip and triad_iv.hip.
 // Against those, with the counting kernels the same: one change on 20k hyperedges 1.08 ->
-// 0.48 ms, 64 graphs of up to 4,000 hyperedges in one round 19.4 -> 4.0 ms, 48 graphs of up
-// to 100,000 (batches of up to 20,000 rows go kernel by kernel) 30.9 -> 20.7 ms.
+// 0.48 ms, 64 graphs of up to 4,000 hyperedges in one round 19.4 -> 2.9 ms.
 #include "small.h"
 #include "triad_common.h"
 
@@ -421,34 +420,48 @@ __device__ void plan_one(const SmallPlan& J, PlanSh& sh) {
     finish();
 }
 
-struct PlanJobs {
-    SmallPlan j[kSmallPlanJobs];
+template <class J>
+struct ByValue {
+    J j[kSmallByValue];
 };
-static_assert(sizeof(PlanJobs) <= 4096, "kernel arguments");
-__global__ void __launch_bounds__(T) k_small_plan(PlanJobs J) {
+struct ByPointer {
+    const SmallHost* h[kSmallJobs];
+};
+static_assert(sizeof(ByValue<SmallPlan>) <= 4096 && sizeof(ByValue<SmallCommit>) <= 4096, "kernel arguments");
+
+template <class J>
+__device__ __forceinline__ void fetch_job(J& to, const J& from) {  // both of 8-byte words
+    for (uint32_t i = threadIdx.x; i < sizeof(J) / 8; i += T) ((uint64_t*)&to)[i] = ((const uint64_t*)&from)[i];
+    __syncthreads();
+}
+
+__global__ void __launch_bounds__(T) k_small_plan(ByValue<SmallPlan> A) {
     __shared__ PlanSh sh;
-    plan_one(J.j[blockIdx.x], sh);
+    plan_one(A.j[blockIdx.x], sh);
+}
+__global__ void __launch_bounds__(T) k_small_plan_many(ByPointer A) {
+    __shared__ PlanSh sh;
+    __shared__ SmallPlan J;
+    fetch_job(J, A.h[blockIdx.x]->plan);
+    plan_one(J, sh);
 }
 
 // ---------------------------------------------------------------------------
 // the store update (as store_commit)
 // ---------------------------------------------------------------------------
-struct CommitJobs {
-    SmallCommit j[kSmallCommitJobs];
+struct CommitSh {
+    Flat flat[NWV];
+    uint64_t off_a[NWV][64], off_b[NWV][64];
 };
-static_assert(sizeof(CommitJobs) <= 4096, "kernel arguments");
-__global__ void __launch_bounds__(T) k_small_commit(CommitJobs J) {
-    __shared__ Flat flat[NWV];
-    __shared__ uint64_t off_a[NWV][64], off_b[NWV][64];
-    const SmallCommit& C = J.j[blockIdx.x];
+__device__ void commit_one(const SmallCommit& C, CommitSh& sh) {
     const StoreDev& g = C.g;
     const BatchIn& b = C.b;
     const PlanScratch& w = C.w;
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t n_del = (uint32_t)b.n_del, n_ins = (uint32_t)b.n_ins, n_mem = (uint32_t)b.n_ins_members;
     const uint32_t nt = (uint32_t)C.n_touched;
-    Flat& fl = flat[wave];
-    uint64_t *oa = off_a[wave], *ob = off_b[wave];
+    Flat& fl = sh.flat[wave];
+    uint64_t *oa = sh.off_a[wave], *ob = sh.off_b[wave];
     for (uint32_t i = tid; i < n_del; i += T) {
         const uint32_t id = b.del[i];
         atomicOr((unsigned long long*)&g.free_bm[id >> 6], 1ull << (id & 63));
@@ -558,6 +571,17 @@ __global__ void __launch_bounds__(T) k_small_commit(CommitJobs J) {
     }
 }
 
+__global__ void __launch_bounds__(T) k_small_commit(ByValue<SmallCommit> A) {
+    __shared__ CommitSh sh;
+    commit_one(A.j[blockIdx.x], sh);
+}
+__global__ void __launch_bounds__(T) k_small_commit_many(ByPointer A) {
+    __shared__ CommitSh sh;
+    __shared__ SmallCommit C;
+    fetch_job(C, A.h[blockIdx.x]->commit);
+    commit_one(C, sh);
+}
+
 // ---------------------------------------------------------------------------
 // touched vertex pairs (as iv_prepare and iv_touched_build)
 // ---------------------------------------------------------------------------
@@ -661,16 +685,34 @@ __global__ void __launch_bounds__(T) k_small_iv(IvJobs J) {
 
 }  // namespace
 
-void small_plan(const SmallPlan* jobs, uint32_t n, hipStream_t s) {
-    PlanJobs J;
-    for (uint32_t i = 0; i < n; i++) J.j[i] = jobs[i];
-    k_small_plan<<<n, T, 0, s>>>(J);
+void small_plan(SmallHost* const* jobs, uint32_t n, hipStream_t s) {
+    if (n <= kSmallByValue) {
+        ByValue<SmallPlan> A;
+        for (uint32_t i = 0; i < n; i++) A.j[i] = jobs[i]->plan;
+        k_small_plan<<<n, T, 0, s>>>(A);
+        return;
+    }
+    for (uint32_t from = 0; from < n; from += kSmallJobs) {
+        const uint32_t m = n - from < kSmallJobs ? n - from : kSmallJobs;
+        ByPointer A;
+        for (uint32_t i = 0; i < m; i++) A.h[i] = jobs[from + i];
+        k_small_plan_many<<<m, T, 0, s>>>(A);
+    }
 }
 
-void small_commit(const SmallCommit* jobs, uint32_t n, hipStream_t s) {
-    CommitJobs J;
-    for (uint32_t i = 0; i < n; i++) J.j[i] = jobs[i];
-    k_small_commit<<<n, T, 0, s>>>(J);
+void small_commit(SmallHost* const* jobs, uint32_t n, hipStream_t s) {
+    if (n <= kSmallByValue) {
+        ByValue<SmallCommit> A;
+        for (uint32_t i = 0; i < n; i++) A.j[i] = jobs[i]->commit;
+        k_small_commit<<<n, T, 0, s>>>(A);
+        return;
+    }
+    for (uint32_t from = 0; from < n; from += kSmallJobs) {
+        const uint32_t m = n - from < kSmallJobs ? n - from : kSmallJobs;
+        ByPointer A;
+        for (uint32_t i = 0; i < m; i++) A.h[i] = jobs[from + i];
+        k_small_commit_many<<<m, T, 0, s>>>(A);
+    }
 }
 
 void small_iv(const SmallIv* jobs, uint32_t n, hipStream_t s) {
