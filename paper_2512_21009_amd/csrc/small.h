@@ -1,6 +1,7 @@
 // small.h -- planning, store update and pair list of small batches (small.hip).
 #pragma once
 
+#include "internal.h"
 #include "store.h"
 
 // A batch that one workgroup plans (of one graph).
@@ -61,6 +62,7 @@ struct SmallHost {  // pinned, one per graph
     BatchSummary sum;
     SmallPlan plan;      // written before the plan is launched, read until its wait
     SmallCommit commit;  // read until the batch's update has run, which the next plan waits for
+    uint64_t counts[HGT_COUNT_WORDS];  // written with the device's at the end of every batch
 };
 void small_plan(SmallHost* const* jobs, uint32_t n, hipStream_t s);
 void small_commit(SmallHost* const* jobs, uint32_t n, hipStream_t s);
