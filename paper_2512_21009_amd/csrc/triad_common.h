@@ -161,6 +161,35 @@ __device__ __forceinline__ void flat_window(Flat& F, const FlatSeg& g, uint32_t 
     if (g.d && g.ex > w0 && g.ex - w0 <= 4096) atomicOr(&F.bits[(g.ex - 1 - w0) >> 5], 1u << ((g.ex - 1 - w0) & 31));
     wave_sync();
 }
+// use(ok, l, v) takes a lane's U entries together, so that what it fetches for one does
+// not wait for the others.
+template <int U, class Load, class Use>
+__device__ __forceinline__ void flat_walk_all(const Flat& F, const FlatSeg& g, uint32_t w0, Load load, Use use) {
+    const uint32_t lane = threadIdx.x & 63;
+    uint32_t kb = (uint32_t)__popcll(__ballot(g.d && g.ex <= w0)) - 1;  // the segment that entry w0 lies in
+    const uint32_t w1 = g.tot - w0 < 4096 ? g.tot : w0 + 4096;
+    for (uint32_t p0 = w0; p0 < w1; p0 += 64 * U) {
+        uint32_t l[U];
+        bool ok[U];
+        decltype(load(0u, 0u)) v[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const uint32_t p = p0 + 64 * u + lane, at = (p0 - w0) / 32 + 2 * u;
+            const uint32_t lo = __builtin_amdgcn_readfirstlane(F.bits[at & 127]);
+            const uint32_t hi = __builtin_amdgcn_readfirstlane(F.bits[(at + 1) & 127]);
+            const uint32_t k = kb + __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
+            kb += __popc(lo) + __popc(hi);
+            v[u] = {};
+            l[u] = 0;
+            ok[u] = p < w1;
+            if (ok[u]) {
+                l[u] = F.own[k];
+                v[u] = load(l[u], p - F.pre[k]);
+            }
+        }
+        use(ok, l, v);
+    }
+}
 template <int U, class Load, class Use>
 __device__ __forceinline__ void flat_walk(const Flat& F, const FlatSeg& g, uint32_t w0, Load load, Use use) {
     const uint32_t lane = threadIdx.x & 63;

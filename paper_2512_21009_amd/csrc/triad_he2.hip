@@ -437,31 +437,42 @@ __device__ void he2_flush_graph(const He2Params& P, uint32_t g, He2Acc& A) {
 // Exclusive prefix over i of f(i), i < n, by the whole workgroup: every wave takes
 // a contiguous part (one reduce pass, one scan pass, one barrier between them).
 // put(i, before) stores the prefix.  Ends without a barrier.
-template <int WG, class F, class S>
+template <int WG, int U, class F, class S>
 __device__ __forceinline__ void wg_prefix(uint32_t n, uint32_t* ws, F f, S put) {
     constexpr uint32_t NW = WG / 64;
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint32_t per = ((n + NW * 64 - 1) / (NW * 64)) * 64;
     const uint32_t b = wave * per < n ? wave * per : n, e = b + per < n ? b + per : n;
     uint32_t sum = 0;
-    for (uint32_t i = b + lane; i < e; i += 64) sum += f(i);
+    for (uint32_t i0 = b; i0 < e; i0 += 64 * U) {
+        uint32_t v[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) v[u] = i0 + 64 * u + lane < e ? f(i0 + 64 * u + lane) : 0;
+#pragma unroll
+        for (int u = 0; u < U; u++) sum += v[u];
+    }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
     if (lane == 0) ws[wave] = sum;
     __syncthreads();
     uint32_t base = 0;
     for (uint32_t w = 0; w < wave; w++) base += ws[w];
-    for (uint32_t i0 = b; i0 < e; i0 += 64) {
-        const uint32_t i = i0 + lane;
-        const uint32_t v = i < e ? f(i) : 0;
-        uint32_t inc = v;
+    for (uint32_t i0 = b; i0 < e; i0 += 64 * U) {
+        uint32_t v[U];
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t t = __shfl_up(inc, o, 64);
-            if (lane >= (uint32_t)o) inc += t;
+        for (int u = 0; u < U; u++) v[u] = i0 + 64 * u + lane < e ? f(i0 + 64 * u + lane) : 0;
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const uint32_t i = i0 + 64 * u + lane;
+            uint32_t inc = v[u];
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t t = __shfl_up(inc, o, 64);
+                if (lane >= (uint32_t)o) inc += t;
+            }
+            if (i < e) put(i, base + inc - v[u]);
+            base += __shfl(inc, 63, 64);
         }
-        if (i < e) put(i, base + inc - v);
-        base += __shfl(inc, 63, 64);
     }
 }
 
@@ -789,7 +800,7 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
         uint32_t* pre = BIG ? lds : arena + AW - (3 * hlen + 4);
         uint64_t* voff = (uint64_t*)(pre + ((hlen + 2) & ~1u));
         if (((uintptr_t)voff & 7) != 0) voff = (uint64_t*)((uint32_t*)voff + 1);
-        wg_prefix<WG>(hlen, sh.ws,
+        wg_prefix<WG, 1>(hlen, sh.ws,
                       [&](uint32_t i) {
                           const uint32_t m = G.g.h2v[sh.hoff + i];
                           voff[i] = G.g.v_off[m];
@@ -845,6 +856,8 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
         base0 += 2 * K;
         uint32_t* bm = BIG ? lds : arena + base0;
         uint32_t* bh = bm + 2 * BM_WORDS;
+        uint32_t* hs = BIG ? bh + BH_WORDS : hm;  // looked through where bh has a bit: with masks only
+        static_assert(!BIG || 2 * BM_WORDS + BH_WORDS + MASK_BITS <= LDS_L, "global stage LDS");
         uint32_t* stash = arena + base0 + (BIG ? 0 : 2 * BM_WORDS + BH_WORDS);
         const uint32_t stash0 = (uint32_t)(stash - arena);
         const uint32_t room = stash0 < AW ? AW - stash0 : 0;
@@ -856,6 +869,7 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
             for (uint32_t i = tid; i < hlen; i += WG) {
                 const uint32_t v = G.g.h2v[sh.hoff + i], b = (v * 2654435761u) >> (32 - BH_LOG);
                 hm[i] = v;
+                if (BIG && masked) hs[i] = v;
                 if (masked) atomicOr(&bh[b >> 5], 1u << (b & 31));
             }
         }
@@ -884,8 +898,8 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
                             const uint32_t hv = v * 2654435761u, bj = hv >> (32 - BH_LOG);
                             uint32_t in = 0;
                             if (bh[bj >> 5] >> (bj & 31) & 1u) {
-                                const uint32_t k = lower_bound_u32(hm, hlen, v);
-                                if (k < hlen && hm[k] == v) {
+                                const uint32_t k = lower_bound_u32(hs, hlen, v);
+                                if (k < hlen && hs[k] == v) {
                                     in = 1u << 31;
                                     atomicOr(&mask[2 * (c0 + l) + (k >> 5)], 1u << (k & 31));
                                 }
@@ -911,8 +925,10 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
             continue;
         }
         // Walks the stashed rows, d(xi) entries of each, and packs what keep() wants to the front
-        // of its row (a row belongs to one wave, which has read what it writes over): keep(ok, xi,
-        // entry) returns the entry's new value, HGT_EMPTY to drop it.  ecnt: the entries left.
+        // of its row (a row belongs to one wave, which has read what it writes over): keep(c0, ok,
+        // l, v) puts new values in place of PU entries, of neighbours c0 + l, HGT_EMPTY to drop
+        // them.  ecnt: the entries left.
+        constexpr int PU = 4;
         auto pack = [&](auto dfn, auto keep) __attribute__((always_inline)) {
             uint32_t left = 0;
             chunks([&](uint32_t c0, uint32_t n) {
@@ -922,11 +938,18 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
                     woff[lane] = row_at[c0 + lane];
                 }
                 wm[lane] = 0;
-                wave_flat<4>(fl, d, [&](uint32_t l, uint32_t r) { return stash[woff[l] + r]; },
-                             [&](bool ok, uint32_t l, uint32_t, uint32_t, uint32_t v) {
-                                 const uint32_t w = ok ? keep(c0 + l, v) : HGT_EMPTY;
-                                 if (w != HGT_EMPTY) stash[woff[l] + atomicAdd(&wm[l], 1u)] = w;
-                             });
+                const FlatSeg g = flat_lay(fl, d);
+                for (uint32_t w0 = 0; w0 < g.tot; w0 += 4096) {
+                    flat_window(fl, g, w0);
+                    flat_walk_all<PU>(fl, g, w0, [&](uint32_t l, uint32_t r) { return stash[woff[l] + r]; },
+                                      [&](const bool (&ok)[PU], const uint32_t (&l)[PU], uint32_t (&v)[PU]) {
+                                          keep(c0, ok, l, v);
+#pragma unroll
+                                          for (int u = 0; u < PU; u++)
+                                              if (v[u] != HGT_EMPTY) stash[woff[l[u]] + atomicAdd(&wm[l[u]], 1u)] = v[u];
+                                      });
+                    wave_sync();
+                }
                 wave_sync();
                 if (lane < n) {
                     ecnt[c0 + lane] = wm[lane];
@@ -938,9 +961,13 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
         };
         {
             const uint32_t left = pack([&](uint32_t i) { return meta_len(nl_meta[i]); },
-                                       [&](uint32_t, uint32_t v) {
-                                           const uint32_t b = (v * 2654435761u) >> (32 - BM_LOG);
-                                           return !(v >> 31) && (bm[BM_WORDS + (b >> 5)] >> (b & 31) & 1u) ? v : HGT_EMPTY;
+                                       [&](uint32_t, const bool (&ok)[PU], const uint32_t (&)[PU], uint32_t (&v)[PU]) {
+#pragma unroll
+                                           for (int u = 0; u < PU; u++) {
+                                               const uint32_t b = (v[u] * 2654435761u) >> (32 - BM_LOG);
+                                               if (!ok[u] || v[u] >> 31 || !(bm[BM_WORDS + (b >> 5)] >> (b & 31) & 1u))
+                                                   v[u] = HGT_EMPTY;
+                                           }
                                        });
             if (left) atomicAdd(&sh.S, left);
         }
@@ -981,10 +1008,42 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
         if (S) {
             for (uint32_t s = tid; s < vcap; s += WG) { tst[s] = HGT_EMPTY; tcnt[s] = 0; }
             __syncthreads();
-            (void)pack([&](uint32_t i) { return ecnt[i]; }, [&](uint32_t, uint32_t v) { return fr_add(tst, tcnt, vcap, v, 1u); });
+            // all entries' probes are in flight together: in the global stage each is a trip to the L2
+            (void)pack([&](uint32_t i) { return ecnt[i]; },
+                       [&](uint32_t, const bool (&ok)[PU], const uint32_t (&)[PU], uint32_t (&v)[PU]) {
+                           if constexpr (!BIG) {
+#pragma unroll
+                               for (int u = 0; u < PU; u++) v[u] = ok[u] ? fr_add(tst, tcnt, vcap, v[u], 1u) : HGT_EMPTY;
+                               return;
+                           }
+                           uint32_t s[PU], k[PU];
+                           uint32_t go = 0;
+#pragma unroll
+                           for (int u = 0; u < PU; u++) {
+                               s[u] = fr_slot(v[u], vcap);
+                               go |= ok[u] ? 1u << u : 0u;
+                           }
+                           for (uint32_t probe = 0; go && probe < vcap; probe++) {
+#pragma unroll
+                               for (int u = 0; u < PU; u++) k[u] = ld_at<BIG>(&tst[s[u]]);
+#pragma unroll
+                               for (int u = 0; u < PU; u++)
+                                   if (k[u] == HGT_EMPTY && (go >> u & 1u)) k[u] = atomicCAS(&tst[s[u]], HGT_EMPTY, v[u]);
+#pragma unroll
+                               for (int u = 0; u < PU; u++) {
+                                   if (k[u] == HGT_EMPTY || k[u] == v[u]) go &= ~(1u << u);
+                                   else if (go >> u & 1u) s[u] = fr_next(s[u], vcap);
+                               }
+                           }
+#pragma unroll
+                           for (int u = 0; u < PU; u++) {
+                               if (ok[u]) atomicAdd(&tcnt[s[u]], 1u);
+                               v[u] = ok[u] ? s[u] : HGT_EMPTY;
+                           }
+                       });
             __syncthreads();
             // run starts (vertices of one neighbour only: an empty run), flagged when the vertex lies in h
-            wg_prefix<WG>(vcap, sh.ws,
+            wg_prefix<WG, BIG ? 4 : 1>(vcap, sh.ws,
                           [&](uint32_t s) {
                               const uint32_t r = ld_at<BIG>(&tcnt[s]);
                               return r >= 2 ? r : 0u;
@@ -1004,11 +1063,32 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
             }
             __syncthreads();
             (void)pack([&](uint32_t i) { return ecnt[i]; },
-                       [&](uint32_t xi, uint32_t s) {
-                           const uint32_t r0 = ld_at<BIG>(&tst[s]) & POS, r1 = ld_at<BIG>(&tst[s + 1]) & POS;
-                           if (r0 == r1) return HGT_EMPTY;
-                           rx[r0 + atomicSub(&tcnt[s], 1u) - 1] = xi;
-                           return s;
+                       [&](uint32_t c0, const bool (&ok)[PU], const uint32_t (&l)[PU], uint32_t (&v)[PU]) {
+                           if constexpr (!BIG) {
+#pragma unroll
+                               for (int u = 0; u < PU; u++) {
+                                   if (!ok[u]) { v[u] = HGT_EMPTY; continue; }
+                                   const uint32_t s0 = tst[v[u]] & POS, s1 = tst[v[u] + 1] & POS;
+                                   if (s0 == s1) v[u] = HGT_EMPTY;
+                                   else rx[s0 + atomicSub(&tcnt[v[u]], 1u) - 1] = c0 + l[u];
+                               }
+                               return;
+                           }
+                           uint32_t r0[PU], r1[PU];
+#pragma unroll
+                           for (int u = 0; u < PU; u++) {
+                               const uint32_t s = ok[u] ? v[u] : 0;
+                               r0[u] = ld_at<BIG>(&tst[s]) & POS;
+                               r1[u] = ld_at<BIG>(&tst[s + 1]) & POS;
+                           }
+#pragma unroll
+                           for (int u = 0; u < PU; u++) {
+                               if (!ok[u] || r0[u] == r1[u]) v[u] = HGT_EMPTY;
+                               else r0[u] += atomicSub(&tcnt[v[u]], 1u) - 1;
+                           }
+#pragma unroll
+                           for (int u = 0; u < PU; u++)
+                               if (v[u] != HGT_EMPTY) rx[r0[u]] = c0 + l[u];
                        });
         }
         __syncthreads();
@@ -1282,9 +1362,12 @@ __global__ void k_he2_work(Multi M, const uint64_t* __restrict__ list, const uin
     if (lane == 0 && sum) atomicAdd((unsigned long long*)total, (unsigned long long)sum);
 }
 
-// Work to slices, and their exclusive prefix, by one workgroup: a slice holds a quarter of
-// a workgroup's share of the whole, so that the last ones end together, and at least
-// SLICE_MIN (what building the tables again costs).
+// Work to slices, and their exclusive prefix, by one workgroup.  A slice holds about a
+// workgroup's share of the whole where there are few centres, half of one where there are
+// several per workgroup, so that the last ones end together: every slice builds its
+// centre's tables again, which for 500 dense centres, one per workgroup, is most of the
+// work (a quarter of a share each: 7.4 ms; this rule: 5.1; all centres whole: 5.4), while
+// 3,300 centres of uneven size gain by being cut (6.5 ms whole, 5.9 so).
 constexpr uint64_t SLICE_MIN = 1ull << 15;
 constexpr uint32_t SLICES_MAX = 64;
 __global__ void __launch_bounds__(1024) k_he2_cut(uint64_t cap, uint32_t slice_lh, uint64_t slice_pairs, uint32_t grid,
@@ -1292,7 +1375,8 @@ __global__ void __launch_bounds__(1024) k_he2_cut(uint64_t cap, uint32_t slice_l
     __shared__ uint32_t ws[16];
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint64_t n = pre[cap];
-    uint64_t per = *total / (4ull * grid);
+    const uint64_t shares = n / 2 < grid ? grid : n / 2 < 2ull * grid ? n / 2 : 2ull * grid;
+    uint64_t per = *total / shares;
     if (per < SLICE_MIN) per = SLICE_MIN;
     if (slice_pairs) per = slice_pairs;
     uint64_t base = 0;
@@ -1300,7 +1384,7 @@ __global__ void __launch_bounds__(1024) k_he2_cut(uint64_t cap, uint32_t slice_l
         const uint64_t c = b + threadIdx.x;
         uint32_t sl = 0;
         if (c < n) {
-            const uint64_t w = slice_lh ? pre[c] : (pre[c] + per - 1) / per;
+            const uint64_t w = slice_lh ? pre[c] : (pre[c] + per / 2) / per;
             sl = w < 1 ? 1 : w > SLICES_MAX ? SLICES_MAX : (uint32_t)w;
         }
         uint32_t inc = sl;
