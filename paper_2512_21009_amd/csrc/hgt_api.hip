@@ -845,7 +845,7 @@ int run_phase(hgt_graph* owner, const PhaseJob* jobs, uint32_t nj, bool minus, b
             N.n_entries = (uint64_t*)(ctr + 10);  // 8-byte aligned slot
             N.entries_cap = z.ecap;
             N.ent_x = c.ent_x.as<uint32_t>();
-            N.ent_d = c.ent_d.as<uint32_t>();
+            (in_window ? N.ent_d : N.ent_k) = c.ent_d.as<uint32_t>();
             N.ent_pay = c.ent_pay.as<uint64_t>();
             N.queue = ctr;
             N.big_queue = ctr + 1;

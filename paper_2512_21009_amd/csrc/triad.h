@@ -112,7 +112,8 @@ struct NbrParams {
     uint64_t* n_entries;         // batch-neighbour entries written (all graphs)
     uint64_t entries_cap;
     uint32_t* ent_x;             // id_base + x
-    uint32_t* ent_d;
+    uint32_t* ent_d;             // NULL: not wanted
+    uint32_t* ent_k;             // an entry's place among its ID's (without ent_d)
     uint64_t* ent_pay;           // rank << 32 | k << 1 | [|d| > k]
     uint32_t* queue;             // queue, big_queue, big_count (consecutive)
     uint32_t* big_queue;

@@ -251,7 +251,7 @@ __device__ void nbr_pass_body(const NbrParams& P, uint32_t* arena, uint64_t aren
                 const uint64_t q = ebase + at;
                 if (q < P.entries_cap) {
                     P.ent_x[q] = (uint32_t)(G.id_base + x);
-                    P.ent_d[q] = h;
+                    if (P.ent_d) P.ent_d[q] = h;
                     P.ent_pay[q] = ((uint64_t)rank << 32) | ((uint64_t)c << 1) | fd;
                 }
             }
@@ -316,12 +316,35 @@ __global__ void k_h_remove(Multi M, const uint64_t* n_entries_p, uint64_t cap, c
 }
 
 // counting sort of the entries by ID slot: per-slot counts, then scatter
+// Entries per ID; with ent_k also an entry's place among its ID's, which saves the scatter
+// an atomic that it has to wait for, and the copy of the offsets that the atomics ate.  BL_U
+// entries of a thread are in flight together.  Bound by the scattered writes of 8 bytes
+// (100k changes on 2M hyperedges, both phases: scatter 1.52 -> 0.66 ms, without the 4 bytes
+// that name the changed hyperedge; count 0.85 -> 0.86).
+constexpr int BL_U = 4;
 __global__ void k_bl_count(const uint64_t* n_entries_p, uint64_t cap, const uint32_t* __restrict__ ent_x,
-                           uint64_t* bl_cnt) {
+                           uint64_t* bl_cnt, uint32_t* ent_k) {
     uint64_t n = *n_entries_p;
     if (n > cap) n = cap;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-        if (ent_x[i] != HGT_EMPTY) atomicAdd((unsigned long long*)&bl_cnt[ent_x[i]], 1ull);
+    const uint64_t step = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i0 < n; i0 += BL_U * step) {
+        uint32_t x[BL_U];
+        uint64_t k[BL_U];
+#pragma unroll
+        for (int u = 0; u < BL_U; u++) x[u] = i0 + u * step < n ? ent_x[i0 + u * step] : HGT_EMPTY;
+        if (!ent_k) {
+#pragma unroll
+            for (int u = 0; u < BL_U; u++)
+                if (x[u] != HGT_EMPTY) atomicAdd((unsigned long long*)&bl_cnt[x[u]], 1ull);
+            continue;
+        }
+#pragma unroll
+        for (int u = 0; u < BL_U; u++)
+            if (x[u] != HGT_EMPTY) k[u] = atomicAdd((unsigned long long*)&bl_cnt[x[u]], 1ull);
+#pragma unroll
+        for (int u = 0; u < BL_U; u++)
+            if (x[u] != HGT_EMPTY) ent_k[i0 + u * step] = (uint32_t)k[u];
+    }
 }
 
 __global__ void k_bl_scatter(const uint64_t* n_entries_p, uint64_t cap, const uint32_t* __restrict__ ent_x,
@@ -334,6 +357,34 @@ __global__ void k_bl_scatter(const uint64_t* n_entries_p, uint64_t cap, const ui
         uint64_t pos = atomicAdd((unsigned long long*)&bl_cur[ent_x[i]], 1ull);
         out_d[pos] = ent_d[i];
         out_pay[pos] = ent_pay[i];
+    }
+}
+
+__global__ void k_bl_place(const uint64_t* n_entries_p, uint64_t cap, const uint32_t* __restrict__ ent_x,
+                           const uint32_t* __restrict__ ent_k, const uint64_t* __restrict__ ent_pay,
+                           const uint64_t* __restrict__ bl_off, uint64_t* __restrict__ out_pay) {
+    uint64_t n = *n_entries_p;
+    if (n > cap) n = cap;
+    const uint64_t step = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i0 < n; i0 += BL_U * step) {
+        uint32_t x[BL_U], k[BL_U];
+        uint64_t pay[BL_U], at[BL_U];
+#pragma unroll
+        for (int u = 0; u < BL_U; u++) {
+            const uint64_t i = i0 + u * step;
+            x[u] = HGT_EMPTY;
+            if (i < n) {
+                x[u] = ent_x[i];
+                k[u] = ent_k[i];
+                pay[u] = ent_pay[i];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < BL_U; u++)
+            if (x[u] != HGT_EMPTY) at[u] = bl_off[x[u]];
+#pragma unroll
+        for (int u = 0; u < BL_U; u++)
+            if (x[u] != HGT_EMPTY) out_pay[at[u] + k[u]] = pay[u];
     }
 }
 
@@ -1424,8 +1475,14 @@ void he2_lists_build(NbrParams& P, uint64_t* bl_cnt, uint64_t* bl_off, uint64_t*
     const uint64_t n_ids = P.M.total_ids;
     hgt_fill_u64(bl_cnt, 0, n_ids, s);
     unsigned g = 2048;
-    k_bl_count<<<g, 256, 0, s>>>(P.n_entries, P.entries_cap, P.ent_x, bl_cnt);
+    // who an entry came from matters to the temporal paths only; without, its place takes the column
+    uint32_t* ent_k = P.ent_d ? nullptr : P.ent_k;
+    k_bl_count<<<g, 256, 0, s>>>(P.n_entries, P.entries_cap, P.ent_x, bl_cnt, ent_k);
     hgt_scan_u64(bl_cnt, bl_off, n_ids, nullptr, nullptr, scan_tmp, s);
+    if (ent_k) {
+        k_bl_place<<<g, 256, 0, s>>>(P.n_entries, P.entries_cap, P.ent_x, ent_k, P.ent_pay, bl_off, bl_pay);
+        return;
+    }
     (void)hipMemcpyAsync(bl_cur, bl_off, n_ids * 8, hipMemcpyDeviceToDevice, s);
     k_bl_scatter<<<g, 256, 0, s>>>(P.n_entries, P.entries_cap, P.ent_x, P.ent_d, P.ent_pay, bl_cur, bl_d, bl_pay);
 }
