@@ -85,6 +85,9 @@ __device__ __forceinline__ uint32_t ld_at(const uint32_t* p) {
     return *p;
 }
 
+// What the kernels below call is inlined throughout: one call that takes the parameter
+// block by reference puts a copy of the block in scratch, and every field is then read from
+// there (the global stage: 5.85 -> 5.61 ms for 100k changes on 2M hyperedges).
 struct Sh2 {
     uint32_t h, rank, hlen, lh, K, W, S, defer, stop, over;
     uint32_t gi, cur_g, skip;
@@ -147,7 +150,7 @@ __device__ __forceinline__ uint64_t nbr_words(uint32_t hlen, uint32_t lh) {
 constexpr uint32_t NBR_TAKE = 8;  // centres a workgroup takes at once
 
 template <bool BIG>
-__device__ void nbr_pass_body(const NbrParams& P, uint32_t* arena, uint64_t arena_words) {
+__device__ __forceinline__ void nbr_pass_body(const NbrParams& P, uint32_t* arena, uint64_t arena_words) {
     __shared__ Sh2 sh;
     __shared__ uint32_t c_gi[NBR_TAKE], c_h[NBR_TAKE], c_rank[NBR_TAKE], c_lh[NBR_TAKE];
     __shared__ uint64_t c_off[NBR_TAKE];
@@ -450,7 +453,7 @@ __device__ __forceinline__ void tmp_pair(const GraphView& g, const Tables& T, Tm
     tmp_add(A, T.tmp[time_code(th, qh, tx, qx, ty, qy, nh, nx, ny, 0, (int)s, hy, 0)], ~0ull);
 }
 template <int WG>
-__device__ void he2_flush_graph(const He2Params& P, uint32_t g, TmpAcc& A) {
+__device__ __forceinline__ void he2_flush_graph(const He2Params& P, uint32_t g, TmpAcc& A) {
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < HGT_N_TEMPORAL_CLASSES; i += WG) {
         uint64_t s = 0;
@@ -465,7 +468,7 @@ __device__ void he2_flush_graph(const He2Params& P, uint32_t g, TmpAcc& A) {
 
 // Adds the workgroup's counts to graph g's phase accumulators and clears them.
 template <int WG>
-__device__ void he2_flush_graph(const He2Params& P, uint32_t g, He2Acc& A) {
+__device__ __forceinline__ void he2_flush_graph(const He2Params& P, uint32_t g, He2Acc& A) {
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < HGT_N_HE_CLASSES * COPIES; i += WG) {
         if (A.pair[i]) atomicAdd((unsigned long long*)&A.tot[i / COPIES], (unsigned long long)A.pair[i]);
@@ -574,7 +577,7 @@ __device__ __forceinline__ void he2_compact(const He2Params& P, const HeGraph& G
 // (f = [|x| > c], c): every pair of neighbours as if x and y were disjoint.
 // cnt: 2 (hlen + 1) LDS words.
 template <int WG>
-__device__ void he2_disjoint(Sh2& sh, const Tables& T, He2Acc& A, const uint32_t* nl_meta, uint32_t K, uint32_t hlen,
+__device__ __forceinline__ void he2_disjoint(Sh2& sh, const Tables& T, He2Acc& A, const uint32_t* nl_meta, uint32_t K, uint32_t hlen,
                              uint32_t* cnt) {
     const uint32_t tid = threadIdx.x, lane = tid & 63, Wc = hlen + 1;
     for (uint32_t i = tid; i < 2 * Wc; i += WG) cnt[i] = 0;
@@ -704,7 +707,7 @@ __device__ __forceinline__ void he2_pair(const He2Params& P, const Tables& T, He
 // (in a full count) h < x, so neighbours are counted by these and the pairs taken by kind:
 // a few dozen kinds in place of hundreds of neighbours.  rep/cnt: gcap slots, list: K words.
 template <int WG, bool BIG, bool GLOBAL>
-__device__ void he2_kinds(const He2Params& P, Sh2& sh, const Tables& T, He2Acc& A, const uint32_t* nl_meta,
+__device__ __forceinline__ void he2_kinds(const He2Params& P, Sh2& sh, const Tables& T, He2Acc& A, const uint32_t* nl_meta,
                           const uint32_t* mask, uint32_t K, uint32_t hlen, uint32_t* rep, uint32_t gcap) {
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint32_t* cnt = rep + gcap;
@@ -752,7 +755,7 @@ __device__ void he2_kinds(const He2Params& P, Sh2& sh, const Tables& T, He2Acc& 
 }
 
 template <int STAGE, int WG, bool TMP>
-__device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW, uint32_t* lds, Sh2& sh, const Tables& T,
+__device__ __forceinline__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW, uint32_t* lds, Sh2& sh, const Tables& T,
                          std::conditional_t<TMP, TmpAcc, He2Acc>& A, uint64_t* st, uint64_t* ph) {
     constexpr uint32_t NW = WG / 64;
     constexpr bool BIG = STAGE == 2, SLICED = STAGE > 0;
@@ -1308,7 +1311,7 @@ __device__ void he2_body(const He2Params& P, uint32_t* arena, const uint32_t AW,
 }
 
 template <int STAGE>
-__device__ void he2_flush_stats(const He2Params& P, const uint64_t* st, const uint64_t* ph) {
+__device__ __forceinline__ void he2_flush_stats(const He2Params& P, const uint64_t* st, const uint64_t* ph) {
     if (P.phase_ticks && threadIdx.x < HE2_PHASES - 1 && ph[threadIdx.x])
         atomicAdd((unsigned long long*)&P.stats[ST_PH0 + HE2_PHASES * STAGE + threadIdx.x],
                   (unsigned long long)ph[threadIdx.x]);
