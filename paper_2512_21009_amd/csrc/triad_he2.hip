@@ -29,7 +29,7 @@
 // to end, four steps' loads in flight, with as many waves as the LDS holds.  Measured with
 // 100k changes on 2M hyperedges of up to 64 members (both phases): sorted entries and pairs
 // enumerated per shared vertex 37.5 ms; counters along all runs 34.8; kinds and flat walks
-// 13.7.  5k changes on 500k hyperedges, where two dense centres went to the 2-hop kernel:
+// 13.7; now 13.0.  5k changes on 500k hyperedges, where two dense centres went to the 2-hop kernel:
 // 134 ms, 9.7, 3.0.
 #include <type_traits>
 
@@ -89,7 +89,7 @@ __device__ __forceinline__ uint32_t ld_at(const uint32_t* p) {
 // block by reference puts a copy of the block in scratch, and every field is then read from
 // there (the global stage: 5.85 -> 5.61 ms for 100k changes on 2M hyperedges).
 struct Sh2 {
-    uint32_t h, rank, hlen, lh, K, W, S, defer, stop, over;
+    uint32_t h, rank, hlen, lh, K, W, S, defer, stop, rows;
     uint32_t gi, cur_g, skip;
     uint32_t slice, nslice;
     uint64_t hoff;
@@ -551,11 +551,12 @@ __device__ __forceinline__ void he2_nh(const GraphView& G, uint32_t h, uint32_t 
 }
 
 // The hash's neighbours as numbers 0 .. K-1: ID and meta (c | len << 14 | eligible
-// << 28 | h < x << 29).
+// << 28 | h < x << 29), and the words of their rows.
 template <int WG, bool GLOBAL>
 __device__ __forceinline__ void he2_compact(const He2Params& P, const HeGraph& G, Sh2& sh, const uint32_t* keys,
                                             const uint32_t* vals, uint32_t cap, uint32_t* nl_x, uint32_t* nl_meta) {
     const uint32_t lane = threadIdx.x & 63;
+    uint32_t lens = 0;
     for (uint32_t s0 = 0; s0 < cap; s0 += WG) {
         const uint32_t s = s0 + threadIdx.x;
         const uint32_t x = s < cap ? ld_at<GLOBAL>(&keys[s]) : HGT_EMPTY;
@@ -569,7 +570,11 @@ __device__ __forceinline__ void he2_compact(const He2Params& P, const HeGraph& G
         const bool elig = P.static_mode || !lower_ranked_member(G.mark[x], G.epoch, sh.rank);
         nl_x[q] = x;
         nl_meta[q] = c | (len << 14) | ((uint32_t)elig << 28) | ((sh.h < x ? 1u : 0u) << 29);
+        lens += len;
     }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) lens += __shfl_xor(lens, o, 64);
+    if (lane == 0) atomicAdd(&sh.rows, lens);
     __syncthreads();
 }
 
@@ -818,7 +823,7 @@ __device__ __forceinline__ void he2_body(const He2Params& P, uint32_t* arena, co
                 sh.hlen = Gq.g.h_len[h];
                 sh.hoff = Gq.g.h_off[h];
                 sh.defer = (3ull * sh.hlen + 4 > (BIG ? LDS_L : AW / 2) || STAGE < P.force_stage) ? 1u : 0u;
-                sh.K = sh.W = sh.S = sh.over = 0;
+                sh.K = sh.W = sh.S = sh.rows = 0;
             }
         }
         __syncthreads();
@@ -915,68 +920,67 @@ __device__ __forceinline__ void he2_body(const He2Params& P, uint32_t* arena, co
         uint32_t* stash = arena + base0 + (BIG ? 0 : 2 * BM_WORDS + BH_WORDS);
         const uint32_t stash0 = (uint32_t)(stash - arena);
         const uint32_t room = stash0 < AW ? AW - stash0 : 0;
-        if (room) {
-            for (uint32_t i = tid; i < 2 * BM_WORDS + BH_WORDS; i += WG) bm[i] = 0;
-            if (masked)
-                for (uint32_t i = tid; i < 2 * K; i += WG) mask[i] = 0;
-            __syncthreads();
-            for (uint32_t i = tid; i < hlen; i += WG) {
-                const uint32_t v = G.g.h2v[sh.hoff + i], b = (v * 2654435761u) >> (32 - BH_LOG);
-                hm[i] = v;
-                if (BIG && masked) hs[i] = v;
-                if (masked) atomicOr(&bh[b >> 5], 1u << (b & 31));
-            }
+        // rows that do not fit are not gathered: a quarter of the centres of a power-law graph
+        // leave stage 0 here (100k changes on 2M hyperedges, left after the gather: stage 0 4.30
+        // -> 3.96 ms, stage 1 3.53 -> 3.38)
+        if (!room || sh.rows > room) {
+            move_on();
+            continue;
+        }
+        for (uint32_t i = tid; i < 2 * BM_WORDS + BH_WORDS; i += WG) bm[i] = 0;
+        if (masked)
+            for (uint32_t i = tid; i < 2 * K; i += WG) mask[i] = 0;
+        __syncthreads();
+        for (uint32_t i = tid; i < hlen; i += WG) {
+            const uint32_t v = G.g.h2v[sh.hoff + i], b = (v * 2654435761u) >> (32 - BH_LOG);
+            hm[i] = v;
+            if (BIG && masked) hs[i] = v;
+            if (masked) atomicOr(&bh[b >> 5], 1u << (b & 31));
         }
         __syncthreads();
         // a wave's chunks of neighbours: rows [c0, c0 + n)
         auto chunks = [&](auto fn) __attribute__((always_inline)) {
             for (uint32_t c0 = wave * per; c0 < K; c0 += NW * per) fn(c0, K - c0 < per ? K - c0 : per);
         };
-        if (room)
-            chunks([&](uint32_t c0, uint32_t n) {
-                uint32_t d = 0;
-                if (lane < n) {
-                    d = meta_len(nl_meta[c0 + lane]);
-                    woff[lane] = G.g.h_off[nl_x[c0 + lane]];
-                }
-                const FlatSeg g = flat_lay(fl, d);
-                uint32_t base = 0;
-                if (lane == 0) base = atomicAdd(&sh.W, g.tot);
-                base = __builtin_amdgcn_readfirstlane(base);
-                if (lane < n) row_at[c0 + lane] = base + g.ex;
-                for (uint32_t w0 = 0; w0 < g.tot; w0 += 4096) {
-                    flat_window(fl, g, w0);
-                    flat_walk<4>(fl, g, w0, [&](uint32_t l, uint32_t r) { return G.g.h2v[woff[l] + r]; },
-                        [&](bool ok, uint32_t l, uint32_t, uint32_t p, uint32_t v) {
-                            if (!ok) return;
-                            const uint32_t hv = v * 2654435761u, bj = hv >> (32 - BH_LOG);
-                            uint32_t in = 0;
-                            if (bh[bj >> 5] >> (bj & 31) & 1u) {
-                                const uint32_t k = lower_bound_u32(hs, hlen, v);
-                                if (k < hlen && hs[k] == v) {
-                                    in = 1u << 31;
-                                    atomicOr(&mask[2 * (c0 + l) + (k >> 5)], 1u << (k & 31));
-                                }
+        chunks([&](uint32_t c0, uint32_t n) {
+            uint32_t d = 0;
+            if (lane < n) {
+                d = meta_len(nl_meta[c0 + lane]);
+                woff[lane] = G.g.h_off[nl_x[c0 + lane]];
+            }
+            const FlatSeg g = flat_lay(fl, d);
+            uint32_t base = 0;
+            if (lane == 0) base = atomicAdd(&sh.W, g.tot);
+            base = __builtin_amdgcn_readfirstlane(base);
+            if (lane < n) row_at[c0 + lane] = base + g.ex;
+            for (uint32_t w0 = 0; w0 < g.tot; w0 += 4096) {
+                flat_window(fl, g, w0);
+                flat_walk<4>(fl, g, w0, [&](uint32_t l, uint32_t r) { return G.g.h2v[woff[l] + r]; },
+                    [&](bool ok, uint32_t l, uint32_t, uint32_t p, uint32_t v) {
+                        if (!ok) return;
+                        const uint32_t hv = v * 2654435761u, bj = hv >> (32 - BH_LOG);
+                        uint32_t in = 0;
+                        if (bh[bj >> 5] >> (bj & 31) & 1u) {
+                            const uint32_t k = lower_bound_u32(hs, hlen, v);
+                            if (k < hlen && hs[k] == v) {
+                                in = 1u << 31;
+                                atomicOr(&mask[2 * (c0 + l) + (k >> 5)], 1u << (k & 31));
                             }
-                            if (base + p < room) stash[base + p] = v | in;
-                            if (in) return;
-                            const uint32_t b = hv >> (32 - BM_LOG), bit = 1u << (b & 31);
-                            if (atomicOr(&bm[b >> 5], bit) & bit) atomicOr(&bm[BM_WORDS + (b >> 5)], bit);
-                        });
-                    wave_sync();
-                }
-            });
+                        }
+                        if (base + p < room) stash[base + p] = v | in;
+                        if (in) return;
+                        const uint32_t b = hv >> (32 - BM_LOG), bit = 1u << (b & 31);
+                        if (atomicOr(&bm[b >> 5], bit) & bit) atomicOr(&bm[BM_WORDS + (b >> 5)], bit);
+                    });
+                wave_sync();
+            }
+        });
         __syncthreads();
         const uint32_t W = sh.W;
         if (tid == 0) {
             // h's row and its members' incidence lists, each neighbour's row and metadata
             if (P.stats)
                 atomicAdd((unsigned long long*)&st[1], (unsigned long long)(4ull * (hlen + lh) + 20ull * K + 4ull * W));
-        }
-        if (W > room || !room) {
-            __syncthreads();
-            move_on();
-            continue;
         }
         // Walks the stashed rows, d(xi) entries of each, and packs what keep() wants to the front
         // of its row (a row belongs to one wave, which has read what it writes over): keep(c0, ok,
