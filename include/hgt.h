@@ -455,7 +455,7 @@ int hgt_profile_read(hgt_graph* g, hgt_kernel_time* out_host, uint32_t n_max, ui
 /* Waits for the graph's work and copies the raw device counters of the
  * profile (algorithmic bytes, hand-overs between kernel stages, wall-clock
  * ticks per phase of the hyperedge-delta stages: counters 16 + 12 s + p for
- * stage s (0: LDS, 2: global) and phase p = 0 member prefix, 1 neighbour hash,
+ * stage s (0, 1: LDS, 2: global) and phase p = 0 member prefix, 1 neighbour hash,
  * 2 compaction, 3 disjoint-pair classes, 4 vertices shared by two neighbours,
  * 5 open paths, 6 intersecting pairs, 7 hand-over, 8 runs of the shared
  * vertices, 11 the longest centre; 56.. temporal counters) to

@@ -141,9 +141,11 @@ thread_local int t_capture = 0;
 // histogram stage, slots of the 2-hop kernels' per-wave hashes, size of a slice of
 // a dense centre); t_tune overrides the graph's own for one round.
 struct TuneChoice {
+    int file_wg, file_skip;  // the numbers that name the choice in the cache file, with
+    uint64_t file_e2;        // wave_slots between them (what they once set is gone)
     int wg_per_cu;
     uint32_t wave_slots;
-    uint64_t slice_pairs;  // pairs per slice of a global-stage centre (0: default)
+    uint64_t slice_pairs;    // work per slice of a centre of stages 1 and 2 (0: by the launch's total)
 };
 thread_local const TuneChoice* t_tune = nullptr;
 thread_local hipEvent_t t_tune_ev[2] = {nullptr, nullptr};  // recorded around an autotuned round's launches
@@ -744,18 +746,21 @@ PhaseShape phase_shape(const hgt_graph* owner, uint64_t n, uint64_t max_lh, uint
     return z;
 }
 
-// The batch-neighbour lists, and the tables of the stages that use them.
-int lists_reserve(PhaseCtx& c, const PhaseShape& z) {
+// The batch-neighbour lists (tmp: that name the changed hyperedges), and the tables of the
+// stages that use them.
+int lists_reserve(PhaseCtx& c, const PhaseShape& z, bool tmp) {
     const uint64_t ids = z.total_ids;
     int rc = 0;
     rc |= ensure(c.ent_x, z.ecap * 4);
     rc |= ensure(c.ent_d, z.ecap * 4);
     rc |= ensure(c.ent_pay, z.ecap * 8);
-    rc |= ensure(c.bl_d, z.ecap * 4);
     rc |= ensure(c.bl_pay, z.ecap * 8);
     rc |= ensure(c.bl_cnt, ids * 8);
     rc |= ensure(c.bl_off, ids * 8);
-    rc |= ensure(c.bl_cur, ids * 8);
+    if (tmp) {
+        rc |= ensure(c.bl_d, z.ecap * 4);
+        rc |= ensure(c.bl_cur, ids * 8);
+    }
     rc |= ensure(c.bl_scan, hgt_scan_tmp_bytes(ids));
     rc |= ensure(c.nb_scratch, z.nb_grid * z.nb_words * 4);
     rc |= ensure(c.t_garena, z.grid_g * z.garena_words * 4);
@@ -765,7 +770,7 @@ int lists_reserve(PhaseCtx& c, const PhaseShape& z) {
 // ... for the temporal family: HGT_ENOMEM leaves it to the 2-hop kernels.
 int paths_reserve(PhaseCtx& c, const PhaseShape& z) {
     if (!z.tmp_lists) return HGT_ENOMEM;
-    int rc = lists_reserve(c, z);
+    int rc = lists_reserve(c, z, true);
     rc |= ensure(c.p_list0, z.total_ids * 4);
     rc |= ensure(c.p_list1, z.total_ids * 4);
     rc |= ensure(c.p_scratch, kPathGrid * kPathWords * 4);
@@ -788,7 +793,7 @@ int phase_reserve(PhaseCtx& c, int family, const PhaseShape& z) {
     rc |= ensure(c.t_slices, (n + 2) * 8);
     rc |= ensure(c.t_slice_scan, hgt_scan_tmp_bytes(n));
     if (family == HGT_TRIAD_HYPEREDGE) {
-        rc |= lists_reserve(c, z);
+        rc |= lists_reserve(c, z, false);
     }
     return rc ? HGT_ENOMEM : HGT_OK;
 }
@@ -868,7 +873,6 @@ int run_phase(hgt_graph* owner, const PhaseJob* jobs, uint32_t nj, bool minus, b
             E.tmp_tab = P.tmp_tab;
             E.bl_off = c.bl_off.as<uint64_t>();
             E.bl_cnt = c.bl_cnt.as<uint64_t>();
-            E.bl_d = c.bl_d.as<uint32_t>();
             E.bl_pay = c.bl_pay.as<uint64_t>();
             E.queue = ctr + 16;
             E.count = ctr + 19;
@@ -2039,8 +2043,10 @@ namespace {
 // best choice's is dropped, and once every remaining choice has kTuneTrials
 // trials the fastest (by its quickest trial) is kept for the key and appended
 // to the cache file, which later processes read first.
-constexpr TuneChoice kTune[] = {{2, 8192, 0},        {1, 8192, 0},        {2, 8192, 1u << 15}, {2, 8192, 1u << 17},
-                                {2, 32768, 0},       {2, 8192, 1u << 19}, {2, 8192, 1u << 21}};
+constexpr TuneChoice kTune[] = {{4, 1, 0, 2, 8192, 0},        {2, 1, 0, 1, 8192, 0},
+                                {8, 1, 0, 2, 8192, 1u << 15}, {4, 0, 0, 2, 8192, 1u << 17},
+                                {4, 1, 0, 2, 32768, 0},       {4, 1, 1u << 18, 2, 8192, 1u << 19},
+                                {4, 1, 1u << 21, 2, 8192, 1u << 21}};
 constexpr int kTuneN = (int)(sizeof(kTune) / sizeof(kTune[0]));
 constexpr int kTuneTrials = 2;
 constexpr float kTuneDrop = 1.25f;
@@ -2087,9 +2093,9 @@ uint64_t tune_key(const std::vector<Pending*>& ps, int n_cu) {
            ((uint64_t)(ilog2_bucket(lh) / 2) << 8);
 }
 
-// Cache file: one line per settled key, "key choice wg_per_cu 0 wave_slots
-// slice_pairs best_ms"; lines whose choice does not match this library's table are
-// ignored.
+// Cache file: one line per settled key, "key choice file_wg file_skip wave_slots file_e2
+// best_ms", the form and the numbers that earlier libraries wrote, whose lines stay good;
+// lines whose choice does not match this library's table are ignored.
 void tune_load(Tuner& T) {
     if (T.loaded) return;
     T.loaded = true;
@@ -2110,8 +2116,8 @@ void tune_load(Tuner& T) {
     unsigned slots;
     float ms;
     while (std::fscanf(f, "%llx %d %d %d %u %llu %f", &key, &choice, &wg, &skip, &slots, &e2, &ms) == 7) {
-        if (choice < 0 || choice >= kTuneN || kTune[choice].wg_per_cu != wg || skip != 0 ||
-            kTune[choice].wave_slots != slots || kTune[choice].slice_pairs != e2)
+        if (choice < 0 || choice >= kTuneN || kTune[choice].file_wg != wg || kTune[choice].file_skip != skip ||
+            kTune[choice].wave_slots != slots || kTune[choice].file_e2 != e2)
             continue;
         TuneEntry& t = T.tab[(uint64_t)key];
         t.pick = choice;
@@ -2136,8 +2142,8 @@ void tune_settle(Tuner& T, uint64_t key, TuneEntry& t) {
     if (T.path.empty()) return;
     if (FILE* f = std::fopen(T.path.c_str(), "a")) {
         const TuneChoice& c = kTune[best];
-        std::fprintf(f, "%llx %d %d 0 %u %llu %.4f\n", (unsigned long long)key, best, c.wg_per_cu, c.wave_slots,
-                     (unsigned long long)c.slice_pairs, t.best_ms[best]);
+        std::fprintf(f, "%llx %d %d %d %u %llu %.4f\n", (unsigned long long)key, best, c.file_wg, c.file_skip, c.wave_slots,
+                     (unsigned long long)c.file_e2, t.best_ms[best]);
         std::fclose(f);
     }
 }

@@ -130,7 +130,6 @@ struct He2Params {
     const uint8_t* tmp_tab;      // the temporal kernels'
     const uint64_t* bl_off;      // per ID slot: batch-neighbour list of x
     const uint64_t* bl_cnt;
-    const uint32_t* bl_d;
     const uint64_t* bl_pay;
     uint32_t* queue;             // per stage (3 consecutive counters)
     uint32_t* count;             // items moved on by each stage (3 consecutive)
