@@ -154,6 +154,11 @@ __device__ __forceinline__ void nbr_pass_body(const NbrParams& P, uint32_t* aren
     __shared__ Sh2 sh;
     __shared__ uint32_t c_gi[NBR_TAKE], c_h[NBR_TAKE], c_rank[NBR_TAKE], c_lh[NBR_TAKE];
     __shared__ uint64_t c_off[NBR_TAKE];
+    // An inserted hyperedge's own histogram, as far as it goes here: nearly all neighbours share
+    // one or two members with it, so their additions meet at a few words (50k inserts and 50k
+    // deletions on 2M hyperedges, additions in global memory: 1.74 ms for both, here 1.09).
+    constexpr uint32_t OWN = 128;
+    __shared__ uint32_t own[OWN];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint64_t n = BIG ? (uint64_t)*P.big_count : P.M.total;
     uint32_t take = BIG ? 1 : take_size(n, gridDim.x, 4);
@@ -232,6 +237,7 @@ __device__ __forceinline__ void nbr_pass_body(const NbrParams& P, uint32_t* aren
         uint64_t* voff = (uint64_t*)(pre + ((hlen + 2) & ~1u));
         if (((uintptr_t)voff & 7) != 0) voff = (uint64_t*)((uint32_t*)voff + 1);
         if (tid == 0) sh.K = 0;
+        if (tid < (int)OWN) own[tid] = 0;
         (void)member_prefix(G.g, hoff, hlen, pre, voff, sh.ws);
         for (uint32_t s = tid; s < cap; s += HGT_WG) { keys[s] = HGT_EMPTY; vals[s] = 0; }
         __syncthreads();
@@ -260,13 +266,16 @@ __device__ __forceinline__ void nbr_pass_body(const NbrParams& P, uint32_t* aren
             }
             if (P.inserting) {
                 uint32_t lx = G.g.h_len[x];
-                atomicAdd(&hd[2 * (c - 1) + (lx > c ? 1u : 0u)], 1u);
+                const uint32_t w = 2 * (c - 1) + (lx > c ? 1u : 0u);
+                if (w < OWN) atomicAdd(&own[w], 1u);
+                else atomicAdd(&hd[w], 1u);
                 // an inserted neighbour builds its own histogram, this one included
                 if ((uint32_t)(G.mark[x] >> 32) != G.epoch)
                     atomicAdd(&G.hpool[2 * G.g.h_off[x] + 2 * (c - 1) + fd], 1u);
             }
         }
         __syncthreads();
+        if (P.inserting && tid < (int)OWN && own[tid]) atomicAdd(&hd[tid], own[tid]);
         // neighbours met at several members took one entry: the rest of the range is void
         if (P.emit_entries)
             for (uint64_t q = ebase + sh.K + tid; q < ebase + lh - hlen; q += HGT_WG)
