@@ -702,6 +702,7 @@ struct PhaseShape {
     BigLayout L;
     uint64_t grid_big, grid_small, grid_tmp, grid_2hop, grid_s0, grid_s1, grid_g, garena_words, nb_grid, nb_words;
     uint32_t wave_slots;
+    bool wide_s1 = false;  // few centres: stage 1 by wide workgroups
     bool tmp_lists;  // temporal: open paths per middle hyperedge, from batch-neighbour lists
 };
 
@@ -733,7 +734,8 @@ PhaseShape phase_shape(const hgt_graph* owner, uint64_t n, uint64_t max_lh, uint
     z.nb_words = 2 * pow2ceil64(2 * std::max<uint64_t>(z.lhm, 32)) + 3 * z.max_card + 8;
     z.nb_grid = std::max<uint64_t>(1, std::min<uint64_t>(lean ? 8 : 256, (1ull << 27) / z.nb_words));
     z.grid_s0 = std::min<uint64_t>(n_cu * 4, n);
-    z.grid_s1 = std::min<uint64_t>(n_cu * 2, 64 * n);
+    z.wide_s1 = n <= n_cu * 2;  // both sides measured where the stages' sizes stand (triad_he2.hip)
+    z.grid_s1 = std::min<uint64_t>(z.wide_s1 ? n_cu : n_cu * 2, 64 * n);
     // the global stage: workgroups of 512 threads, two per CU (their counters take
     // 65 KB of LDS); a dense centre is shared by up to 64 of them
     const int wg_per_cu = t_tune ? t_tune->wg_per_cu : owner->global_wg_per_cu;
@@ -909,7 +911,7 @@ int run_phase(hgt_graph* owner, const PhaseJob* jobs, uint32_t nj, bool minus, b
             E.static_mode = full ? 1 : 0;
             {
                 ProfScope ps(owner, PK_DELTA_SMALL, s);
-                he2_launch_lds(E, (unsigned)z.grid_s0, (unsigned)z.grid_s1, s);
+                he2_launch_lds(E, (unsigned)z.grid_s0, (unsigned)z.grid_s1, z.wide_s1, s);
             }
             {
                 ProfScope ps(owner, PK_DELTA_GLOBAL, s);
@@ -954,7 +956,7 @@ int run_phase(hgt_graph* owner, const PhaseJob* jobs, uint32_t nj, bool minus, b
                 T.stats = Q.stats;
                 tmp_paths_launch(T, (unsigned)owner->n_cu, kPathGrid, s);
                 He2Params E = stages(Q.stats);
-                tmp_launch_lds(E, (unsigned)z.grid_s0, (unsigned)z.grid_s1, s);
+                tmp_launch_lds(E, (unsigned)z.grid_s0, (unsigned)z.grid_s1, z.wide_s1, s);
                 tmp_launch_global(E, (unsigned)z.grid_g, s);
                 Q.paths_apart = 1;
                 Q.big_count = ctr + 21;

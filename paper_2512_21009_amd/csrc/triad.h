@@ -174,10 +174,11 @@ void he2_lists_build(NbrParams& P, uint64_t* bl_cnt, uint64_t* bl_off, uint64_t*
                      uint64_t* bl_pay, void* scan_tmp, hipStream_t s);
 // after the deletion phase: take the deleted hyperedges out of their neighbours' histograms
 void he2_remove_deleted(NbrParams& P, hipStream_t s);
-void he2_launch_lds(He2Params& P, unsigned grid, unsigned grid_mid, hipStream_t s);
+// wide: stage 1 by workgroups of twice the threads and tables, one per CU (few centres)
+void he2_launch_lds(He2Params& P, unsigned grid, unsigned grid_mid, bool wide, hipStream_t s);
 void he2_launch_global(He2Params& P, unsigned grid, hipStream_t s);  // counts the slices first
 // the same stages for the temporal triples inside the centres' neighbourhoods
-void tmp_launch_lds(He2Params& P, unsigned grid, unsigned grid_mid, hipStream_t s);
+void tmp_launch_lds(He2Params& P, unsigned grid, unsigned grid_mid, bool wide, hipStream_t s);
 void tmp_launch_global(He2Params& P, unsigned grid, hipStream_t s);
 
 // incident-vertex family

@@ -41,12 +41,16 @@ using namespace tri;
 
 // Stage 0: 24 KB of LDS tables, 256 threads, four workgroups per CU.  Stage 1: 54 KB, 512
 // threads, two workgroups per CU (one of 1024 threads and 118 KB: 6.6 ms against 3.5 for the
-// centres of 100k changes on 2M hyperedges that stage 0 moves on, 1.1 against 0.5 + 1.6 with
-// stage 2 for 100 dense ones).  Stage 2 (the global stage): tables in global memory, 512
+// centres of 100k changes on 2M hyperedges that stage 0 moves on), unless the launch has at
+// most two centres per CU: then that one large workgroup, which has the CU to itself anyhow
+// and keeps denser centres out of global memory (stages 1 and 2 of 100 + 100 changes among
+// 1,000 hyperedges 2.44 -> 1.08 ms, of one change 0.21 -> 0.15; of 2,000 + 2,000 on 36,000,
+// where the rule says no, 5.43 against 5.72 ms).  Stage 2 (the global stage): tables in global memory, 512
 // threads, two workgroups per CU.
 constexpr uint32_t ARENA_S = 6144;
 constexpr uint32_t ARENA_M = 13824;
-constexpr int WG_M = 512, WG_L = 512;
+constexpr uint32_t ARENA_W = 30208;
+constexpr int WG_M = 512, WG_L = 512, WG_W = 1024;
 constexpr uint32_t CNT_L = 1536;       // stage 2: counter words per wave
 constexpr uint32_t LDS_L = 12800;      // ... LDS words: counters of 8 waves, or bitmaps, or a (c, f) histogram
 static_assert(LDS_L >= (WG_L / 64) * CNT_L, "global stage LDS");
@@ -93,7 +97,7 @@ struct Sh2 {
     uint32_t gi, cur_g, skip;
     uint32_t slice, nslice;
     uint64_t hoff;
-    uint32_t ws[WG_M / 64];
+    uint32_t ws[WG_W / 64];
     uint32_t ncap, G;
     uint64_t g[8];
 };
@@ -1376,6 +1380,10 @@ __device__ __forceinline__ void he2_kernel(const He2Params& P, uint32_t* arena, 
         __shared__ __attribute__((aligned(16))) uint32_t arena[ARENA_M];                                        \
         he2_kernel<1, WG_M, TMP>(P, arena, ARENA_M, nullptr);                                                   \
     }                                                                                                           \
+    __global__ void __launch_bounds__(WG_W, 4) NAME##_s1w(He2Params P) {                                        \
+        __shared__ __attribute__((aligned(16))) uint32_t arena[ARENA_W];                                        \
+        he2_kernel<1, WG_W, TMP>(P, arena, ARENA_W, nullptr);                                                   \
+    }                                                                                                           \
     __global__ void __launch_bounds__(WG_L, 4) NAME##_s2(He2Params P) {                                         \
         __shared__ __attribute__((aligned(16))) uint32_t lds[LDS_L];                                            \
         he2_kernel<2, WG_L, TMP>(P, P.garena + (uint64_t)blockIdx.x * P.garena_words, (uint32_t)P.garena_words, \
@@ -1511,7 +1519,7 @@ void he2_remove_deleted(NbrParams& P, hipStream_t s) {
 namespace {
 
 // Stages 1 and 2: each cuts the centres that the stage before moved on.
-void launch_sliced(He2Params& P, int stage, unsigned grid, bool tmp, hipStream_t s) {
+void launch_sliced(He2Params& P, int stage, unsigned grid, bool wide, bool tmp, hipStream_t s) {
     if (!P.M.total) return;
     const uint64_t cap = P.slice_cap;
     const unsigned waves = (unsigned)((cap + 3) / 4);
@@ -1519,7 +1527,10 @@ void launch_sliced(He2Params& P, int stage, unsigned grid, bool tmp, hipStream_t
     k_he2_work<<<waves < 1024 ? waves : 1024, 256, 0, s>>>(P.M, P.list[stage - 1], &P.count[stage - 1], cap, P.slice_lh,
                                                            tmp ? 1 : 0, P.slice_pre, total);
     k_he2_cut<<<1, 1024, 0, s>>>(cap, P.slice_lh, P.slice_pairs, grid, total, P.slice_pre);
-    if (stage == 1) {
+    if (stage == 1 && wide) {
+        if (tmp) k_tmp_s1w<<<grid, WG_W, 0, s>>>(P);
+        else k_he2_s1w<<<grid, WG_W, 0, s>>>(P);
+    } else if (stage == 1) {
         if (tmp) k_tmp_s1<<<grid, WG_M, 0, s>>>(P);
         else k_he2_s1<<<grid, WG_M, 0, s>>>(P);
     } else {
@@ -1530,14 +1541,14 @@ void launch_sliced(He2Params& P, int stage, unsigned grid, bool tmp, hipStream_t
 
 }  // namespace
 
-void he2_launch_lds(He2Params& P, unsigned grid, unsigned grid_mid, hipStream_t s) {
+void he2_launch_lds(He2Params& P, unsigned grid, unsigned grid_mid, bool wide, hipStream_t s) {
     if (P.M.total) k_he2_s0<<<grid, HGT_WG, 0, s>>>(P);
-    launch_sliced(P, 1, grid_mid, false, s);
+    launch_sliced(P, 1, grid_mid, wide, false, s);
 }
-void he2_launch_global(He2Params& P, unsigned grid, hipStream_t s) { launch_sliced(P, 2, grid, false, s); }
+void he2_launch_global(He2Params& P, unsigned grid, hipStream_t s) { launch_sliced(P, 2, grid, false, false, s); }
 
-void tmp_launch_lds(He2Params& P, unsigned grid, unsigned grid_mid, hipStream_t s) {
+void tmp_launch_lds(He2Params& P, unsigned grid, unsigned grid_mid, bool wide, hipStream_t s) {
     if (P.M.total) k_tmp_s0<<<grid, HGT_WG, 0, s>>>(P);
-    launch_sliced(P, 1, grid_mid, true, s);
+    launch_sliced(P, 1, grid_mid, wide, true, s);
 }
-void tmp_launch_global(He2Params& P, unsigned grid, hipStream_t s) { launch_sliced(P, 2, grid, true, s); }
+void tmp_launch_global(He2Params& P, unsigned grid, hipStream_t s) { launch_sliced(P, 2, grid, false, true, s); }
