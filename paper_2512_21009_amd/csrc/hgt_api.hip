@@ -150,12 +150,19 @@ struct TuneChoice {
 thread_local const TuneChoice* t_tune = nullptr;
 thread_local hipEvent_t t_tune_ev[2] = {nullptr, nullptr};  // recorded around an autotuned round's launches
 
+// HGT_ALLOC_MAX=bytes (tests): a device allocation above it fails as if memory had run out.
+bool alloc_refused(size_t bytes) {
+    const char* m = std::getenv("HGT_ALLOC_MAX");
+    return m && *m && bytes > std::strtoull(m, nullptr, 10);
+}
+
 int dev_alloc(DevBuf& b, size_t bytes) {
     if (t_na) {  // the no-allocation entry point allocates nothing
         if (debug_on()) std::fprintf(stderr, "hgt: allocation of %zu bytes refused (no-allocation call)\n", bytes);
         return HGT_ENOMEM;
     }
     if (bytes == 0) bytes = 256;
+    if (alloc_refused(bytes)) return HGT_ENOMEM;
     void* p = nullptr;
     if (hip_failed(hipMalloc(&p, bytes), "hipMalloc", __LINE__)) return HGT_ENOMEM;
     b.p = p;
@@ -588,6 +595,29 @@ struct PhaseJob {
 
 inline size_t desc_slot_bytes(uint64_t cap) { return cap * sizeof(HeGraph) + 2 * (cap + 1) * 8; }
 
+// Room for the descriptors of n graphs in every slot.
+int desc_reserve(PhaseCtx& c, uint64_t n, hipStream_t s) {
+    if (t_na) return ensure(c.desc, 4 * desc_slot_bytes(1));
+    if (n <= c.desc_cap) return HGT_OK;
+    for (hipEvent_t e : c.desc_ev)
+        if (e) HIP_OK(hipEventSynchronize(e));
+    HIP_OK(hipStreamSynchronize(s));
+    uint64_t cap = std::max<uint64_t>(n, 2 * c.desc_cap);
+    cap = std::max<uint64_t>(cap, 4);
+    if (c.desc_host) (void)hipHostFree(c.desc_host);
+    c.desc_host = nullptr;
+    c.desc_cap = 0;
+    if (hipHostMalloc((void**)&c.desc_host, 4 * desc_slot_bytes(cap), hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        c.desc_host = nullptr;
+        return HGT_ENOMEM;
+    }
+    dev_free(c.desc);
+    if (dev_alloc(c.desc, 4 * desc_slot_bytes(cap))) return HGT_ENOMEM;
+    c.desc_cap = cap;
+    return HGT_OK;
+}
+
 // Uploads the descriptors of `G` into slot `slot` and fills M's device pointers.
 int upload_multi(PhaseCtx& c, int slot, const std::vector<HeGraph>& G, const std::vector<uint64_t>& base,
                  const std::vector<uint64_t>& id_base, Multi& M, hipStream_t s) {
@@ -602,7 +632,6 @@ int upload_multi(PhaseCtx& c, int slot, const std::vector<HeGraph>& G, const std
         // staged from the thread's arena record; the stream orders the copies
         static_assert(sizeof(HeGraph) + 32 <= sizeof(t_na->stage[0]), "descriptor staging");
         if (n != 1) return HGT_EINVAL;
-        if (int rc = ensure(c.desc, 4 * desc_slot_bytes(1))) return rc;
         char* h = t_na->stage[slot];
         char* d = (char*)c.desc.p + slot * desc_slot_bytes(1);
         const size_t bytes = sizeof(HeGraph) + 32;
@@ -618,24 +647,7 @@ int upload_multi(PhaseCtx& c, int slot, const std::vector<HeGraph>& G, const std
         M.total_ids = id_base[1];
         return HGT_OK;
     }
-    if (n > c.desc_cap) {
-        for (hipEvent_t e : c.desc_ev)
-            if (e) HIP_OK(hipEventSynchronize(e));
-        HIP_OK(hipStreamSynchronize(s));
-        uint64_t cap = std::max<uint64_t>(n, 2 * c.desc_cap);
-        cap = std::max<uint64_t>(cap, 4);
-        if (c.desc_host) (void)hipHostFree(c.desc_host);
-        c.desc_host = nullptr;
-        c.desc_cap = 0;
-        if (hipHostMalloc((void**)&c.desc_host, 4 * desc_slot_bytes(cap), hipHostMallocDefault) != hipSuccess) {
-            (void)hipGetLastError();
-            c.desc_host = nullptr;
-            return HGT_ENOMEM;
-        }
-        dev_free(c.desc);
-        if (dev_alloc(c.desc, 4 * desc_slot_bytes(cap))) return HGT_ENOMEM;
-        c.desc_cap = cap;
-    }
+    if (n > c.desc_cap) return HGT_EINVAL;  // reserved before (desc_reserve)
     if (!c.desc_ev[slot] && hipEventCreateWithFlags(&c.desc_ev[slot], hipEventDisableTiming) != hipSuccess) {
         c.desc_ev[slot] = nullptr;
         return HGT_EDEVICE;
@@ -748,35 +760,59 @@ PhaseShape phase_shape(const hgt_graph* owner, uint64_t n, uint64_t max_lh, uint
     return z;
 }
 
-// The batch-neighbour lists (tmp: that name the changed hyperedges), and the tables of the
-// stages that use them.
-int lists_reserve(PhaseCtx& c, const PhaseShape& z, bool tmp) {
+struct Room {
+    DevBuf* b;
+    uint64_t bytes;
+};
+struct Rooms {
+    Room r[16];
+    int n = 0;
+    void add(DevBuf& b, uint64_t bytes) { r[n++] = {&b, bytes}; }
+};
+
+// The batch-neighbour lists (tmp: that name the changed hyperedges, for the open paths of the
+// temporal family), and the tables of the stages that use them.
+Rooms lists_rooms(PhaseCtx& c, const PhaseShape& z, bool tmp) {
     const uint64_t ids = z.total_ids;
-    int rc = 0;
-    rc |= ensure(c.ent_x, z.ecap * 4);
-    rc |= ensure(c.ent_d, z.ecap * 4);
-    rc |= ensure(c.ent_pay, z.ecap * 8);
-    rc |= ensure(c.bl_pay, z.ecap * 8);
-    rc |= ensure(c.bl_cnt, ids * 8);
-    rc |= ensure(c.bl_off, ids * 8);
+    Rooms R;
+    R.add(c.ent_x, z.ecap * 4);
+    R.add(c.ent_d, z.ecap * 4);
+    R.add(c.ent_pay, z.ecap * 8);
+    R.add(c.bl_pay, z.ecap * 8);
+    R.add(c.bl_cnt, ids * 8);
+    R.add(c.bl_off, ids * 8);
+    R.add(c.bl_scan, hgt_scan_tmp_bytes(ids));
+    R.add(c.nb_scratch, z.nb_grid * z.nb_words * 4);
+    R.add(c.t_garena, z.grid_g * z.garena_words * 4);
     if (tmp) {
-        rc |= ensure(c.bl_d, z.ecap * 4);
-        rc |= ensure(c.bl_cur, ids * 8);
+        R.add(c.bl_d, z.ecap * 4);
+        R.add(c.bl_cur, ids * 8);
+        R.add(c.p_list0, ids * 4);
+        R.add(c.p_list1, ids * 4);
+        R.add(c.p_scratch, kPathGrid * kPathWords * 4);
     }
-    rc |= ensure(c.bl_scan, hgt_scan_tmp_bytes(ids));
-    rc |= ensure(c.nb_scratch, z.nb_grid * z.nb_words * 4);
-    rc |= ensure(c.t_garena, z.grid_g * z.garena_words * 4);
-    return rc ? HGT_ENOMEM : HGT_OK;
+    return R;
 }
 
-// ... for the temporal family: HGT_ENOMEM leaves it to the 2-hop kernels.
-int paths_reserve(PhaseCtx& c, const PhaseShape& z) {
-    if (!z.tmp_lists) return HGT_ENOMEM;
-    int rc = lists_reserve(c, z, true);
-    rc |= ensure(c.p_list0, z.total_ids * 4);
-    rc |= ensure(c.p_list1, z.total_ids * 4);
-    rc |= ensure(c.p_scratch, kPathGrid * kPathWords * 4);
-    return rc ? HGT_ENOMEM : HGT_OK;
+int lists_reserve(PhaseCtx& c, const PhaseShape& z, bool tmp) {
+    const Rooms R = lists_rooms(c, z, tmp);
+    for (int i = 0; i < R.n; i++)
+        if (ensure(*R.r[i].b, R.r[i].bytes)) return HGT_ENOMEM;
+    return HGT_OK;
+}
+
+void lists_free(PhaseCtx& c) {
+    const Rooms R = lists_rooms(c, PhaseShape{}, true);
+    for (int i = 0; i < R.n; i++) dev_free(*R.r[i].b);
+}
+
+// Whether the temporal family's lists have their room; without it, the 2-hop kernels run.
+bool paths_fit(PhaseCtx& c, const PhaseShape& z) {
+    if (!z.tmp_lists) return false;
+    const Rooms R = lists_rooms(c, z, true);
+    for (int i = 0; i < R.n; i++)
+        if (!R.r[i].b->p || R.r[i].b->bytes < R.r[i].bytes) return false;
+    return true;
 }
 
 // Every scratch buffer of one family's phase at the shape's sizes.
@@ -794,14 +830,13 @@ int phase_reserve(PhaseCtx& c, int family, const PhaseShape& z) {
     rc |= ensure(c.t_whash, z.grid_2hop * 4 * 2ull * z.wave_slots * 4);
     rc |= ensure(c.t_slices, (n + 2) * 8);
     rc |= ensure(c.t_slice_scan, hgt_scan_tmp_bytes(n));
-    if (family == HGT_TRIAD_HYPEREDGE) {
-        rc |= lists_reserve(c, z, false);
-    }
+    if (family == HGT_TRIAD_HYPEREDGE) rc |= lists_reserve(c, z, false);
     return rc ? HGT_ENOMEM : HGT_OK;
 }
 
 // One phase (deltas of the deleted hyperedges on the old graphs, or of the
-// inserted ones on the new graphs) for every job, in one launch per kernel.
+// inserted ones on the new graphs) for every job, in one launch per kernel.  Allocates
+// nothing: the scratch of both phases was reserved before the batch began.
 // Counter slots in t_ctr: 0-2 neighbour pass, 5 2-hop queue for the centres the
 // histogram stages pass on, 6-8 temporal, 10-11 entry count, 16-18 stage queues,
 // 19-21 stage hand-over counts, 24-27 the estimated work of stages 1 and 2, 32-37 temporal
@@ -816,14 +851,11 @@ int run_phase(hgt_graph* owner, const PhaseJob* jobs, uint32_t nj, bool minus, b
         collect(jobs, nj, family, minus, G, base, id_base, max_lh, sum_lh);
         const uint64_t n = base.back();
         if (n == 0) continue;
-        if (id_base.back() > 0xfffffff0ull) return HGT_EINVAL;  // entry slots are u32
         const PhaseShape z = phase_shape(owner, n, max_lh, sum_lh, id_base.back(), t_na != nullptr);
-        int rc = phase_reserve(c, family, z);
-        if (rc) return rc;
         const BigLayout& L = z.L;
         const uint64_t grid_big = z.grid_big;
         Multi M{};
-        rc = upload_multi(c, (minus ? 0 : 2) + (family == HGT_TRIAD_TEMPORAL ? 1 : 0), G, base, id_base, M, s);
+        int rc = upload_multi(c, (minus ? 0 : 2) + (family == HGT_TRIAD_TEMPORAL ? 1 : 0), G, base, id_base, M, s);
         if (rc) return rc;
         uint32_t* ctr = c.t_ctr.as<uint32_t>();
         TriadParams P{};
@@ -936,7 +968,7 @@ int run_phase(hgt_graph* owner, const PhaseJob* jobs, uint32_t nj, bool minus, b
             Q.do_tmp = 1;
             Q.stats = stats ? stats + ST_TMP0 : nullptr;
             ProfScope ps(owner, PK_TMP, s);
-            if (paths_reserve(c, z) == HGT_OK) {
+            if (paths_fit(c, z)) {
                 // open paths per middle hyperedge, then the triples inside the centres'
                 // neighbourhoods; centres too large for every arena: the 2-hop kernel
                 (void)neighbours(true);
@@ -1153,9 +1185,6 @@ int iv_reserve(hgt_graph* owner, uint64_t n_keys, uint32_t n_graphs) {
 int iv_phase(hgt_graph* owner, const std::vector<std::pair<hgt_graph*, const IvPlan*>>& gs, bool minus, hipStream_t s) {
     if (gs.empty()) return HGT_OK;
     PhaseCtx& c = ctx_of(owner);
-    uint64_t n_all = 0;
-    for (auto& [g, ip] : gs) n_all += ip->n_keys;
-    if (int rc = iv_reserve(owner, n_all, (uint32_t)gs.size())) return rc;
     ProfScope ps(gs[0].first, PK_IV_PAIRS, s);
     for (size_t from = 0; from < gs.size(); from += kIvJobs) {
         IvParams P{};
@@ -1435,18 +1464,18 @@ PhaseJob job_plus(const Pending& p) {
 }
 
 // Every scratch buffer of both phases, reserved before the first kernel that
-// changes the graph.  In a no-allocation call they come from the arena, so a
-// batch whose scratch does not fit is rejected with nothing changed.  With
-// upload set the descriptors of every (phase, family) are uploaded too (on
-// stream s, which may be the null stream), for a round that is then captured
-// into a HIP graph (a second pass if the descriptor buffer had to grow under the
-// first, which moves it).
-int reserve_all_phases(hgt_graph* owner, std::vector<Pending*>& ps, bool upload = false, hipStream_t s = nullptr) {
+// changes the graph, so a batch whose scratch does not fit is rejected with nothing
+// changed.  (In a no-allocation call they come from the arena.)  With upload set the
+// descriptors of every (phase, family) are uploaded too (on stream s, which may be
+// the null stream), for a round that is then captured into a HIP graph.
+int reserve_all_phases(hgt_graph* owner, std::vector<Pending*>& ps, bool upload, hipStream_t s) {
     PhaseCtx& c = ctx_of(owner);
     std::vector<HeGraph> G;
     std::vector<uint64_t> base, id_base;
-    const uint64_t cap0 = c.desc_cap;
+    PhaseShape shape[2][2];  // by phase: of the hyperedge family, of the temporal one
+    bool lists[2][2] = {};   // which of them use lists
     for (int slot = 0; slot < 4; slot++) c.pre_ok[slot] = false;
+    if (int rc = desc_reserve(c, ps.size(), s)) return rc;
     for (int phase = 0; phase < 2; phase++) {
         std::vector<PhaseJob> jobs;
         for (Pending* p : ps) jobs.push_back(phase == 0 ? job_minus(*p) : job_plus(*p));
@@ -1454,22 +1483,33 @@ int reserve_all_phases(hgt_graph* owner, std::vector<Pending*>& ps, bool upload 
             uint64_t max_lh, sum_lh;
             collect(jobs.data(), (uint32_t)jobs.size(), family, phase == 0, G, base, id_base, max_lh, sum_lh);
             if (base.back() == 0) continue;
+            if (id_base.back() > 0xfffffff0ull) return HGT_EINVAL;  // entry slots are u32
             const PhaseShape z = phase_shape(owner, base.back(), max_lh, sum_lh, id_base.back(), t_na != nullptr);
             if (int rc = phase_reserve(c, family, z)) return rc;
-            if (family == HGT_TRIAD_TEMPORAL) (void)paths_reserve(c, z);
+            const int f = family == HGT_TRIAD_TEMPORAL ? 1 : 0;
+            shape[phase][f] = z;
+            lists[phase][f] = f == 0 || z.tmp_lists;
             if (upload) {
-                const int slot = (phase == 0 ? 0 : 2) + (family == HGT_TRIAD_TEMPORAL ? 1 : 0);
+                const int slot = 2 * phase + f;
                 if (int rc = upload_multi(c, slot, G, base, id_base, c.pre[slot], s)) return rc;
                 c.pre_ok[slot] = true;
             }
         }
     }
-    if (upload && c.desc_cap != cap0) return reserve_all_phases(owner, ps, upload, s);
-    if (t_na)
-        if (int rc = ensure(c.desc, 4 * desc_slot_bytes(1))) return rc;
     uint64_t n_keys = 0;
     for (Pending* p : ps) n_keys += p->ip.n_keys;
-    if (n_keys) return iv_reserve(owner, n_keys, (uint32_t)ps.size());
+    if (n_keys)
+        if (int rc = iv_reserve(owner, n_keys, (uint32_t)ps.size())) return rc;
+    // last, what the batch can do without: where the temporal family's lists do not fit, what
+    // they took goes back, and the buffers they share with the hyperedge family are its again
+    for (int phase = 0; phase < 2; phase++) {
+        if (!lists[phase][1] || lists_reserve(c, shape[phase][1], true) == HGT_OK) continue;
+        lists_free(c);
+        for (int q = 0; q < 2; q++)
+            if (lists[q][0])
+                if (int rc = lists_reserve(c, shape[q][0], false)) return rc;
+        break;
+    }
     return HGT_OK;
 }
 
@@ -1489,7 +1529,7 @@ bool fault_injected() {
 // have been queued: a failure after that leaves the graphs of `ps` part-way.
 int apply_locked(hgt_graph* owner, std::vector<Pending*>& ps, hipStream_t s, bool* began) {
     int rc;
-    if (t_na && (rc = reserve_all_phases(owner, ps))) return rc;
+    if (!t_capture && (rc = reserve_all_phases(owner, ps, false, s))) return rc;
     *began = true;
     std::vector<PhaseJob> jobs;
     jobs.reserve(ps.size());

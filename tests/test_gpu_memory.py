@@ -1,0 +1,77 @@
+"""GPU tests of scratch that cannot be allocated.
+
+HGT_ALLOC_MAX=bytes makes every larger device allocation of the library fail on
+the host, as if memory had run out; no kernel runs without its buffers.
+"""
+import numpy as np
+import pytest
+
+from paper_2512_21009_amd import workloads as W
+
+from .gpu_harness import Pair, compare_counts, compare_store
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("route", ["batch", "round", "graph"])
+def test_scratch_that_does_not_fit_refuses_the_batch(gpu_lib, monkeypatch, route):
+    """40 hyperedges built, then 20 deletions and 600 insertions whose 2-hop tables
+    (8 MB) are refused after the batch was planned: HGT_ENOMEM, the graph as it was and
+    not poisoned; with the memory back the same batch matches the oracle."""
+    import torch
+    hgt = gpu_lib
+    st = W.plain_stream("refused", 60, 40, ("uniform", 6, 6), 0.0, 0.0, 1, 600, 20, W.SEED_BASE + 160)
+    p = Pair(st, track=("hyperedge",))
+    args, finish = p.prepare(st.batches[0], "refused")
+
+    def apply():
+        if route == "batch":
+            return p.g.apply_batch(*args, raise_on_error=False)
+        rc, status, outs = hgt.apply_batches([(p.g,) + args], raise_on_error=False, graph=route == "graph")
+        assert status == [rc]
+        return rc, outs[0]
+
+    monkeypatch.setenv("HGT_ALLOC_MAX", str(4 << 20))
+    rc, _ = apply()
+    assert rc == hgt.ENOMEM
+    compare_store(p.g, p.o, "refused")
+    compare_counts(p.g, p.o, p.track, "refused")
+    monkeypatch.delenv("HGT_ALLOC_MAX")
+    rc, out = apply()
+    torch.cuda.synchronize()
+    assert rc == hgt.OK
+    finish(out)
+    compare_store(p.g, p.o, "applied")
+    compare_counts(p.g, p.o, p.track, "applied")
+    p.close()
+
+
+def test_temporal_lists_that_do_not_fit(gpu_lib, monkeypatch):
+    """The lists of the temporal family (4 to 8 bytes a column and entry of 29M) refused at
+    the first column and at the third: the 2-hop kernels give the counts that the lists
+    give, and what was taken for the first columns is not kept."""
+    import torch
+    monkeypatch.setenv("HGT_WAVE_SLOTS", "4096")  # per-wave hashes of 64 MB in all
+    st = W.temporal_stream("lists", 50, 1000, 9000, 1, 50.0, 4, 4, 100.0, 10**7, 800, W.SEED_BASE + 161)
+
+    def run(limit):
+        monkeypatch.setenv("HGT_ALLOC_MAX", str(limit))
+        torch.cuda.empty_cache()
+        free = torch.cuda.mem_get_info()[0]
+        p = Pair(W.Stream("lists", st.n_vertices, st.initial, window=st.window), track=("temporal",))
+        p.g.profile(True)
+        args, _ = p.prepare(st.batches[0], "lists")
+        p.g.apply_batch(*args)
+        counts = p.g.triad_counts("temporal")
+        held = free - torch.cuda.mem_get_info()[0]
+        expanded = p.g.profile_read()["temporal"]["events"]  # by the 2-hop kernels
+        p.close()
+        return counts, held, expanded
+
+    want, most, none = run(1 << 40)
+    one, held1, n1 = run(100 << 20)
+    three, held3, n3 = run(200 << 20)
+    assert sum(want) > 0 and one == want and three == want
+    assert none == 0 and n1 == n3 > 0
+    assert most > held1 + (700 << 20)
+    assert abs(held3 - held1) < 64 << 20, (held1, held3)
