@@ -783,7 +783,6 @@ Rooms lists_rooms(PhaseCtx& c, const PhaseShape& z, bool tmp) {
     R.add(c.bl_off, ids * 8);
     R.add(c.bl_scan, hgt_scan_tmp_bytes(ids));
     R.add(c.nb_scratch, z.nb_grid * z.nb_words * 4);
-    R.add(c.t_garena, z.grid_g * z.garena_words * 4);
     if (tmp) {
         R.add(c.bl_d, z.ecap * 4);
         R.add(c.bl_cur, ids * 8);
@@ -794,16 +793,45 @@ Rooms lists_rooms(PhaseCtx& c, const PhaseShape& z, bool tmp) {
     return R;
 }
 
+uint64_t free_memory() {
+    size_t free = 0, total = 0;
+    if (hip_failed(hipMemGetInfo(&free, &total), "hipMemGetInfo", __LINE__)) return 0;
+    return free;
+}
+
+// The workgroups that the global stage's arenas suffice for.
+uint64_t arenas_held(const PhaseCtx& c, const PhaseShape& z) {
+    return std::min<uint64_t>(z.grid_g, c.t_garena.bytes / (4 * z.garena_words));
+}
+
+// The arenas grow by at most a quarter of the free memory, and where an allocation fails all
+// the same to half as many, and so on: the stage runs with any number of them (512 are 2 GiB,
+// and a single changed hyperedge wants 64, since a dense one is shared by so many workgroups).
+int arenas_reserve(PhaseCtx& c, const PhaseShape& z) {
+    const uint64_t one = 4 * z.garena_words;
+    if (t_na) return ensure(c.t_garena, z.grid_g * one);
+    const uint64_t held = arenas_held(c, z);
+    if (held == z.grid_g) return HGT_OK;
+    uint64_t n = std::min(z.grid_g, std::max<uint64_t>(1, held + free_memory() / 4 / one));
+    if (n <= held) return HGT_OK;
+    while (ensure(c.t_garena, n * one)) {
+        if (n == 1) return HGT_ENOMEM;
+        n /= 2;
+    }
+    return HGT_OK;
+}
+
 int lists_reserve(PhaseCtx& c, const PhaseShape& z, bool tmp) {
     const Rooms R = lists_rooms(c, z, tmp);
     for (int i = 0; i < R.n; i++)
         if (ensure(*R.r[i].b, R.r[i].bytes)) return HGT_ENOMEM;
-    return HGT_OK;
+    return arenas_reserve(c, z);
 }
 
 void lists_free(PhaseCtx& c) {
     const Rooms R = lists_rooms(c, PhaseShape{}, true);
     for (int i = 0; i < R.n; i++) dev_free(*R.r[i].b);
+    dev_free(c.t_garena);
 }
 
 // Whether the temporal family's lists have their room; without it, the 2-hop kernels run.
@@ -812,7 +840,7 @@ bool paths_fit(PhaseCtx& c, const PhaseShape& z) {
     const Rooms R = lists_rooms(c, z, true);
     for (int i = 0; i < R.n; i++)
         if (!R.r[i].b->p || R.r[i].b->bytes < R.r[i].bytes) return false;
-    return true;
+    return arenas_held(c, z) > 0;
 }
 
 // Every scratch buffer of one family's phase at the shape's sizes.
@@ -947,7 +975,7 @@ int run_phase(hgt_graph* owner, const PhaseJob* jobs, uint32_t nj, bool minus, b
             }
             {
                 ProfScope ps(owner, PK_DELTA_GLOBAL, s);
-                he2_launch_global(E, (unsigned)z.grid_g, s);
+                he2_launch_global(E, (unsigned)arenas_held(c, z), s);
             }
             // centres too large for every arena: the 2-hop kernel
             TriadParams B = P;
@@ -989,7 +1017,7 @@ int run_phase(hgt_graph* owner, const PhaseJob* jobs, uint32_t nj, bool minus, b
                 tmp_paths_launch(T, (unsigned)owner->n_cu, kPathGrid, s);
                 He2Params E = stages(Q.stats);
                 tmp_launch_lds(E, (unsigned)z.grid_s0, (unsigned)z.grid_s1, z.wide_s1, s);
-                tmp_launch_global(E, (unsigned)z.grid_g, s);
+                tmp_launch_global(E, (unsigned)arenas_held(c, z), s);
                 Q.paths_apart = 1;
                 Q.big_count = ctr + 21;
                 Q.big_queue = ctr + 5;

@@ -75,3 +75,20 @@ def test_temporal_lists_that_do_not_fit(gpu_lib, monkeypatch):
     assert none == 0 and n1 == n3 > 0
     assert most > held1 + (700 << 20)
     assert abs(held3 - held1) < 64 << 20, (held1, held3)
+
+
+@pytest.mark.parametrize("limit_mb", [5, 33])
+def test_fewer_arenas_where_memory_is_short(gpu_lib, monkeypatch, limit_mb):
+    """Batches whose centres all reach the global stage, with room for one of its arenas (4 MB
+    each, 512 at most) and for eight: fewer workgroups, the same counts."""
+    monkeypatch.setenv("HGT_ALLOC_MAX", str(limit_mb << 20))
+    monkeypatch.setenv("HGT_FORCE_STAGE", "2")
+    monkeypatch.setenv("HGT_WAVE_SLOTS", "64")
+    st = W.plain_stream("arenas", 90, 100, ("uniform", 1, 6), 0.0, 0.0, 2, 40, 50, W.SEED_BASE + 162)
+    p = Pair(st, track=("hyperedge",), pool_words=1 << 16)
+    compare_counts(p.g, p.o, p.track, "arenas build")
+    for k, b in enumerate(st.batches):
+        p.apply(b, f"arenas batch {k}")
+        compare_store(p.g, p.o, f"arenas batch {k}")
+        compare_counts(p.g, p.o, p.track, f"arenas batch {k}")
+    p.close()
