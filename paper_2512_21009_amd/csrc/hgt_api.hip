@@ -156,18 +156,24 @@ bool alloc_refused(size_t bytes) {
     return m && *m && bytes > std::strtoull(m, nullptr, 10);
 }
 
+bool scratch_release();
+
 int dev_alloc(DevBuf& b, size_t bytes) {
     if (t_na) {  // the no-allocation entry point allocates nothing
         if (debug_on()) std::fprintf(stderr, "hgt: allocation of %zu bytes refused (no-allocation call)\n", bytes);
         return HGT_ENOMEM;
     }
     if (bytes == 0) bytes = 256;
-    if (alloc_refused(bytes)) return HGT_ENOMEM;
-    void* p = nullptr;
-    if (hip_failed(hipMalloc(&p, bytes), "hipMalloc", __LINE__)) return HGT_ENOMEM;
-    b.p = p;
-    b.bytes = bytes;
-    return HGT_OK;
+    for (int pass = 0; pass < 2; pass++) {
+        void* p = nullptr;
+        if (!alloc_refused(bytes) && !hip_failed(hipMalloc(&p, bytes), "hipMalloc", __LINE__)) {
+            b.p = p;
+            b.bytes = bytes;
+            return HGT_OK;
+        }
+        if (pass == 0 && !scratch_release()) break;
+    }
+    return HGT_ENOMEM;
 }
 
 void dev_free(DevBuf& b) {
@@ -199,6 +205,12 @@ int arena_take(NoAllocArena& a, DevBuf& b, size_t bytes) {
     b.bytes = want;
     a.used += want;
     return HGT_OK;
+}
+
+// Gives the buffers their own values back (queued kernels keep using the arena regions
+// they were given; the arena is never freed).
+void arena_undo(NoAllocArena& a) {
+    for (; a.n_undo > 0; a.n_undo--) *a.undo[a.n_undo - 1].b = a.undo[a.n_undo - 1].old;
 }
 
 // grow-only scratch (contents not preserved)
@@ -545,7 +557,32 @@ void phase_ctx_free(PhaseCtx& c) {
 }
 
 std::mutex g_ctx_mu;
-std::vector<PhaseCtx*> g_ctx;  // by device
+std::vector<PhaseCtx*> g_ctx;      // by device
+std::vector<PhaseCtx*> g_ctx_all;  // these and the request server's
+thread_local PhaseCtx* t_locked = nullptr;  // the context whose lock this thread holds
+
+void lists_free(PhaseCtx& c);
+
+// When memory runs out: the lists and arenas of the device's contexts that no call holds are
+// given back.  They are the scratch that grows with a batch's neighbourhoods, up to tens of
+// gigabytes, and the next batch that wants them takes what is free then.
+bool scratch_release() {
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess) return false;
+    bool any = false;
+    std::lock_guard<std::mutex> lk(g_ctx_mu);
+    for (PhaseCtx* c : g_ctx_all) {
+        if (c->device != dev || c == t_locked || !c->mu.try_lock()) continue;
+        if (c->ent_x.p || c->t_garena.p) {
+            (void)hipEventSynchronize(c->done);
+            lists_free(*c);
+            any = true;
+        }
+        c->mu.unlock();
+    }
+    return any;
+}
+void ctx_forget(PhaseCtx* c) { g_ctx_all.erase(std::find(g_ctx_all.begin(), g_ctx_all.end(), c)); }
 
 // The phase scratch a call on this thread uses: the request server gives each
 // of its in-flight rounds its own, so their triad phases can overlap on the
@@ -566,6 +603,7 @@ PhaseCtx* phase_ctx_acquire(int device) {
             c = nullptr;
             return nullptr;
         }
+        g_ctx_all.push_back(c);
     }
     c->refs++;
     return c;
@@ -578,6 +616,7 @@ void phase_ctx_release(PhaseCtx* c) {
     (void)hipEventSynchronize(c->done);
     phase_ctx_free(*c);
     g_ctx[c->device] = nullptr;
+    ctx_forget(c);
     delete c;
 }
 
@@ -794,6 +833,7 @@ Rooms lists_rooms(PhaseCtx& c, const PhaseShape& z, bool tmp) {
 }
 
 uint64_t free_memory() {
+    if (const char* m = std::getenv("HGT_FREE_MEMORY")) return std::strtoull(m, nullptr, 10);  // (tests)
     size_t free = 0, total = 0;
     if (hip_failed(hipMemGetInfo(&free, &total), "hipMemGetInfo", __LINE__)) return 0;
     return free;
@@ -832,6 +872,15 @@ void lists_free(PhaseCtx& c) {
     const Rooms R = lists_rooms(c, PhaseShape{}, true);
     for (int i = 0; i < R.n; i++) dev_free(*R.r[i].b);
     dev_free(c.t_garena);
+}
+
+// The temporal family's lists grow only where that leaves at least as much memory free.
+bool lists_welcome(PhaseCtx& c, const PhaseShape& z) {
+    const Rooms R = lists_rooms(c, z, true);
+    uint64_t more = 0;
+    for (int i = 0; i < R.n; i++)
+        if (R.r[i].bytes > R.r[i].b->bytes) more += R.r[i].bytes - R.r[i].b->bytes;
+    return more == 0 || free_memory() / 2 >= more;
 }
 
 // Whether the temporal family's lists have their room; without it, the 2-hop kernels run.
@@ -1531,7 +1580,8 @@ int reserve_all_phases(hgt_graph* owner, std::vector<Pending*>& ps, bool upload,
     // last, what the batch can do without: where the temporal family's lists do not fit, what
     // they took goes back, and the buffers they share with the hyperedge family are its again
     for (int phase = 0; phase < 2; phase++) {
-        if (!lists[phase][1] || lists_reserve(c, shape[phase][1], true) == HGT_OK) continue;
+        if (!lists[phase][1] || !lists_welcome(c, shape[phase][1])) continue;
+        if (lists_reserve(c, shape[phase][1], true) == HGT_OK) continue;
         lists_free(c);
         for (int q = 0; q < 2; q++)
             if (lists[q][0])
@@ -1720,6 +1770,13 @@ int apply_graph(hgt_graph* owner, std::vector<Pending*>& ps, hipStream_t s, bool
 int apply_planned(hgt_graph* owner, std::vector<Pending*>& ps, hipStream_t s, bool graph = false) {
     PhaseCtx& c = ctx_of(owner);
     std::lock_guard<std::mutex> lk(c.mu);
+    struct Locked {  // seen by scratch_release on this thread
+        explicit Locked(PhaseCtx* p) { t_locked = p; }
+        ~Locked() {
+            if (t_na) arena_undo(*t_na);  // nobody else sees the context with arena regions
+            t_locked = nullptr;
+        }
+    } locked(&c);
     HIP_OK(hipStreamWaitEvent(s, c.done, 0));
     if (t_tune_ev[0]) (void)hipEventRecord(t_tune_ev[0], s);
     int rc = kCaptureFailed;
@@ -1810,11 +1867,17 @@ PhaseCtx* hgt_phase_ctx_create(int device) {
         delete c;
         return nullptr;
     }
+    std::lock_guard<std::mutex> lk(g_ctx_mu);
+    g_ctx_all.push_back(c);
     return c;
 }
 
 void hgt_phase_ctx_destroy(PhaseCtx* c) {
     if (!c) return;
+    {
+        std::lock_guard<std::mutex> lk(g_ctx_mu);
+        ctx_forget(c);
+    }
     (void)hipEventSynchronize(c->done);
     phase_ctx_free(*c);
     delete c;
@@ -2096,9 +2159,7 @@ int hgt_apply_batch_noalloc(hgt_graph* g, const uint32_t* del_ids, uint64_t n_de
     rc = apply(g, del_ids, n_del, ins_offsets, ins_members, n_ins_members, ins_ts, n_ins, out_ins_ids,
                (hipStream_t)stream);
     t_na = nullptr;
-    // the graph's own scratch buffers are its again (queued kernels keep using the
-    // arena regions they were given; the arena is never freed)
-    for (int i = a.n_undo - 1; i >= 0; i--) *a.undo[i].b = a.undo[i].old;
+    arena_undo(a);
     if (rc && !g->sticky) g->sticky = rc;
     return rc;
 }

@@ -77,6 +77,42 @@ def test_temporal_lists_that_do_not_fit(gpu_lib, monkeypatch):
     assert abs(held3 - held1) < 64 << 20, (held1, held3)
 
 
+def test_temporal_lists_leave_and_return_memory(gpu_lib, monkeypatch):
+    """The same lists (0.8 GB) where 1.5 GB are free: not taken, the 2-hop kernels run.
+    Taken, they are given back when another allocation fails; the call that failed
+    leaves the graph as it was, and the next one takes them again."""
+    import torch
+    hgt = gpu_lib
+    st = W.temporal_stream("lists", 50, 1000, 9000, 2, 50.0, 4, 4, 100.0, 10**7, 800, W.SEED_BASE + 161)
+    p, q = (Pair(W.Stream("lists", st.n_vertices, st.initial, window=st.window), track=("temporal",)) for _ in range(2))
+    args = [q.prepare(b, "lists")[0] for b in st.batches]
+
+    def expanded(g, a):
+        g.profile(True)
+        g.apply_batch(*a)
+        g.sync()
+        return g.profile_read()["temporal"]["events"]
+
+    monkeypatch.setenv("HGT_FREE_MEMORY", str(1500 << 20))
+    assert expanded(q.g, args[0]) > 0
+    monkeypatch.delenv("HGT_FREE_MEMORY")
+    assert expanded(p.g, args[0]) == 0
+    want = p.g.triad_counts("temporal")
+    assert sum(want) > 0 and q.g.triad_counts("temporal") == want
+    held = torch.cuda.mem_get_info()[0]
+    monkeypatch.setenv("HGT_ALLOC_MAX", "4096")
+    rc, _ = p.g.apply_batch(*args[1], raise_on_error=False)
+    assert rc == hgt.ENOMEM
+    assert torch.cuda.mem_get_info()[0] > held + (700 << 20)
+    assert p.g.triad_counts("temporal") == want
+    monkeypatch.delenv("HGT_ALLOC_MAX")
+    assert expanded(p.g, args[1]) == 0
+    q.g.apply_batch(*args[1])
+    assert q.g.triad_counts("temporal") == p.g.triad_counts("temporal")
+    p.close()
+    q.close()
+
+
 @pytest.mark.parametrize("limit_mb", [5, 33])
 def test_fewer_arenas_where_memory_is_short(gpu_lib, monkeypatch, limit_mb):
     """Batches whose centres all reach the global stage, with room for one of its arenas (4 MB
