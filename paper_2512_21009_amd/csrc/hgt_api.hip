@@ -142,7 +142,7 @@ thread_local int t_capture = 0;
 // a dense centre); t_tune overrides the graph's own for one round.
 struct TuneChoice {
     int file_wg, file_skip;  // the numbers that name the choice in the cache file, with
-    uint64_t file_e2;        // wave_slots between them (what they once set is gone)
+    uint64_t file_e2;        // wave_slots between them
     int wg_per_cu;
     uint32_t wave_slots;
     uint64_t slice_pairs;    // work per slice of a centre of stages 1 and 2 (0: by the launch's total)
@@ -2211,6 +2211,10 @@ Tuner& tuner() {
 
 inline int ilog2_bucket(uint64_t x) { return x ? 64 - __builtin_clzll(x) : 0; }
 
+// The top byte of a key: the kernels and choices that the key's rounds were timed with.  To be
+// raised when either changes, so that what was fastest with others is timed again.
+constexpr uint64_t kTuneVersion = 2;
+
 uint64_t tune_key(const std::vector<Pending*>& ps, int n_cu) {
     uint64_t changes = 0, lh = 0;
     uint32_t mask = 0;
@@ -2219,14 +2223,15 @@ uint64_t tune_key(const std::vector<Pending*>& ps, int n_cu) {
         lh = std::max(lh, std::max(p->sum.max_lh_del, p->sum.max_lh_ins));
         mask |= p->g->track_mask;
     }
-    return ((uint64_t)(n_cu & 0xffff) << 40) | ((uint64_t)(mask & 0xff) << 32) |
+    return (kTuneVersion << 56) | ((uint64_t)(n_cu & 0xffff) << 40) | ((uint64_t)(mask & 0xff) << 32) |
            ((uint64_t)ilog2_bucket(ps.size()) << 24) | ((uint64_t)(ilog2_bucket(changes) / 2) << 16) |
            ((uint64_t)(ilog2_bucket(lh) / 2) << 8);
 }
 
 // Cache file: one line per settled key, "key choice file_wg file_skip wave_slots file_e2
-// best_ms", the form and the numbers that earlier libraries wrote, whose lines stay good;
-// lines whose choice does not match this library's table are ignored.
+// best_ms".  Lines whose choice does not match this library's table are ignored, and so are
+// in effect those of other versions (earlier libraries wrote keys without one): no round has
+// such a key.
 void tune_load(Tuner& T) {
     if (T.loaded) return;
     T.loaded = true;

@@ -186,3 +186,28 @@ def _autotune_child():
         p.close()
     print(f"settled {n}", flush=True)
     assert n >= 1
+
+
+def test_autotuner_times_again_what_others_timed(gpu_lib, tmp_path):
+    """Cache lines of an earlier library (keys without a version) settle nothing: rounds of
+    their keys are timed again, and the keys that are appended name this version."""
+    import os
+    import subprocess
+    import sys
+    cache = tmp_path / "tune.txt"
+    env = dict(os.environ, HGT_TUNE_CACHE=str(cache))
+    env.pop("HGT_TUNE_FORCE", None)
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    code = (
+        "import sys; sys.path.insert(0, %r)\n"
+        "from tests import test_gpu_batched as T\n"
+        "T._autotune_child()\n" % root)
+    runs = []
+    for _ in range(2):
+        r = subprocess.run([sys.executable, "-c", code], env=env, cwd=root, capture_output=True, text=True, timeout=300)
+        assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
+        keys = [int(ln.split()[0], 16) for ln in cache.read_text().splitlines()]
+        runs.append(sorted(keys))
+        cache.write_text("".join(f"{k & (1 << 56) - 1:x} 3 4 0 8192 0 0.0001\n" for k in keys))
+    assert runs[0] and all(k >> 56 == 2 for k in runs[0])
+    assert any(k >> 56 == 2 for k in runs[1])
