@@ -1062,6 +1062,8 @@ int run_phase(hgt_graph* owner, const PhaseJob* jobs, uint32_t nj, bool minus, b
                 T.count = ctr + 35;
                 T.scratch = c.p_scratch.as<uint32_t>();
                 T.words = kPathWords;
+                if (const char* w = std::getenv("HGT_PATH_WORDS"))  // (tests) smaller tables, more parts
+                    T.words = std::min(kPathWords, std::max<uint64_t>(4096, std::strtoull(w, nullptr, 10) & ~1ull));
                 T.stats = Q.stats;
                 tmp_paths_launch(T, (unsigned)owner->n_cu, kPathGrid, s);
                 He2Params E = stages(Q.stats);

@@ -578,3 +578,76 @@ def test_sorts_at_tile_edges(gpu_lib, n):
     assert (voff.astype(np.int64) == ooff).all() and (vmem == omem).all()
     compare_counts(p.g, p.o, p.track, f"sort batch {n}")
     p.close()
+
+
+@pytest.mark.parametrize("words", ["20480", "4096"])
+def test_temporal_paths_in_parts(gpu_lib, monkeypatch, words):
+    """Middle hyperedges of more neighbours than the LDS tables hold, with global tables of
+    2,048 and 409 slots: their neighbours are taken in several to many parts."""
+    from .test_gpu_fullsize import _gpu_delta, _oracle_delta
+    monkeypatch.setenv("HGT_PATH_WORDS", words)
+    st = W.temporal_stream("parts", 3000, 3600, 6, 1, 6.0, 1, 4, 3.0, 10**6, 10**9, W.SEED_BASE + 170, pop_s=2.5)
+    assert np.bincount(st.initial.members).max() > 2600
+    b = st.batches[0]
+    p = Pair(st, track=("temporal",))
+    before = np.array(p.g.triad_counts("temporal"), np.uint64)
+    args, _ = p.prepare(b, "parts")
+    p.g.apply_batch(*args)
+    got = _gpu_delta({"temporal": before}, {"temporal": np.array(p.g.triad_counts("temporal"), np.uint64)})
+    want = _oracle_delta(p.o, b.del_handles, b.ins, b.ins.ts, ("temporal",))[2]
+    assert want["temporal"].any() and np.array_equal(got["temporal"], want["temporal"])
+    p.close()
+
+
+@pytest.mark.parametrize("slice_lh", ["0", "48"])
+@pytest.mark.parametrize("shape", ["hubs", "ties", "long-rows"])
+@pytest.mark.parametrize("stage", ["1", "2"])
+def test_temporal_pair_stages(gpu_lib, monkeypatch, stage, shape, slice_lh):
+    """Temporal centres moved on to the histogram stages 1 (LDS) and 2 (global memory), whole
+    and shared among workgroups: hub vertices, equal timestamps, rows of more than 64 members."""
+    monkeypatch.setenv("HGT_FORCE_STAGE", stage)
+    if slice_lh != "0":
+        monkeypatch.setenv("HGT_SLICE_LH", slice_lh)
+    if shape == "hubs":
+        st = W.temporal_stream("stages", 300, 1500, 300, 2, 1.8, 2, 40, 50.0, 40_000, 20_000, W.SEED_BASE + 171, pop_s=1.1)
+    elif shape == "ties":
+        st = W.temporal_stream("stages", 40, 150, 40, 2, 2.0, 1, 6, 0.3, 200, 40, W.SEED_BASE + 172, pop_s=1.0)
+    else:
+        st = W.temporal_stream("stages", 500, 120, 20, 2, 0.5, 60, 90, 7.0, 400, 10**9, W.SEED_BASE + 173)
+    p = Pair(st, track=("temporal",))
+    compare_counts(p.g, p.o, p.track, f"{shape} build")
+    for k, b in enumerate(st.batches):
+        p.apply(b, f"{shape} batch {k}")
+        compare_counts(p.g, p.o, p.track, f"{shape} batch {k}")
+    p.close()
+
+
+def test_batch_planned_again_keeps_all_families(gpu_lib):
+    """Deletions of more (vertex, hyperedge) pairs than a workgroup plans, found on the device:
+    the batch is planned again, and the counts of all three families equal the oracle's."""
+    st = W.temporal_stream("again", 6000, 200, 20, 2, 1.0, 70, 80, 7.0, 700, 150, W.SEED_BASE + 141)
+    b = st.batches[0]
+    rows = st.initial.offsets.astype(np.int64)
+    assert len(b.del_handles) <= 2048 and b.ins.n <= 2048 and len(b.ins.members) <= 8192
+    assert int((rows[b.del_handles + 1] - rows[b.del_handles]).sum()) + len(b.ins.members) > 8192
+    p = Pair(st, track=ALL)
+    for k, b in enumerate(st.batches):
+        p.apply(b, f"again batch {k}")
+        compare_store(p.g, p.o, f"again batch {k}")
+        compare_counts(p.g, p.o, ALL, f"again batch {k}")
+    p.close()
+
+
+def test_switches_of_removed_stages_change_nothing(gpu_lib, monkeypatch):
+    """The switches of the sorted-entry pair phase, its rules for dense centres and the 148 KB
+    stage are read by nothing: with them set, the results are the oracle's."""
+    for name, value in (("HGT_PAIR_AGG", "0"), ("HGT_E2_2HOP", "1"), ("HGT_W_2HOP", "1"), ("HGT_SKIP_LDS148", "0")):
+        monkeypatch.setenv(name, value)
+    st = W.plain_stream("hub", 400, 700, ("power", 1.6, 2, 150), 1.3, 0.0, 2, 80, 90, W.SEED_BASE + 174)
+    p = Pair(st, track=("hyperedge",))
+    p.g.profile(True)
+    for k, b in enumerate(st.batches):
+        p.apply(b, f"removed switches batch {k}")
+        compare_counts(p.g, p.o, p.track, f"removed switches batch {k}")
+    assert p.g.profile_read()["he_2hop"]["events"] == 0  # no centre went to the 2-hop kernel
+    p.close()
