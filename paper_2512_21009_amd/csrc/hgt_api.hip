@@ -1348,6 +1348,7 @@ struct Pending {
     int is_build = 0;                       // the build: counts by the static mode of the kernels
     const uint32_t* forced_ids = nullptr;   // horizontal operations: the IDs the inserts take
     int keep_seq = 0;                       // horizontal operations: arrival sequences kept
+    bool alone = false;                     // the only batch of its call
     bool small = false;                     // planned by one workgroup
     int rc = HGT_OK;  // this batch's result so far
 };
@@ -1457,8 +1458,9 @@ int plan_begin(Pending& p, const uint32_t* del, uint64_t n_del, const uint64_t* 
                   p.forced_ids, p.keep_seq};
     p.n_mem = n_mem;
     g->epoch += 2;
+    const uint64_t rows = p.alone ? kSmallRowsAlone : kSmallRows;
     // The lists of a row's vertices are disjoint, so its list words fit 32 bits with the graph's.
-    p.small = n_del <= kSmallRows && n_ins <= kSmallRows && n_mem <= kSmallPairs && g->next_id <= kSmallIds &&
+    p.small = n_del <= rows && n_ins <= rows && n_mem <= kSmallPairs && g->next_id <= kSmallIds &&
               g->n_inc + n_mem <= 0xffffffffull;
     if (p.small) return HGT_OK;  // planned with the round's other small batches (plan_wait)
     return plan_large(p, s);
@@ -1816,6 +1818,7 @@ int apply(hgt_graph* g, const uint32_t* del, uint64_t n_del, const uint64_t* ins
           ApplyMode mode = MODE_BATCH, const uint32_t* forced_ids = nullptr) {
     Pending p;
     p.g = g;
+    p.alone = true;
     p.out_ids = out_ids;
     p.check_order = mode == MODE_BATCH ? 1 : 0;
     p.is_build = mode == MODE_BUILD ? 1 : 0;
@@ -2352,6 +2355,7 @@ int apply_batches(hgt_batch* bs, uint32_t n, void* stream, uint32_t flags) {
         hgt_batch& b = bs[i];
         b.status = HGT_OK;
         P[i].g = b.graph;
+        P[i].alone = n == 1;
         P[i].out_ids = b.out_ins_ids;
         P[i].rc = 1;  // nothing to apply
         if (b.graph->poisoned) {

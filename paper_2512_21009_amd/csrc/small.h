@@ -17,10 +17,15 @@ struct SmallPlan {
 };
 
 // The limits are what fits the workgroup's LDS: keys of 8 bytes, and per row and per touched
-// vertex 4 to 8 bytes.  At them a workgroup takes about as long as the kernels it replaces
-// (100 changes of cardinality 2 to 8: 4.35 -> 3.94 ms for the whole batch); the update's
-// list words, which it only passes through, are held to 32 passes of its threads.
+// vertex 4 to 8 bytes.  A batch alone in its call is taken up to fewer rows, since sorting and
+// scanning by one workgroup outgrows the launches that it saves: deleting and inserting n rows
+// of two members among 1M hyperedges takes 0.34 ms so and 0.55 kernel by kernel at n = 100,
+// 0.63 and 0.66 at 1,025, 0.77 and 0.72 at 1,500, 0.85 and 0.71 at 2,048 (among 4M: 0.71 both
+// at 1,024, 0.98 and 0.81 at 2,048).  A round's graphs share the launch, so there the limit is
+// the LDS's.  The update's list words, which it only passes through, are held to 32 passes of
+// its threads.
 constexpr uint64_t kSmallRows = 2048;    // deletions, and inserts
+constexpr uint64_t kSmallRowsAlone = 1280;  // ... of the only batch of a call
 constexpr uint32_t kSmallPairs = 8192;   // (vertex, hyperedge) pairs, or touched vertex pairs
 constexpr uint64_t kSmallIds = 1ull << 22;  // 16 rounds over the free-ID bitmap
 constexpr uint64_t kSmallStage = 32768;  // old list words of the touched vertices

@@ -651,3 +651,21 @@ def test_switches_of_removed_stages_change_nothing(gpu_lib, monkeypatch):
         compare_counts(p.g, p.o, p.track, f"removed switches batch {k}")
     assert p.g.profile_read()["he_2hop"]["events"] == 0  # no centre went to the 2-hop kernel
     p.close()
+
+
+@pytest.mark.parametrize("graphs", [1, 2])
+@pytest.mark.parametrize("rows", [1280, 1281, 2048, 2049])
+def test_row_limits_alone_and_in_rounds(gpu_lib, rows, graphs):
+    """Batches on both sides of the one-workgroup plan's limits of rows: 1,280 for a batch
+    alone in its call, 2,048 in a round of two graphs."""
+    from .gpu_harness import apply_many
+    sts = [W.plain_stream("rows", 9000, 2500, ("uniform", 1, 2), 0.0, 0.0, 2, rows, rows, W.SEED_BASE + 180 + i)
+           for i in range(graphs)]
+    pairs = [Pair(s, track=("hyperedge", "incident_vertex")) for s in sts]
+    for k in range(2):
+        apply_many(pairs, [s.batches[k] for s in sts], f"{rows} rows, round {k}")
+        for i, p in enumerate(pairs):
+            compare_store(p.g, p.o, f"{rows} rows, round {k} graph {i}")
+            compare_counts(p.g, p.o, p.track, f"{rows} rows, round {k} graph {i}")
+    for p in pairs:
+        p.close()
