@@ -23,6 +23,19 @@
  *  - IDs and vertex ids are uint32, CSR offsets uint64, timestamps int64 (any
  *    unit, the same as the temporal window), counts uint64.  Counts are exact
  *    and maintained modulo 2^64 (exact whenever the true count is below 2^64).
+ *  - Scratch: beside each graph's own buffers the library keeps one set of
+ *    triad scratch per GPU, and one per round that a server has in flight.  A
+ *    set grows with the batches: 2-hop tables (up to 1 GiB, and 64 KB for each
+ *    of their waves), neighbour tables (up to 512 MiB), incident-vertex maps
+ *    (1.25 GiB once that family is tracked), temporal path tables (256 MiB),
+ *    global-stage arenas (256 MiB for one changed hyperedge, 2 GiB
+ *    from eight on, but never more than a quarter of the free memory), and
+ *    batch-neighbour lists: 24 bytes per entry of the changed hyperedges'
+ *    member lists, 28 for the temporal family, which takes them up to 32 GiB
+ *    and only where as much stays free, else counts without them.  A batch
+ *    whose scratch does not fit returns HGT_ENOMEM and changes nothing.  When
+ *    an allocation fails, lists and arenas that no call holds are freed first;
+ *    destroying the GPU's last graph (the server) frees the set.
  *  - A batch that fails validation is rejected as a whole: graph state and
  *    counts stay as they were, and the error is returned by that call and
  *    again by hgt_sync().
@@ -202,8 +215,8 @@ int hgt_apply_batches(hgt_batch* batches, uint32_t n, void* stream);
                                   * is launched kernel by kernel. */
 #define HGT_BATCHES_AUTOTUNE 2u  /* launch choices (workgroups per CU of the
                                   * global histogram stage, slots of the
-                                  * per-wave 2-hop hashes, pairs per slice of a
-                                  * dense centre) picked per key of the round:
+                                  * per-wave 2-hop hashes, estimated work per
+                                  * slice of a dense centre) picked per key of the round:
                                   * tracked families, number of graphs, changes
                                   * and the 2-hop load of the heaviest centre,
                                   * in log2/log4 buckets.  Each choice is timed
@@ -213,7 +226,8 @@ int hgt_apply_batches(hgt_batch* batches, uint32_t n, void* stream);
                                   * fastest is kept and appended to the cache
                                   * file named by
                                   * HGT_TUNE_CACHE (default ~/.cache/hgt_tune.txt,
-                                  * "off": none), which later processes read. */
+                                  * "off": none), which later processes read
+                                  * (lines of other library versions settle nothing). */
 
 /* hgt_apply_batches with flags (0: the same call).  Every choice gives the
  * same results; only the launch differs.  HGT_EINVAL for unknown flags. */

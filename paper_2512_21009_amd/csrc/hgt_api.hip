@@ -322,7 +322,7 @@ struct hgt_graph {
     int iv_direct = 0;              // HGT_IV_DIRECT=1 (tests): incident-vertex owners without maps
     int iv_wg_per_cu = 8;           // HGT_IV_WG_PER_CU: workgroups per CU of the incident-vertex global stage
     uint32_t slice_lh = 0;          // HGT_SLICE_LH (tests): list entries per slice of a 2-hop kernel centre
-    uint64_t slice_pairs = 0;       // HGT_SLICE_PAIRS: pairs per slice of a global-stage centre (0: default)
+    uint64_t slice_pairs = 0;       // HGT_SLICE_PAIRS: estimated work per slice of a centre (0: by the launch's total)
     int iv_force_stage = 0;         // HGT_IV_FORCE_STAGE (tests): incident-vertex stages below it pass owners on
     uint32_t wave_slots = 8192;     // HGT_WAVE_SLOTS (tests): slots of the 2-hop kernels' per-wave global hashes
     SmallHost* host = nullptr;  // pinned: the batch summary, and small batches' jobs

@@ -5,7 +5,7 @@
 // device, 3 us on the host): kernel by kernel, planning takes 40 of them per graph, the
 // update 10, the pair list 80, and a round over many graphs pays for each graph.  Here a
 // workgroup of 1024 threads does each of the three, its keys, sorts and scans in LDS
-// (150 KB: one workgroup per CU, and a round has fewer graphs than the chip has CUs).  The
+// (150 KB: one workgroup per CU, so up to 256 graphs run at once).  The
 // steps, their results and their errors are those of store.hip and triad_iv.hip.
 // Against those, with the counting kernels the same: one change on 20k hyperedges 1.08 ->
 // 0.48 ms, 64 graphs of up to 4,000 hyperedges in one round 19.4 -> 2.9 ms.

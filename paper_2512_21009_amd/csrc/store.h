@@ -101,8 +101,6 @@ void store_plan(StoreDev& g, BatchIn& b, PlanScratch& w, hipStream_t s);
 void store_commit(StoreDev& g, BatchIn& b, PlanScratch& w, const BatchSummary& sum, uint64_t h_bump,
                   uint64_t v_bump, uint64_t next_seq, hipStream_t s);
 void store_max_ts(const int64_t* ts, uint64_t n, DevScalars* sc, hipStream_t s);
-void store_counts_update(uint64_t* counts, const uint64_t* plus, const uint64_t* minus, int n,
-                         const DevScalars* sc, hipStream_t s);
 
 // Compaction of the pools (every live list into a fresh pool; the blocks of
 // free IDs and the blocks left behind by relocations are dropped):

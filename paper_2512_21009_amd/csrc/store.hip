@@ -509,12 +509,6 @@ __global__ void k_max_ts(const int64_t* ts, uint64_t n, DevScalars* sc) {
         atomicMax((long long*)&sc->last_ts, (long long)ts[i]);
 }
 
-__global__ void k_counts_update(uint64_t* counts, const uint64_t* plus, const uint64_t* minus, int n, const DevScalars* sc) {
-    if (status_bad(&sc->status)) return;
-    int i = threadIdx.x;
-    if (i < n) counts[i] += plus[i] - minus[i];
-}
-
 // ---------------------------------------------------------------------------
 // compaction: every live list moved into a fresh pool, blocks of dead IDs and
 // blocks left behind by relocations dropped
@@ -711,9 +705,4 @@ void store_commit(StoreDev& g, BatchIn& b, PlanScratch& w, const BatchSummary& s
 
 void store_max_ts(const int64_t* ts, uint64_t n, DevScalars* sc, hipStream_t s) {
     if (n) k_max_ts<<<blocks_for(n > 262144 ? 262144 : n), 256, 0, s>>>(ts, n, sc);
-}
-
-void store_counts_update(uint64_t* counts, const uint64_t* plus, const uint64_t* minus, int n, const DevScalars* sc,
-                         hipStream_t s) {
-    k_counts_update<<<1, 128, 0, s>>>(counts, plus, minus, n, sc);
 }

@@ -43,10 +43,14 @@ using namespace tri;
 // threads, two workgroups per CU (one of 1024 threads and 118 KB: 6.6 ms against 3.5 for the
 // centres of 100k changes on 2M hyperedges that stage 0 moves on), unless the launch has at
 // most two centres per CU: then that one large workgroup, which has the CU to itself anyhow
-// and keeps denser centres out of global memory (stages 1 and 2 of 100 + 100 changes among
-// 1,000 hyperedges 2.44 -> 1.08 ms, of one change 0.21 -> 0.15; of 2,000 + 2,000 on 36,000,
-// where the rule says no, 5.43 against 5.72 ms).  Stage 2 (the global stage): tables in global memory, 512
-// threads, two workgroups per CU.
+// and keeps denser centres out of global memory.  Whole batches, two workgroups against one
+// large one: n + n changes among 1,000 hub-heavy hyperedges 2.85 -> 1.79 ms at n = 100 and 5.73
+// -> 3.43 at 500; one change among 20,000, stages 1 and 2, 0.21 -> 0.15; temporal centres 0.97 ->
+// 0.77 ms at n = 64, 2.11 -> 2.07 at 500.  It loses where the centres outgrow 118 KB too (n = 500
+// among 3,000 of those hyperedges 25.1 against 25.8 ms, n = 130 among 1,520 5.64 against 6.52)
+// and gains less as the launch grows: among 500k hyperedges n = 400 2.259 against 2.266, 512
+// 1.924 against 1.968, and beyond the line 800 2.730 against 2.760; 2,000 on 36,000 5.43 against
+// 5.72.  Stage 2 (the global stage): tables in global memory, 512 threads, two workgroups per CU.
 constexpr uint32_t ARENA_S = 6144;
 constexpr uint32_t ARENA_M = 13824;
 constexpr uint32_t ARENA_W = 30208;
@@ -98,7 +102,7 @@ struct Sh2 {
     uint32_t slice, nslice;
     uint64_t hoff;
     uint32_t ws[WG_W / 64];
-    uint32_t ncap, G;
+    uint32_t G;
     uint64_t g[8];
 };
 
@@ -723,7 +727,10 @@ __device__ __forceinline__ void he2_pair(const He2Params& P, const Tables& T, He
 // Pairs of neighbours that meet inside h, as if they met nowhere else.  What a pair
 // changes depends on x only through its mask of shared members, min(|x| - c, c + 1) and
 // (in a full count) h < x, so neighbours are counted by these and the pairs taken by kind:
-// a few dozen kinds in place of hundreds of neighbours.  rep/cnt: gcap slots, list: K words.
+// a few dozen kinds in place of hundreds of neighbours.  One workgroup does it for a centre, also
+// for one in slices: where every neighbour is a kind of its own, 2,000 neighbours that share 12
+// of a centre's 64 members take 7.7 ms in all, 6,000 of 6 members 70 (the 2-hop kernel: 92 and
+// 97).  rep/cnt: gcap slots, list: K words.
 template <int WG, bool BIG, bool GLOBAL>
 __device__ __forceinline__ void he2_kinds(const He2Params& P, Sh2& sh, const Tables& T, He2Acc& A, const uint32_t* nl_meta,
                           const uint32_t* mask, uint32_t K, uint32_t hlen, uint32_t* rep, uint32_t gcap) {

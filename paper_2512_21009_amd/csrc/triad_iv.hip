@@ -242,7 +242,7 @@ struct IvWave {
     uint32_t qw[192], qk[192];
 };
 struct IvSh {
-    uint32_t oi, stop, L;
+    uint32_t oi, stop;
     uint32_t ws[NWAVE];
 };
 
@@ -440,8 +440,8 @@ __device__ __forceinline__ uint32_t iv_taken(const uint32_t* queue) {  // a look
 }
 
 // Stage 0: every wave takes owners of its own; maps of up to IV_WAVE_WORDS / 2 slots.
-// Three quarters of the owners of a power-law graph fit, and 20 of them share a CU
-// where workgroup-sized ones leave it to four.
+// Three quarters of the owners of a power-law graph fit, and 16 of them share a CU (four
+// workgroups of four waves, 40 KB of LDS each) where workgroup-sized ones leave it to four.
 __global__ void __launch_bounds__(HGT_WG) k_iv_wave(IvParams A) {
     __shared__ __attribute__((aligned(16))) uint32_t arena[NWAVE][IV_WAVE_WORDS];
     __shared__ uint32_t sieve[NWAVE][IV_SIEVE];

@@ -194,7 +194,6 @@ __device__ void paths_body(const PathParams& P, const PathTab& B, uint32_t HS, u
         }
         if (P.stats && tid == 0)
             atomicAdd((unsigned long long*)&P.stats[ST_BYTES_SMALL], (unsigned long long)(4ull * len + 16ull * sh.bn));
-        bool moved_on = false;
         for (uint32_t part = 0; part < nparts && len; part++) {
             __syncthreads();
             if (tid == 0) sh.K = sh.KL = sh.over = 0;
@@ -232,7 +231,6 @@ __device__ void paths_body(const PathParams& P, const PathTab& B, uint32_t HS, u
                 } else if (tid == 0) {
                     moved[atomicAdd(n_moved, 1u)] = sh.slot;
                 }
-                moved_on = true;
                 break;
             }
             // the distinct neighbours with length and batch rank
@@ -305,7 +303,6 @@ __device__ void paths_body(const PathParams& P, const PathTab& B, uint32_t HS, u
                 }
             }
         }
-        (void)moved_on;
         __syncthreads();
     }
     flush();
