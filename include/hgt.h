@@ -32,7 +32,8 @@
  *    from eight on, but never more than a quarter of the free memory), and
  *    batch-neighbour lists: 24 bytes per entry of the changed hyperedges'
  *    member lists, 28 for the temporal family, which takes them up to 32 GiB
- *    and only where as much stays free, else counts without them.  A batch
+ *    (and half as much again as room to grow) and only where as much stays
+ *    free, else counts without them.  A batch
  *    whose scratch does not fit returns HGT_ENOMEM and changes nothing.  When
  *    an allocation fails, lists and arenas that no call holds are freed first;
  *    destroying the GPU's last graph (the server) frees the set.

@@ -213,13 +213,17 @@ void arena_undo(NoAllocArena& a) {
     for (; a.n_undo > 0; a.n_undo--) *a.undo[a.n_undo - 1].b = a.undo[a.n_undo - 1].old;
 }
 
+// what a buffer too small for `bytes` grows to
+size_t grown(const DevBuf& b, size_t bytes) {
+    return (std::max(bytes, b.bytes + b.bytes / 2) + 4095) & ~(size_t)4095;
+}
+
 // grow-only scratch (contents not preserved)
 int ensure(DevBuf& b, size_t bytes) {
     if (t_na) return arena_take(*t_na, b, bytes);
     if (b.p && b.bytes >= bytes) return HGT_OK;
     if (t_capture) return HGT_ENOMEM;  // everything was reserved before the capture
-    size_t nb = std::max(bytes, b.bytes + b.bytes / 2);
-    nb = (nb + 4095) & ~(size_t)4095;
+    const size_t nb = grown(b, bytes);
     dev_free(b);
     return dev_alloc(b, nb);
 }
@@ -879,7 +883,7 @@ bool lists_welcome(PhaseCtx& c, const PhaseShape& z) {
     const Rooms R = lists_rooms(c, z, true);
     uint64_t more = 0;
     for (int i = 0; i < R.n; i++)
-        if (R.r[i].bytes > R.r[i].b->bytes) more += R.r[i].bytes - R.r[i].b->bytes;
+        if (R.r[i].bytes > R.r[i].b->bytes) more += grown(*R.r[i].b, R.r[i].bytes) - R.r[i].b->bytes;
     return more == 0 || free_memory() / 2 >= more;
 }
 

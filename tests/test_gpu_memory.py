@@ -78,12 +78,16 @@ def test_temporal_lists_that_do_not_fit(gpu_lib, monkeypatch):
 
 
 def test_temporal_lists_leave_and_return_memory(gpu_lib, monkeypatch):
-    """The same lists (0.8 GB) where 1.5 GB are free: not taken, the 2-hop kernels run.
+    """Lists as above (0.8 GB) where 1.5 GB are free: not taken, the 2-hop kernels run.
     Taken, they are given back when another allocation fails; the call that failed
-    leaves the graph as it was, and the next one takes them again."""
+    leaves the graph as it was, and the next one takes them again.  Buffers grow by half
+    at least, which counts: a last batch that needs 1.27 times the lists held would fit
+    half of 1.2 GB free, 1.5 times do not."""
     import torch
     hgt = gpu_lib
-    st = W.temporal_stream("lists", 50, 1000, 9000, 2, 50.0, 4, 4, 100.0, 10**7, 800, W.SEED_BASE + 161)
+    st = W.temporal_stream("lists", 50, 1000, 9000, 3, 50.0, 4, 4, 100.0, 10**7, 800, W.SEED_BASE + 161)
+    b = st.batches[2]
+    st.batches[2] = W.Batch(b.del_handles, b.ins.rows(np.arange(8000)), b.ins_handles[:8000])
     p, q = (Pair(W.Stream("lists", st.n_vertices, st.initial, window=st.window), track=("temporal",)) for _ in range(2))
     args = [q.prepare(b, "lists")[0] for b in st.batches]
 
@@ -108,6 +112,11 @@ def test_temporal_lists_leave_and_return_memory(gpu_lib, monkeypatch):
     monkeypatch.delenv("HGT_ALLOC_MAX")
     assert expanded(p.g, args[1]) == 0
     q.g.apply_batch(*args[1])
+    assert q.g.triad_counts("temporal") == p.g.triad_counts("temporal")
+    monkeypatch.setenv("HGT_FREE_MEMORY", str(1200 << 20))
+    assert expanded(p.g, args[2]) > 0
+    monkeypatch.delenv("HGT_FREE_MEMORY")
+    assert expanded(q.g, args[2]) == 0
     assert q.g.triad_counts("temporal") == p.g.triad_counts("temporal")
     p.close()
     q.close()
